@@ -718,6 +718,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   P.c_on_lines = reinterpret_cast<uintptr_t>(C) % 128 == 0;
   P.x_on_lines = reinterpret_cast<uintptr_t>(A.X_out) % 128 == 0;
   P.tilesum_half = h->tilesum_half;
+  P.rho = Z.rho;
   P.feedback = !A.fixed_schedule;
   P.checking = A.tol > 0.f;
   P.max_iters = A.max_iters;

@@ -103,6 +103,7 @@ struct Problem {
   int slab_k = 0;             // group lasso: rows per lane of the slab kernel, 0 = two-pass path
   int nruns = 0;              // group lasso: runs of equal labels
   size_t tilesum_half = 0;    // capacity of one half of the tile-total buffer
+  float rho = 0.f;            // stepsize
   bool feedback = true;       // the host reads the status block during the solve
   bool checking = false;      // a tolerance was given
   int max_iters = 0;
@@ -118,6 +119,8 @@ struct Carry {
   double plan_density = -1.0;
   long long epoch_gen = -1;      // sweep that last recorded the screening bounds
   int refresh_period = kFirstRefreshPeriod;
+  bool bounds_from_points = false;  // ... from a cost formed from point clouds (no bounds by line then), or a stored one
+  float bounds_rho = 0.f;           // ... with this stepsize
   bool sums_valid = false;       // the row-segment sums of the last sweep describe the X in memory
   int sums_strip = 0;            // ... in pieces of this many columns
   bool lines_valid = false;      // the same for the lean sweep's line flags
@@ -230,14 +233,17 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
   T.dense_plan = P.resume && carry.dense_plan;
   T.plan_density = P.resume ? carry.plan_density : -1.0;
   T.by_lines = P.resume && carry.by_lines;
-  T.drift_gen = P.resume && carry.drift_valid ? T.k_base : -1;
+  // (the bounds are of varphi_j - rho C_ij as the sweep that recorded them formed it, and the sweeps over point clouds
+  // record none by line: where the cost comes from elsewhere now, or the stepsize is another, new ones come first)
+  const bool bounds_hold = P.resume && carry.bounds_from_points == P.from_points && carry.bounds_rho == P.rho;
+  T.drift_gen = bounds_hold && carry.drift_valid ? T.k_base : -1;
   // (a continued solve starts from the X the last one returned, so its row-segment sums still hold;
   // the warm start's sums are those of 256-column segments)
   T.sums_gen = P.warm ? (P.slab_k ? -1 : 0)
                       : (P.resume && carry.sums_valid && carry.sums_strip == S.sums_strip) ? T.k_base : -1;
   T.lines_gen = (P.resume && carry.lines_valid && T.sums_gen >= 0) ? T.k_base : -1;
-  T.epoch_gen = P.resume ? carry.epoch_gen : -1;
-  T.refresh_period = P.resume ? carry.refresh_period : S.early_lines ? kFirstPeriodLines : kFirstRefreshPeriod;
+  T.epoch_gen = bounds_hold ? carry.epoch_gen : -1;
+  T.refresh_period = bounds_hold ? carry.refresh_period : S.early_lines ? kFirstPeriodLines : kFirstRefreshPeriod;
   if (T.refresh_period > S.refresh_max) T.refresh_period = S.refresh_max;
   return T;
 }
@@ -488,6 +494,8 @@ inline Carry finish(const Static& S, const Problem& P, const State& T, bool conv
   C.drift_valid = !converged && epoch_kept && P.max_iters > 0 && T.drift_gen == T.k_base + T.k;
   C.epoch_gen = (converged || !epoch_ran) ? -1 : T.epoch_gen;
   C.refresh_period = (converged || !epoch_ran) ? kFirstRefreshPeriod : T.refresh_period;
+  C.bounds_from_points = P.from_points;
+  C.bounds_rho = P.rho;
   C.sums_valid = !converged && P.max_iters > 0 && T.sums_gen == T.k_base + T.k;
   C.lines_valid = C.sums_valid && T.lines_gen == T.k_base + T.k;
   C.sums_strip = S.sums_strip;

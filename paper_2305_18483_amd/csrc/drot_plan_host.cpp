@@ -12,21 +12,22 @@ using namespace drot_plan;
 
 extern "C" {
 
-// problem[14]: m, n, reg_kind, from_points, warm, resume, has_weights, c_on_lines, x_on_lines, slab_k,
-//              nruns, feedback, checking, max_iters
+// problem[17]: m, n, reg_kind, from_points, warm, resume, has_weights, c_on_lines, x_on_lines, slab_k,
+//              nruns, feedback, checking, max_iters, line_bounds, prompt_looks, rho * 1e9
 // options[9]:  check_every, resident, fused_update, skip_cost, skip_unchanged, screening, nontemporal,
 //              force_two_pass, gap_every
-// carry[8] (in and out): dense_plan, plan_density * 1e6, epoch_gen, refresh_period, sums_valid, sums_strip,
-//              lines_valid, iters_done
-// densities[nstatus]: what the k-th status of the call reports (fraction of nonzero row segments);
-//              statuses past the end repeat the last one.  stop_at_status >= 0: that status reports convergence.
+// carry[12] (in and out): dense_plan, plan_density * 1e6, epoch_gen, refresh_period, sums_valid, sums_strip,
+//              lines_valid, iters_done, by_lines, drift_valid, bounds_from_points, bounds_rho * 1e9
+// densities[nstatus]: what the k-th status of the call reports (fraction of nonzero row segments), lines[nstatus] (or null)
+//              the fraction of nonzero lines, reported where the last sweep was a lean one; statuses past the end repeat the
+//              last one.  stop_at_status >= 0: that status reports convergence.
 // rows [capacity][12]: sweep, mode, first, prev_sums, lines_in, refresh, pro, tilesum, update, ra_ntr * 16 + ra_cgroup,
 //              profile_kind, flags (1: last sweep of a stretch, 2: that stretch is a probe, 4: its status carries the gap,
 //              8: a gap evaluated there may take the lean pass, 16: with the lean sweep's line flags)
 // statics[10]: nseg, ntr, resident, pad_c, pad_x, small, fused, may_screen, adaptive, nt
 // Returns the number of sweeps (launches) planned, or -1 if capacity was too small.
-int drot_plan_trace(const int* problem, const int* options, long long* carry, const double* densities, int nstatus,
-                    int stop_at_status, int* rows, int capacity, int* statics, int* iters_done) {
+int drot_plan_trace(const int* problem, const int* options, long long* carry, const double* densities,
+                    const double* lines, int nstatus, int stop_at_status, int* rows, int capacity, int* statics, int* iters_done) {
   Problem P;
   P.m = problem[0];
   P.n = problem[1];
@@ -42,6 +43,9 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   P.feedback = problem[11] != 0;
   P.checking = problem[12] != 0;
   P.max_iters = problem[13];
+  P.line_bounds = problem[14] != 0;
+  P.prompt_looks = problem[15] != 0;
+  P.rho = (float)problem[16] * 1e-9f;
   P.tilesum_half = (size_t)ceil_div(P.n, kSegCols) * (size_t)ceil_div(P.m, kTileRows);
   if (P.tilesum_half < 4096) P.tilesum_half = 4096;
   Options O;
@@ -63,6 +67,11 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   C.sums_strip = (int)carry[5];
   C.lines_valid = carry[6] != 0;
   C.iters_done = carry[7];
+  C.by_lines = carry[8] != 0;
+  C.drift_valid = carry[9] != 0;
+  C.bounds_from_points = carry[10] != 0;
+  C.bounds_rho = (float)carry[11] * 1e-9f;
+
 
   const Static S = make_static(P, O);
   statics[0] = S.nseg;
@@ -78,8 +87,7 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   State T = start_state(S, P, C);
   int nrows = 0, checks = 0;
   bool converged = false;
-  bool was_probe[2] = {false, false};
-  int status_iters[2] = {0, 0};
+  bool was_probe[2] = {false, false}, was_lean[2] = {false, false};
   int slot = 0, stop_iters = -1;
   while (T.k < P.max_iters && !converged) {
     const Stretch R = next_stretch(S, P, O, T);
@@ -106,15 +114,17 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
     }
     if (S.status_at_checks) {
       was_probe[slot] = R.probe;
-      status_iters[slot] = T.k;
+      was_lean[slot] = T.last_lean;
       if (checks == stop_at_status && stop_iters < 0) stop_iters = T.k;  // (the device raises its stop flag here)
-      if (checks > 0 && P.feedback) {
-        // the host reads the previous stretch's status while this one is queued
-        const int prev = checks - 1;
-        if (stop_at_status >= 0 && prev >= stop_at_status) converged = true;
-        const double d = nstatus > 0 ? densities[prev < nstatus ? prev : nstatus - 1] : 0.0;
-        on_status(S, T, d, -1.0, was_probe[slot ^ 1]);
-      }
+      auto read_status = [&](int which, int slot_of) {
+        if (stop_at_status >= 0 && which >= stop_at_status) converged = true;
+        const int e = which < nstatus ? which : nstatus - 1;
+        on_status(S, T, nstatus > 0 ? densities[e] : 0.0, nstatus > 0 && lines && was_lean[slot_of] ? lines[e] : -1.0,
+                  was_probe[slot_of]);
+      };
+      // the host reads the previous stretch's status while this one is queued, and where it waits for it this one's too
+      if (checks > 0 && P.feedback) read_status(checks - 1, slot ^ 1);
+      if (P.feedback && R.prompt) read_status(checks, slot);
       slot ^= 1;
       ++checks;
     }
@@ -130,8 +140,11 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   carry[5] = F.sums_strip;
   carry[6] = F.lines_valid;
   carry[7] = F.iters_done;
+  carry[8] = F.by_lines;
+  carry[9] = F.drift_valid;
+  carry[10] = F.bounds_from_points;
+  carry[11] = (long long)(F.bounds_rho * 1e9 + 0.5);
   *iters_done = reported;
-  (void)status_iters;
   return nrows;
 }
 

@@ -1110,6 +1110,42 @@ def test_point_cloud_screening_changes_no_bit(drot, oracle, m, n, d, kind):
     _say(f"point-cloud cost, screened: plan error / scale = {ratio:.2e}; kinds {kinds.count(8)} screened, {kinds.count(9)} recording")
 
 
+def test_bounds_do_not_travel_to_another_cost_or_stepsize(drot, oracle):
+    # one state taken on by a solve over point clouds, then one over the stored cost, then one with half the stepsize: each
+    # screens with bounds of its own (the line bytes on the handle are an unrelated problem's before the stored-cost sweeps
+    # write theirs); the bits are those of the sweeps that read all of C
+    m, n, d = 2100, 8232, 8
+    P = drot_inputs.random_problem(m, n, seed=2350, d=d, reg_kind=1, lam=0.01)
+    scale = float(np.float32(1.0 / P.cmax))
+    P.C = oracle.sqdist_cost(P.xs, P.xt, scale)
+    other = drot_inputs.random_problem(m, n, seed=2351, d=2, reg_kind=0)
+    dev = torch.device("cuda:0")
+    C, p, q, _ = pu.to_dev(P)
+    xs, xt = torch.from_numpy(P.xs).to(dev), torch.from_numpy(P.xt).to(dev)
+    kw = dict(reg_kind=1, lam=P.lam, tol=1e-12)
+    _say(f"bounds across costs and stepsizes, {m}x{n}")
+    outs = []
+    for screening in (0, 1):
+        solver = drot.Solver(m, n, check_every=25)
+        solver.set_skip_cost(0)
+        solver.set_screening(screening)
+        pu.gpu_solve(solver, other, 150, tol=1e-12)
+        X = torch.empty((m, n), device=dev)
+        solver.solve_points(xs, xt, scale, p, q, max_iters=300, X_out=X, **kw)
+        solver.set_continue(True)
+        solver.set_profile(True)
+        after = []
+        for stepsize in (float(P.rho), 0.5 * float(P.rho)):
+            solver.solve(C, p, q, stepsize=stepsize, max_iters=60, X_out=X, **kw)
+            after.append([X.clone(), *solver.duals(m, n, dev)])
+            if screening:
+                kinds = [k for _, k in solver.profile_sweeps()]
+                assert kinds[0] == 6 and 7 in kinds[1:], kinds  # bounds first, then the sweep by lines
+        outs.append(after)
+    for a, b in zip(outs[0], outs[1]):
+        assert all(torch.equal(s, t) for s, t in zip(a, b))
+
+
 def test_ot_cost_gradient_is_the_plan(drot, oracle):
     # Section "Backpropagation through regularized OT-costs": grad_C OT_h(C) = X* when the
     # solution is unique (quadratic term).  Checked against the oracle's plan at convergence and

@@ -14,7 +14,7 @@ import pytest
 RESIDENT, PRO32, PLAIN32, TALL64, SCREENED8, LEAN, POINTS, SLAB, TWOPASS, POINTS_LEAN = range(10)
 NO_UPDATE, SEPARATE, MERGED_SLAB, MERGED_TILES = range(4)
 COLS = ("sweep", "mode", "first", "prev_sums", "lines_in", "refresh", "pro", "tilesum", "update", "ra", "kind", "flags")
-FRESH_CARRY = (0, -1000000, -1, 8, 0, 0, 0, 0)
+FRESH_CARRY = (0, -1000000, -1, 8, 0, 0, 0, 0)  # (what is left out of a carry is 0)
 
 
 @pytest.fixture(scope="module")
@@ -40,20 +40,22 @@ class Trace:
 
 def trace(lib, m, n, max_iters, reg_kind=0, from_points=0, warm=0, resume=0, weights=0, c_on_lines=1, x_on_lines=1,
           slab_k=0, nruns=0, feedback=1, checking=1, check_every=100, resident=-1, fused_update=-1, skip_cost=-1,
-          skip_unchanged=-1, screening=-1, nontemporal=-1, force_two_pass=0, gap_every=0, densities=(), stop_at_status=-1,
-          carry=FRESH_CARRY):
-    problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, warm, resume, weights, c_on_lines, x_on_lines, slab_k, nruns,
-                                  feedback, checking, max_iters)
+          skip_unchanged=-1, screening=-1, nontemporal=-1, force_two_pass=0, gap_every=0, densities=(), lines=None,
+          stop_at_status=-1, carry=FRESH_CARRY, line_bounds=0, prompt_looks=0, rho=0):
+    problem = (ctypes.c_int * 17)(m, n, reg_kind, from_points, warm, resume, weights, c_on_lines, x_on_lines, slab_k, nruns,
+                                  feedback, checking, max_iters, line_bounds, prompt_looks, rho)
     options = (ctypes.c_int * 9)(check_every, resident, fused_update, skip_cost, skip_unchanged, screening, nontemporal,
                                  force_two_pass, gap_every)
-    carry_io = (ctypes.c_longlong * 8)(*carry)
+    carry_io = (ctypes.c_longlong * 12)(*carry)
     dens = (ctypes.c_double * max(1, len(densities)))(*densities)
+    assert lines is None or len(lines) == len(densities)
+    nz_lines = None if lines is None else (ctypes.c_double * max(1, len(lines)))(*lines)
     cap = max_iters + 8
     rows = (ctypes.c_int * (12 * cap))()
     statics = (ctypes.c_int * 10)()
     iters = ctypes.c_int()
-    nrows = lib.drot_plan_trace(problem, options, carry_io, dens, len(densities), stop_at_status, rows, cap, statics,
-                                ctypes.byref(iters))
+    nrows = lib.drot_plan_trace(problem, options, carry_io, dens, nz_lines, len(densities), stop_at_status, rows, cap,
+                                statics, ctypes.byref(iters))
     assert nrows >= 0
     arr = np.array(rows[:12 * nrows], dtype=np.int64).reshape(nrows, 12)
     names = ("nseg", "ntr", "resident", "pad_c", "pad_x", "small", "fused", "may_screen", "adaptive", "nt")
@@ -173,6 +175,26 @@ def test_a_continued_call_goes_on_where_the_last_one_stopped(planlib):
     # without continuation state (another option set, say) nothing is taken for granted
     cold = trace(planlib, 20000, 20000, 10, resume=1, carry=(0, 50000, -1, 8, 0, 0, 0, 150), reg_kind=1)
     assert cold.col("prev_sums")[0] == 0 and cold.col("kind")[0] == 6
+
+
+def test_bounds_go_on_only_to_calls_with_the_cost_and_the_stepsize_they_were_recorded_with(planlib):
+    # a solve over point clouds leaves bounds without the bounds by line, a stored-cost one none of the sweep's own costs;
+    # both are of varphi - rho C: where the next call's cost comes from elsewhere, or its stepsize is another, it renews first
+    handle = dict(reg_kind=1, checking=0, line_bounds=1, prompt_looks=1)
+    points = dict(handle, from_points=1, rho=50000, densities=(0.9, 0.6, 0.2, 0.05))
+    stored = dict(handle, from_points=0, rho=50000, densities=(0.9, 0.6, 0.2, 0.05))
+    lean_kind, full_kind = {0: 7, 1: 8}, {0: 6, 1: 9}
+    for first, second in ((points, stored), (stored, points), (points, dict(points, rho=25000)),
+                          (stored, dict(stored, rho=25000)), (points, points), (stored, stored)):
+        a = trace(planlib, 20000, 20000, 500, **first)
+        assert a.carry[2] > 0 and a.carry[4] == 1  # bounds, and sums that describe the plan
+        b = trace(planlib, 20000, 20000, 60, resume=1, carry=a.carry, **dict(second, densities=(0.05,)))
+        kinds = b.col("kind")
+        lean = kinds.index(lean_kind[second["from_points"]])
+        same = first["from_points"] == second["from_points"] and first["rho"] == second["rho"]
+        assert (lean == 0) == same
+        if not same:  # nothing certified before a sweep of this call has recorded the bounds
+            assert full_kind[second["from_points"]] in kinds[:lean] and 5 not in kinds[:lean]
 
 
 def test_a_stop_at_a_check_forgets_what_the_sweeps_queued_behind_it_would_have_left(planlib):
