@@ -124,13 +124,17 @@ __device__ __forceinline__ f4v load_varphi_padded(const float* __restrict__ varp
 // |v| of a varphi entry, 0 for the mask value of the columns past n.
 __device__ __forceinline__ float unmasked_abs(float v) { return v == kMaskedOut ? 0.f : fabsf(v); }
 
-// [x + phi_i + varphi_j - rho c]_+   (first half of eq. (8))
+// [x + phi_i + varphi_j - rho c]_+   (first half of eq. (8)).  What is added to x is formed first: where x > 0 its terms all
+// but cancel, so that x is added to a number of its own size; x + (phi_i + varphi_j) in fp32 first rounds at the size of
+// rho c.  Plans against the iteration in 64 bits, that order and this one: 100 x 100 after 2000 iterations 9.8e-6 and
+// 6.0e-7, 1000 x 1000 after 1000 3.7e-6 and 1.5e-6, 8191 x 8191 with a strong quadratic term after 300 1.54e-7 and 1.17e-7
+// (in even/odd pairs 1.29e-7 and 1.19e-7).
 __device__ __forceinline__ f4v xbar4(f4v x, f4v c, f4v pv, float rho) {
   f4v v;
-  v.x = fmaxf(fmaf(-rho, c.x, x.x + pv.x), 0.f);
-  v.y = fmaxf(fmaf(-rho, c.y, x.y + pv.y), 0.f);
-  v.z = fmaxf(fmaf(-rho, c.z, x.z + pv.z), 0.f);
-  v.w = fmaxf(fmaf(-rho, c.w, x.w + pv.w), 0.f);
+  v.x = fmaxf(x.x + fmaf(-rho, c.x, pv.x), 0.f);
+  v.y = fmaxf(x.y + fmaf(-rho, c.y, pv.y), 0.f);
+  v.z = fmaxf(x.z + fmaf(-rho, c.z, pv.z), 0.f);
+  v.w = fmaxf(x.w + fmaf(-rho, c.w, pv.w), 0.f);
   return v;
 }
 

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
     float rowacc = 0.f;
 #pragma unroll
     for (int e = 0; e < CPL; ++e) {
-      const float v = fmaxf(fmaf(-rho, c[e], x[e] + (vp[e] + ph)), 0.f) * scale;
+      const float v = fmaxf(x[e] + fmaf(-rho, c[e], vp[e] + ph), 0.f) * scale;
       x[e] = v;
       rowacc += v;
       lds_col[wave][j0 + e] = v;
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
         float rowacc = 0.f;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          float v = fmaxf(fmaf(-rho, c[r][e], x[r][e] + (vp[e] + ph)), 0.f);
+          float v = fmaxf(x[r][e] + fmaf(-rho, c[r][e], vp[e] + ph), 0.f);
           if (SCALED) v *= scale;
           x[r][e] = v;
           colacc[e] = r == 0 ? v : colacc[e] + v;

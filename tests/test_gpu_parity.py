@@ -1176,6 +1176,46 @@ def test_ot_cost_gradient_is_the_plan(drot, oracle):
     assert abs((up - down) / (2 * eps) - directional) <= 1e-2 * abs(directional)
 
 
+def _plan_error(C, p, q, X, lam, iters):
+    # relative error (2-norm) of a plan against the iteration of eqs. (8) and (6) in 64 bits, from X_0 = 0
+    m, n = C.shape
+    C, p, q = C.double(), p.double(), q.double()
+    rho = float(np.float32(2.0) / np.float32(m + n))
+    scale = 1.0 / (1.0 + rho * float(np.float32(lam)))
+    f0, v0 = (1.0 + m / (m + n)) / (3.0 * (m + n)), (1.0 + n / (m + n)) / (3.0 * (m + n))
+    phi, varphi = torch.full_like(p, f0), torch.full_like(q, v0)
+    a, b = n * (f0 + v0) - p, m * (f0 + v0) - q
+    theta = a.sum() / (m + n)
+    Y = torch.zeros_like(C)
+    for _ in range(iters):
+        Y = (Y + phi[:, None] + varphi[None, :] - rho * C).clamp_(min=0.0) * scale
+        r, t = Y.sum(1) - p, Y.sum(0) - q
+        eta = r.sum() / (m + n)
+        phi, varphi = (a - 2.0 * r + (2.0 * eta - theta)) / n, (b - 2.0 * t + (2.0 * eta - theta)) / m
+        a, b, theta = a - r, b - t, theta - eta
+    return float((X.double() - Y).norm() / Y.norm())
+
+
+def test_dense_plans_lose_no_precision_to_the_sweep_by_lines(drot):
+    # a strong quadratic term over 12 million entries: the automatic choice (lines) against the even/odd pairs that it
+    # replaces here.  Both round phi + varphi - rho C once per entry and iteration at the size of rho C; measured over eight
+    # problems of 12 to 33 million entries their errors are within 0.91 to 0.99 of each other (a third rounding of that size
+    # makes it 1.18 to 1.34)
+    m, n, K = 3700, 3900, 150
+    lam = 0.25 * (m * n) ** 0.5
+    P = drot_inputs.random_problem(m, n, seed=2900, d=6, reg_kind=1, lam=lam)
+    C, p, q, _ = pu.to_dev(P)
+    _say(f"dense plan, lines against pairs, {m}x{n}")
+    errors = {}
+    for mode in (-1, 1):
+        solver = drot.Solver(m, n)
+        solver.set_skip_cost(mode)
+        X = solver.solve(C, p, q, reg_kind=1, lam=lam, max_iters=K, tol=1e-9).X
+        errors[mode] = _plan_error(C, p, q, X, lam, K)
+    _say(f"error of the plan: {errors[-1]:.3e} by lines, {errors[1]:.3e} in pairs")
+    assert errors[-1] <= 1.08 * errors[1]
+
+
 @pytest.mark.parametrize("m,n", [(33, 257), (129, 2), (64, 9000), (1000, 1000), (1000, 8000), (2047, 3600), (2047, 5101),
                                  (2049, 257), (2300, 2500), (2999, 3307), (6000, 300), (20, 5000)])
 def test_grid_resident_stretches_give_the_bits_of_single_launches(drot, m, n):
