@@ -40,8 +40,8 @@ def _run(cmd, verbose):
 
 
 def build_plan(verbose: bool = False) -> str:
-    """Compile the launch planner with the host compiler (no GPU code in it)."""
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-o", PLAN_LIB_PATH, PLAN_SOURCE], verbose)
+    """Compile the launch planner and the certificates with the host compiler (no GPU code in them)."""
+    _run(["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-fPIC", "-shared", "-Wall", "-Wextra", "-o", PLAN_LIB_PATH, PLAN_SOURCE], verbose)
     return PLAN_LIB_PATH
 
 

@@ -43,6 +43,8 @@
 namespace {
 #include "drot_common.h"
 #include "drot_sweep.h"
+#define DROT_FN __device__ __forceinline__
+#include "drot_bounds.h"
 #include "drot_screened.h"
 #include "drot_points.h"
 #include "drot_group_lasso.h"
@@ -776,7 +778,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   const plan::Static& S = Z.S;
 
   Z.V = VecState{h->phi, h->varphi, h->a, h->b, h->theta, h->sum_p, h->r, h->s, h->part, h->resid, h->done, h->status};
-  hipLaunchKernelGGL(mask_tail_kernel, dim3(1), dim3(256), 0, stream, h->varphi, h->varphi0, h->drift, n);
+  hipLaunchKernelGGL(mask_tail_kernel, dim3(1), dim3(256), 0, stream, h->varphi, h->varphi0, h->moved, h->drift, n);
   if (resume) hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(1), 0, stream, Z.V);
   else if (!A.warm) hipLaunchKernelGGL(init_kernel, dim3(1), dim3(1024), 0, stream, Z.V, A.p, A.q, m, n);
 

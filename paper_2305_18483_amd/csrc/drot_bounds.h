@@ -1,0 +1,35 @@
+// The screening bounds by line and the certificates of the lean sweep: plain arithmetic, no HIP in here.  drot.hip
+// includes it with DROT_FN set for device code, the CPU tests compile the same lines for the host.
+
+// The bounds by line: how far below M the largest t_j of each of the segment's eight 128-byte lines (32 columns) lies, one
+// byte per line.  The byte is the number's exponent and three bits of its fraction, cut off (towards 0: M minus the
+// decoded number is never below the line's true maximum), over 32 octaves around the size of rho (costs are of order 1):
+// from 2^-15 rho, below which it says 0, to 2^17 rho, where it saturates.
+DROT_FN int line_code_base(float rho) { return ((__builtin_bit_cast(int, rho) >> 23) - 15) * 8; }
+DROT_FN unsigned line_code(float below, int base) {
+  const int code = (__builtin_bit_cast(int, below) >> 20) - base;
+  return (unsigned)(code < 0 ? 0 : code > 255 ? 255 : code);
+}
+DROT_FN float line_decode(unsigned code, int base) {
+  return code == 0 ? 0.f : __builtin_bit_cast(float, ((int)code + base) << 20);
+}
+
+// The two certificates of the lean sweep.  A segment: max(M + drift of column j*, M2 + largest drift) + phi_i; one of its
+// lines: M minus the line's byte (below: decoded) + the line's drift + phi_i.  (With the drift of the line of j* in place
+// of its own, three times as many lines are read after a hundred sweeps.)  mag: magnitude of the largest drift plus that of
+// varphi.  Margin 16 half units in the last place (2^-20) of what stands beside M.  With u half a unit, a number t_j on
+// record is off by u |t_j|, a drift d_j by u |d_j|, their sum and the sum with phi_i by u of what they come to, and the
+// sweep adds phi_i to varphi_j within u of that.  Where the true sum is close to zero, |t_j| <= |d_j| + |phi_i|, and all of
+// it is at most u (2 |d_j| + 3 |phi_i| + |varphi_j|); where |t_j| is more than twice |d_j| + |phi_i|, the sign is that of
+// t_j.  Of column j* the drift can be anything: its magnitude is drift1's own.  Any other column lies below M2 + drift by
+// at least what its drift is below the largest one, which covers u of it.  (The line's byte: M counts as well.)
+constexpr float kLeanEps = 9.53674316e-7f;  // 2^-20
+DROT_FN bool certified_segment(float m1, float m2, float drift1, float drift, float mag, float ph) {
+  const float bound = fmaxf(m1 + drift1, m2 + drift) + ph;
+  return bound + kLeanEps * (fabsf(ph) + mag + fabsf(drift1)) <= 0.f;  // (-inf where every pair of the segment is forbidden)
+}
+DROT_FN bool certified_line(float m1, float below, float drift, float mag, float ph) {
+  if (m1 == -INFINITY) return true;
+  const float bound = ((m1 - below) + drift) + ph;
+  return bound + kLeanEps * (fabsf(m1) + fabsf(ph) + mag) <= 0.f;
+}

@@ -1,12 +1,17 @@
-// Host-only wrapper of the launch planner (drot_plan.h) for tests that run without a GPU.
+// Host-only wrapper of the launch planner (drot_plan.h) and of the screening certificates (drot_bounds.h) for tests that
+// run without a GPU.
 //
 // drot_plan_trace() replays the host loop of a solve -- stretches, sweeps, statuses read one stretch
 // late -- with the densities and the stop a test scripts in place of what a GPU would report, and
 // writes down what the planner decided for every sweep.  Built with a plain C++ compiler into
 // libdrot_plan.so; the product library includes the same header and does not use this file.
+#include <cmath>
 #include <cstring>
 
 #include "drot_plan.h"
+
+#define DROT_FN inline
+#include "drot_bounds.h"
 
 using namespace drot_plan;
 
@@ -146,6 +151,18 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   carry[11] = (long long)(F.bounds_rho * 1e9 + 0.5);
   *iters_done = reported;
   return nrows;
+}
+
+// The lean sweep's certificates for `count` row segments resp. lines.  lines: below is encoded and decoded with rho first.
+void drot_certify_segments(int count, const float* m1, const float* m2, const float* drift1, const float* drift, const float* mag,
+                           const float* phi, unsigned char* out) {
+  for (int k = 0; k < count; ++k) out[k] = certified_segment(m1[k], m2[k], drift1[k], drift[k], mag[k], phi[k]);
+}
+void drot_certify_lines(int count, float rho, const float* m1, const float* below, const float* drift, const float* mag,
+                        const float* phi, unsigned char* out) {
+  const int base = line_code_base(rho);
+  for (int k = 0; k < count; ++k)
+    out[k] = certified_line(m1[k], line_decode(line_code(below[k], base), base), drift[k], mag[k], phi[k]);
 }
 
 // Grid-resident stretches: problem, options as in drot_plan_trace.  out[4]: tiles per workgroup (0: none), rows per tile,

@@ -79,19 +79,6 @@ __device__ __forceinline__ void segment_top2(f4v t, int lane, float& M, int& jst
   M2 = wave_max(lane == L ? m2l : m1);  // (a tie between lanes leaves M2 = M)
 }
 
-// The bounds by line: how far below M the largest t_j of each of the segment's eight 128-byte lines (32 columns) lies, one
-// byte per line.  The byte is the number's exponent and three bits of its fraction, cut off (towards 0: M minus the
-// decoded number is never below the line's true maximum), over 32 octaves around the size of rho (costs are of order 1):
-// from 2^-15 rho, below which it says 0, to 2^17 rho, where it saturates.
-__device__ __forceinline__ int line_code_base(float rho) { return ((fbits(rho) >> 23) - 15) * 8; }
-__device__ __forceinline__ unsigned line_code(float below, int base) {
-  const int code = (fbits(below) >> 20) - base;
-  return (unsigned)min(max(code, 0), 255);
-}
-__device__ __forceinline__ float line_decode(unsigned code, int base) {
-  return code == 0 ? 0.f : __builtin_bit_cast(float, ((int)code + base) << 20);
-}
-
 // Largest of the four values of a lane over the eight lanes that hold one line.
 __device__ __forceinline__ float line_max(f4v t) {
   float v = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w));
@@ -117,23 +104,6 @@ __device__ __forceinline__ unsigned lines_of(unsigned long long lanes) {
   lanes |= lanes >> 2;
   lanes |= lanes >> 1;
   return (unsigned)(((lanes & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
-}
-
-// The two certificates of the lean sweep.  A segment: max(M + drift of column j*, M2 + largest
-// drift) + phi_i; one of its lines: M minus the line's byte (below: decoded) + the line's drift + phi_i.  (With the drift
-// of the line of j* in place of its own, three times as many lines are read after a hundred sweeps.)  mag: magnitude of
-// the drift plus that of varphi.  Margin 16 half units in the last place (2^-20) of what stands beside M: the record, the
-// drift, the sums here and the sweep's own evaluation round by at most 14 of them altogether where |M| (or |M2|) is no
-// more than twice |drift| + |phi_i|, and where it is more, the sign is that of M.  (The line's byte: M counts as well.)
-constexpr float kLeanEps = 9.53674316e-7f;  // 2^-20
-__device__ __forceinline__ bool certified_segment(float m1, float m2, float drift1, float drift, float mag, float ph) {
-  const float bound = fmaxf(m1 + drift1, m2 + drift) + ph;
-  return bound + kLeanEps * (fabsf(ph) + mag) <= 0.f;  // (-inf where every pair of the segment is forbidden)
-}
-__device__ __forceinline__ bool certified_line(float m1, float below, float drift, float mag, float ph) {
-  if (m1 == -INFINITY) return true;
-  const float bound = ((m1 - below) + drift) + ph;
-  return bound + kLeanEps * (fabsf(m1) + fabsf(ph) + mag) <= 0.f;
 }
 
 // The certificate, evaluated by lane l for row l from its record (m1, m2, j) and phi_l; dv: this lane's

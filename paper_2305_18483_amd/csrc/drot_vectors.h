@@ -53,11 +53,12 @@ __global__ __launch_bounds__(1024) void init_kernel(VecState V, const float* __r
 // varphi and the screening epoch's copy of it hold the mask value from column n to the end of the last
 // 256-column segment (the sweeps load them without an edge case).  One workgroup.
 __global__ __launch_bounds__(256) void mask_tail_kernel(float* __restrict__ varphi, float* __restrict__ varphi0,
-                                                       float2* __restrict__ drift, int n) {
+                                                       float* __restrict__ moved, float2* __restrict__ drift, int n) {
   const int j = n + (int)threadIdx.x;
   if (j < (n + kSegCols - 1) / kSegCols * kSegCols) {
     varphi[j] = kMaskedOut;
     varphi0[j] = kMaskedOut;
+    if (moved) moved[j] = 0.f;  // (j* of a row segment whose pairs are all forbidden can lie there)
   }
   // (lines of columns past n: no drift, whatever is there)
   const int line = (n + 31) / 32 + (int)threadIdx.x;

@@ -21,8 +21,9 @@ FRESH_CARRY = (0, -1000000, -1, 8, 0, 0, 0, 0)  # (what is left out of a carry i
 def planlib():
     from paper_2305_18483_amd import build
 
-    if not os.path.exists(build.PLAN_LIB_PATH) or os.path.getmtime(build.PLAN_LIB_PATH) < max(
-            os.path.getmtime(build.PLAN_SOURCE), os.path.getmtime(os.path.join(os.path.dirname(build.PLAN_SOURCE), "drot_plan.h"))):
+    csrc = os.path.dirname(build.PLAN_SOURCE)
+    sources = (build.PLAN_SOURCE, os.path.join(csrc, "drot_plan.h"), os.path.join(csrc, "drot_bounds.h"))
+    if not os.path.exists(build.PLAN_LIB_PATH) or os.path.getmtime(build.PLAN_LIB_PATH) < max(map(os.path.getmtime, sources)):
         build.build_plan()
     lib = ctypes.CDLL(build.PLAN_LIB_PATH)
     lib.drot_plan_trace.restype = ctypes.c_int
@@ -195,6 +196,56 @@ def test_bounds_go_on_only_to_calls_with_the_cost_and_the_stepsize_they_were_rec
         assert (lean == 0) == same
         if not same:  # nothing certified before a sweep of this call has recorded the bounds
             assert full_kind[second["from_points"]] in kinds[:lean] and 5 not in kinds[:lean]
+
+
+def test_what_the_certificates_of_the_sweep_by_lines_pass_stays_zero(planlib):
+    # four columns of a line or row segment with x = 0: the bounds recorded at an epoch, the certificate evaluated after
+    # varphi has moved, the sweep's own value beside it.  Entries on the edge of becoming positive, a column that has moved
+    # up to 2^12 times as far as everything else is large, every column of the four as the recorded one
+    f = np.float32
+    fma = lambda a, b, c: (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(f)  # noqa: E731
+    fp, up = ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_ubyte)
+
+    def certify(entry, *arrays):
+        out = np.zeros(len(arrays[-1]), dtype=np.uint8)
+        held = [np.ascontiguousarray(a, dtype=f) if isinstance(a, np.ndarray) else ctypes.c_float(a) for a in arrays]
+        entry(len(out), *[a.ctypes.data_as(fp) if isinstance(a, np.ndarray) else a for a in held], out.ctypes.data_as(up))
+        return out.astype(bool)
+
+    rng = np.random.default_rng(23)
+    N, rho = 400000, f(2.0 / 4000)
+    for ratio in (1.0, 4.0, 16.0, 64.0, 4096.0):
+        for fallen in (True, False):
+            small = f(1.0e-4)
+            phi = (small * rng.uniform(-1, 1, N)).astype(f)
+            now = (small * rng.uniform(-1, 1, (N, 4))).astype(f)
+            then = (now + small * rng.uniform(-1, 1, (N, 4)) * rng.choice([0.0, 1.0], (N, 1))).astype(f)
+            big = (ratio * small * rng.uniform(0.5, 1, N)).astype(f)
+            then[:, 0] = big if fallen else -big  # the one that moves far
+            # the first column (and at random the others) within a few units of the edge, the others well below it
+            edge = (now.astype(np.float64) + phi[:, None].astype(np.float64))
+            cost = (edge / float(rho) * (1 + rng.uniform(-8, 8, (N, 4)) * 2.0 ** -24)
+                    + rng.uniform(-4, 4, (N, 4)) * 2.0 ** -24 * (ratio * float(small)) / float(rho)).astype(f)
+            cost[:, 1:] += (rng.choice([0.0, 1.0, 50.0], (N, 3)) * float(small) / float(rho)).astype(f)
+            rhos = np.full((N, 4), rho, dtype=f)
+            t = fma(-rhos, cost, then)
+            order = np.argsort(-t, axis=1, kind="stable")
+            star = order[:, 0]
+            m1, m2 = np.take_along_axis(t, order[:, :1], 1)[:, 0], np.take_along_axis(t, order[:, 1:2], 1)[:, 0]
+            moved = (now - then).astype(f)
+            drift1 = np.take_along_axis(moved, star[:, None], 1)[:, 0]
+            drift = moved.max(axis=1)
+            mag = (np.abs(drift) + np.abs(now).max(axis=1)).astype(f)
+            value = fma(-rhos, cost, (now + phi[:, None]).astype(f)).max(axis=1)  # what the sweep clamps
+            passed = certify(planlib.drot_certify_segments, m1, m2, drift1, drift, mag, phi)
+            assert not (passed & (value > 0)).any(), (ratio, fallen, int((passed & (value > 0)).sum()))
+            # the same four as a line of a segment whose largest t lies further up
+            top = (m1 + rng.choice([0.0, 0.3, 30.0], N) * float(rho)).astype(f)
+            line = certify(planlib.drot_certify_lines, float(rho), top, (top - m1).astype(f), drift, mag, phi)
+            assert not (line & (value > 0)).any(), (ratio, fallen, int((line & (value > 0)).sum()))
+            # neither is vacuous: a hundred units below the edge almost everything passes
+            low = (phi - f(2.0e-4) * f(ratio)).astype(f)
+            assert certify(planlib.drot_certify_segments, m1, m2, drift1, drift, mag, low).mean() > 0.5
 
 
 def test_a_stop_at_a_check_forgets_what_the_sweeps_queued_behind_it_would_have_left(planlib):
