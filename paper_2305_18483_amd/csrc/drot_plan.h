@@ -142,6 +142,7 @@ struct Static {
   bool can_pair = false, adaptive_pairs = false, may_screen = false, adaptive = false;
   bool points_screen = false;    // point-cloud variant: screened sweeps once the plan is known to be sparse
   int refresh_max = kMaxRefreshPeriod;
+  bool lean_fits = false;        // the rows of a tile of the lean sweep are within 32 bits of bytes from its first one
   bool early_lines = false;      // the lean sweep does not wait for a sparse plan
   double pairs_until = 0.5;      // the pairs end below this fraction of nonzero row segments
   int sums_strip = kSegCols;
@@ -201,7 +202,9 @@ inline Static make_static(const Problem& P, const Options& O) {
                     (O.screening > 0 || (O.screening == -1 && (size_t)m * (size_t)n >= kScreenFrom));
   S.adaptive = P.feedback && (S.adaptive_pairs || S.may_screen || S.points_screen);
   // (smaller problems, screened when asked to, lie in the caches: lines gain nothing over row segments there)
-  S.early_lines = P.line_bounds && S.may_screen && (size_t)m * (size_t)n >= kScreenFrom;
+  // (offsets of 32 bits within a tile: rows of up to 16.7 million columns; wider ones stay with the 8-wave tiles)
+  S.lean_fits = (size_t)kTallTileRows * 4 * (size_t)S.ld_pad <= 0xffffffffu;
+  S.early_lines = S.lean_fits && P.line_bounds && S.may_screen && (size_t)m * (size_t)n >= kScreenFrom;
   if (S.early_lines) S.pairs_until = 0.995;  // (below it the sweep by lines waits)
   S.refresh_max = O.screening >= 2 ? O.screening : kMaxRefreshPeriod;
   S.sums_strip = P.slab_k ? kSlabCols : kSegCols;
@@ -388,7 +391,7 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
     // row segments still nonzero.  At 20000 x 20000 sweeps 9 to 96 took 24 ms in row segments and take 9 by lines)
     const bool sparse = T.plan_density >= 0.0 && T.plan_density < 0.25;
     const bool drift_known = !P.line_bounds || T.drift_gen == sw - 1;
-    lean = screened && T.epoch_gen >= 0 && Q.prev_sums && drift_known && (sparse || (S.early_lines && T.by_lines && !T.dense_lines));
+    lean = screened && S.lean_fits && T.epoch_gen >= 0 && Q.prev_sums && drift_known && (sparse || (S.early_lines && T.by_lines && !T.dense_lines));
     Q.refresh = screened && !lean && (T.epoch_gen < 0 || sw - T.epoch_gen >= T.refresh_period);
     tiles64 = R.tall && !Q.first && mode == 0;
     if (tiles64) Q.tilesum = true;

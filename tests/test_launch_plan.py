@@ -119,6 +119,13 @@ def test_cold_start_of_a_large_sparse_problem_moves_to_the_lean_sweep(planlib):
     assert set(t.col("mode")) == {0}
 
 
+def test_the_lean_sweep_stays_within_its_32_bit_offsets(planlib):
+    # 64 rows of a tile, 4 bytes an entry, counted from the tile's first row: up to 2^24 - 1 columns, rounded up to whole lines
+    for n, fits in ((16777184, True), (16777185, False), (17200000, False)):
+        t = trace(planlib, 64, n, 130, reg_kind=1, checking=0, densities=(0.05,), lines=(0.01,), line_bounds=1)
+        assert (7 in t.col("kind")) == fits and 6 in t.col("kind"), n
+
+
 def test_gap_pass_goes_lean_once_bounds_and_flags_describe_the_plan(planlib):
     # stretch ends of the cold start above: no bounds after the first sweeps of a call; row-segment sums serve as
     # flags after the 8-wave sweeps, the line flags after lean sweeps; never on paths that do not screen
