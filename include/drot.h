@@ -167,6 +167,12 @@ int drot_destroy(drot_handle h);
  *       32 columns in one workgroup's registers, 12 bytes per element) when every class has at most 1024 rows,
  *       consecutive or, unless the classes are many and small (under 48 rows on average), anywhere; and
  *       otherwise the two-pass path (any labels, 20 bytes per element); 1 forces the two-pass path.
+ *   DROT_OPT_GRID_POLLS [33554432], 1 .. 1073741824: how often a workgroup of a cooperative launch asks for a
+ *       number that another one owes it before the launch gives up (the default is about half a minute).  Such a
+ *       launch needs all its workgroups on the GPU at once; where it gives up, or is not accepted, the handle
+ *       launches every sweep by itself from then on (every handle of the process, where the runtime has no such
+ *       launches for it: it lets one process at a time have them on a GPU).  A solve that starts from X_0 = 0 is run again that way, within
+ *       the call; a warm or continued one returns DROT_ERR_HIP (X_inout is lost).
  *   DROT_OPT_NONTEMPORAL [-1], -1/0/1: mark the sweep's loads and stores of X and C non-temporal (best when
  *       they are far larger than the caches); -1 decides from 8*m*n bytes.  Same results.
  */
@@ -182,7 +188,8 @@ typedef enum {
   DROT_OPT_FUSED_UPDATE = 8,
   DROT_OPT_RESIDENT = 9,
   DROT_OPT_GROUP_TWO_PASS = 10,
-  DROT_OPT_NONTEMPORAL = 11
+  DROT_OPT_NONTEMPORAL = 11,
+  DROT_OPT_GRID_POLLS = 12
 } drot_option;
 
 int drot_set_option(drot_handle h, drot_option option, int value);
@@ -333,7 +340,7 @@ int drot_solve_points_warm(drot_handle h, const float* xs, const float* xt, int 
  * that need no report on the plan's density (no even/odd pairs, no lean sweep; same iterates as drot_solve
  * unless that switches to the even/odd pairs).  The return value says whether the work was enqueued (DROT_OK),
  * not whether the tolerance was reached: read info_out (iters -1: a launch whose workgroups wait for one another gave up,
- * after half a minute, on one that found no place on the GPU; the outputs are not valid).
+ * after half a minute, on one that found no place on the GPU; X_out, phi_out and varphi_out are filled with NaN then).
  * All calls on one GPU share the one workspace, which keeps the last call's contents (everything that must
  * start from zero is cleared by the call): calls that overlap on one GPU -- from two streams or two threads --
  * race; calls on different GPUs are independent.

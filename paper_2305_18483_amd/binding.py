@@ -31,7 +31,7 @@ EXPORTED_SYMBOLS = (
 # drot_option
 (DROT_OPT_CHECK_EVERY, DROT_OPT_COMPUTE_GAP, DROT_OPT_GAP_EVERY, DROT_OPT_CONTINUE, DROT_OPT_PROFILE,
  DROT_OPT_SKIP_UNCHANGED, DROT_OPT_SCREENING, DROT_OPT_SKIP_COST, DROT_OPT_FUSED_UPDATE, DROT_OPT_RESIDENT,
- DROT_OPT_GROUP_TWO_PASS, DROT_OPT_NONTEMPORAL) = range(12)
+ DROT_OPT_GROUP_TWO_PASS, DROT_OPT_NONTEMPORAL, DROT_OPT_GRID_POLLS) = range(13)
 
 
 class drot_reg_params(ctypes.Structure):
@@ -150,9 +150,13 @@ def solve_static(C: torch.Tensor, p: torch.Tensor, q: torch.Tensor, X_out: torch
 
 
 def read_info(info_out: torch.Tensor) -> drot_info:
-    """The drot_info block a drot_solve_static call left in a device buffer (synchronises with the device)."""
+    """The drot_info block a drot_solve_static call left in a device buffer (synchronises with the device).  Raises
+    DrotError where a launch of that call gave up (its outputs hold no plan)."""
     raw = info_out.view(torch.uint8).cpu().numpy().tobytes()[:ctypes.sizeof(drot_info)]
-    return drot_info.from_buffer_copy(raw)
+    info = drot_info.from_buffer_copy(raw)
+    if info.iters < 0:
+        raise DrotError(DROT_ERR_HIP, "drot_solve_static")
+    return info
 
 
 class Solver:
@@ -211,6 +215,9 @@ class Solver:
 
     def set_nontemporal(self, mode: int) -> None:
         self.set_option(DROT_OPT_NONTEMPORAL, mode)
+
+    def set_grid_polls(self, attempts: int) -> None:
+        self.set_option(DROT_OPT_GRID_POLLS, attempts)
 
     def set_gap_tolerance(self, gap_tol: float) -> None:
         rc = self._lib.drot_set_gap_tolerance(self._h, float(gap_tol))

@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -148,9 +149,10 @@ struct drot_handle_s {
   float* gpart = nullptr;   // two-pass path: [nchunks][n] squared sums of the chunks
   size_t gpart_len = 0;
   int max_runs = 0;       // rows of colpart available
-  // grid-resident stretches: compute units of the device (0: no cooperative launches), the exchange buffer (made on
-  // demand) and the last number used in it
+  // grid-resident stretches: compute units of the device (0: no cooperative launches, or none any more), how long their
+  // waits last, the exchange buffer (made on demand) and the last number used in it
   int compute_units = 0;
+  int grid_polls = kGridPolls;
   u64* xchg = nullptr;
   size_t xchg_len = 0;
   unsigned xchg_tag = 0;
@@ -458,7 +460,26 @@ GridWords grid_words(const plan::Static& S, int m, int n) {
   return W;
 }
 
-// The sweeps first .. last of a stretch, and all their vector updates but the last one's, in one launch.
+constexpr int kMaxDevices = 64;
+
+// Devices on which the runtime has told this process that it gets no cooperative launches at all (hipErrorIllegalState:
+// the driver lets one process at a time have them, and another one does).  To be told so takes 40 ms a time, so nobody
+// asks again.
+std::atomic<bool> g_no_cooperative[kMaxDevices];
+
+// Compute units for grid-resident stretches (0: no cooperative launches).
+int cooperative_units(int device) {
+  int cooperative = 0, units = 0;
+  if (device < 0 || device >= kMaxDevices || g_no_cooperative[device].load(std::memory_order_relaxed)) return 0;
+  if (hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, device) != hipSuccess || !cooperative) return 0;
+  return hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess ? units : 0;
+}
+
+// What a solve returns inside this file where a cooperative launch was not accepted, and where one gave up waiting.
+constexpr int kGridRefused = -1001, kGridGaveUp = -1002;
+
+// The sweeps first .. last of a stretch, and all their vector updates but the last one's, in one launch.  kGridRefused:
+// nothing has been enqueued that counts.
 int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   drot_handle h = Z.h;
   const plan::Static& S = Z.S;
@@ -469,6 +490,10 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   const GridWords W = grid_words(S, Z.m, Z.n);
   const size_t need = 2 * W.half, had = h->xchg_len;
   const int rc = grow_buffer(&h->xchg, &h->xchg_len, need, Z.stream);
+  if (rc == DROT_ERR_ALLOC) {
+    (void)hipGetLastError();
+    return kGridRefused;
+  }
   if (rc != DROT_OK) return rc;
   // (words that carry no number yet, and, should the numbers ever run out, none that carries an old one)
   if (h->xchg_len != had || h->xchg_tag > 0xffffffffu - (unsigned)iters - 1u) h->xchg_clean = false;
@@ -506,6 +531,7 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   A.nblk_n = nblk_n;
   A.iters = iters;
   A.first = first.first ? 1 : 0;
+  A.polls = h->grid_polls;
   A.tag0 = h->xchg_tag + 1;
   h->xchg_tag += (unsigned)iters;
   const int wgs = S.grid_wgs;
@@ -525,7 +551,13 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
       default: e = launch_grid<16, 16, 2, 5, 2, 1>(A, wgs, Z.stream); break;
     }
   }
-  DROT_HIP(e);
+  // (a device that reports more compute units than this process or stream may use, for one; what is wrong with more than
+  // the launch shows at the single launches that follow)
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (e == hipErrorIllegalState) g_no_cooperative[h->device].store(true, std::memory_order_relaxed);
+    return kGridRefused;
+  }
   return DROT_OK;
 }
 
@@ -724,7 +756,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   P.feedback = !A.fixed_schedule;
   P.checking = A.tol > 0.f;
   P.max_iters = A.max_iters;
-  P.compute_units = h->compute_units;
+  P.compute_units = h->compute_units > 0 && g_no_cooperative[h->device].load(std::memory_order_relaxed) ? 0 : h->compute_units;
   P.line_bounds = h->codes != nullptr;
   P.prompt_looks = !A.fixed_schedule;
   P.single_launches = h->profile != 0;  // (every launch timed)
@@ -887,15 +919,22 @@ int iterate(Solve& Z, bool* converged_out) {
     const int k_end = Z.T.k + R.chunk;
     const int grid_head = plan::grid_head(S, Z.P, Z.T, R);
     for (int c = 0; Z.T.k < k_end; ++c) {
-      const plan::Step Q = plan::next_sweep(S, Z.P, Z.O, Z.T, R, c);
       if (c == grid_head) {  // the rest of the stretch in one launch
-        plan::Step L = Q;
-        while (Z.T.k < k_end) L = plan::next_sweep(S, Z.P, Z.O, Z.T, R, ++c);
-        const int rc = enqueue_grid(Z, Q, L);
-        if (rc != DROT_OK) return rc;
-        enqueue_update(Z, L);
-        break;
+        const plan::State before = Z.T;
+        const plan::Step F = plan::next_sweep(S, Z.P, Z.O, Z.T, R, c);
+        plan::Step L = F;
+        for (int e = c; Z.T.k < k_end;) L = plan::next_sweep(S, Z.P, Z.O, Z.T, R, ++e);
+        const int rc = enqueue_grid(Z, F, L);
+        if (rc == DROT_OK) {
+          enqueue_update(Z, L);
+          break;
+        }
+        if (rc != kGridRefused) return rc;
+        Z.T = before;  // (one by one, here and in the solves to come)
+        Z.P.single_launches = true;
+        h->compute_units = 0;
       }
+      const plan::Step Q = plan::next_sweep(S, Z.P, Z.O, Z.T, R, c);
       const bool timed = h->profile && h->prof_used < kMaxProfiled;
       const int pe = h->prof_used;
       if (timed) {
@@ -933,7 +972,7 @@ int iterate(Solve& Z, bool* converged_out) {
       auto read_status = [&](int which) -> int {
         DROT_HIP(hipEventSynchronize(h->ev[which]));
         const DeviceStatus& st = h->host_status[which];
-        if (st.broken) return DROT_ERR_HIP;
+        if (st.broken) return kGridGaveUp;
         if (st.converged) converged = true;
         if (!was_probe[which]) record_check(h, st);
         plan::on_status(S, Z.T, st.nz_segments / ((double)Z.m * (double)S.nseg),
@@ -956,7 +995,7 @@ int iterate(Solve& Z, bool* converged_out) {
   return DROT_OK;
 }
 
-int solve_impl(drot_handle h, const SolveCall& A) {
+int solve_once(drot_handle h, const SolveCall& A) {
   Solve Z;
   int rc = prepare(h, A, Z);
   if (rc != DROT_OK) {
@@ -994,7 +1033,7 @@ int solve_impl(drot_handle h, const SolveCall& A) {
     return fail(DROT_ERR_HIP);
 
   const DeviceStatus& st = h->host_status[0];
-  if (st.broken) return fail(DROT_ERR_HIP);
+  if (st.broken) return fail(kGridGaveUp);
   h->prof_count = 0;
   if (h->profile) {
     const int timed = h->prof_used;
@@ -1026,6 +1065,17 @@ int solve_impl(drot_handle h, const SolveCall& A) {
   return DROT_OK;
 }
 
+// A launch that gave up leaves no plan.  From then on the handle launches every sweep by itself; a cold start is run again
+// that way, a warm or continued one has lost the point it started from and reports the error.
+int solve_impl(drot_handle h, const SolveCall& A) {
+  const bool cold = h && !A.warm && !h->continue_next;
+  int rc = solve_once(h, A);
+  if (rc != kGridGaveUp) return rc;
+  fprintf(stderr, "drot: a launch whose workgroups wait for one another gave up; single launches from now on\n");
+  h->compute_units = 0;
+  return cold ? solve_once(h, A) : DROT_ERR_HIP;
+}
+
 // ------------------------------------------------------------------------------------------
 // drot_solve_static: the same solve out of a workspace that is part of the loaded code object, for
 // callers that cannot allocate.  Every GPU holds its own copy of the array at its own address.
@@ -1034,7 +1084,6 @@ constexpr int kStaticMaxM = DROT_STATIC_MAX_M, kStaticMaxN = DROT_STATIC_MAX_N;
 constexpr size_t kScratchBytes = (size_t)12 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
-constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch`, per device (the array's name is no device address on the host)
 std::mutex g_scratch_mutex;
 
@@ -1102,18 +1151,30 @@ size_t carve_static(drot_handle_s& H, unsigned char* base) {
   return off;
 }
 
-// Result block and dual vectors from the workspace into the caller's device buffers.
+// Result block and dual vectors from the workspace into the caller's device buffers.  Where a launch gave up, NaN goes
+// into all of them and into the plan: a caller that does not ask for the block must not take them for a result.
 __global__ __launch_bounds__(256) void export_kernel(const DeviceStatus* __restrict__ st, drot_info* __restrict__ info,
                                                      const float* __restrict__ phi, const float* __restrict__ varphi,
-                                                     float* __restrict__ phi_out, float* __restrict__ varphi_out, int m, int n,
-                                                     int max_iters) {
+                                                     float* __restrict__ X_out, float* __restrict__ phi_out,
+                                                     float* __restrict__ varphi_out, int m, int n, int max_iters) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+  if (st->broken) {
+    constexpr unsigned kNaN = 0x7fc00000u;
+    auto fill = [&](float* out, size_t count) {
+      for (size_t e = t; out && e < count; e += stride) reinterpret_cast<unsigned*>(out)[e] = kNaN;
+    };
+    fill(X_out, (size_t)m * (size_t)n);
+    fill(phi_out, (size_t)m);
+    fill(varphi_out, (size_t)n);
+    if (t == 0 && info) *info = drot_info{-1, 0, INFINITY, INFINITY, 0.0, 0.0, 0.0};
+    return;
+  }
   if (phi_out)
     for (int i = t; i < m; i += stride) phi_out[i] = phi[i];
   if (varphi_out)
     for (int j = t; j < n; j += stride) varphi_out[j] = varphi[j];
   if (t == 0 && info) {
-    info->iters = max_iters == 0 ? 0 : st->broken ? -1 : st->iters;
+    info->iters = max_iters == 0 ? 0 : st->iters;
     info->converged = st->converged;
     info->r_row = max_iters == 0 ? INFINITY : (float)sqrt(st->r2);
     info->r_col = max_iters == 0 ? INFINITY : (float)sqrt(st->s2);
@@ -1146,10 +1207,7 @@ int solve_static_impl(SolveCall A, float* phi_out, float* varphi_out, drot_info*
   int rc = static_workspace(H.device, &base);
   if (rc != DROT_OK) return rc;
   carve_static(H, base);
-  int cooperative = 0, units = 0;
-  if (hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, H.device) == hipSuccess && cooperative &&
-      hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, H.device) == hipSuccess)
-    H.compute_units = units;
+  H.compute_units = cooperative_units(H.device);
   A.fixed_schedule = true;
   Solve Z;
   rc = prepare(&H, A, Z);
@@ -1161,7 +1219,7 @@ int solve_static_impl(SolveCall A, float* phi_out, float* varphi_out, drot_info*
   if (Z.T.k > 0) enqueue_status(Z, Z.T.k, Z.P.checking, false);
   enqueue_gap(Z, nullptr, false);
   hipLaunchKernelGGL(export_kernel, dim3(16), dim3(256), 0, Z.stream, (const DeviceStatus*)H.status, info_out,
-                     (const float*)H.phi, (const float*)H.varphi, phi_out, varphi_out, A.m, A.n, A.max_iters);
+                     (const float*)H.phi, (const float*)H.varphi, A.X_out, phi_out, varphi_out, A.m, A.n, A.max_iters);
   DROT_HIP(hipGetLastError());
   return DROT_OK;
 }
@@ -1194,10 +1252,7 @@ int drot_create(drot_handle* out, int max_m, int max_n) {
   }
   h->max_m = max_m;
   h->max_n = max_n;
-  int cooperative = 0, units = 0;
-  if (hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, h->device) == hipSuccess && cooperative &&
-      hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess)
-    h->compute_units = units;
+  h->compute_units = cooperative_units(h->device);
   const size_t nseg = (size_t)ceil_div(max_n, kSegCols);
   const size_t ntr = (size_t)ceil_div(max_m, kTileRows);
   const size_t nb = (size_t)ceil_div(max_m, 64) + (size_t)ceil_div(max_n, 64);
@@ -1304,6 +1359,10 @@ int drot_set_option(drot_handle h, drot_option option, int value) {
       h->opt.resident = value;
       return DROT_OK;
     case DROT_OPT_GROUP_TWO_PASS: h->opt.force_two_pass = value ? 1 : 0; return DROT_OK;
+    case DROT_OPT_GRID_POLLS:
+      if (!in(1, kGridPollsMax)) return DROT_ERR_INVALID_ARG;
+      h->grid_polls = value;
+      return DROT_OK;
     case DROT_OPT_NONTEMPORAL:
       if (!in(-1, 1)) return DROT_ERR_INVALID_ARG;
       h->opt.nontemporal = value;

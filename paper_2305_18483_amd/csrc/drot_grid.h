@@ -36,11 +36,16 @@
 // launches do, and the ordinary vector update follows it.
 //
 // The workgroups wait for one another, so they must all be on the chip: a cooperative launch, at most one workgroup per
-// compute unit.  Every wait is bounded: a word that has not come after kGridPolls attempts (about half a minute) ends the kernel
-// with the `broken` mark in the status block and the stop flag up, which the host reports as an error.
+// compute unit.  Every wait is bounded: a word that has not come after GridArgs::polls attempts (2^25 as a rule, about half a
+// minute) ends the kernel with the `broken` mark in the status block and the stop flag up.  The host goes back to single
+// launches then, as it does where the launch is refused.
+// This kernel has not been seen to give up of itself.  The same exchange, in a form for the slabs of the group lasso that
+// was tried and taken out, has, at one shape (three slabs, five workgroups that only own blocks, a kernel with spilled
+// registers), and neither reading it nor running it on a CPU showed why: a wait that runs out is taken for possible here.
 // ------------------------------------------------------------------------------------------
 typedef unsigned long long u64;
 constexpr int kGridPolls = 1 << 25;
+constexpr int kGridPollsMax = 1 << 30;
 constexpr int kGridBlock = 8;    // rows or columns per owner wave
 constexpr int kGridCopies = 32;  // of 2 eta - theta: workgroup b reads copy b % kGridCopies
 
@@ -67,6 +72,7 @@ struct GridArgs {
   int iters;              // sweeps to run (>= 2)
   int first;              // X_0 = 0: nothing to read
   unsigned tag0;          // the exchange of sweep k (counted from 0) carries the number tag0 + k; never 0
+  int polls;              // attempts before a wait is given up (>= 1)
 };
 
 // (a word is addressed by its number in the buffer's half: a scalar base and 32 bits of offset)
@@ -84,15 +90,15 @@ __device__ __forceinline__ double grid_value(u64 hi, u64 lo) { return __builtin_
 // Fetches the words at[0 .. N-1] until every lane has all of its own with the number `tag`.  All of them are asked for
 // again together: a word waited for by itself would cost a trip to the memory-side cache each.
 template <int N>
-__device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const unsigned (&at)[N], unsigned tag, bool& lost) {
-  for (int polls = 0;; ++polls) {
+__device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const unsigned (&at)[N], unsigned tag, int limit, bool& lost) {
+  for (int polls = 1;; ++polls) {
     bool there = true;
 #pragma unroll
     for (int k = 0; k < N; ++k) v[k] = grid_load(half, at[k]);
 #pragma unroll
     for (int k = 0; k < N; ++k) there = there && (unsigned)(v[k] >> 32) == tag;
     if (__builtin_amdgcn_ballot_w64(!there) == 0) return;
-    if (polls > kGridPolls) {
+    if (polls >= limit) {
       lost = true;
       return;
     }
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         unsigned at[NP];
 #pragma unroll
         for (int b = 0; b < NP; ++b) at[b] = part_word + part_lane + (unsigned)(min(part_index(k0, b), nparts - 1) * kGridBlock);
-        grid_gather<NP>(half, v, at, tag, lost);
+        grid_gather<NP>(half, v, at, tag, A.polls, lost);
         if (!grouped) {
 #pragma unroll
           for (int b = 0; b < NP; ++b) sh[b & 1] += part_index(k0, b) < nparts ? (double)grid_value(v[b]) : 0.0;
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
           unsigned at[G];
 #pragma unroll
           for (int b = 0; b < G; ++b) at[b] = A.tot_word + (unsigned)(e * G + (total_there(e, b) ? b : 0));
-          grid_gather<G>(half, v, at, tag, lost);
+          grid_gather<G>(half, v, at, tag, A.polls, lost);
           float g = grid_value(v[0]);
 #pragma unroll
           for (int b = 1; b < G; ++b) g += total_there(e, b) ? grid_value(v[b]) : 0.f;
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         at[2 * k] = from + 2u * (unsigned)min(lane, last);
         at[2 * k + 1] = at[2 * k] + 1;
       }
-      grid_gather<2 * kSlots + 2>(half, v, at, tag, lost);
+      grid_gather<2 * kSlots + 2>(half, v, at, tag, A.polls, lost);
       const double cst = grid_value(v[2 * kSlots], v[2 * kSlots + 1]);
 #pragma unroll
       for (int k = 0; k < kSlots; ++k) {
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     if (failed[1]) break;
   }
 
-  if (failed[0] || failed[1]) {  // (never seen: a workgroup that is not on the chip)
+  if (failed[0] || failed[1]) {  // (a workgroup that is not on the chip, or a word lost)
     if (t == 0) {
       A.status->broken = 1;
       __threadfence();

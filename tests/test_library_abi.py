@@ -65,6 +65,22 @@ def test_struct_layouts_match_the_header():
     assert binding.drot_reg_params.weights.offset == 24
 
 
+def test_an_info_block_of_a_launch_that_gave_up_is_no_result():
+    import pytest
+    import torch
+
+    from paper_2305_18483_amd import binding
+
+    def block(iters):
+        info = binding.drot_info(iters, 0, 1.0, 2.0, 3.0, 4.0, 5.0)
+        return torch.frombuffer(bytearray(bytes(info)) + bytearray(24), dtype=torch.uint8)
+
+    assert binding.read_info(block(7)).iters == 7 and binding.read_info(block(0)).objective == 3.0
+    with pytest.raises(binding.DrotError) as e:
+        binding.read_info(block(-1))
+    assert e.value.code == binding.DROT_ERR_HIP
+
+
 def test_input_generators_are_seeded_and_normalised():
     import numpy as np
 

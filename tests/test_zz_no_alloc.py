@@ -121,3 +121,25 @@ def test_static_entry_point_under_graph_capture(drot):
         other = torch.empty_like(C)
         drot.solve_static(C, p, q, other, **dict(kw, max_iters=57))
         torch.cuda.synchronize()
+
+
+def test_static_entry_point_returns_before_the_stream_has_run(drot):
+    # a schedule with cooperative launches in it, behind work that takes a while: the call comes back first
+    dev = torch.device("cuda:0")
+    P = drot_inputs.random_problem(1000, 1024, seed=5120, reg_kind=1, lam=0.3)
+    C, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.p, P.q))
+    X = torch.empty_like(C)
+    kw = dict(reg_kind=1, lam=P.lam, max_iters=1000, tol=1e-12)
+    drot.solve_static(C, p, q, X, **kw)  # (what a first call loads is loaded)
+    torch.cuda.synchronize()
+    ref = X.clone()
+    big = torch.empty(1 << 28, device=dev)
+    _say("returns without waiting")
+    for _ in range(300):
+        big.fill_(1.0)  # (1 GiB each: some 70 ms in all)
+    drot.solve_static(C, p, q, X, **kw)
+    ev = torch.cuda.Event()
+    ev.record()
+    assert not ev.query()
+    torch.cuda.synchronize()
+    assert torch.equal(X, ref)
