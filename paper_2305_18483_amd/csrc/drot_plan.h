@@ -69,7 +69,11 @@ constexpr int kGridTiles32 = 5;       // 32-row tiles (two rows per wave, 16 wav
 constexpr int kGridTiles64 = 3;       // 64-row tiles (eight rows per wave, 8 waves of 256 registers)
 constexpr int kGridWaves32 = 16, kGridWaves64 = 8;
 constexpr int kGridBlock = 8;         // rows or columns whose part of eq. (6) a wave forms
-constexpr int kGridMinSweeps = 4;     // shorter stretches are not worth fetching the plan and the cost for
+// Shorter stretches are not worth fetching the plan and the cost for.  Per iteration, in single launches and in one launch,
+// stretches of 4, 6, 8 and 10 sweeps: 200 x 300 10.4 and 13.6 us, 8.9 and 10.1, 8.3 and 8.5, 7.9 and 7.4; 1000 x 1000 11.3
+// and 13.7, 9.9 and 10.2, 9.9 and 8.5, 9.4 and 7.5 (one tile a workgroup); 2048 x 3072 24.0 and 18.5 at 4, 64-row tiles of
+// 2300 x 2500 17.8 and 17.8, 2999 x 3307 21.3 and 21.3.
+constexpr int kGridMinSweeps = 4, kGridMinSweepsOneTile = 8;
 // (a full sweep takes 230 to 260 us at 12000 x 12000, d = 32, the screened one 7 for every percent of the row segments left)
 constexpr double kPointsSparse = 0.33;
 constexpr int kPromptLooksUntil = 128; // ... of which the host waits for those of a point-cloud solve until the plan is sparse
@@ -465,7 +469,8 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
   if (!S.grid_tiles || P.single_launches) return -1;
   const bool cold = T.k_base + T.k == 0 && !P.warm;
   const int head = S.grid_tall && cold ? 1 : 0;
-  return R.chunk - head >= kGridMinSweeps ? head : -1;
+  const int least = !S.grid_tall && S.grid_tiles == 1 ? kGridMinSweepsOneTile : kGridMinSweeps;
+  return R.chunk - head >= least ? head : -1;
 }
 
 // A status has come back: the density of the plan it reports steers the next stretches

@@ -339,11 +339,13 @@ __global__ __launch_bounds__(kReduceThreads) void residual_norms_kernel(VecState
   if (*V.done) return;
   __shared__ double red[kReduceThreads];
   sum_residual_norms(V, nbm, nbn, red);
-  double lines = 0.0;
-  if (reads)
+  double lines = -1.0;
+  if (reads) {
+    lines = 0.0;
     for (int e = threadIdx.x; e < nwg; e += kReduceThreads) lines += (double)(reads[e] - waste[e]);
-  lines = block_sum_f64(lines, red);
-  if (threadIdx.x == 0) V.resid[3] = reads ? lines : -1.0;
+    lines = block_sum_f64(lines, red);
+  }
+  if (threadIdx.x == 0) V.resid[3] = lines;
 }
 
 // Both halves of S5 in one launch, for the sweeps on 64-row tiles of large problems.  What stands

@@ -429,7 +429,10 @@ def test_grid_resident_stretches_where_the_registers_of_the_chip_hold_the_proble
     # every row and column needs a wave to form its part of eq. (6), eight to a wave
     assert grid(32, 5000)[:2] == (1, 32) and grid(2, 65000)[0] == 0
     # short stretches and callers that want every sweep in a launch of its own
-    assert grid(1000, 1000, check_every=3)[2] == -1 and grid(1000, 1000, iters=3)[2] == -1 and grid(1000, 1000, iters=4)[2] == 0
+    assert grid(1000, 1000, check_every=3)[2] == -1 and grid(1000, 1000, iters=3)[2] == -1
+    assert grid(1000, 1000, iters=7)[2] == -1 and grid(1000, 1000, iters=8)[2] == 0          # one tile a workgroup: 8 sweeps
+    assert grid(2048, 3072, iters=3)[2] == -1 and grid(2048, 3072, iters=4)[2] == 0          # more tiles, or 64-row tiles: 4
+    assert grid(2999, 3307, iters=4)[2] == -1 and grid(2999, 3307, iters=5)[2] == 1 and grid(2049, 256, iters=5)[2] == 1
     assert grid(1000, 1000, single=1)[2] == -1 and grid(1000, 1000, units=0)[0] == 0
     assert grid(1000, 1000, units=32)[0] == 4 and grid(2048, 2048, units=32)[0] == 0  # a smaller partition of the chip
     assert grid(1000, 1000, from_points=1)[0] == 0 and grid(1000, 1000, reg_kind=2)[0] == 0
