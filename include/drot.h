@@ -152,9 +152,10 @@ int drot_destroy(drot_handle h);
  *       sweep; the better scheme for dense plans, as the skipping is for sparse ones.  -1 follows the plan:
  *       the vector update counts the nonzero row segments (the sweep by lines its lines), the host reads the
  *       count with the status of every stretch (one stretch late, without waiting) and switches to the pairs above
- *       90 % nonzero row segments (85 % of the lines) and back below 50 % (99.5 % of the row segments where the
- *       sweep by lines waits); never for problems held in registers; with a switch the result depends, within rounding, on check_every and on how a
- *       solve is cut into continued calls.  1: pairs wherever they apply; 0: never.
+ *       90 % nonzero row segments (85 % of the lines) and back below 50 % (where the sweep by lines waits, at
+ *       90 %, in the first 512 iterations below 99.5 %); never for problems held in registers; with a switch the
+ *       result depends, within rounding, on check_every and on how a solve is cut into continued calls.
+ *       1: pairs wherever they apply; 0: never.
  *   DROT_OPT_FUSED_UPDATE [-1], -1/0: small problems (at most 2048 rows and 4096 tiles of 32 x 256) compute
  *       the O(m+n) update of eq. (6) at the head of the next sweep, one launch per iteration instead of
  *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations up to the

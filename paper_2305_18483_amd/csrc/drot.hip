@@ -758,7 +758,6 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   P.max_iters = A.max_iters;
   P.compute_units = h->compute_units > 0 && g_no_cooperative[h->device].load(std::memory_order_relaxed) ? 0 : h->compute_units;
   P.line_bounds = h->codes != nullptr;
-  P.prompt_looks = !A.fixed_schedule;
   P.single_launches = h->profile != 0;  // (every launch timed)
   if (A.fixed_schedule) {
     // (a captured graph would replay the exchange with the numbers of its first run)

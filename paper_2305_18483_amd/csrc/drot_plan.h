@@ -112,8 +112,7 @@ struct Problem {
   bool checking = false;      // a tolerance was given
   int max_iters = 0;
   int compute_units = 0;      // workgroups of a cooperative launch that are on the chip together (0: no such launches)
-  bool prompt_looks = false;     // the host may wait for an early look at the density
-  bool line_bounds = false;      // the workspace holds the bounds by line: the lean sweep need not wait for a sparse plan
+  bool line_bounds = false;      // the workspace holds the bounds by line, without which there is no lean sweep
   bool single_launches = false;  // every sweep in a launch of its own all the same (profile mode, callers that may capture)
 };
 
@@ -148,7 +147,7 @@ struct Static {
   int refresh_max = kMaxRefreshPeriod;
   bool lean_fits = false;        // the rows of a tile of the lean sweep are within 32 bits of bytes from its first one
   bool early_lines = false;      // the lean sweep does not wait for a sparse plan
-  double pairs_until = 0.5;      // the pairs end below this fraction of nonzero row segments
+  double pairs_until = 0.5;      // the pairs end below this fraction of nonzero row segments, where they would not start
   int sums_strip = kSegCols;
   int grid_tiles = 0;            // grid-resident stretches: tiles per workgroup, 0: none
   int grid_wgs = 0;              // ... and workgroups
@@ -209,7 +208,7 @@ inline Static make_static(const Problem& P, const Options& O) {
   // (offsets of 32 bits within a tile: rows of up to 16.7 million columns; wider ones stay with the 8-wave tiles)
   S.lean_fits = (size_t)kTallTileRows * 4 * (size_t)S.ld_pad <= 0xffffffffu;
   S.early_lines = S.lean_fits && P.line_bounds && S.may_screen && (size_t)m * (size_t)n >= kScreenFrom;
-  if (S.early_lines) S.pairs_until = 0.995;  // (below it the sweep by lines waits)
+  if (S.early_lines) S.pairs_until = 0.995;  // (the sweep by lines waits: whatever does not start the pairs ends them)
   S.refresh_max = O.screening >= 2 ? O.screening : kMaxRefreshPeriod;
   S.sums_strip = P.slab_k ? kSlabCols : kSegCols;
   S.status_at_checks = P.checking || S.adaptive || O.gap_every > 0;
@@ -278,7 +277,7 @@ inline Stretch next_stretch(const Static& S, const Problem& P, const Options& O,
     if (S.adaptive && !P.resume && k < kEarlyLooksUntil) {
       // (point clouds: every 8 iterations at first, read at once.  Not to know for 32 to 64 sweeps that the plan has
       // become sparse costs 10 ms of 44 at 12000 x 12000, waiting 10 us a look)
-      const bool often = P.prompt_looks && P.from_points && k < kPromptLooksUntil && !(T.plan_density >= 0.0 && T.plan_density < kPointsSparse);
+      const bool often = P.from_points && k < kPromptLooksUntil && !(T.plan_density >= 0.0 && T.plan_density < kPointsSparse);
       const int next = k < 16 ? 16 : often ? (k / 8 + 1) * 8 : (k / 32 + 1) * 32;
       R.prompt = often;
       if (next - k < R.chunk) {
@@ -346,20 +345,20 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
     if (S.points_screen) {
       // full sweeps record the bounds; the screened sweep runs on them while the plan is
       // known to be sparse, until they are due for renewal (after 8, 16, 32, ... sweeps: varphi moves fast at first).
-      // Where the host looks at the density promptly only the last full sweep before a look need record them, every
-      // other one is a tenth faster without (12000 x 12000: 285 instead of 320 us)
+      // Only the last full sweep before a look at the density need record them, every other one is a tenth faster without
+      // (12000 x 12000: 285 instead of 320 us)
       const bool due = T.epoch_gen < 0 || sw - T.epoch_gen >= T.refresh_period;
-      const bool sparse = T.plan_density >= 0.0 && T.plan_density < (P.prompt_looks ? kPointsSparse : 0.25);
+      const bool sparse = T.plan_density >= 0.0 && T.plan_density < kPointsSparse;
       const bool lean_points = !Q.first && !due && Q.prev_sums && sparse;
       if (lean_points) {
         Q.sweep = kPointsLean;
         Q.profile_kind = 8;
         Q.ra_ntr = ceil_div(P.m, kStripRows);
         Q.ra_cgroup = 1;
-      } else if (!Q.first && (!P.prompt_looks || sparse || c == R.chunk - 1)) {
+      } else if (!Q.first && (sparse || c == R.chunk - 1)) {
         Q.refresh = true;
         Q.profile_kind = 9;
-        if (T.epoch_gen >= 0 && due && (!P.prompt_looks || sparse))
+        if (T.epoch_gen >= 0 && due && sparse)
           T.refresh_period = T.refresh_period * 2 < S.refresh_max ? T.refresh_period * 2 : S.refresh_max;
         T.epoch_gen = sw;
       }
@@ -394,8 +393,7 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
     // (by lines: from the second epoch of bounds on -- sweep 9 of a cold start, with 70 to 80 % of the lines and all of the
     // row segments still nonzero.  At 20000 x 20000 sweeps 9 to 96 took 24 ms in row segments and take 9 by lines)
     const bool sparse = T.plan_density >= 0.0 && T.plan_density < 0.25;
-    const bool drift_known = !P.line_bounds || T.drift_gen == sw - 1;
-    lean = screened && S.lean_fits && T.epoch_gen >= 0 && Q.prev_sums && drift_known && (sparse || (S.early_lines && T.by_lines && !T.dense_lines));
+    lean = screened && S.lean_fits && T.epoch_gen >= 0 && Q.prev_sums && T.drift_gen == sw - 1 && (sparse || (S.early_lines && T.by_lines && !T.dense_lines));
     Q.refresh = screened && !lean && (T.epoch_gen < 0 || sw - T.epoch_gen >= T.refresh_period);
     tiles64 = R.tall && !Q.first && mode == 0;
     if (tiles64) Q.tilesum = true;
@@ -474,7 +472,8 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
 }
 
 // A status has come back: the density of the plan it reports steers the next stretches
-// (hysteresis; the early looks never start the pairs: every plan is dense in its first iterations).  Above 90 % of the row
+// (hysteresis; the early looks never start the pairs: every plan is dense in its first iterations; where the sweep by lines
+// waits they end them below 99.5 %, the checks, which see the same number, where they would not start them).  Above 90 % of the row
 // segments nonzero: the sweeps that skip what is zero leave out a few percent of the bytes there, the pairs a sixth.
 // lines: fraction of the lines of X that hold a nonzero, where the last sweep counted them (else negative).  It is the
 // better measure (at 8191 x 8191 with a strong quadratic term 95 % of the row segments but 34 % of the lines are nonzero

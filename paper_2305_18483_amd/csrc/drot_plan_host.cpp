@@ -17,8 +17,8 @@ using namespace drot_plan;
 
 extern "C" {
 
-// problem[17]: m, n, reg_kind, from_points, warm, resume, has_weights, c_on_lines, x_on_lines, slab_k,
-//              nruns, feedback, checking, max_iters, line_bounds, prompt_looks, rho * 1e9
+// problem[16]: m, n, reg_kind, from_points, warm, resume, has_weights, c_on_lines, x_on_lines, slab_k,
+//              nruns, feedback, checking, max_iters, line_bounds, rho * 1e9
 // options[9]:  check_every, resident, fused_update, skip_cost, skip_unchanged, screening, nontemporal,
 //              force_two_pass, gap_every
 // carry[12] (in and out): dense_plan, plan_density * 1e6, epoch_gen, refresh_period, sums_valid, sums_strip,
@@ -49,8 +49,7 @@ int drot_plan_trace(const int* problem, const int* options, long long* carry, co
   P.checking = problem[12] != 0;
   P.max_iters = problem[13];
   P.line_bounds = problem[14] != 0;
-  P.prompt_looks = problem[15] != 0;
-  P.rho = (float)problem[16] * 1e-9f;
+  P.rho = (float)problem[15] * 1e-9f;
   P.tilesum_half = (size_t)ceil_div(P.n, kSegCols) * (size_t)ceil_div(P.m, kTileRows);
   if (P.tilesum_half < 4096) P.tilesum_half = 4096;
   Options O;

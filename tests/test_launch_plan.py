@@ -42,9 +42,11 @@ class Trace:
 def trace(lib, m, n, max_iters, reg_kind=0, from_points=0, warm=0, resume=0, weights=0, c_on_lines=1, x_on_lines=1,
           slab_k=0, nruns=0, feedback=1, checking=1, check_every=100, resident=-1, fused_update=-1, skip_cost=-1,
           skip_unchanged=-1, screening=-1, nontemporal=-1, force_two_pass=0, gap_every=0, densities=(), lines=None,
-          stop_at_status=-1, carry=FRESH_CARRY, line_bounds=0, prompt_looks=0, rho=0):
-    problem = (ctypes.c_int * 17)(m, n, reg_kind, from_points, warm, resume, weights, c_on_lines, x_on_lines, slab_k, nruns,
-                                  feedback, checking, max_iters, line_bounds, prompt_looks, rho)
+          stop_at_status=-1, carry=FRESH_CARRY, line_bounds=None, rho=0):
+    # (a handle holds the bounds by line, the fixed workspace, whose schedule has no feedback, does not)
+    line_bounds = feedback if line_bounds is None else line_bounds
+    problem = (ctypes.c_int * 16)(m, n, reg_kind, from_points, warm, resume, weights, c_on_lines, x_on_lines, slab_k, nruns,
+                                  feedback, checking, max_iters, line_bounds, rho)
     options = (ctypes.c_int * 9)(check_every, resident, fused_update, skip_cost, skip_unchanged, screening, nontemporal,
                                  force_two_pass, gap_every)
     carry_io = (ctypes.c_longlong * 12)(*carry)
@@ -97,9 +99,57 @@ def test_padded_copies_when_rows_are_off_the_128_byte_lines(planlib):
     assert s["resident"] and not s["pad_c"] and not s["pad_x"]               # the resident kernel takes any pitch
 
 
-def test_cold_start_of_a_large_sparse_problem_moves_to_the_lean_sweep(planlib):
+def test_cold_start_of_a_large_problem_moves_to_lines_after_two_epochs_of_bounds(planlib):
+    t = trace(planlib, 20000, 20000, 300, reg_kind=1, checking=1, densities=(0.9, 0.6, 0.2, 0.05), lines=(0.3, 0.1, 0.04, 0.03))
+    kinds = t.col("kind")
+    # sweep 1 has nothing to read; sweeps 2 and 8 record the bounds, the sweep by lines runs from 9 on whatever the density,
+    # on the line flags that sweep 8 leaves, and renews by itself
+    assert kinds == [0, 6] + [5] * 5 + [6] + [7] * 292
+    assert t.col("lines_in") == [0] * 8 + [1] * 292
+    ends = [i + 1 for i, f in enumerate(t.col("flags")) if f & 1]
+    assert ends[:6] == [16, 32, 64, 96, 100, 128]
+    assert [bool(t.col("flags")[e - 1] & 2) for e in ends[:6]] == [True, True, True, True, False, True]
+    assert set(t.col("update")[1:]) == {MERGED_TILES} and t.col("update")[0] == SEPARATE
+    # column partials: 625 rows for the 32-row tiles, 313 in groups of four for the 64-row tiles, 79 for the lean sweep
+    assert t.col("ra")[0] == 625 * 16 + 1 and t.col("ra")[5] == 313 * 16 + 4 and t.col("ra")[100] == 79 * 16 + 1
+    assert set(t.col("mode")) == {0}
+    assert t.carry[8] == 1 and t.carry[9] == 1 and t.carry[6] == 1  # by lines, drift and line flags as a continued call finds them
+    # a third of the lines nonzero in nearly all row segments: still by lines; with a period that was asked for, sooner
+    t = trace(planlib, 20000, 20000, 700, reg_kind=1, checking=1, densities=(0.95,), lines=(0.34,))
+    assert set(t.col("kind")[8:]) == {7}
+    t = trace(planlib, 20000, 20000, 30, reg_kind=1, checking=1, screening=3, densities=(0.95,), lines=(0.34,))
+    assert t.col("kind")[:8] == [0, 6, 5, 5, 6, 7, 7, 7]
+
+
+def test_dense_lines_go_to_the_even_odd_pairs_and_come_back(planlib):
+    # statuses 0 .. 21 end the looks of the first 512 iterations and the checks among them, then there is one every 100
+    steps = [(1.0, 0.97)] * 22 + [(0.99, 0.4)] * 3 + [(0.89, 0.4)]
+    t = trace(planlib, 20000, 20000, 1500, reg_kind=1, checking=1, densities=[d for d, _ in steps], lines=[x for _, x in steps])
+    kinds = t.col("kind")
+    # early looks start nothing; the check at 100, read while 101 .. 128 are queued, does (more than 85 % of the lines)
+    assert set(kinds[8:128]) == {7} and kinds[128:130] == [1, 2]
+    # back at a check that finds no more than 90 % of the row segments nonzero (its status is read while the next stretch is
+    # queued): bounds first, then the lines
+    back = kinds.index(6, 128)
+    ends = [i + 1 for i, f in enumerate(t.col("flags")) if f & 1]
+    assert ends[21] == 512 and set(kinds[128:back]) == {1, 2} and back == ends[26]
+    assert set(kinds[back + 1:]) == {7} and t.col("lines_in")[back + 1] == 1
+    # at an early look below 99.5 % (half of the lines, were they independent)
+    steps = [(1.0, 0.97)] * 9 + [(0.996, 0.4), (0.994, 0.4)]
+    t = trace(planlib, 20000, 20000, 500, reg_kind=1, checking=1, densities=[d for d, _ in steps], lines=[x for _, x in steps])
+    kinds, ends = t.col("kind"), [i + 1 for i, f in enumerate(t.col("flags")) if f & 1]
+    assert t.col("flags")[ends[10] - 1] & 2 and kinds.index(6, 128) == ends[11] and set(kinds[128:ends[11]]) == {1, 2}
+    # between 85 and 92 % of the lines: pairs as well; below, the lines stay although no row segment is empty
+    t = trace(planlib, 20000, 20000, 400, reg_kind=1, checking=1, densities=(1.0,), lines=(0.9,))
+    assert set(t.col("kind")[128:]) == {1, 2}
+    t = trace(planlib, 20000, 20000, 400, reg_kind=1, checking=1, densities=(1.0,), lines=(0.8,))
+    assert set(t.col("kind")[8:]) == {7}
+
+
+def test_cold_start_of_a_small_screened_problem_moves_to_the_lean_sweep(planlib):
+    # (screened because it was asked for; below 11.5 million entries the sweep by lines waits for a sparse plan)
     # statuses: the looks after 16, 32, 64 ... iterations report 90 %, 60 %, 20 %, 5 % nonzero row segments
-    t = trace(planlib, 20000, 20000, 300, reg_kind=1, checking=1, densities=(0.9, 0.6, 0.2, 0.05))
+    t = trace(planlib, 2300, 2500, 300, reg_kind=1, checking=1, screening=1, densities=(0.9, 0.6, 0.2, 0.05))
     kinds = t.col("kind")
     # sweep 1 has nothing to read; sweep 2 records the bounds, then after 8, 16, 32 sweeps again
     assert kinds[:12] == [0, 6] + [5] * 7 + [6, 5, 5]
@@ -113,8 +163,8 @@ def test_cold_start_of_a_large_sparse_problem_moves_to_the_lean_sweep(planlib):
     assert first_lean == 96 and set(kinds[96:]) == {7}
     assert t.col("lines_in")[96] == 0 and set(t.col("lines_in")[97:]) == {1}  # flags are valid from one lean sweep to the next
     assert set(t.col("update")[1:]) == {MERGED_TILES} and t.col("update")[0] == SEPARATE
-    # column partials: 625 rows for the 32-row tiles, 313 in groups of four for the 64-row tiles, 79 for the lean sweep
-    assert t.col("ra")[0] == 625 * 16 + 1 and t.col("ra")[5] == 313 * 16 + 4 and t.col("ra")[100] == 79 * 16 + 1
+    # column partials: 72 rows for the 32-row tiles, 36 in groups of four for the 64-row tiles, 9 for the lean sweep
+    assert t.col("ra")[0] == 72 * 16 + 1 and t.col("ra")[5] == 36 * 16 + 4 and t.col("ra")[100] == 9 * 16 + 1
     # never the even/odd pairs here: the dense readings came from early looks
     assert set(t.col("mode")) == {0}
 
@@ -122,14 +172,16 @@ def test_cold_start_of_a_large_sparse_problem_moves_to_the_lean_sweep(planlib):
 def test_the_lean_sweep_stays_within_its_32_bit_offsets(planlib):
     # 64 rows of a tile, 4 bytes an entry, counted from the tile's first row: up to 2^24 - 1 columns, rounded up to whole lines
     for n, fits in ((16777184, True), (16777185, False), (17200000, False)):
-        t = trace(planlib, 64, n, 130, reg_kind=1, checking=0, densities=(0.05,), lines=(0.01,), line_bounds=1)
+        t = trace(planlib, 64, n, 130, reg_kind=1, checking=0, densities=(0.05,), lines=(0.01,))
         assert (7 in t.col("kind")) == fits and 6 in t.col("kind"), n
 
 
 def test_gap_pass_goes_lean_once_bounds_and_flags_describe_the_plan(planlib):
-    # stretch ends of the cold start above: no bounds after the first sweeps of a call; row-segment sums serve as
+    # stretch ends of the cold starts above: no bounds after the first sweeps of a call; row-segment sums serve as
     # flags after the 8-wave sweeps, the line flags after lean sweeps; never on paths that do not screen
     t = trace(planlib, 20000, 20000, 300, reg_kind=1, checking=1, check_every=100, densities=(0.9, 0.6, 0.2, 0.02))
+    assert all(f & 8 and f & 16 for f in t.col("flags") if f & 1)
+    t = trace(planlib, 2300, 2500, 300, reg_kind=1, checking=1, check_every=100, screening=1, densities=(0.9, 0.6, 0.2, 0.02))
     flags = t.col("flags")
     ends = {i + 1: f for i, f in enumerate(flags) if f & 1}
     assert all(f & 8 for f in ends.values())  # (bounds exist from sweep 2 on)
@@ -188,7 +240,7 @@ def test_a_continued_call_goes_on_where_the_last_one_stopped(planlib):
 def test_bounds_go_on_only_to_calls_with_the_cost_and_the_stepsize_they_were_recorded_with(planlib):
     # a solve over point clouds leaves bounds without the bounds by line, a stored-cost one none of the sweep's own costs;
     # both are of varphi - rho C: where the next call's cost comes from elsewhere, or its stepsize is another, it renews first
-    handle = dict(reg_kind=1, checking=0, line_bounds=1, prompt_looks=1)
+    handle = dict(reg_kind=1, checking=0)
     points = dict(handle, from_points=1, rho=50000, densities=(0.9, 0.6, 0.2, 0.05))
     stored = dict(handle, from_points=0, rho=50000, densities=(0.9, 0.6, 0.2, 0.05))
     lean_kind, full_kind = {0: 7, 1: 8}, {0: 6, 1: 9}
@@ -302,7 +354,8 @@ def test_point_clouds_and_warm_starts(planlib):
     # a warm start with the cost from point clouds: X_0 is read where its sums say so, and the sweep records bounds
     t = trace(planlib, 3000, 3000, 4, from_points=1, warm=1, reg_kind=1, checking=0, screening=1)
     assert set(t.col("sweep")) == {POINTS} and t.col("first") == [0, 0, 0, 0] and t.col("prev_sums") == [1, 1, 1, 1]
-    assert t.col("refresh") == [1, 1, 1, 1] and set(t.col("kind")) == {9}
+    # (the last sweep before a look at the density records the bounds)
+    assert t.col("refresh") == [0, 0, 0, 1] and t.col("kind") == [0, 0, 0, 9]
 
 
 def test_label_analysis(planlib):
@@ -386,15 +439,23 @@ def test_class_chunks_of_the_two_pass_group_lasso_path(planlib):
 
 
 def test_point_cloud_variant_screens_once_the_plan_is_sparse(planlib):
-    t = trace(planlib, 20000, 20000, 200, from_points=1, reg_kind=1, checking=0, densities=(0.9, 0.6, 0.2, 0.05))
+    # looks at 16, 24, 32, ... while the plan is dense, each read at once: 40 % are too many yet, 30 % are not
+    t = trace(planlib, 20000, 20000, 200, from_points=1, reg_kind=1, checking=0, densities=(0.9, 0.6, 0.4, 0.3, 0.05))
     kinds = t.col("kind")
-    assert kinds[0] == 0 and set(kinds[1:96]) == {9}        # full sweeps, all but the first recording the bounds
-    # lean from sweep 97 (the status after 64 iterations is read while the stretch to 96 is queued), on the bounds
-    # of sweep 96; they are renewed by one full sweep after 8 sweeps, then after 16, 32, ...
-    assert kinds[96:103] == [8] * 7 and kinds[103] == 9 and kinds[104:119] == [8] * 15 and kinds[119] == 9
-    assert t.col("sweep")[96] == POINTS_LEAN and t.col("sweep")[103] == POINTS
+    # full sweeps, the last one before a look recording the bounds
+    assert kinds[:40] == [0] * 15 + [9] + ([0] * 7 + [9]) * 3
+    ends = [i + 1 for i, f in enumerate(t.col("flags")) if f & 1]
+    assert ends[:7] == [16, 24, 32, 40, 64, 96, 100]
+    # lean from sweep 41, on the bounds of sweep 40; they are renewed by one full sweep after 8 sweeps, then after 16, 32, ...
+    assert kinds[40:47] == [8] * 7 and kinds[47] == 9 and kinds[48:63] == [8] * 15 and kinds[63] == 9
+    assert t.col("sweep")[40] == POINTS_LEAN and t.col("sweep")[47] == POINTS
+    # a plan that stays dense: looks every 8 iterations up to 128, then every 32
+    t2 = trace(planlib, 20000, 20000, 240, from_points=1, reg_kind=1, checking=0, densities=(0.9,))
+    ends = [i + 1 for i, f in enumerate(t2.col("flags")) if f & 1]
+    assert ends == sorted({16, 100, 200, 240} | set(range(24, 129, 8)) | {160, 192, 224}) and 8 not in t2.col("kind")
+    assert [k == 9 for k in t2.col("kind")] == [i + 1 in ends for i in range(240)]
     # column sums: eight 32-row tiles of the full sweep are added first, as the strips of the screened sweep store them
-    assert t.col("ra")[5] == 625 * 16 + 8 and t.col("ra")[100] == 79 * 16 + 1 and t.col("ra")[0] == 625 * 16 + 8
+    assert t.col("ra")[5] == 625 * 16 + 8 and t.col("ra")[41] == 79 * 16 + 1 and t.col("ra")[0] == 625 * 16 + 8
     # one launch for the vector update: the sweeps store the totals of their tiles (the screened one of its strips)
     assert set(t.col("update")) == {MERGED_TILES} and set(t.col("tilesum")) == {1}
     # small problems, or with the screening off: the full sweep only, column sums ungrouped
@@ -402,6 +463,12 @@ def test_point_cloud_variant_screens_once_the_plan_is_sparse(planlib):
     assert set(t.col("kind")) == {0} and set(t.col("ra")) == {94 * 16 + 8}
     t = trace(planlib, 20000, 20000, 120, from_points=1, reg_kind=1, checking=0, screening=0, densities=(0.05,))
     assert set(t.col("kind")) == {0}
+    # a warm start looks as early as a cold one; a continued call not at all before its checks, and records before them
+    t = trace(planlib, 20000, 20000, 60, from_points=1, warm=1, reg_kind=1, checking=0, densities=(0.3,))
+    assert t.col("kind")[:17] == [0] * 15 + [9, 8]
+    t = trace(planlib, 20000, 20000, 250, from_points=1, reg_kind=1, checking=1, resume=1, densities=(0.3,),
+              carry=(0, -1000000, -1, 8, 1, 256, 0, 100))
+    assert t.col("kind") == ([0] * 99 + [9]) * 2 + [8] * 7 + [9] + [8] * 15 + [9] + [8] * 26
     # a continued call goes on with the bounds it finds
     first = trace(planlib, 20000, 20000, 100, from_points=1, reg_kind=1, checking=0, densities=(0.9, 0.6, 0.2, 0.05))
     cont = trace(planlib, 20000, 20000, 20, from_points=1, reg_kind=1, checking=0, resume=1, carry=first.carry, densities=(0.05,))
