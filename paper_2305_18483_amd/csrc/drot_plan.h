@@ -482,7 +482,7 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
 inline void on_status(const Static& S, State& T, double density, double lines, bool was_probe) {
   if (!S.adaptive) return;
   T.plan_density = density;
-  if (lines >= 0.0) T.dense_lines = lines > 0.92 && !was_probe;
+  if (lines >= 0.0) T.dense_lines = lines > 0.92 && (T.dense_lines || !was_probe);
   else if (density < 0.995) T.dense_lines = false;  // (independent lines: 0.995 of the row segments are half of the lines)
   const bool dense = lines >= 0.0 ? lines > 0.85 : density > 0.9;
   if (dense && !was_probe) T.dense_plan = S.adaptive_pairs;

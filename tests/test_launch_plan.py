@@ -144,6 +144,9 @@ def test_dense_lines_go_to_the_even_odd_pairs_and_come_back(planlib):
     assert set(t.col("kind")[128:]) == {1, 2}
     t = trace(planlib, 20000, 20000, 400, reg_kind=1, checking=1, densities=(1.0,), lines=(0.8,))
     assert set(t.col("kind")[8:]) == {7}
+    # without the pairs, above 92 %: row segments, until lines pay again
+    t = trace(planlib, 20000, 20000, 400, reg_kind=1, checking=1, skip_cost=0, densities=(1.0,), lines=(0.97,))
+    assert set(t.col("kind")[8:128]) == {7} and 7 not in t.col("kind")[128:] and 5 in t.col("kind")[128:]
 
 
 def test_cold_start_of_a_small_screened_problem_moves_to_the_lean_sweep(planlib):
