@@ -1,5 +1,6 @@
-// The screening bounds by line and the certificates of the lean sweep: plain arithmetic, no HIP in here.  drot.hip
-// includes it with DROT_FN set for device code, the CPU tests compile the same lines for the host.
+// The screening bounds by line, the certificates of the lean sweep and the rule by which it renews its bounds: plain
+// arithmetic, no HIP in here.  drot.hip includes it with DROT_FN set for device code, the CPU tests compile the same lines
+// for the host.
 
 // The bounds by line: how far below M the largest t_j of each of the segment's eight 128-byte lines (32 columns) lies, one
 // byte per line.  The byte is the number's exponent and three bits of its fraction, cut off (towards 0: M minus the
@@ -32,4 +33,23 @@ DROT_FN bool certified_line(float m1, float below, float drift, float mag, float
   if (m1 == -INFINITY) return true;
   const float bound = ((m1 - below) + drift) + ph;
   return bound + kLeanEps * (fabsf(m1) + fabsf(ph) + mag) <= 0.f;
+}
+
+// When the lean sweep renews its bounds, the classic rent-or-buy rule: reading lines in vain (zero before and zero after:
+// the bounds failed to certify them) is the rent, renewing the bounds (all of C once) the purchase.  Renew when the rent
+// paid since the last renewal has reached the price.  That stays within a factor 2 of the best schedule in hindsight,
+// whatever the drift of varphi does, and needs no model of it.
+struct Renewal {
+  int renew;  // the next lean sweep renews the bounds
+  int since;  // lean sweeps since the last renewal
+  int paid;   // lines read in vain since
+};
+// After a lean sweep that read `waste` lines in vain, or, where it was asked to, has renewed the bounds.
+DROT_FN Renewal after_lean_sweep(Renewal R, int waste, int price, int max_since) {
+  if (R.renew) return Renewal{0, 0, 0};
+  constexpr int kMost = 1000000000;  // (a sum that stays in range whatever the size)
+  R.since += 1;
+  R.paid += waste < kMost - R.paid ? waste : kMost - R.paid;
+  R.renew = R.paid >= price || R.since >= max_since;
+  return R;
 }

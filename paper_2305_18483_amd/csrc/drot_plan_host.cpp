@@ -164,6 +164,15 @@ void drot_certify_lines(int count, float rho, const float* m1, const float* belo
     out[k] = certified_line(m1[k], line_decode(line_code(below[k], base), base), drift[k], mag[k], phi[k]);
 }
 
+// The renewals of `count` lean sweeps, waste[k] the lines the k-th reads in vain unless it renews the bounds: renewed[k].
+void drot_renewals(int count, const int* waste, int price, int max_since, unsigned char* renewed) {
+  Renewal R{0, 0, 0};
+  for (int k = 0; k < count; ++k) {
+    renewed[k] = R.renew != 0;
+    R = after_lean_sweep(R, waste[k], price, max_since);
+  }
+}
+
 // Grid-resident stretches: problem, options as in drot_plan_trace.  out[4]: tiles per workgroup (0: none), rows per tile,
 // sweeps launched one by one at the head of the first stretch (-1: all of them), automatic even/odd pairs.
 void drot_plan_grid(const int* problem, const int* options, int compute_units, int single_launches, int* out) {

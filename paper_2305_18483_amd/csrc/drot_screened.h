@@ -128,14 +128,9 @@ __device__ __forceinline__ bool certified_zero(float m1, float m2, unsigned j, f
   return bound + kEps * (fabsf(ph) + mag + fabsf(bound)) <= 0.f;
 }
 
-// Control words of the lean sweep's own refresh schedule (device memory, updated by
-// reduce_update_kernel after every lean sweep): the classic rent-or-buy rule.  Reading lines in vain (zero before and
-// zero after: the bounds failed to certify them) is the rent, renewing the bounds (all of C once) the purchase: renew
-// when the rent paid since the last renewal has reached the price.  That stays within a factor 2 of the best schedule in
-// hindsight, whatever the drift of varphi does, and needs no model of it.
-constexpr int kCtlRenew = 0;   // the next lean sweep renews the bounds
-constexpr int kCtlSince = 1;   // lean sweeps since the last renewal
-constexpr int kCtlPaid = 2;    // lines read in vain since
+// Control words of the lean sweep's own refresh schedule (device memory; a Renewal, brought up to date by
+// reduce_update_kernel after every lean sweep).
+constexpr int kCtlRenew = 0, kCtlSince = 1, kCtlPaid = 2;
 constexpr int kCtlWords = 4;
 
 constexpr int kScreenRows = 8, kScreenWaves = 8;
@@ -306,8 +301,6 @@ struct LeanTile {
   int waste;    // ... whose line of X was zero before and is zero after (a renewal: is zero after)
 };
 
-// New bounds (the vector update before this sweep has asked for them): every row segment is processed, four columns to a
-// lane, and its M, M2, j* and line bytes are recorded against the varphi of now.
 // Lane u: the lines of row u's segment of X that hold a nonzero (bit g: columns 32g .. 32g+31).  From the flags the
 // previous lean sweep, or the sweep that recorded the bounds, left; after any other sweep from the row sums (nonzero
 // sum: any line may hold something).
@@ -316,6 +309,8 @@ __device__ __forceinline__ unsigned lean_flags(const LeanArgs& A, size_t tile, u
   return (!A.sums_known || fbits((A.rowpart + tile)[ul]) != 0) ? 0xffu : 0u;
 }
 
+// New bounds (the vector update before this sweep has asked for them): every row segment is processed, four columns to a
+// lane, and its M, M2, j* and line bytes are recorded against the varphi of now.
 template <bool EDGE>
 __device__ __forceinline__ f4v lean_renew(const LeanArgs& A, int lane, int seg, int tr, LeanTile& out) {
   const int j0 = seg * kSegCols + lane * 4;
@@ -343,55 +338,39 @@ __device__ __forceinline__ f4v lean_renew(const LeanArgs& A, int lane, int seg, 
   unsigned newlines = 0;
   int nonzero_lines = 0;
   f4v tile_acc = {0.f, 0.f, 0.f, 0.f}, group_acc = {0.f, 0.f, 0.f, 0.f};
-  constexpr int kWalk = 1;
-  for (int u0 = 0; u0 < nrows; u0 += kWalk) {
-    f4v c[kWalk], x[kWalk];
-#pragma unroll
-    for (int b = 0; b < kWalk; ++b) {
-      const int u = min(u0 + b, nrows - 1);
-      c[b] = ld4<EDGE, false>(Cp + u * ldc, nmem);
-      x[b] = f4v{0.f, 0.f, 0.f, 0.f};
-      if (((unsigned)__builtin_amdgcn_readlane((int)oldlines, u) >> myline) & 1) x[b] = ld4<EDGE, false>(Xp + u * ldx, nmem);
+  for (int u = 0; u < nrows; ++u) {
+    const unsigned ol = (unsigned)__builtin_amdgcn_readlane((int)oldlines, u);
+    f4v x = {0.f, 0.f, 0.f, 0.f};
+    if ((ol >> myline) & 1) x = ld4<EDGE, false>(Xp + u * ldx, nmem);
+    const f4v c = ld4<EDGE, false>(Cp + u * ldc, nmem);
+    if ((u & 7) == 0 && u != 0) {
+      tile_acc += group_acc;
+      tile_tot += group_tot;
+      group_acc = f4v{0.f, 0.f, 0.f, 0.f};
+      group_tot = 0.f;
     }
-    unsigned wl[kWalk];
-#pragma unroll
-    for (int b = 0; b < kWalk; ++b) {
-      const int u = u0 + b;
-      wl[b] = 0;
-      if (u >= nrows) continue;
-      if ((u & 7) == 0 && u != 0) {
-        tile_acc += group_acc;
-        tile_tot += group_tot;
-        group_acc = f4v{0.f, 0.f, 0.f, 0.f};
-        group_tot = 0.f;
-      }
-      const float phu = __builtin_bit_cast(float, __builtin_amdgcn_readlane(fbits(ph), u));
-      const f4v v = xbar4(x[b], c[b], vp + phu, rho) * scale;
-      const bool nonzero = ((fbits(v.x) | fbits(v.y)) | (fbits(v.z) | fbits(v.w))) != 0;
-      const unsigned nl = lines_of(__builtin_amdgcn_ballot_w64(nonzero));
-      wl[b] = (unsigned)__builtin_amdgcn_readlane((int)oldlines, u) | nl;
-      newlines = (lane == u) ? nl : newlines;
-      nonzero_lines += __builtin_popcount(nl);
-      group_acc += v;
-      const float tot = wave_sum((v.x + v.y) + (v.z + v.w));
-      rowkeep = (lane == u) ? tot : rowkeep;
-      group_tot += tot;
-      const f4v t = {fmaf(-rho, c[b].x, vp.x), fmaf(-rho, c[b].y, vp.y), fmaf(-rho, c[b].z, vp.z), fmaf(-rho, c[b].w, vp.w)};
-      float mm, mm2;
-      int jj;
-      segment_top2(t, lane, mm, jj, mm2);
-      unsigned lo, hi;
-      line_codes(t, mm, base, lo, hi);
-      mkeep = (lane == u) ? mm : mkeep;
-      m2keep = (lane == u) ? mm2 : m2keep;
-      jkeep = (lane == u) ? jj : jkeep;
-      ckeep.x = (lane == u) ? lo : ckeep.x;
-      ckeep.y = (lane == u) ? hi : ckeep.y;
-      x[b] = v;
-    }
-#pragma unroll
-    for (int b = 0; b < kWalk; ++b)
-      if ((wl[b] >> myline) & 1) st4<EDGE, false>(Xp + (u0 + b) * ldx, x[b], nmem);
+    const float phu = __builtin_bit_cast(float, __builtin_amdgcn_readlane(fbits(ph), u));
+    const f4v v = xbar4(x, c, vp + phu, rho) * scale;
+    const bool nonzero = ((fbits(v.x) | fbits(v.y)) | (fbits(v.z) | fbits(v.w))) != 0;
+    const unsigned nl = lines_of(__builtin_amdgcn_ballot_w64(nonzero));
+    newlines = (lane == u) ? nl : newlines;
+    nonzero_lines += __builtin_popcount(nl);
+    group_acc += v;
+    const float tot = wave_sum((v.x + v.y) + (v.z + v.w));
+    rowkeep = (lane == u) ? tot : rowkeep;
+    group_tot += tot;
+    const f4v t = {fmaf(-rho, c.x, vp.x), fmaf(-rho, c.y, vp.y), fmaf(-rho, c.z, vp.z), fmaf(-rho, c.w, vp.w)};
+    float mm, mm2;
+    int jj;
+    segment_top2(t, lane, mm, jj, mm2);
+    unsigned lo, hi;
+    line_codes(t, mm, base, lo, hi);
+    mkeep = (lane == u) ? mm : mkeep;
+    m2keep = (lane == u) ? mm2 : m2keep;
+    jkeep = (lane == u) ? jj : jkeep;
+    ckeep.x = (lane == u) ? lo : ckeep.x;
+    ckeep.y = (lane == u) ? hi : ckeep.y;
+    if (((ol | nl) >> myline) & 1) st4<EDGE, false>(Xp + u * ldx, v, nmem);
   }
   tile_acc += group_acc;
   tile_tot += group_tot;

@@ -665,19 +665,13 @@ __global__ __launch_bounds__(64 * kMergedWaves) void reduce_update_kernel(Reduce
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(stop_ld)) return;
   if (t == 0 && blockIdx.x == gridDim.x - 1 && K.mode != 0) {
-    if (K.mode == 1 || renewed) {  // new bounds: nothing paid yet
-      K.ctl[kCtlRenew] = 0;
-      K.ctl[kCtlSince] = 0;
-      K.ctl[kCtlPaid] = 0;
-    } else {
-      int total = 0;
-      for (int k = 0; k < NW; ++k) total += readw[k];
-      const int since = K.ctl[kCtlSince] + 1;
-      const int paid = K.ctl[kCtlPaid] + min(total, 1000000000 - K.ctl[kCtlPaid]);
-      K.ctl[kCtlSince] = since;
-      K.ctl[kCtlPaid] = paid;
-      if (paid >= K.price || since >= K.max_since) K.ctl[kCtlRenew] = 1;
-    }
+    int total = 0;
+    for (int k = 0; k < NW; ++k) total += readw[k];
+    Renewal R{0, 0, 0};  // (a sweep that the host had renew the bounds: nothing paid yet)
+    if (K.mode == 2) R = after_lean_sweep(Renewal{renewed, K.ctl[kCtlSince], K.ctl[kCtlPaid]}, total, K.price, K.max_since);
+    K.ctl[kCtlRenew] = R.renew;
+    K.ctl[kCtlSince] = R.since;
+    K.ctl[kCtlPaid] = R.paid;
   }
   if (t >= kE) return;  // (waves 0 .. V - 1 finish: one entry per thread, one block of 64 entries per wave)
   // the 16 shares of the entry (the fixed tree sum_partials_16 ends with), the residual, the block's sums

@@ -1261,7 +1261,7 @@ def test_two_threads_solve_on_two_streams(drot):
 def test_sweeps_by_lines_change_no_bit(drot, m, n, scale, forbid):
     # from sweep 9 of a cold start the sweep moves 128-byte lines: a last tile of one row, a last column segment of one
     # column, forbidden pairs (whole lines without a bound), costs far above and below 1 (the line bytes saturate and
-    # vanish); renewals by the device's own rule and every 5 sweeps, against the sweeps that read all of C
+    # vanish); renewals by the device's own rule alone and every 5 sweeps at the latest, against the sweeps that read all of C
     P = drot_inputs.with_entrywise_terms(drot_inputs.random_problem(m, n, seed=2800 + m, d=5, reg_kind=1, lam=0.01),
                                          seed=2801, forbid_frac=forbid)
     P.C = (P.C * np.float32(scale)).astype(np.float32)
@@ -1281,8 +1281,12 @@ def test_sweeps_by_lines_change_no_bit(drot, m, n, scale, forbid):
         outs.append((X, phi, varphi, res.objective, res.gap))
         if mode:
             assert set(kinds[8:]) == {7}, kinds
+            # renewals read every line: the device's rule has asked for several (measured: 9 to 44 in these sweeps) and not for
+            # all; with a period of 5 there are no more than five sweeps between two
             reads = solver.profile_reads()
-            assert min(reads[8:]) < 0.5 and any(r == 1.0 for r in reads[9:]) == (mode == 5 or max(reads[20:]) == 1.0)
+            full = [k for k, r in enumerate(reads) if k >= 9 and r == 1.0]
+            assert min(reads[8:]) < 0.5 and 5 <= len(full) <= 60, full
+            assert mode != 5 or max(np.diff([8] + full + [230])) <= 6, full
     for other in outs[1:]:
         for a, b in zip(outs[0][:3], other[:3]):
             assert np.array_equal(a, b)

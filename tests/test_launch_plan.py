@@ -310,6 +310,34 @@ def test_what_the_certificates_of_the_sweep_by_lines_pass_stays_zero(planlib):
             assert certify(planlib.drot_certify_segments, m1, m2, drift1, drift, mag, low).mean() > 0.5
 
 
+def test_the_sweep_by_lines_renews_when_the_rent_has_reached_the_price(planlib):
+    def renewals(waste, price, max_since):
+        w = np.ascontiguousarray(waste, dtype=np.int32)
+        out = np.zeros(len(w), dtype=np.uint8)
+        planlib.drot_renewals(len(w), w.ctypes.data_as(ctypes.POINTER(ctypes.c_int)), price, max_since,
+                              out.ctypes.data_as(ctypes.POINTER(ctypes.c_ubyte)))
+        return np.flatnonzero(out).tolist()
+
+    assert renewals([10] * 40, 100, 1024) == [10, 21, 32]        # ten sweeps' rent, then the one that renews
+    assert renewals([10] * 40, 101, 1024) == [11, 23, 35]        # reached, not exceeded
+    assert renewals([0] * 40, 100, 5) == [5, 11, 17, 23, 29, 35]  # at the latest after max_since sweeps
+    assert renewals([0] * 3000, 100, 1024) == [1024, 2049]
+    assert renewals([99, 0, 0, 1, 7, 100, 3], 100, 1024) == [4, 6]  # what the renewing sweep itself reads counts for nothing
+    assert renewals([2 ** 31 - 1] * 6, 1000000000, 1024) == [1, 3, 5]  # (lines read in vain beyond the range of the sum)
+    # the sum of what was paid since the last renewal, with any rents
+    rng = np.random.default_rng(3)
+    waste, price = rng.integers(0, 50, 2000), 400
+    expect, paid, renew = [], 0, False
+    for k, w in enumerate(waste):
+        if renew:
+            expect.append(k)
+            paid, renew = 0, False
+        else:
+            paid += int(w)
+            renew = paid >= price
+    assert renewals(waste, price, 1024) == expect
+
+
 def test_a_stop_at_a_check_forgets_what_the_sweeps_queued_behind_it_would_have_left(planlib):
     # check_every 25, the check at iteration 100 passes; the stretch 101..125 is already queued, and the
     # host-ordered refresh at sweep 122 lies in it: it never runs, so the continued call must not count on it
