@@ -35,6 +35,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0      # MI355X published HBM3E bandwidth
 MFMA_F32_PEAK_TFLOPS = 157.3
+HELD_ENTRIES = 12_600_000  # problems up to this many entries can be held in the registers of the GPU
 SEG_COLS = 256             # columns of a row segment, the unit of the zero-segment skipping
 STEADY_WARMUP, STEADY_STEPS = 200, 500
 ALIGN_STEPS = 2000  # (one copy of X out of the padded working copy per call: 1 % of 600 iterations at n = 10239, 0.3 % of 2000)
@@ -224,6 +225,9 @@ def main() -> int:
                                "launch at 12 B per element")
         if line_frac:
             roof["nonzero_line_fraction"] = round(line_frac, 6)
+        if P.reg_kind != 2 and set(per_kind) <= {0, 4} and m * n <= HELD_ENTRIES and (args.skip_unchanged != 0 or m <= 2048):
+            roof["of_another_launch"] = ("the timed run keeps X and C in registers, the iterations between two checks in one "
+                                         "cooperative launch; profile mode launches every sweep by itself, and these are its kernels")
         sweep_ms = sum(e["ms"] for e in per_kind.values()) / max(1, len(recs))
         total_bytes = sum(e["bytes"] for e in per_kind.values()) / max(1, len(recs))
         ms_per_step = elapsed / K * 1e3

@@ -117,8 +117,9 @@ int drot_destroy(drot_handle h);
  *       has run or the sizes differ.  drot_info.iters counts the iterations of the call.
  *   DROT_OPT_PROFILE [0], 0/1: take the start and the end of every sweep kernel (the first 256 of a solve),
  *       as the hardware stamps them, through a pair of HIP events attached to the launch, and count what the
- *       sweep read; see drot_get_profile.  Costs a few tiny kernels per iteration, so leave it off when
- *       timing a solve.
+ *       sweep read; see drot_get_profile.  Costs a few tiny kernels per iteration, and every sweep is launched by
+ *       itself: problems that otherwise run from check to check in one cooperative launch (DROT_OPT_FUSED_UPDATE)
+ *       run other kernels then, to the same bits.  So leave it off when timing a solve.
  *
  * Which kernels run (tuning; the iterates do not depend on these unless stated)
  *   DROT_OPT_SKIP_UNCHANGED [-1 = on], -1/0/1: X >= 0, so a row segment (256 consecutive columns of a
@@ -223,7 +224,8 @@ typedef struct {
 int drot_get_checks(drot_handle h, drot_check* out, int capacity, int* count);
 
 /*
- * Sweep timings of the last solve in profile mode, in launch order (at most the first 256 sweeps).
+ * Sweep timings of the last solve in profile mode, in launch order (at most the first 256 sweeps).  Cooperative
+ * launches are not among them: profile mode makes none.
  *   ms          duration of the sweep kernel: from its start to its end as the hardware stamps them, read
  *               through a pair of HIP events attached to the launch (the group-lasso sweep of three
  *               launches: from the start of the first to the end of the last)

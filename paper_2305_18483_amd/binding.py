@@ -257,7 +257,8 @@ class Solver:
         return [(float(r.ms), int(r.kind)) for r in self.profile_records()]
 
     def profile_reads(self) -> list:
-        """Fraction of the row segments of C that each timed sweep of the last solve read."""
+        """Fraction of the row segments of C (the sweep by lines, kind 7: of its lines) that each timed sweep of the last
+        solve read."""
         return [float(r.c_fraction) for r in self.profile_records()]
 
     def solve(self, C: torch.Tensor, p: torch.Tensor, q: torch.Tensor, *, stepsize: float = 0.0,
