@@ -295,7 +295,6 @@ struct Solve {
   float rho = 0.f, lambda = 0.f, mu = 0.f, tol = 0.f;
   const float *p = nullptr, *q = nullptr;
   const int* row_class = nullptr;
-  bool mapped_rows = false;   // the slab kernel fetches the rows of a class through a table
   size_t ngroups = 0;
   float* X_out = nullptr;
   const float* Cw = nullptr;  // the arrays the kernels work on: the caller's, or the padded copies
@@ -370,7 +369,7 @@ void enqueue_sweep(Solve& Z, const plan::Step& Q, bool timed, hipEvent_t e0, hip
     case plan::kSlab: {
       const SlabArgs SL{A, h->runbuf, h->runbuf + Z.P.nruns, Z.thr, h->runbuf + 2 * Z.P.nruns};
       const dim3 slab_grid(S.nstrips, Z.P.nruns > 0 ? Z.P.nruns : 1);
-      auto* const slab = Z.mapped_rows ? launch_slab<true> : launch_slab<false>;
+      auto* const slab = Z.P.mapped_rows ? launch_slab<true> : launch_slab<false>;
       slab(Q.first, Q.pro, Z.P.slab_k, slab_grid, stream, e0, e1, SL, fused_args(Z, sw, S.nstrips, Z.P.nruns));
       break;
     }
@@ -784,7 +783,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
       std::vector<int> table(L.start);  // run_start[0..nruns), run_len[0..nruns), the rows where they are not consecutive
       table.insert(table.end(), L.len.begin(), L.len.end());
       table.insert(table.end(), L.rows.begin(), L.rows.end());
-      Z.mapped_rows = !L.rows.empty();
+      P.mapped_rows = !L.rows.empty();
       const int rc2 = grow_buffer(&h->runbuf, &h->runbuf_len, table.size(), stream);
       if (rc2 != DROT_OK) return rc2;
       DROT_HIP(hipMemcpy(h->runbuf, table.data(), sizeof(int) * table.size(), hipMemcpyHostToDevice));
@@ -875,7 +874,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   // the partial sums the reduction reads: per 256-column segment and 32-row tile, or, on the
   // group-resident path, per 32-column strip and label run
   Z.RA = ReduceArgs{Z.V, h->rowpart, h->colpart, A.p, A.q, m, n, P.slab_k ? S.nstrips : S.nseg,
-                    P.slab_k ? P.nruns : S.ntr, S.nbm, S.nbn, Z.SA.mp, Z.SA.np, 1};
+                    P.slab_k ? plan::slab_col_rows(P.nruns, P.mapped_rows) : S.ntr, S.nbm, S.nbn, Z.SA.mp, Z.SA.np, 1};
   Z.UA = UpdateArgs{Z.V, nullptr, 0, nullptr, nullptr, nullptr, nullptr, m, n, S.nbm, S.nbn, 0};
 
   if (A.warm) {
@@ -1270,7 +1269,7 @@ int drot_create(drot_handle* out, int max_m, int max_n) {
   // (rows of the per-row-segment arrays and of the column sums are pitched at multiples of 64 entries)
   const size_t mpad = (size_t)ceil_div(max_m, 64) * 64, npad = (size_t)ceil_div(max_n, 64) * 64;
   h->rowpart_half = (size_t)ceil_div(max_n, kSlabCols) * mpad;  // 32-column strips (group-resident path) are the finest
-  h->colpart_half = ntr * npad;
+  h->colpart_half = (size_t)plan::most_col_rows(max_m) * npad;
   h->tilesum_half = nseg * ntr > 4096 ? nseg * ntr : 4096;  // (the group-resident path has up to 4096 slabs)
   take(dev_alloc(&h->rowpart, 2 * h->rowpart_half));
   take(dev_alloc(&h->colpart, 2 * h->colpart_half));

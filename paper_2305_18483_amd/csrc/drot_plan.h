@@ -81,6 +81,14 @@ constexpr int kEarlyLooksUntil = 512;  // cold starts: extra density readings ov
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Rows of column sums that the slabs leave: one per run, two per class whose rows are fetched through a table (its sums in
+// two parts).  There are at most m / (kMappedFill 128) such classes.
+inline int slab_col_rows(int nruns, bool mapped) { return mapped ? 2 * nruns : nruns; }
+inline int most_col_rows(int m) {
+  const int tiles = ceil_div(m, kTileRows), parts = slab_col_rows((int)(m / (kMappedFill * kSlabRowLanes)), true);
+  return tiles > parts ? tiles : parts;
+}
+
 enum Regularizer { kNone = 0, kQuadratic = 1, kGroupLasso = 2 };
 
 struct Options {
@@ -106,6 +114,7 @@ struct Problem {
   bool x_on_lines = true;     // base address of X_out is a multiple of 128
   int slab_k = 0;             // group lasso: rows per lane of the slab kernel, 0 = two-pass path
   int nruns = 0;              // group lasso: runs of equal labels
+  bool mapped_rows = false;   // group lasso: the slab kernel fetches the rows of a class through a table
   size_t tilesum_half = 0;    // capacity of one half of the tile-total buffer
   float rho = 0.f;            // stepsize
   bool feedback = true;       // the host reads the status block during the solve
@@ -323,7 +332,7 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
   Q.sw = sw;
   Q.first = sw == 1 && !P.warm;
   Q.tilesum = S.small;
-  Q.ra_ntr = P.slab_k ? P.nruns : S.ntr;
+  Q.ra_ntr = P.slab_k ? slab_col_rows(P.nruns, P.mapped_rows) : S.ntr;
   Q.ra_cgroup = 1;
   const bool skipping = O.skip_unchanged != 0;
   bool tiles64 = false, lean = false, slab_totals = false;

@@ -1216,6 +1216,29 @@ def test_dense_plans_lose_no_precision_to_the_sweep_by_lines(drot):
     assert errors[-1] <= 1.08 * errors[1]
 
 
+def test_column_sums_of_scattered_classes_keep_what_a_tile_of_rows_keeps(drot):
+    # one iteration that leaves the plan as it is (no cost, no duals, no weights): the residual reported is that of the sums
+    # of X_0.  Four interleaved classes; per class and column one entry of 1/8 and one a quarter of its last place, in
+    # different tiles of 32 rows: in one fp32 word per class the small ones would be gone and the column residual 0
+    m, n = 512, 96
+    small = 2.0 ** -28
+    X0 = np.zeros((m, n), dtype=np.float32)
+    X0[:4], X0[256:260] = 0.125, small
+    dev = torch.device("cuda:0")
+    labels = torch.arange(m, device=dev, dtype=torch.int32) % 4
+    C, q = torch.zeros((m, n), device=dev), torch.full((n,), 0.5, device=dev)
+    p = torch.from_numpy(X0.sum(axis=1, dtype=np.float64).astype(np.float32)).to(dev)
+    phi0, varphi0 = torch.zeros(m, device=dev), torch.zeros(n, device=dev)
+    for two_pass in (False, True):
+        solver = drot.Solver(m, n)
+        solver.set_group_two_pass(two_pass)
+        X = torch.from_numpy(X0).to(dev)
+        res = solver.solve(C, p, q, reg_kind=2, row_class=labels, num_classes=4, max_iters=1, X_out=X, phi0=phi0, varphi0=varphi0)
+        assert np.array_equal(X.cpu().numpy(), X0)
+        _say(f"column residual {res.r_col:.6e}, two passes: {two_pass}")
+        assert abs(res.r_col - n ** 0.5 * 4 * small) <= 1e-3 * n ** 0.5 * 4 * small
+
+
 @pytest.mark.parametrize("m,n", [(33, 257), (129, 2), (64, 9000), (1000, 1000), (1000, 8000), (2047, 3600), (2047, 5101),
                                  (2049, 257), (2300, 2500), (2999, 3307), (6000, 300), (20, 5000)])
 def test_grid_resident_stretches_give_the_bits_of_single_launches(drot, m, n):
