@@ -1223,7 +1223,7 @@ def test_column_sums_of_scattered_classes_keep_what_a_tile_of_rows_keeps(drot):
     m, n = 512, 96
     small = 2.0 ** -28
     X0 = np.zeros((m, n), dtype=np.float32)
-    X0[:4], X0[256:260] = 0.125, small
+    X0[:4], X0[260:264] = 0.125, small
     dev = torch.device("cuda:0")
     labels = torch.arange(m, device=dev, dtype=torch.int32) % 4
     C, q = torch.zeros((m, n), device=dev), torch.full((n,), 0.5, device=dev)
