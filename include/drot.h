@@ -330,7 +330,8 @@ int drot_solve_points_warm(drot_handle h, const float* xs, const float* xt, int 
  * harnesses that forbid hipMalloc: drot_solve without a handle.  The workspace is a fixed array inside the
  * library's code object (12 MiB, held by every GPU the library runs on until the process ends), so the call
  * allocates nothing, on the device or the host; it only enqueues kernels on `stream` and returns WITHOUT
- * waiting for them.  Results arrive in the caller's DEVICE buffers once the stream has run:
+ * waiting for them.  (The first cooperative launch of a process, here or in drot_solve, has the runtime set up
+ * a queue for such launches, some 7 ms; a call made under a stream capture makes none.)  Results arrive in the caller's DEVICE buffers once the stream has run:
  *   X_out [out]       DEVICE, m*n, as drot_solve
  *   phi_out, varphi_out [out]  DEVICE, m resp. n floats, or NULL: phi and varphi of the returned iterate
  *   info_out [out]    DEVICE pointer to one drot_info (all fields, the gap ones included), or NULL
