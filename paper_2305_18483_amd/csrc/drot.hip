@@ -462,7 +462,7 @@ GridWords grid_words(const plan::Static& S, int m, int n) {
 constexpr int kMaxDevices = 64;
 
 // Devices on which the runtime has told this process that it gets no cooperative launches at all (hipErrorIllegalState:
-// the driver lets one process at a time have them, and another one does).  To be told so takes 40 ms a time, so nobody
+// the system lets one process at a time have them, and another one does).  To be told so takes 40 ms a time, so nobody
 // asks again.
 std::atomic<bool> g_no_cooperative[kMaxDevices];
 

@@ -1,6 +1,6 @@
 """Launches whose workgroups wait for one another, where they are refused or give up: the solves come out by single launches.
 
-The child processes come first: a driver may let only one process at a time launch that way, and this one has done so once a
+The child processes come first: a system may let only one process at a time launch that way, and this one has done so once a
 solve has run in it.
 """
 import os
@@ -69,7 +69,7 @@ phi, varphi = torch.zeros(m, device=dev), torch.zeros(n, device=dev)
 drot.solve_static(C[:1024], p[:1024].contiguous(), q, Xs[:1024], phi_out=phi[:1024], varphi_out=varphi, info_out=info, **kw)
 torch.cuda.synchronize()
 assert shim.lowered() == (1 if shim.failed() else 2)
-if shim.failed():  # (the driver lets one process at a time launch that way: the caller's, where it has done so before)
+if shim.failed():  # (the system lets one process at a time launch that way: the caller's, where it has done so before)
     print("gave up True 0.0: not tried", flush=True)
 else:
     try:
