@@ -23,6 +23,10 @@ def _say(msg):
     print(f"[gpu-cooperative] {msg}", flush=True)
 
 
+def _child_env():
+    return dict(os.environ, PYTHONPATH=os.pathsep.join(x for x in (ROOT, os.environ.get("PYTHONPATH")) if x))
+
+
 @pytest.fixture(scope="module")
 def drot():
     import paper_2305_18483_amd as drot_mod
@@ -126,7 +130,7 @@ extern "C" int hipLaunchCooperativeKernel(const void* f, dim3 grid, dim3 block, 
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", str(lib), str(src)], check=True)
     _say("refused launches, in a child process")
     proc = subprocess.run([sys.executable, "-c", _REFUSED, str(lib)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
-                          text=True, timeout=100, env=dict(os.environ, PYTHONPATH=ROOT))
+                          text=True, timeout=100, env=_child_env())
     assert proc.returncode == 0 and "refused and done 4" in proc.stdout and "gave up True 0.0" in proc.stdout and "asked 1" in proc.stdout, proc.stdout
 
 
@@ -150,7 +154,7 @@ def test_a_second_process_on_the_gpu(drot, tmp_path):
     _, X, _, _ = pu.gpu_solve(drot.Solver(P.m, P.n), P, 130)
     out = tmp_path / "second.npy"
     proc = subprocess.run([sys.executable, "-c", _SECOND, str(out)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
-                          text=True, timeout=100, env=dict(os.environ, PYTHONPATH=ROOT))
+                          text=True, timeout=100, env=_child_env())
     assert proc.returncode == 0, proc.stdout
     assert np.array_equal(np.load(out), X)
 
