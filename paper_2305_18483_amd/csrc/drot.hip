@@ -88,6 +88,12 @@ void launch_slab(bool first, bool pro, int k, dim3 grid, hipStream_t stream, hip
   else launch_slab_k<false, false, MAPPED>(k, grid, stream, e0, e1, a, f);
 }
 
+// The status block with, behind it, the records of the checks that the last launch made by itself.
+struct StatusBlock {
+  DeviceStatus status;
+  CheckRecord checks[plan::kRunChecks];
+};
+
 constexpr int kMaxProfiled = 256;   // sweeps timed per solve in profile mode
 constexpr int kMaxChecks = 65536;   // residual checks recorded per solve
 
@@ -159,8 +165,10 @@ struct drot_handle_s {
   bool xchg_clean = false;  // no word carries a number above xchg_tag
   int* done = nullptr;
   DeviceStatus* status = nullptr;
-  // pinned host mirror of the status block, two slots for the pipelined residual checks
+  CheckRecord* run_checks = nullptr;  // ... behind the status block (none in a fixed workspace)
+  // pinned host mirror of the status block, two slots for the pipelined residual checks, and of the block with its records
   DeviceStatus* host_status = nullptr;
+  StatusBlock* host_run = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   drot_info info{};
   std::vector<drot_check> checks;  // the residual checks of the last solve
@@ -208,7 +216,7 @@ void free_all(drot_handle h) {
   for (float* b : fbufs) (void)hipFree(b);
   for (double* b : dbufs) (void)hipFree(b);
   for (int* b : ibufs) (void)hipFree(b);
-  (void)hipFree(h->status);
+  (void)hipFree(h->status);  // (the first member of its block)
   (void)hipFree(h->xlines);
   (void)hipFree(h->codes);
   (void)hipFree(h->drift);
@@ -308,6 +316,9 @@ struct Solve {
   float thr = 0.f;  // rho * mu
   ChunkArgs CK{};   // two-pass group lasso: the classes' rows in chunks
   int num_classes = 0;
+  CheckArgs check{};  // checks inside the launch that is being enqueued (out null: none)
+  int tested_k = -1;  // iterations of the call whose status has been enqueued, with the test that ends the call
+  int run_unread = 0; // checks made inside the last launch that the host has not looked at yet
 
   double* a_buf(long long g) const { return h->a + (size_t)(g & 1) * (size_t)h->max_m; }
   double* b_buf(long long g) const { return h->b + (size_t)(g & 1) * (size_t)h->max_n; }
@@ -344,10 +355,8 @@ void enqueue_sweep(Solve& Z, const plan::Step& Q, bool timed, hipEvent_t e0, hip
   const FusedUpdateArgs none{};
   switch (Q.sweep) {
     case plan::kResident: {
-      const long long last = sw + Q.iters - 1;  // the state leaves in that generation's buffers
-      const ResidentArgs RS{Z.Xw, Z.Cw, Z.p, Z.q, Z.V, Z.a_buf(sw - 1), Z.b_buf(sw - 1), Z.a_buf(last), Z.b_buf(last),
-                            (int)((sw - 1) & 1), (int)(last & 1), m, n, Z.ldx, Z.ldc, Z.rho, A.scale, Q.iters,
-                            Q.first ? 1 : 0};
+      const ResidentArgs RS{Z.Xw, Z.Cw, Z.p, Z.q, Z.V, Z.a_buf(sw - 1), Z.b_buf(sw - 1), Z.a_buf(sw), Z.b_buf(sw),
+                            (int)((sw - 1) & 1), m, n, Z.ldx, Z.ldc, Z.rho, A.scale, Q.iters, Q.first ? 1 : 0, Z.check};
       launch_resident(RS, stream, e0, e1);
       break;
     }
@@ -445,7 +454,7 @@ hipError_t launch_grid(const GridArgs& A, int workgroups, hipStream_t stream) {
 
 // Where the words of one half of the exchange buffer start, and how many there are (GridArgs).
 struct GridWords {
-  size_t col, tot, ent, cst, half;
+  size_t col, tot, ent, sq, cst, half;
 };
 GridWords grid_words(const plan::Static& S, int m, int n) {
   const size_t nblk_m = (size_t)ceil_div(m, kGridBlock), nblk_n = (size_t)ceil_div(n, kGridBlock);
@@ -454,7 +463,8 @@ GridWords grid_words(const plan::Static& S, int m, int n) {
   W.col = nblk_m * (size_t)S.nseg * kGridBlock;
   W.tot = W.col + nblk_n * ntr * kGridBlock;
   W.ent = W.tot + (size_t)S.nseg * (ntr + kColGroup);  // (totals: whole groups of kColGroup tile rows for the 64-row tiles)
-  W.cst = (W.ent + 2 * (nblk_m + nblk_n) * kGridBlock + 31) / 32 * 32;
+  W.sq = W.ent + 2 * (nblk_m + nblk_n) * kGridBlock;
+  W.cst = (W.sq + 2 * (nblk_m + nblk_n) + 31) / 32 * 32;
   W.half = W.cst + 32 * kGridCopies;
   return W;
 }
@@ -477,7 +487,7 @@ int cooperative_units(int device) {
 // What a solve returns inside this file where a cooperative launch was not accepted, and where one gave up waiting.
 constexpr int kGridRefused = -1001, kGridGaveUp = -1002;
 
-// The sweeps first .. last of a stretch, and all their vector updates but the last one's, in one launch.  kGridRefused:
+// The sweeps first .. last of a stretch, all their vector updates and the checks of Z.check in one launch.  kGridRefused:
 // nothing has been enqueued that counts.
 int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   drot_handle h = Z.h;
@@ -511,10 +521,10 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   A.q = Z.q;
   A.a_in = Z.a_buf(first.sw - 1);
   A.b_in = Z.b_buf(first.sw - 1);
-  A.a_out = Z.a_buf(last.sw - 1);
-  A.b_out = Z.b_buf(last.sw - 1);
+  A.a_alt = Z.a_buf(first.sw);
+  A.b_alt = Z.b_buf(first.sw);
   A.theta_in = h->theta + ((first.sw - 1) & 1);
-  A.theta_out = h->theta + ((last.sw - 1) & 1);
+  A.theta_alt = h->theta + (first.sw & 1);
   A.sum_p = h->sum_p;
   A.status = h->status;
   A.done = h->done;
@@ -524,6 +534,12 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   A.tot_word = (unsigned)W.tot;
   A.ent_word = (unsigned)W.ent;
   A.cst_word = (unsigned)W.cst;
+  A.sq_word = (unsigned)W.sq;
+  A.check = Z.check;
+  A.phi_out = h->phi;
+  A.varphi_out = h->varphi;
+  A.r = h->r;
+  A.s = h->s;
   A.nseg = S.nseg;
   A.ntr = ntr;
   A.nblk_m = nblk_m;
@@ -661,6 +677,19 @@ void record_check(drot_handle h, const DeviceStatus& st) {
   c.gap = c.gap_evaluated ? st.gap : 0.0;
   c.dual_res = c.gap_evaluated ? st.dual_res : 0.0;
   h->checks.push_back(c);
+}
+
+// The `count` checks of a launch that makes them itself, as far as it got.  True: the last of them passed.
+bool record_run(drot_handle h, const CheckRecord* rec, int count) {
+  for (int c = 0; c < count; ++c) {
+    DeviceStatus st{};
+    st.r2 = rec[c].r2;
+    st.s2 = rec[c].s2;
+    st.iters = rec[c].iters;
+    record_check(h, st);
+    if (rec[c].converged) return true;
+  }
+  return false;
 }
 
 // Arguments as handed over by the entry points.
@@ -912,25 +941,65 @@ int iterate(Solve& Z, bool* converged_out) {
   bool converged = false;
   bool was_probe[2] = {false, false};
   h->prof_used = 0;
+  auto read_status = [&](int which) -> int {
+    DROT_HIP(hipEventSynchronize(h->ev[which]));
+    const DeviceStatus& st = h->host_status[which];
+    if (st.broken) return kGridGaveUp;
+    if (st.converged) converged = true;
+    if (!was_probe[which]) record_check(h, st);
+    plan::on_status(S, Z.T, st.nz_segments / ((double)Z.m * (double)S.nseg),
+                    st.nz_lines < 0.0 ? -1.0 : st.nz_lines / ((double)Z.m * (double)ceil_div(Z.n, 32)), was_probe[which]);
+    return DROT_OK;
+  };
   while (Z.T.k < Z.P.max_iters && !converged) {
-    const plan::Stretch R = plan::next_stretch(S, Z.P, Z.O, Z.T);
+    plan::Stretch R = plan::next_stretch(S, Z.P, Z.O, Z.T);
+    bool run = plan::runs_through_checks(S, Z.P, Z.O);  // (the launch makes the checks)
+    if (run) {
+      const plan::Stretch W = plan::draw_out(Z.P, Z.O, Z.T, R);
+      // (the first sweep of a cold start, where it is launched by itself, must not end at a check)
+      run = S.resident || (plan::grid_head(S, Z.P, Z.T, W) >= 0 && plan::grid_head(S, Z.P, Z.T, W) < R.chunk);
+      if (run) R = W;
+    }
+    if (run && checks > 0) {  // (what the launches check by check have left to read comes first)
+      const int rc = read_status(slot ^ 1);
+      if (rc != DROT_OK) return rc;
+      checks = 0;
+      if (converged) break;
+    }
     const int k_end = Z.T.k + R.chunk;
     const int grid_head = plan::grid_head(S, Z.P, Z.T, R);
+    bool refused = false, tested = false;
+    int run_checks = 0;
+    // the checks behind the sweeps from here to the end of the stretch; tol: of the test (0: none)
+    auto checks_from_here = [&](float tol) {
+      const int every = Z.O.check_every, k = Z.T.k, to_check = run ? every - k % every : k_end - k;
+      const int first = (to_check < k_end - k ? to_check : k_end - k) - 1;
+      run_checks = 1 + ceil_div(k_end - k - 1 - first, every);
+      Z.check = CheckArgs{h->run_checks, h->status, h->resid, h->done, (double)tol, first, every, k};
+    };
     for (int c = 0; Z.T.k < k_end; ++c) {
+      if (run && S.resident) checks_from_here(Z.tol);
       if (c == grid_head) {  // the rest of the stretch in one launch
+        // (a launch ends with the residuals of its last sweep; the test is its own unless the gap has a say in it)
+        tested = Z.O.gap_every < 1;
+        checks_from_here(tested && Z.P.checking ? Z.tol : 0.f);
         const plan::State before = Z.T;
         const plan::Step F = plan::next_sweep(S, Z.P, Z.O, Z.T, R, c);
         plan::Step L = F;
         for (int e = c; Z.T.k < k_end;) L = plan::next_sweep(S, Z.P, Z.O, Z.T, R, ++e);
         const int rc = enqueue_grid(Z, F, L);
+        Z.check = CheckArgs{};
         if (rc == DROT_OK) {
-          enqueue_update(Z, L);
+          Z.T.norms_pending = false;
           break;
         }
         if (rc != kGridRefused) return rc;
         Z.T = before;  // (one by one, here and in the solves to come)
         Z.P.single_launches = true;
         h->compute_units = 0;
+        tested = false;
+        refused = run;
+        if (refused) break;
       }
       const plan::Step Q = plan::next_sweep(S, Z.P, Z.O, Z.T, R, c);
       const bool timed = h->profile && h->prof_used < kMaxProfiled;
@@ -956,10 +1025,31 @@ int iterate(Solve& Z, bool* converged_out) {
         hipLaunchKernelGGL(sum_counts_kernel<double>, dim3(1), dim3(1024), 0, stream,
                            (const double*)(h->part + 2 * (S.nbm + S.nbn)), S.nbm, h->prof_counts + 2 * pe + 1);
     }
+    Z.check = CheckArgs{};
+    if (refused) continue;  // (planned again, check by check)
+    if (tested) Z.tested_k = Z.T.k;
+    if (run) {
+      Z.tested_k = Z.T.k;
+      Z.run_unread = run_checks;
+      DROT_HIP(hipGetLastError());
+      if (Z.T.k == Z.P.max_iters) break;  // (read with the end of the call)
+      DROT_HIP(hipMemcpyAsync(h->host_run, h->status, offsetof(StatusBlock, checks) + sizeof(CheckRecord) * (size_t)run_checks,
+                              hipMemcpyDeviceToHost, stream));
+      DROT_HIP(hipStreamSynchronize(stream));
+      if (h->host_run->status.broken) return kGridGaveUp;
+      converged = record_run(h, h->host_run->checks, run_checks);
+      Z.run_unread = 0;
+      continue;
+    }
+    if (tested && !Z.P.feedback) {
+      DROT_HIP(hipGetLastError());
+      continue;
+    }
     if (S.status_at_checks) {
       // the test runs on the device; the host reads it one stretch late so the queue never drains
       if (R.gap) enqueue_gap(Z, h->done, true);  // (behind the stop flag: it runs only if every sweep before it ran)
       enqueue_status(Z, Z.T.k, Z.P.checking && !R.probe, R.gap);
+      if (!R.probe) Z.tested_k = Z.T.k;
       if (!Z.P.feedback) {  // (the stop flag alone ends the solve: the sweeps queued behind it return at once)
         DROT_HIP(hipGetLastError());
         continue;
@@ -967,16 +1057,6 @@ int iterate(Solve& Z, bool* converged_out) {
       DROT_HIP(hipMemcpyAsync(&h->host_status[slot], h->status, sizeof(DeviceStatus), hipMemcpyDeviceToHost, stream));
       DROT_HIP(hipEventRecord(h->ev[slot], stream));
       was_probe[slot] = R.probe;
-      auto read_status = [&](int which) -> int {
-        DROT_HIP(hipEventSynchronize(h->ev[which]));
-        const DeviceStatus& st = h->host_status[which];
-        if (st.broken) return kGridGaveUp;
-        if (st.converged) converged = true;
-        if (!was_probe[which]) record_check(h, st);
-        plan::on_status(S, Z.T, st.nz_segments / ((double)Z.m * (double)S.nseg),
-                        st.nz_lines < 0.0 ? -1.0 : st.nz_lines / ((double)Z.m * (double)ceil_div(Z.n, 32)), was_probe[which]);
-        return DROT_OK;
-      };
       int rc = checks > 0 ? read_status(slot ^ 1) : DROT_OK;
       if (rc == DROT_OK && R.prompt) rc = read_status(slot);  // (read again, to no effect, when the next stretch is queued)
       if (rc != DROT_OK) return rc;
@@ -1019,19 +1099,21 @@ int solve_once(drot_handle h, const SolveCall& A) {
   rc = iterate(Z, &converged);
   if (rc != DROT_OK) return fail(rc);
   const int k = Z.T.k;
-  // final state: residuals of the returned iterate (no-op if the stop flag is already up)
-  if (k > 0) enqueue_status(Z, k, Z.P.checking, false);
+  // final state: residuals of the returned iterate, where the last stretch has not ended with them
+  if (k > 0 && Z.tested_k != k) enqueue_status(Z, k, Z.P.checking, false);
   // (a stop seen in the loop means the last stretch was enqueued behind it and did not run; without feedback
   // the host cannot tell)
   if (h->compute_gap) enqueue_gap(Z, nullptr, !converged && (Z.P.feedback || !Z.P.checking));
   const bool untouched = A.max_iters == 0 && !Z.P.resume && !A.warm;
   if (S.pad_x && !untouched) copy_rows(A.X_out, (size_t)Z.n, h->xpad, (size_t)S.ld_pad, Z.m, Z.n, stream);
-  if (hipMemcpyAsync(&h->host_status[0], h->status, sizeof(DeviceStatus), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+  if (hipMemcpyAsync(h->host_run, h->status, offsetof(StatusBlock, checks) + sizeof(CheckRecord) * (size_t)Z.run_unread,
+                     hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
     return fail(DROT_ERR_HIP);
 
-  const DeviceStatus& st = h->host_status[0];
+  const DeviceStatus& st = h->host_run->status;
   if (st.broken) return fail(kGridGaveUp);
+  record_run(h, h->host_run->checks, Z.run_unread);
   h->prof_count = 0;
   if (h->profile) {
     const int timed = h->prof_used;
@@ -1142,7 +1224,10 @@ size_t carve_static(drot_handle_s& H, unsigned char* base) {
   take(&H.wg_reads, nseg * (size_t)ceil_div(ceil_div(kStaticMaxM, 64), kLeanWaves));
   take(&H.gap_part, nseg * ntr * 3);
   take(&H.done, 1);
-  take(&H.status, 1);
+  StatusBlock* block = nullptr;
+  take(&block, 1);
+  H.status = block ? &block->status : nullptr;
+  H.run_checks = block ? block->checks : nullptr;
   // (the largest grid-resident problem here has 2048 rows: 1024 tiles of 32 rows)
   H.xchg_len = 2 * ((size_t)2048 * nseg + (size_t)ceil_div(2048, kTileRows) * N + 2 * (M + N) + 4096);
   take(&H.xchg, H.xchg_len);
@@ -1214,7 +1299,7 @@ int solve_static_impl(SolveCall A, float* phi_out, float* varphi_out, drot_info*
   bool converged = false;
   rc = iterate(Z, &converged);
   if (rc != DROT_OK) return rc;
-  if (Z.T.k > 0) enqueue_status(Z, Z.T.k, Z.P.checking, false);
+  if (Z.T.k > 0 && Z.tested_k != Z.T.k) enqueue_status(Z, Z.T.k, Z.P.checking, false);
   enqueue_gap(Z, nullptr, false);
   hipLaunchKernelGGL(export_kernel, dim3(16), dim3(256), 0, Z.stream, (const DeviceStatus*)H.status, info_out,
                      (const float*)H.phi, (const float*)H.varphi, A.X_out, phi_out, varphi_out, A.m, A.n, A.max_iters);
@@ -1288,11 +1373,19 @@ int drot_create(drot_handle* out, int max_m, int max_n) {
   h->max_runs = (int)ntr;
   take(dev_alloc(&h->gap_part, nseg * ntr * 3));
   take(dev_alloc(&h->done, 1));
-  take(dev_alloc(&h->status, 1));
-  if (rc == DROT_OK && hipHostMalloc(reinterpret_cast<void**>(&h->host_status), 2 * sizeof(DeviceStatus)) != hipSuccess) {
+  StatusBlock* block = nullptr;
+  take(dev_alloc(&block, 1));
+  if (block) {
+    h->status = &block->status;
+    h->run_checks = block->checks;
+  }
+  static_assert(offsetof(StatusBlock, status) == 0 && sizeof(DeviceStatus) % alignof(StatusBlock) == 0, "one allocation each");
+  if (rc == DROT_OK &&
+      hipHostMalloc(reinterpret_cast<void**>(&h->host_status), 2 * sizeof(DeviceStatus) + sizeof(StatusBlock)) != hipSuccess) {
     h->host_status = nullptr;
     rc = DROT_ERR_ALLOC;
   }
+  if (h->host_status) h->host_run = reinterpret_cast<StatusBlock*>(h->host_status + 2);
   for (auto& e : h->ev)
     if (rc == DROT_OK && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
       e = nullptr;

@@ -167,6 +167,45 @@ struct DeviceStatus {
   int broken;                    // a grid-resident launch gave up waiting for one of its workgroups
 };
 
+// Residual checks made inside a launch that runs many iterations (the resident kernel, grid-resident stretches): what
+// status_kernel does behind a launch that ends at the check.
+struct CheckRecord {
+  double r2, s2;
+  int iters;
+  int converged;
+};
+struct CheckArgs {
+  CheckRecord* out;      // one record per check, in order (null: no checks in this launch)
+  DeviceStatus* status;
+  double* resid;
+  int* done;
+  double tol;
+  int first;             // the launch's sweep (from 0) behind which its first check stands; the others `every` apart, one behind
+  int every;             // the last sweep
+  int k0;                // iterations of the call before the launch
+};
+
+// One thread: the c-th check of the launch, behind its sweep `it`.  True: it passes, the solve ends here.
+__device__ __forceinline__ bool make_check(const CheckArgs& K, int c, int it, double r2, double s2) {
+  const bool pass = K.tol > 0.0 && r2 <= K.tol * K.tol && s2 <= K.tol * K.tol;
+  K.out[c] = CheckRecord{r2, s2, K.k0 + it + 1, pass ? 1 : 0};
+  K.resid[0] = r2;
+  K.resid[1] = s2;
+  K.resid[2] = 0.0;
+  K.resid[3] = -1.0;
+  K.status->r2 = r2;
+  K.status->s2 = s2;
+  K.status->nz_segments = 0.0;
+  K.status->nz_lines = -1.0;
+  K.status->iters = K.k0 + it + 1;
+  if (pass) {
+    K.status->converged = 1;
+    __threadfence();
+    *K.done = 1;
+  }
+  return pass;
+}
+
 struct SweepArgs {
   float* X;
   const float* C;

@@ -21,8 +21,13 @@
 //
 // Measured on MI355X, per iteration, before (single launches) and now: 500 x 500 6.7 -> 3.1 us (0.55 sweep, 0.2 fold
 // and publish, 1.0 hop 1, 1.2 hop 2), 1000 x 1000 6.7 -> 3.0, 2048 x 3072 22.6 -> 6.4, 2999 x 3307 18.6 -> 7.8 (2.4 of
-// it the sweep: 8 operations for each of the 49000 entries of a compute unit); a stretch adds 40 us (the launch, fetching
-// X and C, the last vector update, the check).
+// it the sweep: 8 operations for each of the 49000 entries of a compute unit).
+//
+// The launch runs on through the residual checks (GridArgs::check).  At a check the owners publish the squared residuals of
+// their entries, too, the first workgroup adds them up, tests, and sends the answer behind 2 eta - theta: one hop more,
+// 2 us.  Ending the launch at every check instead (the launch, fetching X and C, the last vector update, norms, status and
+// its copy to the host) cost 40 us: 1000 x 1000, 1000 sweeps checked every 100 3.48 -> 3.11 ms, every 10 7.18 -> 3.39.
+// The sweeps without a check are a loop of their own, which the check costs no register.
 //
 // Two halves of the exchange buffers, used in turn, are enough: a word of iteration k is overwritten in iteration
 // k + 2, whose sweep needs the 2 eta - theta of k + 1, which needs the total of every tile of k + 1, which every
@@ -32,8 +37,8 @@
 //
 // The arithmetic and its order are those of the launches this kernel stands for, so that the results are the same
 // bits: 32-row tiles of 16 waves x 2 rows (small problems, update fused into the sweep) or 64-row tiles of 8 waves x 8
-// rows (the sweeps that skip zero row segments).  The last sweep of the stretch leaves X and its partial sums in memory as those
-// launches do, and the ordinary vector update follows it.
+// rows (the sweeps that skip zero row segments).  The last sweep leaves X, its partial sums and the state after its vector
+// update in memory as those launches do.
 //
 // The workgroups wait for one another, so they must all be on the chip: a cooperative launch, at most one workgroup per
 // compute unit.  Every wait is bounded: a word that has not come after GridArgs::polls attempts (2^25 as a rule, about half a
@@ -53,12 +58,12 @@ struct GridArgs {
   SweepArgs S;            // rowpart, colpart, tilesum: where the last sweep leaves its sums
   const float* p;
   const float* q;
-  const double* a_in;     // eq. (6) state before the first sweep's update
-  const double* b_in;
-  double* a_out;          // ... and after the last update made here (that of the last sweep but one)
-  double* b_out;
-  const double* theta_in;
-  double* theta_out;
+  double* a_in;           // eq. (6) state before the first sweep's update
+  double* b_in;
+  double* a_alt;          // ... and the other halves: the state after 1, 3, 5, ... updates goes there, after 2, 4, 6, ... back
+  double* b_alt;          // to where it came from
+  double* theta_in;
+  double* theta_alt;
   const double* sum_p;
   DeviceStatus* status;
   int* done;
@@ -73,7 +78,26 @@ struct GridArgs {
   int first;              // X_0 = 0: nothing to read
   unsigned tag0;          // the exchange of sweep k (counted from 0) carries the number tag0 + k; never 0
   int polls;              // attempts before a wait is given up (>= 1)
+  // checks inside the launch: the last sweep's vector update is made here, too, and the state left is that of the iterate
+  // of the check the launch ends at
+  CheckArgs check;
+  unsigned sq_word;       // [row blocks][2], [column blocks][2]: squared residuals of eight entries
+  float* phi_out;
+  float* varphi_out;
+  double* r;
+  double* s;
 };
+
+// The arguments once more, fetched where they are used: what only a check or the end of the launch needs would sit in
+// registers all the while otherwise, or in spilled ones.
+__device__ __forceinline__ const GridArgs& late_args() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const GridArgs*)p;
+}
+// Blocks of 64 rows or columns that the owner waves of 256 workgroups (the planner takes no more) stand for.
+template <int NW>
+constexpr int kGridSquares = 32 * NW + 2;
 
 // (a word is addressed by its number in the buffer's half: a scalar base and 32 bits of offset)
 __device__ __forceinline__ u64 grid_load(const u64* half, unsigned word) {
@@ -88,8 +112,9 @@ __device__ __forceinline__ float grid_value(u64 w) { return __builtin_bit_cast(f
 __device__ __forceinline__ double grid_value(u64 hi, u64 lo) { return __builtin_bit_cast(double, (hi << 32) | (unsigned)lo); }
 
 // Fetches the words at[0 .. N-1] until every lane has all of its own with the number `tag`.  All of them are asked for
-// again together: a word waited for by itself would cost a trip to the memory-side cache each.
-template <int N>
+// again together: a word waited for by itself would cost a trip to the memory-side cache each.  PAUSE: between two
+// attempts, in units of 64 cycles.
+template <int N, int PAUSE = 0>
 __device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const unsigned (&at)[N], unsigned tag, int limit, bool& lost) {
   for (int polls = 1;; ++polls) {
     bool there = true;
@@ -102,6 +127,7 @@ __device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const 
       lost = true;
       return;
     }
+    if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
   }
 }
 
@@ -176,6 +202,12 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   constexpr int kSide = NW / NT;         // tiles side by side in the workgroup's waves
   constexpr int kTiles = kSide * TW;     // tiles of the workgroup
   constexpr int kShareBlocks = 1024 / 64, kSB = kShareBlocks / NW;  // the tile totals are dealt out to 1024 shares
+  // Pauses between the attempts of a wait leave the memory-side cache to the words on their way.  Where the workgroups differ
+  // in the tiles they hold, or a tile takes long, the waits are long: per iteration without a pause, with 64, 128, 256 and 512
+  // cycles 2048 x 2048 (two tiles) 4.96, 4.89, 4.88, 4.85, 4.92 us, 2048 x 3072 (three) 6.55, 6.48, 6.43, 6.37, 6.35,
+  // 2999 x 3307 (64 rows) 8.50, 8.33, 8.33, 8.34, 8.38, 2100 x 1800 6.10, 5.94, 5.96, 5.94, 6.01.  With one tile of 32 rows
+  // each attempt is of use (1000 x 1000 3.11, 3.13, 3.17, 3.24, 3.41), and with four or five it makes no difference.
+  constexpr int kPause = U == 8 ? 2 : TW == 2 || TW == 3 ? 4 : 0;
   static_assert(kRows <= 64 && NW % NT == 0 && kShareBlocks % NW == 0, "layout");
   __shared__ f4v c_lds[CL > 0 ? CL : 1][NW * U][64];
   __shared__ float cs[kTiles][NT][kSegCols];  // column sums of a wave's rows
@@ -184,6 +216,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   __shared__ float lds_row[kTiles][kRows];
   __shared__ float wt[kTiles][NT];            // totals of a wave's rows
   __shared__ double red[kShareBlocks];
+  __shared__ double sq64[kGridSquares<NW>];  // checks: squared residuals of 64 entries each
   __shared__ int failed[2];  // a word that never came: among the tile totals; among the others
   const SweepArgs& S = A.S;
   if (*A.done) return;
@@ -281,8 +314,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   const unsigned col_lane = (unsigned)((lane >> 3) * A.ntr * kGridBlock + (lane & 7));
   __syncthreads();
 
-  for (int it = 0;; ++it) {
-    // ---- sweep ----
+  auto sweep = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < TW; ++q) {
       const int lt = q * kSide + side;
@@ -308,8 +340,13 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       if (TW * U > 8) __builtin_amdgcn_sched_barrier(0);  // (one set of tiles at a time: the registers are full of X and C)
     }
     __syncthreads();
-    if (it == A.iters - 1) break;
-
+  };
+  // Publishes the sums of sweep `it` and brings phi and varphi back.  check_here: with the check that stands behind it
+  // (the sweeps without one, nearly all of them, pay nothing for it: neither registers nor branches).
+  enum { kGoesOn, kPasses, kGaveUp };
+  int nchecks = 0;
+  auto exchange = [&](auto check_here, int it) __attribute__((always_inline)) -> int {
+    constexpr bool check = decltype(check_here)::value;
     // ---- publish the sums of the tiles ----
     const unsigned tag = A.tag0 + (unsigned)it;
     u64* __restrict__ half = A.xchg + (size_t)(tag & 1u) * A.half_words;
@@ -341,7 +378,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         unsigned at[NP];
 #pragma unroll
         for (int b = 0; b < NP; ++b) at[b] = part_word + part_lane + (unsigned)(min(part_index(k0, b), nparts - 1) * kGridBlock);
-        grid_gather<NP>(half, v, at, tag, A.polls, lost);
+        grid_gather<NP, kPause>(half, v, at, tag, A.polls, lost);
         if (!grouped) {
 #pragma unroll
           for (int b = 0; b < NP; ++b) sh[b & 1] += part_index(k0, b) < nparts ? (double)grid_value(v[b]) : 0.0;
@@ -365,6 +402,17 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       if (entry_exists && lane < 2 * kGridBlock)
         grid_store(half, A.ent_word + (unsigned)((blk * kGridBlock + (lane & 7)) * 2 + (lane >> 3)),
                    lane < kGridBlock ? (unsigned)(out >> 32) : (unsigned)out, tag);
+      if (check) {
+        // the residual's square over the eight entries, in the order of the first steps of wave_sum_f64
+        double sq = entry_exists ? res * res : 0.0;
+        sq += dpp_mov_f64<0xB1, 0xF>(sq);
+        sq += dpp_mov_f64<0x4E, 0xF>(sq);
+        sq += dpp_mov_f64<0x141, 0xF>(sq);
+        const u64 w = __builtin_bit_cast(u64, sq);
+        const GridArgs& L = late_args();
+        if (lane < 2) grid_store(half, L.sq_word + (unsigned)(blk * 2 + lane), lane == 0 ? (unsigned)(w >> 32) : (unsigned)w, tag);
+        if (entry_exists && lane < kGridBlock) (own_rows ? L.r : L.s)[entry] = res;
+      }
     }
     if (keeper) {
 #pragma unroll
@@ -376,7 +424,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
           unsigned at[G];
 #pragma unroll
           for (int b = 0; b < G; ++b) at[b] = A.tot_word + (unsigned)(e * G + (total_there(e, b) ? b : 0));
-          grid_gather<G>(half, v, at, tag, A.polls, lost);
+          grid_gather<G, kPause>(half, v, at, tag, A.polls, lost);
           float g = grid_value(v[0]);
 #pragma unroll
           for (int b = 1; b < G; ++b) g += total_there(e, b) ? grid_value(v[b]) : 0.f;
@@ -385,9 +433,29 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         acc = G == 1 ? butterfly_f64(acc) : wave_sum_f64(acc);
         if (lane == 0) red[wave + sb * NW] = acc;
       }
+      if (check) {
+        // the squared norms, added up as reduce_kernel, residual_norms_kernel and block_sum_f64 of 1024 threads do: over 64
+        // entries first (eight words, in the order of wave_sum_f64)
+        const GridArgs& L = late_args();
+        for (int side_n = 0; side_n < 2; ++side_n) {
+          const int blocks = side_n ? L.nblk_n : L.nblk_m;
+          const unsigned word = L.sq_word + (side_n ? 2u * (unsigned)L.nblk_m : 0u);
+          for (int b0 = 64 * wave; b0 < blocks && !lost; b0 += 64 * NW) {
+            const unsigned w0 = word + 2u * (unsigned)min(b0 + lane, blocks - 1);
+            u64 v[2];
+            const unsigned at[2] = {w0, w0 + 1};
+            grid_gather<2>(half, v, at, tag, A.polls, lost);
+            double sq = b0 + lane < blocks ? grid_value(v[0], v[1]) : 0.0;
+            sq += dpp_mov_f64<0xB1, 0xF>(sq);
+            sq += dpp_mov_f64<0x4E, 0xF>(sq);
+            sq += dpp_mov_f64<0x141, 0xF>(sq);
+            if ((lane & 7) == 0 && b0 + lane < blocks) sq64[(side_n ? (L.nblk_m + 7) / 8 : 0) + (b0 + lane) / 8] = sq;
+          }
+        }
+      }
       if (lost) failed[0] = 1;
       __syncthreads();
-      if (failed[0]) break;
+      if (failed[0]) return kGaveUp;
       double sum_x = 0.0;
 #pragma unroll
       for (int k = 0; k < kShareBlocks; ++k) sum_x += red[k];
@@ -397,6 +465,22 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       static_assert(kGridCopies == 32, "two words per copy, one wave");
       if (wave == 0)
         grid_store(half, A.cst_word + 32u * (unsigned)(lane >> 1) + (unsigned)(lane & 1), (lane & 1) ? (unsigned)cst : (unsigned)(cst >> 32), tag);
+      if (check) {
+        const GridArgs& L = late_args();
+        if (wave == 0) {  // (at most 1024 blocks of 64 entries: one to a share)
+          double norm2[2];
+          for (int side_n = 0; side_n < 2; ++side_n) {
+            const int rows64 = (L.nblk_m + 7) / 8, from = side_n ? rows64 : 0, count = side_n ? (L.nblk_n + 7) / 8 : rows64;
+            double sum = 0.0;
+            for (int k = 0; k < count; k += 64) sum += butterfly_f64(k + lane < count ? sq64[from + k + lane] : 0.0);
+            norm2[side_n] = sum;
+          }
+          bool pass = false;
+          if (lane == 0) pass = make_check(L.check, nchecks, it, norm2[0], norm2[1]);
+          const unsigned word = __builtin_amdgcn_ballot_w64(pass) != 0 ? 1u : 0u;
+          if (lane < kGridCopies) grid_store(half, L.cst_word + 32u * (unsigned)lane + 2u, word, tag);
+        }
+      }
     }
 
     // ---- hop 2: phi and varphi of the tiles ----
@@ -419,7 +503,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         at[2 * k] = from + 2u * (unsigned)min(lane, last);
         at[2 * k + 1] = at[2 * k] + 1;
       }
-      grid_gather<2 * kSlots + 2>(half, v, at, tag, A.polls, lost);
+      grid_gather<2 * kSlots + 2, kPause>(half, v, at, tag, A.polls, lost);
       const double cst = grid_value(v[2 * kSlots], v[2 * kSlots + 1]);
 #pragma unroll
       for (int k = 0; k < kSlots; ++k) {
@@ -430,11 +514,33 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         }
       }
     }
+    int result = kGoesOn;
+    if (check) {  // (whether it passes, for everybody; the word comes behind all of the iteration's others)
+      u64 v[1];
+      const unsigned at[1] = {cst_at + 2u};
+      grid_gather<1>(half, v, at, tag, A.polls, lost);
+      if (!lost && (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v[0]) != 0) result = kPasses;
+    }
     if (lost) failed[1] = 1;
     __syncthreads();
-    if (failed[1]) break;
+    return failed[1] ? kGaveUp : result;
+  };
+  int result = kGoesOn, it = 0;
+  int upto = A.check.first;  // (the next sweep with a check behind it)
+  for (;;) {
+    for (; it < upto && result == kGoesOn; ++it) {
+      sweep();
+      result = exchange(std::false_type{}, it);
+    }
+    if (result != kGoesOn) break;
+    sweep();
+    result = exchange(std::true_type{}, it);
+    if (result != kGoesOn || it == A.iters - 1) break;
+    ++nchecks;
+    ++it;
+    const GridArgs& L = late_args();
+    upto = min(it - 1 + L.check.every, L.iters - 1);
   }
-
   if (failed[0] || failed[1]) {  // (a workgroup that is not on the chip, or a word lost)
     if (t == 0) {
       A.status->broken = 1;
@@ -444,6 +550,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     return;
   }
 
+  const GridArgs& E = late_args();
   // ---- leave the last sweep's plan and sums, and the state after the last update, in memory ----
 #pragma unroll
   for (int q = 0; q < TW; ++q) {
@@ -453,7 +560,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     const int r0 = tr * kRows + stack * U;
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (tl < ntiles && r0 + u < S.m && j0 < S.n_mem) *reinterpret_cast<f4v*>(S.X + (size_t)(r0 + u) * S.ldx + j0) = x[q][u];
+      if (tl < ntiles && r0 + u < S.m && j0 < S.n_mem) *reinterpret_cast<f4v*>(E.S.X + (size_t)(r0 + u) * E.S.ldx + j0) = x[q][u];
   }
   for (int s = wave; s < 5 * kTiles; s += NW) {
     const int lt = s / 5, part = s - lt * 5;
@@ -465,16 +572,23 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       float sum = 0.f;
 #pragma unroll
       for (int k = 0; k < NT; ++k) sum += cs[lt][k][cc];
-      if (j < S.n) S.colpart[(size_t)tr * S.np + j] = sum;
+      if (j < S.n) {
+        E.S.colpart[(size_t)tr * E.S.np + j] = sum;
+        if (tr == 0) E.varphi_out[j] = lds_varphi[lt][cc];
+      }
     } else {
       const int i = tr * kRows + lane;
-      if (lane < kRows && i < S.m) S.rowpart[(size_t)seg * S.mp + i] = lds_row[lt][lane];
+      if (lane < kRows && i < S.m) {
+        E.S.rowpart[(size_t)seg * E.S.mp + i] = lds_row[lt][lane];
+        if (seg == 0) E.phi_out[i] = lds_phi[lt][lane];
+      }
       float tot = 0.f;
 #pragma unroll
       for (int k = 0; k < NT; ++k) tot += wt[lt][k];
-      if (lane == 0) S.tilesum[(size_t)tr * A.nseg + seg] = tot;
+      if (lane == 0) E.S.tilesum[(size_t)tr * A.nseg + seg] = tot;
     }
   }
-  if (entry_exists && lane < kGridBlock) (own_rows ? A.a_out : A.b_out)[entry] = state;
-  if (keeper && t == 0) *A.theta_out = theta;
+  const bool alt = (it & 1) == 0;  // (behind an odd number of updates)
+  if (entry_exists && lane < kGridBlock) (own_rows ? (alt ? E.a_alt : E.a_in) : (alt ? E.b_alt : E.b_in))[entry] = state;
+  if (keeper && t == 0) *(alt ? E.theta_alt : E.theta_in) = theta;
 }

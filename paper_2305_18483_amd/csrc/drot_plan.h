@@ -68,6 +68,7 @@ constexpr int kFirstPeriodLines = 6;  // ... where the sweep by lines takes over
 constexpr int kGridTiles32 = 5;       // 32-row tiles (two rows per wave, 16 waves of 128 registers)
 constexpr int kGridTiles64 = 3;       // 64-row tiles (eight rows per wave, 8 waves of 256 registers)
 constexpr int kGridWaves32 = 16, kGridWaves64 = 8;
+constexpr int kGridMostUnits = 256;   // workgroups at most
 constexpr int kGridBlock = 8;         // rows or columns whose part of eq. (6) a wave forms
 // Shorter stretches are not worth fetching the plan and the cost for.  Per iteration, in single launches and in one launch,
 // stretches of 4, 6, 8 and 10 sweeps: 200 x 300 10.4 and 13.6 us, 8.9 and 10.1, 8.3 and 8.5, 7.9 and 7.4; 1000 x 1000 11.3
@@ -196,14 +197,16 @@ inline Static make_static(const Problem& P, const Options& O) {
   // small-problem path on 32-row tiles, those that only skip zero segments on 64-row tiles (the same bits either way).
   // Above their size a problem is screened or streamed.
   const bool sweeps64 = S.can_pair && !S.small && O.skip_cost != 1 && O.skip_unchanged != 0 && !S.may_screen;
-  if (P.compute_units > 0 && !S.resident && ((S.fused && !P.slab_k) || sweeps64)) {
+  // (a launch has room for the squared residuals of the blocks that so many workgroups own)
+  const int units = P.compute_units < kGridMostUnits ? P.compute_units : kGridMostUnits;
+  if (units > 0 && !S.resident && ((S.fused && !P.slab_k) || sweeps64)) {
     const int tiles = sweeps64 ? S.nseg * S.ntr_tall : S.ntiles;
-    const int per_wg = ceil_div(tiles, P.compute_units);
+    const int per_wg = ceil_div(tiles, units);
     // (the first workgroup keeps theta, the waves of the others own the blocks of eq. (6): workgroups without a tile where
     // an oblong problem has more blocks than its tiles' workgroups have waves)
     const int owners = ceil_div(ceil_div(m, kGridBlock) + ceil_div(n, kGridBlock), sweeps64 ? kGridWaves64 : kGridWaves32);
     const int wgs = ceil_div(tiles, per_wg) > 1 + owners ? ceil_div(tiles, per_wg) : 1 + owners;
-    if (per_wg <= (sweeps64 ? kGridTiles64 : kGridTiles32) && wgs <= P.compute_units) {
+    if (per_wg <= (sweeps64 ? kGridTiles64 : kGridTiles32) && wgs <= units) {
       S.grid_tiles = per_wg;
       S.grid_wgs = wgs;
       S.grid_tall = sweeps64;
@@ -467,6 +470,27 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
   }
   T.k += 1;
   return Q;
+}
+
+// Checks inside the launch: where the sweeps between two checks are one launch anyway and nothing but the residual test hangs
+// on a check, the launch runs on through the checks and tests by itself.  Per check that saves the launch, the last vector
+// update, the norms, the status and its copy, and the fetching of X and C: 40 us in grid-resident stretches, 17 in the
+// resident kernel, of stretches of 100 sweeps that take 300 and 95.  The host looks at the checks after kRunSweeps sweeps
+// (of some 10 us at most, so that other work on the GPU waits no longer than tens of milliseconds) or kRunChecks checks.
+constexpr int kRunSweeps = 4096, kRunChecks = 256;
+
+inline bool runs_through_checks(const Static& S, const Problem& P, const Options& O) {
+  return (S.resident || S.grid_tiles > 0) && P.feedback && P.checking && !P.single_launches && !S.adaptive && O.gap_every < 1;
+}
+
+// Stretch R, which ends at a check or with the call, drawn out over the checks that follow.
+inline Stretch draw_out(const Problem& P, const Options& O, const State& T, Stretch R) {
+  for (int checks = 1; checks < kRunChecks && T.k + R.chunk < P.max_iters; ++checks) {
+    const int left = P.max_iters - (T.k + R.chunk), more = O.check_every < left ? O.check_every : left;
+    if (R.chunk > kRunSweeps - more) break;
+    R.chunk += more;
+  }
+  return R;
 }
 
 // How many sweeps of stretch R are launched one by one before a single grid-resident launch takes the rest, or -1 if

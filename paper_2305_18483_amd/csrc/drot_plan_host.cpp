@@ -205,6 +205,29 @@ void drot_plan_grid(const int* problem, const int* options, int compute_units, i
   out[3] = S.adaptive_pairs;
 }
 
+// Launches that make the residual checks themselves: the sweeps of the first one of a call that has done k iterations (0: it
+// makes none), problem and options as in drot_plan_trace.
+int drot_plan_run(const int* problem, const int* options, int compute_units, int single_launches, int k) {
+  Problem P;
+  P.m = problem[0];
+  P.n = problem[1];
+  P.reg_kind = problem[2];
+  P.feedback = problem[11] != 0;
+  P.checking = problem[12] != 0;
+  P.max_iters = problem[13];
+  P.compute_units = compute_units;
+  P.single_launches = single_launches != 0;
+  Options O;
+  O.check_every = options[0];
+  O.resident = options[1];
+  O.gap_every = options[8];
+  const Static S = make_static(P, O);
+  if (!runs_through_checks(S, P, O)) return 0;
+  State T = start_state(S, P, Carry{});
+  T.k = k;
+  return draw_out(P, O, T, next_stretch(S, P, O, T)).chunk;
+}
+
 // Label analysis of the group-lasso path: returns slab_k (0: two-pass), -1 for a label out of range;
 // *nruns receives the number of runs.
 int drot_plan_labels(const int* labels, int m, int num_classes, int max_runs, int force_two_pass, int* nruns) {

@@ -3,8 +3,8 @@
 
 // ------------------------------------------------------------------------------------------
 // Resident solver for tiny problems (at most 128 x 256): one workgroup of 16 waves keeps X and C in registers
-// and runs a whole stretch of iterations (the ones between two residual checks) in one launch, so
-// an iteration costs two workgroup barriers instead of a kernel launch.  The eq. (6) state lives in
+// and runs on through the residual checks in one launch, so an iteration costs two workgroup barriers instead of a kernel
+// launch (a launch for every check: 2.27 ms for 2000 iterations of 100 x 100, checked every 100; so 2.03).  The eq. (6) state lives in
 // registers of "owner" threads: thread t < m owns row t (a_t, p_t), the column owners follow further
 // up (b_j, q_j); phi and varphi travel through LDS.  Per iteration: (A) every wave updates its rows
 // (first half of eq. (8) and the quadratic scaling), leaves the row sums and its column partials in
@@ -18,18 +18,44 @@ struct ResidentArgs {
   const float* p;
   const float* q;
   VecState V;
-  const double* a_in;
-  const double* b_in;
-  double* a_out;
-  double* b_out;
-  int theta_in, theta_out;  // entries of V.theta to read and to write
+  double* a_in;   // a, b before the launch; what they are after an odd number of sweeps goes to the other halves, after an
+  double* b_in;   // even number back to where it came from
+  double* a_alt;
+  double* b_alt;
+  int theta_in;   // entry of V.theta to read
   int m, n, ldx, ldc;
   float rho, scale;
   int iters;  // sweeps to run (>= 1)
   int first;  // X_0 = 0: nothing to read
+  CheckArgs check;
 };
 
 constexpr int kResidentCols = 256, kResidentMaxRows = 128;
+
+// The check behind sweep `it`, by the whole workgroup: the norms as block_sum_f64 forms them, with few registers.
+__device__ __forceinline__ bool resident_check(const ResidentArgs& A, double r2, double s2, int nchecks, int it, double* red, int* passed) {
+  const int t = threadIdx.x;
+  double norm2[2] = {0.0, 0.0};
+#pragma unroll 1
+  for (int k = 0; k < 2; ++k) {
+    double v = k == 0 ? r2 : s2;
+#pragma unroll 1
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    __syncthreads();
+    if ((t & 63) == 0) red[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+      double sum = 0.0;
+#pragma unroll 1
+      for (int w = 0; w < 16; ++w) sum += red[w];
+      if (k == 0) norm2[0] = sum;
+      else norm2[1] = sum;
+    }
+  }
+  if (t == 0) *passed = make_check(A.check, nchecks, it, norm2[0], norm2[1]) ? 1 : 0;
+  __syncthreads();
+  return *passed != 0;
+}
 
 // At most 16 rows: a row to each of 16 waves, CPL columns to a lane (n <= 64 * CPL).
 constexpr int kResidentRows = 16;
@@ -43,6 +69,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
   __shared__ float lds_row[kResidentMaxRows];
   __shared__ float lds_col[NW][64 * CPL];
   __shared__ double red[NW];
+  __shared__ int passed;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int j0 = lane * CPL;
@@ -79,7 +106,12 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
   const bool owner_wave = wave < 2 || (wave >= 4 && wave < 8);
   double res = 0.0;  // the owner's residual after the latest sweep
   float dual = 0.f;  // the owner's phi_t resp. varphi_j
-  for (int it = 0; it < A.iters; ++it) {
+  // (stretches of sweeps up to a check, or all of them)
+  const bool checks = A.check.out != nullptr;
+  int nchecks = 0, it = 0, upto = checks ? A.check.first + 1 : A.iters;
+  for (;;) {
+#pragma unroll 1
+  for (; it < upto; ++it) {
     // (A) sweep
     float vp[CPL];
 #pragma unroll
@@ -120,24 +152,31 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
     }
     __syncthreads();
   }
+  if (!checks) break;
+  if (resident_check(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  ++nchecks;
+  upto = min(it + A.check.every, A.iters);
+  }
+  const bool alt = (it & 1) != 0;
 
 #pragma unroll
   for (int e = 0; e < CPL; ++e)
     if (wave < A.m && j0 + e < A.n) A.X[(size_t)wave * A.ldx + j0 + e] = x[e];
   if (row_owner) {
     A.V.phi[t] = dual;
-    A.a_out[t] = state;
+    (alt ? A.a_alt : A.a_in)[t] = state;
     A.V.r[t] = res;
   }
   if (col_owner) {
     A.V.varphi[jc] = dual;
-    A.b_out[jc] = state;
+    (alt ? A.b_alt : A.b_in)[jc] = state;
     A.V.s[jc] = res;
   }
+  if (t == 0) A.V.theta[A.theta_in ^ (alt ? 1 : 0)] = theta;
+  if (checks) return;  // (the last check has left the norms)
   const double r2 = block_sum_f64(row_owner ? res * res : 0.0, red);
   const double s2 = block_sum_f64(col_owner ? res * res : 0.0, red);
   if (t == 0) {
-    A.V.theta[A.theta_out] = theta;
     A.V.resid[0] = r2;
     A.V.resid[1] = s2;
     A.V.resid[2] = 0.0;
@@ -165,6 +204,7 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
   __shared__ float lds_row[kResidentMaxRows];
   __shared__ float lds_col[NW][64 * EQ];
   __shared__ double red[NW];
+  __shared__ int passed;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int col = lane & 15, group = lane >> 4;
@@ -209,8 +249,12 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
   const int col_at = 16 * (((group & 1) << 1) | (group >> 1)) + col;
   double res = 0.0;  // the owner's residual after the latest sweep
   float dual = 0.f;  // the owner's phi_t resp. varphi_j
+  // (stretches of sweeps up to a check, or all of them)
+  const bool checks = A.check.out != nullptr;
+  int nchecks = 0, it = 0, upto = checks ? A.check.first + 1 : A.iters;
+  for (;;) {
 #pragma unroll 1
-  for (int it = 0; it < A.iters; ++it) {
+  for (; it < upto; ++it) {
     // (A) sweep
     float vp[E], colacc[4 * EQ];
 #pragma unroll
@@ -280,6 +324,12 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
     }
     __syncthreads();
   }
+  if (!checks) break;
+  if (resident_check(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  ++nchecks;
+  upto = min(it + A.check.every, A.iters);
+  }
+  const bool alt = (it & 1) != 0;
 
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -290,18 +340,19 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
   }
   if (row_owner) {
     A.V.phi[t] = dual;
-    A.a_out[t] = state;
+    (alt ? A.a_alt : A.a_in)[t] = state;
     A.V.r[t] = res;
   }
   if (col_owner) {
     A.V.varphi[jc] = dual;
-    A.b_out[jc] = state;
+    (alt ? A.b_alt : A.b_in)[jc] = state;
     A.V.s[jc] = res;
   }
+  if (t == 0) A.V.theta[A.theta_in ^ (alt ? 1 : 0)] = theta;
+  if (checks) return;  // (the last check has left the norms)
   const double r2 = block_sum_f64(row_owner ? res * res : 0.0, red);
   const double s2 = block_sum_f64(col_owner ? res * res : 0.0, red);
   if (t == 0) {
-    A.V.theta[A.theta_out] = theta;
     A.V.resid[0] = r2;
     A.V.resid[1] = s2;
     A.V.resid[2] = 0.0;

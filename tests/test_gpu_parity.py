@@ -1256,6 +1256,45 @@ def test_grid_resident_stretches_give_the_bits_of_single_launches(drot, m, n):
     assert (res.r_row, res.r_col, res.objective, res.gap) == (res1.r_row, res1.r_col, res1.objective, res1.gap)
 
 
+@pytest.mark.parametrize("m,n", [(16, 200), (60, 60), (128, 256), (129, 2), (1000, 1000), (2047, 5101), (2300, 2500), (2999, 3307),
+                                 (20, 5000)])
+def test_checks_inside_a_launch_are_those_of_a_launch_each(drot, m, n):
+    # one launch runs through many checks: the records of all of them, a stop at one in the middle (behind an even and an odd
+    # number of sweeps), what is left for a continued call, more checks than one launch makes.  Profile mode launches and
+    # tests one by one.
+    P = drot_inputs.random_problem(m, n, seed=2680 + m, reg_kind=1, lam=0.3)
+    solver, ref = drot.Solver(m, n, check_every=7), drot.Solver(m, n, check_every=7)
+    ref.set_profile(True)
+    _say(f"checks inside a launch {m}x{n}")
+
+    def same(K, X=None, X1=None, **kw):
+        a, b = pu.gpu_solve(solver, P, K, X_out=X, **kw), pu.gpu_solve(ref, P, K, X_out=X1, **kw)
+        for u, v in zip(a[1:], b[1:]):
+            assert np.array_equal(u, v)
+        assert (a[0].iters, a[0].converged, a[0].r_row, a[0].r_col, a[0].objective) == (b[0].iters, b[0].converged, b[0].r_row, b[0].r_col, b[0].objective)
+        ca, cb = solver.checks(), ref.checks()
+        assert [(c.iters, c.r_row, c.r_col) for c in ca] == [(c.iters, c.r_row, c.r_col) for c in cb]
+        return a[0], ca
+
+    _, checks = same(60, tol=1e-12)
+    assert [c.iters for c in checks] == [7, 14, 21, 28, 35, 42, 49, 56, 60]
+    # (the worst residual so far falls at the checks up to the stop: the first check at or below it is the one that stops)
+    worst = [max(c.r_row, c.r_col) for c in checks]
+    X, X1 = torch.empty((m, n), device="cuda:0"), torch.empty((m, n), device="cuda:0")
+    for stop in (2, 5):  # (behind 21 and 42 sweeps, or sooner)
+        tol = float(np.nextafter(np.float32(worst[stop]), np.float32(1)))
+        first = next(k for k, w in enumerate(worst) if w <= tol)
+        res, seen = same(60, X, X1, tol=tol)
+        assert res.converged and res.iters == checks[first].iters and len(seen) == first + 1
+        solver.set_continue(True), ref.set_continue(True)
+        same(20, X, X1, tol=1e-12)
+        same(9, X, X1)
+        solver.set_continue(False), ref.set_continue(False)
+    solver.set_check_every(1), ref.set_check_every(1)
+    _, checks = same(300, tol=1e-12)
+    assert [c.iters for c in checks] == list(range(1, 301))
+
+
 def test_two_threads_solve_on_two_streams(drot):
     # launches whose workgroups wait for one another, from two handles at once: one after the other on the chip
     import threading

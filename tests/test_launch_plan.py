@@ -536,3 +536,21 @@ def test_grid_resident_stretches_where_the_registers_of_the_chip_hold_the_proble
     assert grid(1000, 1000, from_points=1)[0] == 0 and grid(1000, 1000, reg_kind=2)[0] == 0
     # no even/odd pairs where nothing is streamed, whoever asks for single launches
     assert grid(2999, 3307)[3] == 0 and grid(2999, 3307, single=1)[3] == 0 and grid(2999, 3307, units=0)[3] == 1
+
+
+def test_launches_run_on_through_the_residual_checks(planlib):
+    def run(m, n, iters, check_every=100, k=0, feedback=1, checking=1, resident=-1, gap_every=0, units=256, single=0):
+        problem = (ctypes.c_int * 14)(m, n, 1, 0, 0, 0, 0, 1, 1, 0, 0, feedback, checking, iters)
+        options = (ctypes.c_int * 9)(check_every, resident, -1, -1, -1, -1, -1, 0, gap_every)
+        return planlib.drot_plan_run(problem, options, units, single, k)
+
+    for m, n in ((100, 100), (1000, 1000), (2999, 3307)):
+        assert run(m, n, 1000) == 1000 and run(m, n, 130) == 130 and run(m, n, 130, k=70) == 60 and run(m, n, 7, check_every=1) == 7
+        # the host looks at them after 4096 sweeps or 256 checks, at a check each time
+        assert run(m, n, 100000) == 4000 and run(m, n, 100000, k=150) == 50 + 4000 and run(m, n, 1000, check_every=1) == 256
+        assert run(m, n, 100000, check_every=5000) == 5000 and run(m, n, 6000, check_every=5000, k=5000) == 1000
+        # not where the gap is evaluated at checks, nothing is tested, the host reads no status, or every sweep is timed
+        assert run(m, n, 1000, gap_every=1) == 0 and run(m, n, 1000, checking=0) == 0 and run(m, n, 1000, feedback=0) == 0
+        assert run(m, n, 1000, single=1) == 0
+    assert run(100, 100, 1000, units=0) == 1000 and run(1000, 1000, 1000, units=0) == 0 and run(5000, 5000, 1000) == 0
+    assert run(2, 32600, 1000) == 1000 and run(2, 32640, 1000) == 0  # (more blocks of columns than workgroups own)
