@@ -53,6 +53,7 @@ namespace {
 #include "drot_resident.h"
 #include "drot_gap.h"
 #include "drot_grid.h"
+#include "drot_grid_slab.h"
 
 // ------------------------------------------------------------------------------------------
 // host side
@@ -63,7 +64,7 @@ using plan::ceil_div;
 // the planner's picture of the kernels' geometry must be the kernels' own
 static_assert(plan::kSegCols == kSegCols && plan::kTileRows == kTileRows && plan::kAlignElems == kAlignElems, "tiles");
 static_assert(plan::kTallTileRows == kScreenRows * kScreenWaves && plan::kTallTileRows == 64, "64-row tiles");
-static_assert(plan::kSlabCols == kSlabCols && plan::kSlabRowLanes == kSlabRowLanes && plan::kSlabMaxRows == kSlabMaxRows, "slabs");
+static_assert(plan::kSlabCols == kSlabCols && plan::kSlabLanes == kSlabLanes && plan::kSlabRowLanes == kSlabRowLanes && plan::kSlabMaxRows == kSlabMaxRows, "slabs");
 static_assert(plan::kResidentMaxRows == kResidentMaxRows && plan::kResidentCols == kResidentCols, "resident kernel");
 static_assert(plan::kColGroup == kColGroup, "column-sum groups of the lean sweep");
 static_assert(plan::kGridBlock == kGridBlock, "owner blocks of the grid-resident kernel");
@@ -456,17 +457,27 @@ hipError_t launch_grid(const GridArgs& A, int workgroups, hipStream_t stream) {
 struct GridWords {
   size_t col, tot, ent, sq, cst, half;
 };
-GridWords grid_words(const plan::Static& S, int m, int n) {
-  const size_t nblk_m = (size_t)ceil_div(m, kGridBlock), nblk_n = (size_t)ceil_div(n, kGridBlock);
-  const size_t ntr = (size_t)(S.grid_tall ? S.ntr_tall : S.ntr);
+GridWords grid_words(const plan::Static& S, const plan::Problem& P) {
+  const size_t nblk_m = (size_t)ceil_div(P.m, kGridBlock), nblk_n = (size_t)ceil_div(P.n, kGridBlock);
+  const size_t parts = S.grid_slab_lanes ? (size_t)(kSlabLanes / S.grid_slab_lanes) : 1;  // (of a slab)
+  const size_t nseg = (S.grid_slab_lanes ? (size_t)S.nstrips : (size_t)S.nseg) * parts;
+  const size_t ntr = (size_t)(S.grid_slab_lanes ? plan::slab_col_rows(P.nruns, P.mapped_rows) : S.grid_tall ? S.ntr_tall : S.ntr);
   GridWords W;
-  W.col = nblk_m * (size_t)S.nseg * kGridBlock;
+  W.col = nblk_m * nseg * kGridBlock;
   W.tot = W.col + nblk_n * ntr * kGridBlock;
-  W.ent = W.tot + (size_t)S.nseg * (ntr + kColGroup);  // (totals: whole groups of kColGroup tile rows for the 64-row tiles)
+  W.ent = W.tot + nseg * (ntr + kColGroup);  // (totals: whole groups of kColGroup tile rows for the 64-row tiles)
   W.sq = W.ent + 2 * (nblk_m + nblk_n) * kGridBlock;
   W.cst = (W.sq + 2 * (nblk_m + nblk_n) + 31) / 32 * 32;
   W.half = W.cst + 32 * kGridCopies;
   return W;
+}
+
+template <int K, int CX, int TW>
+hipError_t launch_grid_slab(const GridArgs& A, const GridSlabArgs& B, int workgroups, hipStream_t stream) {
+  void* args[] = {const_cast<GridArgs*>(&A), const_cast<GridSlabArgs*>(&B)};
+  const void* kernel = B.rows ? reinterpret_cast<const void*>(grid_slab_kernel<K, CX, TW, true>)
+                              : reinterpret_cast<const void*>(grid_slab_kernel<K, CX, TW, false>);
+  return hipLaunchCooperativeKernel(kernel, dim3(workgroups), dim3(kSlabRowLanes * CX), args, 0, stream);
 }
 
 constexpr int kMaxDevices = 64;
@@ -492,11 +503,12 @@ constexpr int kGridRefused = -1001, kGridGaveUp = -1002;
 int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   drot_handle h = Z.h;
   const plan::Static& S = Z.S;
-  const int ntr = S.grid_tall ? S.ntr_tall : S.ntr;
+  const bool slab = S.grid_slab_lanes != 0;
+  const int ntr = slab ? plan::slab_col_rows(Z.P.nruns, Z.P.mapped_rows) : S.grid_tall ? S.ntr_tall : S.ntr;
   const int nblk_m = ceil_div(Z.m, kGridBlock), nblk_n = ceil_div(Z.n, kGridBlock);
   const int iters = (int)(last.sw - first.sw) + 1;
   // (totals: groups of kColGroup tile rows for the 64-row tiles, none missing)
-  const GridWords W = grid_words(S, Z.m, Z.n);
+  const GridWords W = grid_words(S, Z.P);
   const size_t need = 2 * W.half, had = h->xchg_len;
   const int rc = grow_buffer(&h->xchg, &h->xchg_len, need, Z.stream);
   if (rc == DROT_ERR_ALLOC) {
@@ -540,7 +552,7 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   A.varphi_out = h->varphi;
   A.r = h->r;
   A.s = h->s;
-  A.nseg = S.nseg;
+  A.nseg = slab ? S.nstrips : S.nseg;
   A.ntr = ntr;
   A.nblk_m = nblk_m;
   A.nblk_n = nblk_n;
@@ -551,7 +563,21 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   h->xchg_tag += (unsigned)iters;
   const int wgs = S.grid_wgs;
   hipError_t e;
-  if (S.grid_tall) {
+  if (slab) {
+    const int* const table = h->runbuf + 2 * Z.P.nruns;  // (the classes' rows, then all rows class by class)
+    const int pitch = kSlabRowLanes * Z.P.slab_k;
+    const bool mapped = Z.P.mapped_rows;
+    const GridSlabArgs B{h->runbuf, h->runbuf + Z.P.nruns, mapped ? table : nullptr,
+                         mapped ? table + (size_t)Z.P.nruns * (size_t)pitch : nullptr, pitch, Z.P.nruns, Z.thr, S.small ? 1 : 0};
+    const bool k8 = S.grid_slab_k == 8;
+    switch (S.grid_slab_lanes) {
+      case 4: e = k8 ? launch_grid_slab<8, 4, 1>(A, B, wgs, Z.stream) : launch_grid_slab<4, 4, 1>(A, B, wgs, Z.stream); break;
+      default:
+        e = k8 ? launch_grid_slab<8, 8, 1>(A, B, wgs, Z.stream)
+               : S.grid_tiles == 2 ? launch_grid_slab<4, 8, 2>(A, B, wgs, Z.stream) : launch_grid_slab<4, 8, 1>(A, B, wgs, Z.stream);
+        break;
+    }
+  } else if (S.grid_tall) {
     switch (S.grid_tiles) {
       case 1: e = launch_grid<8, 8, 8, 1, 0, kColGroup>(A, wgs, Z.stream); break;
       case 2: e = launch_grid<8, 8, 8, 2, 1, kColGroup>(A, wgs, Z.stream); break;
@@ -811,8 +837,16 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
     if (L.slab_k) {
       std::vector<int> table(L.start);  // run_start[0..nruns), run_len[0..nruns), the rows where they are not consecutive
       table.insert(table.end(), L.len.begin(), L.len.end());
-      table.insert(table.end(), L.rows.begin(), L.rows.end());
       P.mapped_rows = !L.rows.empty();
+      if (P.mapped_rows) {
+        table.insert(table.end(), L.rows.begin(), L.rows.end());
+        // all rows class by class, and where each class begins there
+        const size_t pitch = (size_t)kSlabRowLanes * (size_t)L.slab_k;
+        for (size_t c = 0, first = 0; c < L.len.size(); first += (size_t)L.len[c], ++c) {
+          table[c] = (int)first;
+          table.insert(table.end(), L.rows.begin() + (ptrdiff_t)(c * pitch), L.rows.begin() + (ptrdiff_t)(c * pitch) + L.len[c]);
+        }
+      }
       const int rc2 = grow_buffer(&h->runbuf, &h->runbuf_len, table.size(), stream);
       if (rc2 != DROT_OK) return rc2;
       DROT_HIP(hipMemcpy(h->runbuf, table.data(), sizeof(int) * table.size(), hipMemcpyHostToDevice));
@@ -832,7 +866,7 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   }
   Z.S = plan::make_static(P, Z.O);
   // (a fixed workspace does not grow)
-  if (A.fixed_schedule && Z.S.grid_tiles && 2 * grid_words(Z.S, m, n).half > h->xchg_len) P.single_launches = true;
+  if (A.fixed_schedule && Z.S.grid_tiles && 2 * grid_words(Z.S, P).half > h->xchg_len) P.single_launches = true;
   Z.T = plan::start_state(Z.S, P, h->carry);
   const plan::Static& S = Z.S;
 
@@ -991,6 +1025,7 @@ int iterate(Solve& Z, bool* converged_out) {
         Z.check = CheckArgs{};
         if (rc == DROT_OK) {
           Z.T.norms_pending = false;
+          if (S.grid_slab_lanes) Z.T.sums_gen = -1;  // (the slabs leave no sums)
           break;
         }
         if (rc != kGridRefused) return rc;

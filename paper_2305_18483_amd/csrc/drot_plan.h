@@ -43,6 +43,7 @@ constexpr int kTileRows = 32;         // rows of the small tile
 constexpr int kTallTileRows = 64;     // rows of the tile of Tall64, Screened8 and Lean
 constexpr int kAlignElems = 32;       // rows must start on 128-byte lines
 constexpr int kSlabCols = 32;         // columns of a group-lasso slab
+constexpr int kSlabLanes = 8;         // lanes along them
 constexpr int kSlabRowLanes = 128;    // row lanes of the slab kernel (K = 1, 2, 4, 8 rows per lane)
 constexpr int kSlabMaxRows = 1024;    // longest class the slab kernel holds
 // The fused update has every slab's workgroup add up all the partial sums of its rows and columns again: cheap as long as
@@ -74,6 +75,9 @@ constexpr int kGridBlock = 8;         // rows or columns whose part of eq. (6) a
 // stretches of 4, 6, 8 and 10 sweeps: 200 x 300 10.4 and 13.6 us, 8.9 and 10.1, 8.3 and 8.5, 7.9 and 7.4; 1000 x 1000 11.3
 // and 13.7, 9.9 and 10.2, 9.9 and 8.5, 9.4 and 7.5 (one tile a workgroup); 2048 x 3072 24.0 and 18.5 at 4, 64-row tiles of
 // 2300 x 2500 17.8 and 17.8, 2999 x 3307 21.3 and 21.3.
+// Slabs (drot_grid_slab.h): rows per thread at least (idle ones cost little), and at most, over a workgroup's slabs (registers
+// hold X, the LDS C).  Half slabs to a workgroup where all of them are on the chip at once, else whole ones, else two.
+constexpr int kGridSlabLeastK = 4, kGridSlabRows = 8;
 constexpr int kGridMinSweeps = 4, kGridMinSweepsOneTile = 8;
 // (a full sweep takes 230 to 260 us at 12000 x 12000, d = 32, the screened one 7 for every percent of the row segments left)
 constexpr double kPointsSparse = 0.33;
@@ -162,6 +166,8 @@ struct Static {
   int grid_tiles = 0;            // grid-resident stretches: tiles per workgroup, 0: none
   int grid_wgs = 0;              // ... and workgroups
   bool grid_tall = false;        // ... of 64 rows each (else 32)
+  int grid_slab_lanes = 0;       // slabs in place of tiles: lanes along the columns of a workgroup (8, or 4: half a slab), else 0
+  int grid_slab_k = 0;           // ... and rows per thread
   bool status_at_checks = false; // the stretches end with a status kernel (stopping test and / or density)
 };
 
@@ -211,6 +217,22 @@ inline Static make_static(const Problem& P, const Options& O) {
       S.grid_wgs = wgs;
       S.grid_tall = sweeps64;
     }
+  }
+  // (group lasso: every workgroup holds slabs, none owns blocks only)
+  if (units > 0 && P.slab_k && (S.small ? S.fused : (size_t)S.nstrips * (size_t)P.nruns <= P.tilesum_half)) {
+    const int k = P.slab_k < kGridSlabLeastK ? kGridSlabLeastK : P.slab_k;
+    const int slabs = S.nstrips * P.nruns, blocks = ceil_div(m, kGridBlock) + ceil_div(n, kGridBlock);
+    auto take = [&](int lanes, int per_wg) {
+      const int wgs = ceil_div(slabs * (kSlabLanes / lanes), per_wg), owners = ceil_div(blocks, kSlabRowLanes * lanes / 64);
+      if (S.grid_tiles || wgs > units || 1 + owners > wgs) return;
+      S.grid_tiles = per_wg;
+      S.grid_wgs = wgs;
+      S.grid_slab_lanes = lanes;
+      S.grid_slab_k = k;
+    };
+    take(4, 1);
+    take(8, 1);
+    if (k * 2 <= kGridSlabRows) take(8, 2);
   }
   S.adaptive_pairs = P.feedback && S.can_pair && !S.small && O.skip_cost == -1 && O.skip_unchanged != 0 && !S.grid_tiles;
   S.points_screen = P.from_points && O.skip_unchanged != 0 &&
@@ -500,7 +522,7 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
   if (!S.grid_tiles || P.single_launches) return -1;
   const bool cold = T.k_base + T.k == 0 && !P.warm;
   const int head = S.grid_tall && cold ? 1 : 0;
-  const int least = !S.grid_tall && S.grid_tiles == 1 ? kGridMinSweepsOneTile : kGridMinSweeps;
+  const int least = S.grid_slab_lanes || (!S.grid_tall && S.grid_tiles == 1) ? kGridMinSweepsOneTile : kGridMinSweeps;
   return R.chunk - head >= least ? head : -1;
 }
 

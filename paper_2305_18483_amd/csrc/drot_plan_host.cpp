@@ -205,6 +205,27 @@ void drot_plan_grid(const int* problem, const int* options, int compute_units, i
   out[3] = S.adaptive_pairs;
 }
 
+// Grid-resident slabs of a group-lasso problem.  out[4]: slabs per workgroup (0: none), lanes along the columns, rows per
+// thread, workgroups.
+void drot_plan_slabs(int m, int n, int slab_k, int nruns, int mapped, int fused_update, int compute_units, int* out) {
+  Problem P;
+  P.m = m;
+  P.n = n;
+  P.reg_kind = kGroupLasso;
+  P.slab_k = slab_k;
+  P.nruns = nruns;
+  P.mapped_rows = mapped != 0;
+  P.tilesum_half = 4096;
+  P.compute_units = compute_units;
+  Options O;
+  O.fused_update = fused_update;
+  const Static S = make_static(P, O);
+  out[0] = S.grid_tiles;
+  out[1] = S.grid_slab_lanes;
+  out[2] = S.grid_slab_k;
+  out[3] = S.grid_wgs;
+}
+
 // Launches that make the residual checks themselves: the sweeps of the first one of a call that has done k iterations (0: it
 // makes none), problem and options as in drot_plan_trace.
 int drot_plan_run(const int* problem, const int* options, int compute_units, int single_launches, int k) {

@@ -186,3 +186,15 @@ def test_a_launch_that_gives_up_is_replaced_by_single_launches(drot, m, n):
     for bad in (0, -1, (1 << 30) + 1):
         with pytest.raises(drot.DrotError):
             solver.set_grid_polls(bad)
+
+
+def test_a_launch_of_slabs_that_gives_up_is_replaced_by_single_launches(drot):
+    P = drot_inputs.random_problem(1500, 1000, seed=2655, reg_kind=2, lam=0.1, mu=0.02, num_classes=2)
+    _say("a launch of slabs that gives up")
+    _, X_ref, phi_ref, varphi_ref = pu.gpu_solve(drot.Solver(P.m, P.n), P, 150, tol=1e-12)
+    solver = drot.Solver(P.m, P.n)
+    solver.set_grid_polls(1)
+    for _ in range(2):
+        res, X, phi, varphi = pu.gpu_solve(solver, P, 150, tol=1e-12)
+        assert res.iters == 150 and [c.iters for c in solver.checks()] == [100, 150]
+        assert np.array_equal(X, X_ref) and np.array_equal(phi, phi_ref) and np.array_equal(varphi, varphi_ref)

@@ -1295,6 +1295,45 @@ def test_checks_inside_a_launch_are_those_of_a_launch_each(drot, m, n):
     assert [c.iters for c in checks] == list(range(1, 301))
 
 
+@pytest.mark.parametrize("m,n,classes,order", [(1500, 1000, 2, "runs"), (1201, 1001, 2, "anywhere"), (333, 517, 3, "runs"), (258, 1057, 2, "anywhere"),
+                                               (2000, 1501, 5, "anywhere"), (1203, 2047, 5, "runs"), (1999, 2017, 5, "anywhere"),
+                                               (1000, 3001, 1, "runs"), (1024, 8190, 1, "runs"), (1000, 2000, 8, "runs")])
+def test_grid_resident_slabs_give_the_bits_of_single_launches(drot, m, n, classes, order):
+    # half slabs, whole ones, two to a workgroup; up to 512 and up to 1024 rows to a class; last halves and whole last parts
+    # past n; checks in the middle and a stop at one, a continued call, a warm start.  Profile mode launches every sweep by itself.
+    P = drot_inputs.random_problem(m, n, seed=2900 + m + n, reg_kind=2, lam=0.1, mu=0.02, num_classes=classes)
+    if order == "anywhere":
+        P.row_class = np.random.default_rng(m).permutation(P.row_class)
+    solver, ref = drot.Solver(m, n, check_every=13), drot.Solver(m, n, check_every=13)
+    ref.set_profile(True)
+    _say(f"grid-resident slabs {m}x{n}, {classes} classes, {order}")
+    C, p, q, rc = pu.to_dev(P)
+    kw = dict(reg_kind=2, lam=P.lam, mu=P.mu, row_class=rc, num_classes=classes)
+
+    def same(K, X=None, X1=None, **more):
+        a, b = pu.gpu_solve(solver, P, K, X_out=X, **more), pu.gpu_solve(ref, P, K, X_out=X1, **more)
+        for u, v in zip(a[1:], b[1:]):
+            assert np.array_equal(u, v)
+        # (the residuals' squares of rows anywhere are added up class by class)
+        assert (a[0].iters, a[0].converged) == (b[0].iters, b[0].converged) and np.allclose([a[0].r_row, a[0].r_col], [b[0].r_row, b[0].r_col], rtol=1e-6)
+        assert [c.iters for c in solver.checks()] == [c.iters for c in ref.checks()]
+        return a
+
+    _, X60, phi60, varphi60 = same(60, tol=1e-12)
+    worst = [max(c.r_row, c.r_col) for c in solver.checks()]
+    X, X1 = torch.empty((m, n), device="cuda:0"), torch.empty((m, n), device="cuda:0")
+    same(60, X, X1, tol=float(np.float32(worst[2]) * np.float32(1.0001)))
+    solver.set_continue(True), ref.set_continue(True)
+    same(21, X, X1)
+    solver.set_continue(False), ref.set_continue(False)
+    phi, varphi = torch.from_numpy(phi60).cuda(), torch.from_numpy(varphi60).cuda()
+    outs = []
+    for s in (solver, ref):
+        X.copy_(torch.from_numpy(X60))
+        outs.append(s.solve(C, p, q, X_out=X, phi0=phi, varphi0=varphi, max_iters=17, **kw).X.cpu().numpy())
+    assert np.array_equal(*outs)
+
+
 def test_two_threads_solve_on_two_streams(drot):
     # launches whose workgroups wait for one another, from two handles at once: one after the other on the chip
     import threading

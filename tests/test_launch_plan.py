@@ -554,3 +554,22 @@ def test_launches_run_on_through_the_residual_checks(planlib):
         assert run(m, n, 1000, single=1) == 0
     assert run(100, 100, 1000, units=0) == 1000 and run(1000, 1000, 1000, units=0) == 0 and run(5000, 5000, 1000) == 0
     assert run(2, 32600, 1000) == 1000 and run(2, 32640, 1000) == 0  # (more blocks of columns than workgroups own)
+
+
+def test_grid_resident_slabs_where_every_workgroup_holds_one(planlib):
+    def slabs(m, n, k, nruns, mapped=0, fused_update=-1, units=256):
+        out = (ctypes.c_int * 4)()
+        planlib.drot_plan_slabs(m, n, k, nruns, mapped, fused_update, units, out)
+        return tuple(out)
+
+    assert slabs(1500, 1000, 8, 2) == (1, 4, 8, 128) == slabs(1500, 1000, 8, 2, mapped=1)     # half slabs
+    assert slabs(150, 300, 1, 2) == (1, 4, 4, 40)                                             # idle rows
+    assert slabs(2048, 2048, 8, 2) == (1, 4, 8, 256) and slabs(2048, 2049, 8, 2) == (1, 8, 8, 130)
+    assert slabs(2000, 1500, 4, 5) == (1, 8, 4, 235) and slabs(1024, 8192, 8, 1) == (1, 8, 8, 256)
+    assert slabs(2000, 2500, 4, 5) == (2, 8, 4, 198) and slabs(2048, 4096, 4, 4) == (2, 8, 4, 256)
+    assert slabs(2048, 4097, 4, 4)[0] == 0 and slabs(1024, 8193, 8, 1)[0] == 0 and slabs(5000, 5000, 4, 10)[0] == 0
+    # no workgroup without a slab: their waves own the blocks of eight rows and columns
+    assert slabs(700, 90, 8, 1)[0] == 0 and slabs(1024, 256, 8, 1)[0] == 0 and slabs(1024, 384, 8, 1) == (1, 4, 8, 24)
+    # not beside the separate vector update it is compared with, nor without cooperative launches; a smaller partition
+    assert slabs(1500, 1000, 8, 2, fused_update=0)[0] == 0 and slabs(1500, 1000, 8, 2, units=0)[0] == 0
+    assert slabs(1500, 1000, 8, 2, units=64) == (1, 8, 8, 64) and slabs(1500, 1000, 8, 2, units=32)[0] == 0
