@@ -33,6 +33,7 @@ struct ResidentArgs {
 constexpr int kResidentCols = 256, kResidentMaxRows = 128;
 
 // The check behind sweep `it`, by the whole workgroup: the norms as block_sum_f64 forms them, with few registers.
+template <int NW>
 __device__ __forceinline__ bool resident_check(const ResidentArgs& A, double r2, double s2, int nchecks, int it, double* red, int* passed) {
   const int t = threadIdx.x;
   double norm2[2] = {0.0, 0.0};
@@ -47,7 +48,7 @@ __device__ __forceinline__ bool resident_check(const ResidentArgs& A, double r2,
     if (t == 0) {
       double sum = 0.0;
 #pragma unroll 1
-      for (int w = 0; w < 16; ++w) sum += red[w];
+      for (int w = 0; w < (NW == 16 ? 16 : (int)blockDim.x >> 6); ++w) sum += red[w];
       if (k == 0) norm2[0] = sum;
       else norm2[1] = sum;
     }
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
     __syncthreads();
   }
   if (!checks) break;
-  if (resident_check(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  if (resident_check<NW>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
   ++nchecks;
   upto = min(it + A.check.every, A.iters);
   }
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
 }
 
 // The general case: 16 lanes to a row, four rows to a wave at a time, R times.  What bounds an iteration is the issue of
-// vector instructions, 16 waves on one compute unit, and then the fp64 chain of the owners (0.4 us of it all).  With 64
+// vector instructions, all waves on one compute unit, and then the fp64 chain of the owners (0.4 us of it all).  With 64
 // lanes to a row the sums over the lanes, row after row, were a third of the instructions; over 16 lanes they are four
 // steps for four rows, and the columns' sums over the wave's four rows two exchanges that fold two columns at once.
 // Columns come in sets of 16 (E of them), so few are idle, and a wave skips a set of rows past m.  The column owners sit
@@ -194,10 +195,10 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
 // scale of 1 (SCALED) 0.95, 1.65, 0.61 and 0.48.
 // SCALED: with a quadratic term; without one the scale is exactly 1 and its product, a seventh of the sweep, left out.
 // Lane l, group g = l / 16: rows 4 (wave + 16 r) + g, columns 16 e + l % 16.
-template <int R, int E, bool SCALED>
-__global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
-  constexpr int NW = 16, EQ = (E + 3) / 4;
-  static_assert(64 * R <= kResidentMaxRows && 16 * E <= kResidentCols, "layout");
+template <int NW, int R, int E, bool SCALED>
+__global__ __launch_bounds__(64 * NW) void resident_wide_kernel(ResidentArgs A) {
+  constexpr int EQ = (E + 3) / 4;  // (64 columns to a wave of column owners)
+  static_assert(4 * NW * R <= kResidentMaxRows && 16 * E <= kResidentCols && 2 + EQ <= NW, "layout");
   if (*A.V.done) return;
   __shared__ float lds_phi[kResidentMaxRows];
   __shared__ float lds_varphi[64 * EQ];
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
     __syncthreads();
   }
   if (!checks) break;
-  if (resident_check(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  if (resident_check<NW>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
   ++nchecks;
   upto = min(it + A.check.every, A.iters);
   }
@@ -360,13 +361,21 @@ __global__ __launch_bounds__(1024) void resident_wide_kernel(ResidentArgs A) {
   }
 }
 
+// Eight waves or sixteen: fewer waves are fewer column sums to fold, cheaper barriers and longer independent work in each;
+// sixteen are ahead where a wave of eight would have little to overlap (rows beyond 64, few columns).  Per iteration, 16 waves
+// and 8: 64 x 64 0.75 and 0.68 us, 40 x 40 0.69 and 0.60, 64 x 256 1.23 and 1.15, 128 x 256 1.79 and 1.60 (with a quadratic
+// term 1.97 and 1.86), 100 x 200 1.43 and 1.39; but 100 x 40 0.71 and 0.85, 128 x 64 0.94 and 0.96; 100 x 100 1.01 and 1.03, with
+// a quadratic term 1.09 and 1.03.
+template <int E, bool SCALED>
+void launch_resident_wide(const ResidentArgs& RS, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+  constexpr int kWaves = E > 8 || (E > 6 && SCALED) ? 8 : 16;
+  if (RS.m <= 64) launch_timed((resident_wide_kernel<8, 2, E, SCALED>), dim3(1), dim3(512), stream, e0, e1, RS);
+  else launch_timed((resident_wide_kernel<kWaves, 32 / kWaves, E, SCALED>), dim3(1), dim3(64 * kWaves), stream, e0, e1, RS);
+}
 template <int E>
 void launch_resident_wide(const ResidentArgs& RS, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
-  const bool scaled = RS.scale != 1.f;
-  if (RS.m <= 64 && scaled) launch_timed((resident_wide_kernel<1, E, true>), dim3(1), dim3(1024), stream, e0, e1, RS);
-  else if (RS.m <= 64) launch_timed((resident_wide_kernel<1, E, false>), dim3(1), dim3(1024), stream, e0, e1, RS);
-  else if (scaled) launch_timed((resident_wide_kernel<2, E, true>), dim3(1), dim3(1024), stream, e0, e1, RS);
-  else launch_timed((resident_wide_kernel<2, E, false>), dim3(1), dim3(1024), stream, e0, e1, RS);
+  if (RS.scale != 1.f) launch_resident_wide<E, true>(RS, stream, e0, e1);
+  else launch_resident_wide<E, false>(RS, stream, e0, e1);
 }
 
 // Few rows and many columns leave most waves without a row of their own there: up to 16 rows of more than 96 columns take
