@@ -159,16 +159,17 @@ int drot_destroy(drot_handle h);
  *       1: pairs wherever they apply; 0: never.
  *   DROT_OPT_FUSED_UPDATE [-1], -1/0: small problems (at most 2048 rows and 4096 tiles of 32 x 256) compute
  *       the O(m+n) update of eq. (6) at the head of the next sweep, one launch per iteration instead of
- *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations up to the
- *       next residual check in one cooperative launch; 0 always runs the separate kernels.  Same bits.  (Larger
+ *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations and their
+ *       residual checks in one cooperative launch (4096 iterations or 256 checks at a time); 0 always runs the separate kernels.  Same bits.  (Larger
  *       problems that fit, up to 12.6 million entries, take the one launch where they are neither screened nor paired.)
  *   DROT_OPT_RESIDENT [-1], -1/0: problems of at most 128 x 256 without group lasso, from a stored cost, run
- *       in a single workgroup that keeps X and C in registers: all the iterations up to the next residual
- *       check are one launch.  Agrees with the other paths to rounding (different summation order).
+ *       in a single workgroup that keeps X and C in registers: all the iterations and their residual checks are
+ *       one launch (4096 or 256 at a time).  Agrees with the other paths to rounding (different summation order).
  *   DROT_OPT_GROUP_TWO_PASS [0], 0/1: a group-lasso solve uses the group-resident kernel (a whole class x
  *       32 columns in one workgroup's registers, 12 bytes per element) when every class has at most 1024 rows,
  *       consecutive or, unless the classes are many and small (under 48 rows on average), anywhere; and
- *       otherwise the two-pass path (any labels, 20 bytes per element); 1 forces the two-pass path.
+ *       otherwise the two-pass path (any labels, 20 bytes per element); 1 forces the two-pass path.  Up to 512 such pieces
+ *       (256 of classes of more than 512 rows) stay in the registers of the GPU for all the iterations of a call, the same bits.
  *   DROT_OPT_GRID_POLLS [33554432], 1 .. 1073741824: how often a workgroup of a cooperative launch asks for a
  *       number that another one owes it before the launch gives up (the default is about half a minute).  Such a
  *       launch needs all its workgroups on the GPU at once; where it gives up, or is not accepted, the handle
@@ -279,6 +280,8 @@ int drot_solve(drot_handle h, const float* C, const float* p, const float* q, in
  * On-the-fly cost: like drot_solve, but the cost is C_ij = cost_scale * ||xs_i - xt_j||_2^2 for two
  * point clouds and is recomputed in every sweep instead of being read from memory (8 instead of 12
  * bytes per element of HBM traffic, 2d flops per element on the matrix cores; no m x n cost array).
+ * Where plan and cost fit the registers of the GPU (10.5 million entries) it is formed once per launch, in registers, and
+ * all the iterations are one cooperative launch: the same bits.
  *   xs [in]  DEVICE, m*d fp32 row-major (source points), xt [in] DEVICE, n*d fp32 (target points), d >= 1
  *   cost_scale > 0; 1/max_ij ||xs_i - xt_j||^2 gives the normalisation the stepsize default assumes
  * The cost is evaluated in fp32 as cost_scale*max(|xs_i|^2 + |xt_j|^2 - 2 xs_i.xt_j, 0) (squared

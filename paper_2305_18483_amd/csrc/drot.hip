@@ -465,7 +465,8 @@ GridWords grid_words(const plan::Static& S, const plan::Problem& P) {
   GridWords W;
   W.col = nblk_m * nseg * kGridBlock;
   W.tot = W.col + nblk_n * ntr * kGridBlock;
-  W.ent = W.tot + nseg * (ntr + kColGroup);  // (totals: whole groups of kColGroup tile rows for the 64-row tiles)
+  // (totals: whole groups of kColGroup tile rows for the 64-row tiles, of kPointsColGroup for point clouds)
+  W.ent = W.tot + nseg * (ntr + (S.grid_points ? kPointsColGroup : kColGroup));
   W.sq = W.ent + 2 * (nblk_m + nblk_n) * kGridBlock;
   W.cst = (W.sq + 2 * (nblk_m + nblk_n) + 31) / 32 * 32;
   W.half = W.cst + 32 * kGridCopies;
@@ -552,6 +553,7 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   A.varphi_out = h->varphi;
   A.r = h->r;
   A.s = h->s;
+  A.points = Z.PT;
   A.nseg = slab ? S.nstrips : S.nseg;
   A.ntr = ntr;
   A.nblk_m = nblk_m;
@@ -576,6 +578,14 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
         e = k8 ? launch_grid_slab<8, 8, 1>(A, B, wgs, Z.stream)
                : S.grid_tiles == 2 ? launch_grid_slab<4, 8, 2>(A, B, wgs, Z.stream) : launch_grid_slab<4, 8, 1>(A, B, wgs, Z.stream);
         break;
+    }
+  } else if (S.grid_points) {
+    switch (S.grid_points) {
+      case 1: e = launch_grid<16, 16, 2, 1, 0, kPointsColGroup>(A, wgs, Z.stream); break;
+      case 2: e = launch_grid<16, 16, 2, 2, 0, kPointsColGroup>(A, wgs, Z.stream); break;
+      case 3: e = launch_grid<16, 16, 2, 3, 1, kPointsColGroup>(A, wgs, Z.stream); break;
+      case 4: e = launch_grid<16, 16, 2, 4, 2, kPointsColGroup>(A, wgs, Z.stream); break;
+      default: e = launch_grid<16, 16, 2, 5, 2, kPointsColGroup>(A, wgs, Z.stream); break;
     }
   } else if (S.grid_tall) {
     switch (S.grid_tiles) {

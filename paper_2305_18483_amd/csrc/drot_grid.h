@@ -86,6 +86,7 @@ struct GridArgs {
   float* varphi_out;
   double* r;
   double* s;
+  PointArgs points;       // where the cost is formed from point clouds (G = kPointsColGroup), once per launch
 };
 
 // The arguments once more, fetched where they are used: what only a check or the end of the launch needs would sit in
@@ -208,6 +209,10 @@ __device__ __forceinline__ double butterfly_f64(double v) {  // the bits of the 
   return v;
 }
 
+// G = kPointsColGroup: the cost comes from point clouds, formed tile by tile at the start of the launch as
+// sweep_points_kernel forms it in every sweep (the same instructions per element, the same bits), and the sums are grouped as
+// that kernel's are.  Calls of 300 sweeps, single launches and so: 400 x 400, d = 8 3.18 and 1.36 ms; 1000 x 1000, d = 32 3.50 and
+// 1.37; 2000 x 2000 3.84 and 2.00; 2500 x 2500 4.94 and 3.31.
 // NW waves; a tile is NT stacks of U rows, one stack per wave, so the workgroup works on NW / NT tiles at a time and on
 // TW such sets; C of the first CL of them sits in LDS (registers are what limits the size).  G consecutive tile rows are added up in fp32 before anything else (1, or kColGroup for 64-row tiles).
 template <int NW, int NT, int U, int TW, int CL, int G>
@@ -229,6 +234,11 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   __shared__ float lds_phi[kTiles][kRows];
   __shared__ float lds_row[kTiles][kRows];
   __shared__ float wt[kTiles][NT];            // totals of a wave's rows
+  // (inner products of a tile: in the column sums' place where that is large enough)
+  constexpr bool kPoints = G == kPointsColGroup;
+  static_assert(!kPoints || (NW == kSweepWaves && NT == kSweepWaves && U == kSweepRows), "tiles of sweep_points_kernel");
+  constexpr bool kDotsApart = kPoints && kTiles * NT * kSegCols < kTileRows * kDotPitch;
+  __shared__ float dots_apart[kDotsApart ? kTileRows * kDotPitch : 1];
   __shared__ double red[kShareBlocks];
   __shared__ double sq64[kGridSquares<NW>];  // checks: squared residuals of 64 entries each
   __shared__ int failed[2];  // a word that never came: among the tile totals; among the others
@@ -249,13 +259,28 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     const int seg = tl / A.ntr, tr = tl - seg * A.ntr;
     const int j0 = seg * kSegCols + lane * 4;
     const int r0 = tr * kRows + stack * U;
+    float (*dots)[kDotPitch] = nullptr;
+    f4v ysq = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (kPoints) {
+      dots = reinterpret_cast<float (*)[kDotPitch]>(kDotsApart ? dots_apart : &cs[0][0][0]);
+      if (q > 0) __syncthreads();  // (the last tile's have been read)
+      if (tl < ntiles) {           // (the same for the whole workgroup)
+        points_tile(A.points, dots, lane, wave, seg, tr, S.m);
+        ysq = load4(A.points.xt_sq + j0, min(max(S.n - j0, 0), 4));
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       x[q][u] = f4v{0.f, 0.f, 0.f, 0.f};
       f4v cc = {0.f, 0.f, 0.f, 0.f};
       if (tl < ntiles && r0 + u < S.m && j0 < S.n_mem) {
-        cc = *reinterpret_cast<const f4v*>(S.C + (size_t)(r0 + u) * S.ldc + j0);
+        if constexpr (!kPoints) cc = *reinterpret_cast<const f4v*>(S.C + (size_t)(r0 + u) * S.ldc + j0);
         if (!A.first) x[q][u] = *reinterpret_cast<const f4v*>(S.X + (size_t)(r0 + u) * S.ldx + j0);
+      }
+      if constexpr (kPoints) {
+        if (tl < ntiles && r0 + u < S.m)
+          cc = points_cost(A.points, *reinterpret_cast<const f4v*>(&dots[stack * U + u][lane * 4]), A.points.xs_sq[r0 + u], ysq);
       }
       if constexpr (CL > 0) {
         if (q < CL) c_lds[q][wave * U + u][lane] = cc;
@@ -293,7 +318,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   auto over = [&](double v, double count, double recip) { return (float)(kRecip ? divide_by(v, count, recip) : v / count); };
   // where the words lie.  Partial sums of the owned block: per round 32 single ones (shares w, w + 8, w + 16, w + 24:
   // 16 k + share) or 16 groups of G; a lane with nothing to fetch asks for a word that somebody else needs
-  constexpr int NP = G == 1 ? 4 : 2 * G;
+  constexpr int NP = G == 1 || kPoints ? 4 : 2 * G;
   const bool grouped = G > 1 && !own_rows;  // (row sums never are)
   const int nparts = own_rows ? A.nseg : A.ntr, round_parts = grouped ? 16 * G : 8 * NP;
   const unsigned part_word = (own_rows ? 0u : A.col_word) + (unsigned)(bi * nparts * kGridBlock);
@@ -390,16 +415,33 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     if (owner) {
       double sh[2] = {0.0, 0.0};
       // (one round as a rule; more for large and for oblong problems)
-      for (int k0 = 0; k0 < nparts && !lost; k0 += round_parts) {
+      for (int k0 = 0; kPoints && grouped && k0 < nparts && !lost; k0 += round_parts) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {  // (half a group at a time: registers)
+          float g = 0.f;
+#pragma unroll 1
+          for (int e0 = 0; e0 < G; e0 += 4) {
+            u64 v[4];
+            unsigned at[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) at[e] = part_word + part_lane + (unsigned)(min(part_index(k0, b * G + e0 + e), nparts - 1) * kGridBlock);
+            grid_gather<4, kPause>(half, v, at, tag, A.polls, lost);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) g += part_index(k0, b * G + e0 + e) < nparts ? grid_value(v[e]) : 0.f;
+          }
+          sh[b] += part_index(k0, b * G) < nparts ? (double)g : 0.0;
+        }
+      }
+      for (int k0 = 0; !(kPoints && grouped) && k0 < nparts && !lost; k0 += kPoints ? 8 * NP : round_parts) {
         u64 v[NP];
         unsigned at[NP];
 #pragma unroll
         for (int b = 0; b < NP; ++b) at[b] = part_word + part_lane + (unsigned)(min(part_index(k0, b), nparts - 1) * kGridBlock);
         grid_gather<NP, kPause>(half, v, at, tag, A.polls, lost);
-        if (!grouped) {
+        if (kPoints || !grouped) {
 #pragma unroll
           for (int b = 0; b < NP; ++b) sh[b & 1] += part_index(k0, b) < nparts ? (double)grid_value(v[b]) : 0.0;
-        } else {
+        } else if constexpr (!kPoints) {
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             float g = grid_value(v[b * G]);
@@ -437,14 +479,18 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         double acc = 0.0;
         for (int e0 = (wave + sb * NW) * 64; e0 < ngroups && !lost; e0 += 1024) {
           const int e = min(e0 + lane, ngroups - 1);
-          u64 v[G];
-          unsigned at[G];
+          constexpr int kAtOnce = G > 4 ? 4 : G;
+          float g = 0.f;
+#pragma unroll 1
+          for (int b0 = 0; b0 < G; b0 += kAtOnce) {
+            u64 v[kAtOnce];
+            unsigned at[kAtOnce];
 #pragma unroll
-          for (int b = 0; b < G; ++b) at[b] = A.tot_word + (unsigned)(e * G + (total_there(e, b) ? b : 0));
-          grid_gather<G, kPause>(half, v, at, tag, A.polls, lost);
-          float g = grid_value(v[0]);
+            for (int b = 0; b < kAtOnce; ++b) at[b] = A.tot_word + (unsigned)(e * G + (total_there(e, b0 + b) ? b0 + b : 0));
+            grid_gather<kAtOnce, kPause>(half, v, at, tag, A.polls, lost);
 #pragma unroll
-          for (int b = 1; b < G; ++b) g += total_there(e, b) ? grid_value(v[b]) : 0.f;
+            for (int b = 0; b < kAtOnce; ++b) g += total_there(e, b0 + b) ? grid_value(v[b]) : 0.f;
+          }
           acc += e0 + lane < ngroups ? (double)g : 0.0;
         }
         acc = G == 1 ? butterfly_f64(acc) : wave_sum_f64(acc);

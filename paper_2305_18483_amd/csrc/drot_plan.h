@@ -166,6 +166,7 @@ struct Static {
   int grid_tiles = 0;            // grid-resident stretches: tiles per workgroup, 0: none
   int grid_wgs = 0;              // ... and workgroups
   bool grid_tall = false;        // ... of 64 rows each (else 32)
+  int grid_points = 0;           // the same with the cost formed from point clouds: 32-row tiles per workgroup
   int grid_slab_lanes = 0;       // slabs in place of tiles: lanes along the columns of a workgroup (8, or 4: half a slab), else 0
   int grid_slab_k = 0;           // ... and rows per thread
   bool status_at_checks = false; // the stretches end with a status kernel (stopping test and / or density)
@@ -203,6 +204,8 @@ inline Static make_static(const Problem& P, const Options& O) {
   // small-problem path on 32-row tiles, those that only skip zero segments on 64-row tiles (the same bits either way).
   // Above their size a problem is screened or streamed.
   const bool sweeps64 = S.can_pair && !S.small && O.skip_cost != 1 && O.skip_unchanged != 0 && !S.may_screen;
+  S.points_screen = P.from_points && O.skip_unchanged != 0 &&
+                    (O.screening > 0 || (O.screening == -1 && (size_t)m * (size_t)n >= kScreenFrom));
   // (a launch has room for the squared residuals of the blocks that so many workgroups own)
   const int units = P.compute_units < kGridMostUnits ? P.compute_units : kGridMostUnits;
   if (units > 0 && !S.resident && ((S.fused && !P.slab_k) || sweeps64)) {
@@ -216,6 +219,15 @@ inline Static make_static(const Problem& P, const Options& O) {
       S.grid_tiles = per_wg;
       S.grid_wgs = wgs;
       S.grid_tall = sweeps64;
+    }
+  }
+  if (units > 0 && P.from_points && O.skip_unchanged != 0 && !S.points_screen) {
+    const int per_wg = ceil_div(S.ntiles, units);
+    const int owners = ceil_div(ceil_div(m, kGridBlock) + ceil_div(n, kGridBlock), kGridWaves32);
+    const int wgs = ceil_div(S.ntiles, per_wg) > 1 + owners ? ceil_div(S.ntiles, per_wg) : 1 + owners;
+    if (per_wg <= kGridTiles32 && wgs <= units) {
+      S.grid_points = per_wg;
+      S.grid_wgs = wgs;
     }
   }
   // (group lasso: every workgroup holds slabs, none owns blocks only)
@@ -235,8 +247,6 @@ inline Static make_static(const Problem& P, const Options& O) {
     if (k * 2 <= kGridSlabRows) take(8, 2);
   }
   S.adaptive_pairs = P.feedback && S.can_pair && !S.small && O.skip_cost == -1 && O.skip_unchanged != 0 && !S.grid_tiles;
-  S.points_screen = P.from_points && O.skip_unchanged != 0 &&
-                    (O.screening > 0 || (O.screening == -1 && (size_t)m * (size_t)n >= kScreenFrom));
   S.adaptive = P.feedback && (S.adaptive_pairs || S.may_screen || S.points_screen);
   // (smaller problems, screened when asked to, lie in the caches: lines gain nothing over row segments there)
   // (offsets of 32 bits within a tile: rows of up to 16.7 million columns; wider ones stay with the 8-wave tiles)
@@ -502,7 +512,7 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
 constexpr int kRunSweeps = 4096, kRunChecks = 256;
 
 inline bool runs_through_checks(const Static& S, const Problem& P, const Options& O) {
-  return (S.resident || S.grid_tiles > 0) && P.feedback && P.checking && !P.single_launches && !S.adaptive && O.gap_every < 1;
+  return (S.resident || S.grid_tiles > 0 || S.grid_points > 0) && P.feedback && P.checking && !P.single_launches && !S.adaptive && O.gap_every < 1;
 }
 
 // Stretch R, which ends at a check or with the call, drawn out over the checks that follow.
@@ -519,10 +529,10 @@ inline Stretch draw_out(const Problem& P, const Options& O, const State& T, Stre
 // there is no such launch in it.  (The first sweep of a cold start has its own tiles and vector update where the others
 // run on 64-row tiles.)
 inline int grid_head(const Static& S, const Problem& P, const State& T, const Stretch& R) {
-  if (!S.grid_tiles || P.single_launches) return -1;
+  if ((!S.grid_tiles && !S.grid_points) || P.single_launches) return -1;
   const bool cold = T.k_base + T.k == 0 && !P.warm;
   const int head = S.grid_tall && cold ? 1 : 0;
-  const int least = S.grid_slab_lanes || (!S.grid_tall && S.grid_tiles == 1) ? kGridMinSweepsOneTile : kGridMinSweeps;
+  const int least = S.grid_slab_lanes || (!S.grid_tall && S.grid_tiles + S.grid_points == 1) ? kGridMinSweepsOneTile : kGridMinSweeps;
   return R.chunk - head >= least ? head : -1;
 }
 

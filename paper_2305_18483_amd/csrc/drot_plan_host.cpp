@@ -233,6 +233,7 @@ int drot_plan_run(const int* problem, const int* options, int compute_units, int
   P.m = problem[0];
   P.n = problem[1];
   P.reg_kind = problem[2];
+  P.from_points = problem[3] != 0;
   P.feedback = problem[11] != 0;
   P.checking = problem[12] != 0;
   P.max_iters = problem[13];
@@ -241,6 +242,8 @@ int drot_plan_run(const int* problem, const int* options, int compute_units, int
   Options O;
   O.check_every = options[0];
   O.resident = options[1];
+  O.skip_unchanged = options[4];
+  O.screening = options[5];
   O.gap_every = options[8];
   const Static S = make_static(P, O);
   if (!runs_through_checks(S, P, O)) return 0;

@@ -1334,6 +1334,40 @@ def test_grid_resident_slabs_give_the_bits_of_single_launches(drot, m, n, classe
     assert np.array_equal(*outs)
 
 
+@pytest.mark.parametrize("m,n,d", [(33, 257, 2), (400, 401, 7), (257, 9000, 3), (1000, 1003, 32), (1500, 2100, 17), (2600, 2500, 4), (3333, 3111, 16),
+                                   (12000, 640, 5)])
+def test_grid_resident_point_clouds_give_the_bits_of_single_launches(drot, m, n, d):
+    # 1 to 5 tiles per workgroup, groups of eight tile rows of which the last is short, last column segments of one to four
+    # quarters; checks in the middle, a stop at one, a continued call, a warm start.  Profile mode launches every sweep by itself.
+    rng = np.random.default_rng(2950 + m)
+    xs, xt = (torch.from_numpy(rng.random((k, d), dtype=np.float32)).cuda() for k in (m, n))
+    p, q = (torch.from_numpy((w / w.sum()).astype(np.float32)).cuda() for w in (rng.random(m) + 0.5, rng.random(n) + 0.5))
+    kw = dict(reg_kind=1, lam=0.3)
+    solver, ref = drot.Solver(m, n, check_every=13), drot.Solver(m, n, check_every=13)
+    ref.set_profile(True)
+    _say(f"grid-resident point clouds {m}x{n}, d = {d}")
+    Xs = [torch.empty((m, n), device="cuda:0") for _ in range(2)]
+
+    def same(K, **more):
+        out = []
+        for s, X in zip((solver, ref), Xs):
+            r = s.solve_points(xs, xt, 1.0 / d, p, q, X_out=X, max_iters=K, **kw, **more)
+            out.append((r, X.cpu().numpy(), *(v.cpu().numpy() for v in s.duals(m, n, X.device)), [(c.iters, c.r_row, c.r_col) for c in s.checks()]))
+        a, b = out
+        assert all(np.array_equal(u, v) for u, v in zip(a[1:4], b[1:4])) and a[4] == b[4]
+        assert (a[0].iters, a[0].converged, a[0].r_row, a[0].r_col, a[0].objective) == (b[0].iters, b[0].converged, b[0].r_row, b[0].r_col, b[0].objective)
+        return a
+
+    res, X40, phi40, varphi40, checks = same(40, tol=1e-12)
+    same(40, tol=float(np.float32(max(checks[1][1:])) * np.float32(1.0001)))
+    solver.set_continue(True), ref.set_continue(True)
+    same(15)
+    solver.set_continue(False), ref.set_continue(False)
+    for X in Xs:
+        X.copy_(torch.from_numpy(X40))
+    same(17, phi0=torch.from_numpy(phi40).cuda(), varphi0=torch.from_numpy(varphi40).cuda())
+
+
 def test_two_threads_solve_on_two_streams(drot):
     # launches whose workgroups wait for one another, from two handles at once: one after the other on the chip
     import threading

@@ -539,9 +539,10 @@ def test_grid_resident_stretches_where_the_registers_of_the_chip_hold_the_proble
 
 
 def test_launches_run_on_through_the_residual_checks(planlib):
-    def run(m, n, iters, check_every=100, k=0, feedback=1, checking=1, resident=-1, gap_every=0, units=256, single=0):
-        problem = (ctypes.c_int * 14)(m, n, 1, 0, 0, 0, 0, 1, 1, 0, 0, feedback, checking, iters)
-        options = (ctypes.c_int * 9)(check_every, resident, -1, -1, -1, -1, -1, 0, gap_every)
+    def run(m, n, iters, check_every=100, k=0, feedback=1, checking=1, resident=-1, gap_every=0, units=256, single=0, from_points=0,
+            skip_unchanged=-1, screening=-1):
+        problem = (ctypes.c_int * 14)(m, n, 1, from_points, 0, 0, 0, 1, 1, 0, 0, feedback, checking, iters)
+        options = (ctypes.c_int * 9)(check_every, resident, -1, -1, skip_unchanged, screening, -1, 0, gap_every)
         return planlib.drot_plan_run(problem, options, units, single, k)
 
     for m, n in ((100, 100), (1000, 1000), (2999, 3307)):
@@ -553,6 +554,10 @@ def test_launches_run_on_through_the_residual_checks(planlib):
         assert run(m, n, 1000, gap_every=1) == 0 and run(m, n, 1000, checking=0) == 0 and run(m, n, 1000, feedback=0) == 0
         assert run(m, n, 1000, single=1) == 0
     assert run(100, 100, 1000, units=0) == 1000 and run(1000, 1000, 1000, units=0) == 0 and run(5000, 5000, 1000) == 0
+    # point clouds: up to five 32-row tiles per workgroup, whatever the rows; not where screened or told to move every byte
+    assert run(100, 100, 1000, from_points=1) == 1000 and run(3200, 3072, 1000, from_points=1) == 1000
+    assert run(3200, 3328, 1000, from_points=1) == 0 and run(5000, 5000, 1000, from_points=1) == 0
+    assert run(1000, 1000, 1000, from_points=1, screening=1) == 0 and run(1000, 1000, 1000, from_points=1, skip_unchanged=0) == 0
     assert run(2, 32600, 1000) == 1000 and run(2, 32640, 1000) == 0  # (more blocks of columns than workgroups own)
 
 
