@@ -318,6 +318,9 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   auto over = [&](double v, double count, double recip) { return (float)(kRecip ? divide_by(v, count, recip) : v / count); };
   // where the words lie.  Partial sums of the owned block: per round 32 single ones (shares w, w + 8, w + 16, w + 24:
   // 16 k + share) or 16 groups of G; a lane with nothing to fetch asks for a word that somebody else needs
+  // (more than 32 partial sums in one round of eight words a lane where registers allow: 2048 x 2048 4.85 -> 4.54 us per
+  // iteration, 1500 x 500 3.99 -> 3.68; with three tiles 6.31 and 6.29, with five 9.55 and 9.85)
+  constexpr bool kManyAtOnce = G == 1 && TW <= 2;
   constexpr int NP = G == 1 || kPoints ? 4 : 2 * G;
   const bool grouped = G > 1 && !own_rows;  // (row sums never are)
   const int nparts = own_rows ? A.nseg : A.ntr, round_parts = grouped ? 16 * G : 8 * NP;
@@ -416,23 +419,38 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       double sh[2] = {0.0, 0.0};
       // (one round as a rule; more for large and for oblong problems)
       for (int k0 = 0; kPoints && grouped && k0 < nparts && !lost; k0 += round_parts) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {  // (half a group at a time: registers)
-          float g = 0.f;
 #pragma unroll 1
-          for (int e0 = 0; e0 < G; e0 += 4) {
-            u64 v[4];
-            unsigned at[4];
+        for (int b = 0; b < 2; ++b) {  // (a group, or half of one, at a time: registers)
+          float g = 0.f;
+          constexpr int kPart = TW <= 3 ? G : 4;  // (1000 x 1000 4.53 us per iteration by halves, 4.03 whole)
+#pragma unroll 1
+          for (int e0 = 0; e0 < G; e0 += kPart) {
+            u64 v[kPart];
+            unsigned at[kPart];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) at[e] = part_word + part_lane + (unsigned)(min(part_index(k0, b * G + e0 + e), nparts - 1) * kGridBlock);
-            grid_gather<4, kPause>(half, v, at, tag, A.polls, lost);
+            for (int e = 0; e < kPart; ++e) at[e] = part_word + part_lane + (unsigned)(min(part_index(k0, b * G + e0 + e), nparts - 1) * kGridBlock);
+            grid_gather<kPart, kPause>(half, v, at, tag, A.polls, lost);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) g += part_index(k0, b * G + e0 + e) < nparts ? grid_value(v[e]) : 0.f;
+            for (int e = 0; e < kPart; ++e) g += part_index(k0, b * G + e0 + e) < nparts ? grid_value(v[e]) : 0.f;
           }
-          sh[b] += part_index(k0, b * G) < nparts ? (double)g : 0.0;
+          const double add = part_index(k0, b * G) < nparts ? (double)g : 0.0;
+          if (b == 0) sh[0] += add;
+          else sh[1] += add;
         }
       }
-      for (int k0 = 0; !(kPoints && grouped) && k0 < nparts && !lost; k0 += kPoints ? 8 * NP : round_parts) {
+      const bool many = kManyAtOnce && nparts > 8 * NP;
+      if (many) {  // (64 partial sums in one round: a second one would be a second trip)
+        for (int k0 = 0; k0 < nparts && !lost; k0 += 64) {
+          u64 v[8];
+          unsigned at[8];
+#pragma unroll
+          for (int b = 0; b < 8; ++b) at[b] = part_word + part_lane + (unsigned)(min(k0 + (lane >> 3) + 8 * b, nparts - 1) * kGridBlock);
+          grid_gather<8, kPause>(half, v, at, tag, A.polls, lost);
+#pragma unroll
+          for (int b = 0; b < 8; ++b) sh[b & 1] += k0 + (lane >> 3) + 8 * b < nparts ? (double)grid_value(v[b]) : 0.0;
+        }
+      }
+      for (int k0 = 0; !many && !(kPoints && grouped) && k0 < nparts && !lost; k0 += kPoints ? 8 * NP : round_parts) {
         u64 v[NP];
         unsigned at[NP];
 #pragma unroll

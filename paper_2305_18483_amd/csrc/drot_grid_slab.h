@@ -57,7 +57,7 @@ __device__ __forceinline__ void grid_gather_pairs(const u64* half, u64 (&v)[2 * 
 
 // What a wave does in the exchange besides publishing the sums of its own slab: it owns a block of eight rows or columns,
 // or, in the first workgroup, keeps theta (grid_resident_kernel has the same, with its tiles' sums).
-template <int NW, int SUB, int PAUSE>
+template <int NW, int SUB, int PAUSE, bool WIDE>
 struct GridOwner {
   static constexpr int kShareBlocks = 1024 / 64, kSB = kShareBlocks / NW;
   static_assert(kShareBlocks % NW == 0, "the slab totals are dealt out to 1024 shares");
@@ -90,21 +90,22 @@ struct GridOwner {
   }
 
   // The 16 shares of the entry's partial sums, lane 8 w + i those numbered w and w + 8 of entry i; N parts each, added first.
-  template <int N>
+  // W partial sums per lane and round: one round as a rule, each is a trip.
+  template <int N, int W>
   __device__ __forceinline__ double gather_parts(const GridArgs& A, const u64* __restrict__ half, unsigned tag, int lane, bool& lost) const {
     double sh[2] = {0.0, 0.0};
-    for (int k0 = 0; k0 < nparts && !lost; k0 += 32) {  // (one round as a rule)
-      u64 v[4 * N];
-      unsigned at[4 * N];
+    for (int k0 = 0; k0 < nparts && !lost; k0 += 8 * W) {
+      u64 v[W * N];
+      unsigned at[W * N];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < W; ++b) {
         const int k = min(k0 + (lane >> 3) + 8 * b, nparts - 1);
 #pragma unroll
         for (int e = 0; e < N; ++e) at[N * b + e] = part_word + (unsigned)((k * N + e) * kGridBlock);
       }
-      grid_gather<4 * N, PAUSE>(half, v, at, tag, A.polls, lost);
+      grid_gather<W * N, PAUSE>(half, v, at, tag, A.polls, lost);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < W; ++b) {
         float g = grid_value(v[N * b]);
         if constexpr (N == 2) g = grid_value(v[2 * b]) + grid_value(v[2 * b + 1]);
         sh[b & 1] += k0 + (lane >> 3) + 8 * b < nparts ? (double)g : 0.0;
@@ -117,7 +118,8 @@ struct GridOwner {
   // Hop 1 for an owner wave: the partial sums of its entries, a - 2r and b - 2s published; at a check the squares, too.
   template <bool CHECK>
   __device__ __forceinline__ void own(const GridArgs& A, u64* __restrict__ half, unsigned tag, int lane, bool& lost) {
-    const double total = own_rows ? gather_parts<SUB>(A, half, tag, lane, lost) : gather_parts<1>(A, half, tag, lane, lost);
+    const double total = !own_rows ? gather_parts<1, 4>(A, half, tag, lane, lost)
+                         : WIDE && nparts > 32 ? gather_parts<SUB, 8>(A, half, tag, lane, lost) : gather_parts<SUB, 4>(A, half, tag, lane, lost);
     const double res = total - target;
     const u64 out = __builtin_bit_cast(u64, state - 2.0 * res);
     state = state - res;
@@ -303,7 +305,8 @@ __global__ __launch_bounds__(kSlabRowLanes * CX) void grid_slab_kernel(GridArgs 
     if (t < COLS) lds_varphi[q][t] = t < M.cols ? S.varphi[M.col0 + t] : kMaskedOut;
   }
   if (t < 2) failed[t] = 0;
-  GridOwner<NW, SUB, kPause> own;
+  // (WIDE: more than 32 strips in one round, where that needs no scratch)
+  GridOwner<NW, SUB, kPause, CX == 4 || (K == 4 && TW == 1)> own;
   own.init(A, MAPPED ? B.perm : nullptr, wave, lane);
   const unsigned cst_at = A.cst_word + 32u * (blockIdx.x % kGridCopies);
   __syncthreads();
