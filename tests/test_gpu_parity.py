@@ -501,6 +501,28 @@ def test_group_lasso_rows_anywhere_with_weights_warm_and_continued(drot, oracle)
     assert np.array_equal(X1, X2) and np.array_equal(phi1, phi2)
 
 
+@pytest.mark.parametrize("m,n,classes,order", [(500, 413, 3, "runs"), (300, 415, 3, "runs"), (500, 413, 3, "anywhere"), (900, 225, 1, "runs")])
+@pytest.mark.parametrize("fused", [-1, 0])
+def test_slabs_do_not_see_what_lies_behind_a_padded_row(drot, m, n, classes, order, fused):
+    # the slabs read and write whole lines: what an earlier, wider problem left past column n (infinite costs, a plan) has no
+    # part in the plan or the sums
+    wide = drot_inputs.with_entrywise_terms(drot_inputs.random_problem(1000, 639, seed=77, reg_kind=1, lam=0.1), seed=78,
+                                            weight_scale=0.0, forbid_frac=0.3)
+    P = drot_inputs.random_problem(m, n, seed=79 + m + n, reg_kind=2, lam=0.1, mu=0.02, num_classes=classes)
+    if order == "anywhere":
+        P.row_class = np.random.default_rng(m).permutation(P.row_class)
+    used, fresh = drot.Solver(1000, 639), drot.Solver(m, n)
+    pu.gpu_solve(used, wide, 30)
+    outs = []
+    for s in (used, fresh):
+        s.set_profile(True)  # (every sweep a launch of its own)
+        s.set_fused_update(fused)
+        _say(f"slabs on used padding {m}x{n}, {classes} classes, {order}, fused {fused}")
+        outs.append(pu.gpu_solve(s, P, 40))
+    for u, v in zip(outs[0][1:], outs[1][1:]):
+        assert np.array_equal(u, v)
+
+
 @pytest.mark.parametrize("m,n", [(16, 96), (16, 97), (5, 129), (17, 1), (20, 129), (61, 176), (64, 256), (65, 17), (100, 112),
                                  (113, 193), (127, 241), (128, 65), (128, 225)])
 def test_resident_kernel_at_the_edges_of_its_sets_of_rows_and_columns(drot, oracle, m, n):
