@@ -44,9 +44,9 @@
 // compute unit.  Every wait is bounded: a word that has not come after GridArgs::polls attempts (2^25 as a rule, about half a
 // minute) ends the kernel with the `broken` mark in the status block and the stop flag up.  The host goes back to single
 // launches then, as it does where the launch is refused.
-// This kernel has not been seen to give up of itself.  The same exchange, in a form for the slabs of the group lasso that
-// was tried and taken out, has, at one shape (three slabs, five workgroups that only own blocks, a kernel with spilled
-// registers), and neither reading it nor running it on a CPU showed why: a wait that runs out is taken for possible here.
+// This kernel has not been seen to give up of itself.  The same exchange, in a first form for the slabs of the group lasso
+// (three slabs, five workgroups that only owned blocks, a kernel with spilled registers), has, and neither reading it nor
+// running it on a CPU showed why (drot_grid_slab.h has the present form): a wait that runs out is taken for possible here.
 // ------------------------------------------------------------------------------------------
 typedef unsigned long long u64;
 constexpr int kGridPolls = 1 << 25;
@@ -69,7 +69,7 @@ struct GridArgs {
   int* done;
   // the exchange buffer, two halves of half_words words: [row blocks][nseg][8] row sums, [column blocks][ntr][8] column
   // sums, [groups of tiles][G] totals, [row blocks][8][2] a - 2r, [column blocks][8][2] b - 2s, [kGridCopies][16][2]
-  // 2 eta - theta (each copy on a 256-byte stretch of its own), starting at these words of a half
+  // 2 eta - theta (each copy on a 256-byte stretch of its own; the answer of a check behind it), starting at these words of a half
   u64* xchg;
   unsigned half_words, col_word, tot_word, ent_word, cst_word;
   int nseg, ntr;          // ntr: rows of tiles (32 or 64 rows each)
