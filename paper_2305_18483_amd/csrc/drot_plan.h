@@ -71,13 +71,13 @@ constexpr int kGridTiles64 = 3;       // 64-row tiles (eight rows per wave, 8 wa
 constexpr int kGridWaves32 = 16, kGridWaves64 = 8;
 constexpr int kGridMostUnits = 256;   // workgroups at most
 constexpr int kGridBlock = 8;         // rows or columns whose part of eq. (6) a wave forms
+// Slabs (drot_grid_slab.h): rows per thread at least (idle ones cost little), and at most, over a workgroup's slabs (registers
+// hold X, the LDS C).  Half slabs to a workgroup where all of them are on the chip at once, else whole ones, else two.
+constexpr int kGridSlabLeastK = 4, kGridSlabRows = 8;
 // Shorter stretches are not worth fetching the plan and the cost for.  Per iteration, in single launches and in one launch,
 // stretches of 4, 6, 8 and 10 sweeps: 200 x 300 10.4 and 13.6 us, 8.9 and 10.1, 8.3 and 8.5, 7.9 and 7.4; 1000 x 1000 11.3
 // and 13.7, 9.9 and 10.2, 9.9 and 8.5, 9.4 and 7.5 (one tile a workgroup); 2048 x 3072 24.0 and 18.5 at 4, 64-row tiles of
 // 2300 x 2500 17.8 and 17.8, 2999 x 3307 21.3 and 21.3.
-// Slabs (drot_grid_slab.h): rows per thread at least (idle ones cost little), and at most, over a workgroup's slabs (registers
-// hold X, the LDS C).  Half slabs to a workgroup where all of them are on the chip at once, else whole ones, else two.
-constexpr int kGridSlabLeastK = 4, kGridSlabRows = 8;
 constexpr int kGridMinSweeps = 4, kGridMinSweepsOneTile = 8;
 // (a full sweep takes 230 to 260 us at 12000 x 12000, d = 32, the screened one 7 for every percent of the row segments left)
 constexpr double kPointsSparse = 0.33;
