@@ -186,17 +186,22 @@ struct CheckArgs {
 };
 
 // One thread: the c-th check of the launch, behind its sweep `it`.  True: it passes, the solve ends here.
+// HERE: the constants stored are formed at the check.  The compiler lifts them out of the kernel's loop otherwise, where they
+// hold eight registers during the sweeps.
+template <bool HERE>
 __device__ __forceinline__ bool make_check(const CheckArgs& K, int c, int it, double r2, double s2) {
   const bool pass = K.tol > 0.0 && r2 <= K.tol * K.tol && s2 <= K.tol * K.tol;
+  double none = 0.0, no_lines = -1.0;
+  if (HERE) asm volatile("" : "+v"(none), "+v"(no_lines));
   K.out[c] = CheckRecord{r2, s2, K.k0 + it + 1, pass ? 1 : 0};
   K.resid[0] = r2;
   K.resid[1] = s2;
-  K.resid[2] = 0.0;
-  K.resid[3] = -1.0;
+  K.resid[2] = none;
+  K.resid[3] = no_lines;
   K.status->r2 = r2;
   K.status->s2 = s2;
-  K.status->nz_segments = 0.0;
-  K.status->nz_lines = -1.0;
+  K.status->nz_segments = none;
+  K.status->nz_lines = no_lines;
   K.status->iters = K.k0 + it + 1;
   if (pass) {
     K.status->converged = 1;

@@ -557,7 +557,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
             norm2[side_n] = sum;
           }
           bool pass = false;
-          if (lane == 0) pass = make_check(L.check, nchecks, it, norm2[0], norm2[1]);
+          if (lane == 0) pass = make_check<false>(L.check, nchecks, it, norm2[0], norm2[1]);
           const unsigned word = __builtin_amdgcn_ballot_w64(pass) != 0 ? 1u : 0u;
           if (lane < kGridCopies) grid_store(half, L.cst_word + 32u * (unsigned)lane + 2u, word, tag);
         }

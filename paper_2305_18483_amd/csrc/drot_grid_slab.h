@@ -202,7 +202,7 @@ struct GridOwner {
           norm2[side] = sum;
         }
         bool pass = false;
-        if (lane == 0) pass = make_check(L.check, nchecks, it, norm2[0], norm2[1]);
+        if (lane == 0) pass = make_check<false>(L.check, nchecks, it, norm2[0], norm2[1]);
         const unsigned word = __builtin_amdgcn_ballot_w64(pass) != 0 ? 1u : 0u;
         if (lane < kGridCopies) grid_store(half, L.cst_word + 32u * (unsigned)lane + 2u, word, tag);
       }

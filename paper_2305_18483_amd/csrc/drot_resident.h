@@ -2,7 +2,7 @@
 // Part of drot.hip (included there, inside its anonymous namespace, in this order); not a stand-alone header.
 
 // ------------------------------------------------------------------------------------------
-// Resident solver for tiny problems (at most 128 x 256): one workgroup of 16 waves keeps X and C in registers
+// Resident solver for tiny problems (at most 128 x 256): one workgroup of 16 (or 8) waves keeps X and C in registers
 // and runs on through the residual checks in one launch, so an iteration costs two workgroup barriers instead of a kernel
 // launch (a launch for every check: 2.27 ms for 2000 iterations of 100 x 100, checked every 100; so 2.03).  The eq. (6) state lives in
 // registers of "owner" threads: thread t < m owns row t (a_t, p_t), the column owners follow further
@@ -33,7 +33,7 @@ struct ResidentArgs {
 constexpr int kResidentCols = 256, kResidentMaxRows = 128;
 
 // The check behind sweep `it`, by the whole workgroup: the norms as block_sum_f64 forms them, with few registers.
-template <int NW>
+template <int NW, bool HERE>
 __device__ __forceinline__ bool resident_check(const ResidentArgs& A, double r2, double s2, int nchecks, int it, double* red, int* passed) {
   const int t = threadIdx.x;
   double norm2[2] = {0.0, 0.0};
@@ -48,12 +48,12 @@ __device__ __forceinline__ bool resident_check(const ResidentArgs& A, double r2,
     if (t == 0) {
       double sum = 0.0;
 #pragma unroll 1
-      for (int w = 0; w < (NW == 16 ? 16 : (int)blockDim.x >> 6); ++w) sum += red[w];
+      for (int w = 0; w < NW; ++w) sum += red[w];
       if (k == 0) norm2[0] = sum;
       else norm2[1] = sum;
     }
   }
-  if (t == 0) *passed = make_check(A.check, nchecks, it, norm2[0], norm2[1]) ? 1 : 0;
+  if (t == 0) *passed = make_check<HERE>(A.check, nchecks, it, norm2[0], norm2[1]) ? 1 : 0;
   __syncthreads();
   return *passed != 0;
 }
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
     __syncthreads();
   }
   if (!checks) break;
-  if (resident_check<NW>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  if (resident_check<NW, false>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
   ++nchecks;
   upto = min(it + A.check.every, A.iters);
   }
@@ -194,11 +194,15 @@ __global__ __launch_bounds__(1024) void resident_kernel(ResidentArgs A) {
 // 1.84 and 1.01 us, 128 x 256 2.95 and 1.81, 64 x 64 1.00 and 0.62, 10 x 10 0.56 and 0.48; without the product with a
 // scale of 1 (SCALED) 0.95, 1.65, 0.61 and 0.48.
 // SCALED: with a quadratic term; without one the scale is exactly 1 and its product, a seventh of the sweep, left out.
-// Lane l, group g = l / 16: rows 4 (wave + 16 r) + g, columns 16 e + l % 16.
+// Lane l, group g = l / 16: rows 4 (wave + NW r) + g, columns 16 e + l % 16.
 template <int NW, int R, int E, bool SCALED>
 __global__ __launch_bounds__(64 * NW) void resident_wide_kernel(ResidentArgs A) {
   constexpr int EQ = (E + 3) / 4;  // (64 columns to a wave of column owners)
   static_assert(4 * NW * R <= kResidentMaxRows && 16 * E <= kResidentCols && 2 + EQ <= NW, "layout");
+  // The check's constants: out of the loop or formed there.  With many columns registers run out (2000 iterations 128 x 256 3.54
+  // and 3.42 ms, 65 x 256 2.77 and 2.60); with few it is the schedule that changes: 100 x 16 1.41 and 1.26, 50 x 20 1.32 and
+  // 1.16, 40 x 40 1.33 and 1.20, but 100 x 48 1.42 and 1.62, 50 x 80 1.48 and 1.58, 100 x 100 2.02 and 2.01.
+  constexpr bool kHere = E > 8 || E == 1 || (R == 1 && E <= 3);
   if (*A.V.done) return;
   __shared__ float lds_phi[kResidentMaxRows];
   __shared__ float lds_varphi[64 * EQ];
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(64 * NW) void resident_wide_kernel(ResidentArgs A) 
     __syncthreads();
   }
   if (!checks) break;
-  if (resident_check<NW>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
+  if (resident_check<NW, kHere>(A, row_owner ? res * res : 0.0, col_owner ? res * res : 0.0, nchecks, it - 1, red, &passed) || it == A.iters) break;
   ++nchecks;
   upto = min(it + A.check.every, A.iters);
   }
@@ -361,16 +365,16 @@ __global__ __launch_bounds__(64 * NW) void resident_wide_kernel(ResidentArgs A) 
   }
 }
 
-// Eight waves or sixteen: fewer waves are fewer column sums to fold, cheaper barriers and longer independent work in each;
-// sixteen are ahead where a wave of eight would have little to overlap (rows beyond 64, few columns).  Per iteration, 16 waves
-// and 8: 64 x 64 0.75 and 0.68 us, 40 x 40 0.69 and 0.60, 64 x 256 1.23 and 1.15, 128 x 256 1.79 and 1.60 (with a quadratic
-// term 1.97 and 1.86), 100 x 200 1.43 and 1.39; but 100 x 40 0.71 and 0.85, 128 x 64 0.94 and 0.96; 100 x 100 1.01 and 1.03, with
-// a quadratic term 1.09 and 1.03.
+// A wave for every four rows, sixteen at most, four rows twice beyond 64: at most eight rows of a column are added up in fp32
+// (four up to 64 rows), the rest in fp64.  Eight waves with twice the rows each would fold half as many sums (2000 iterations,
+// 16 waves and 8: 64 x 64 1.47 and 1.35 ms, 64 x 256 2.44 and 2.29, 128 x 256 3.42 and 3.16, 100 x 200 2.86 and 2.76), but
+// twice the rows in fp32; with the two halves of their rows kept apart up to the fp64 sum they are behind (1.68, 2.57, 3.46,
+// 3.13).  Up to 32 rows eight waves have four rows each: 10 x 10 1.05 (16 waves) and 0.89, 20 x 30 1.07 and 0.94.
 template <int E, bool SCALED>
 void launch_resident_wide(const ResidentArgs& RS, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
-  constexpr int kWaves = E > 8 || (E > 6 && SCALED) ? 8 : 16;
-  if (RS.m <= 64) launch_timed((resident_wide_kernel<8, 2, E, SCALED>), dim3(1), dim3(512), stream, e0, e1, RS);
-  else launch_timed((resident_wide_kernel<kWaves, 32 / kWaves, E, SCALED>), dim3(1), dim3(64 * kWaves), stream, e0, e1, RS);
+  if (RS.m <= 32) launch_timed((resident_wide_kernel<8, 1, E, SCALED>), dim3(1), dim3(512), stream, e0, e1, RS);
+  else if (RS.m <= 64) launch_timed((resident_wide_kernel<16, 1, E, SCALED>), dim3(1), dim3(1024), stream, e0, e1, RS);
+  else launch_timed((resident_wide_kernel<16, 2, E, SCALED>), dim3(1), dim3(1024), stream, e0, e1, RS);
 }
 template <int E>
 void launch_resident_wide(const ResidentArgs& RS, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {

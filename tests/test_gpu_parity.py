@@ -565,6 +565,25 @@ def test_resident_kernel_for_tiny_problems(drot, oracle, m, n, kind):
     assert np.array_equal(X_two, X_one) and np.array_equal(phi_two, phi_one)
 
 
+@pytest.mark.parametrize("m,n", [(30, 30), (40, 33), (64, 256), (65, 130), (100, 100), (128, 200)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_resident_kernel_adds_no_more_rows_in_fp32_than_four_or_eight(drot, m, n, kind):
+    # rows 4 s .. 4 s + 3, with 64 on to them, are added up in fp32, the sets in fp64: next to an entry of 1/8 one of 2^-28 is a
+    # quarter of fp32's last place, and is all that is left of a residual where the two rows are of different sets
+    dev = torch.device("cuda:0")
+    solver = drot.Solver(m, n)
+    _say(f"resident column sums {m}x{n} kind={kind}")
+    for i, k in [(0, 4), (3, 28), (0, 32), (5, 37), (1, 63), (0, 100), (70, 90), (36, 127)]:
+        if max(i, k) >= m:
+            continue
+        X, C = torch.zeros(m, n, device=dev), torch.zeros(m, n, device=dev)
+        X[i, n // 2], X[k, n // 2] = 0.125, 2.0 ** -28
+        p, q = X.sum(1), torch.zeros(n, device=dev)
+        q[n // 2] = 0.125
+        res = solver.solve(C, p, q, reg_kind=kind, lam=0.0, max_iters=1, X_out=X, phi0=torch.zeros(m, device=dev), varphi0=torch.zeros(n, device=dev))
+        assert res.r_row == 0.0 and res.r_col == 2.0 ** -28, (i, k, res.r_row, res.r_col)
+
+
 def test_resident_kernel_stops_at_the_same_check_as_the_oracle(drot, oracle):
     P = _config(1)
     solver = drot.Solver(P.m, P.n, check_every=10)
