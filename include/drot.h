@@ -160,8 +160,10 @@ int drot_destroy(drot_handle h);
  *   DROT_OPT_FUSED_UPDATE [-1], -1/0: small problems (at most 2048 rows and 4096 tiles of 32 x 256) compute
  *       the O(m+n) update of eq. (6) at the head of the next sweep, one launch per iteration instead of
  *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations and their
- *       residual checks in one cooperative launch (4096 iterations or 256 checks at a time); 0 always runs the separate kernels.  Same bits.  (Larger
- *       problems that fit, up to 12.6 million entries, take the one launch where they are neither screened nor paired.)
+ *       residual checks in one cooperative launch (4096 iterations or 256 checks at a time, in which no other launch gets onto
+ *       the GPU: up to 60 ms); point clouds and group lasso that fit do the same.  0 always runs the separate kernels, a launch for
+ *       every sweep.  Same bits.  (Larger problems over a stored cost that fit, up to 12.6 million entries, take the one launch
+ *       whatever this is set to, where they are neither screened nor paired.)
  *   DROT_OPT_RESIDENT [-1], -1/0: problems of at most 128 x 256 without group lasso, from a stored cost, run
  *       in a single workgroup that keeps X and C in registers: all the iterations and their residual checks are
  *       one launch (4096 or 256 at a time).  Agrees with the other paths to rounding (different summation order).

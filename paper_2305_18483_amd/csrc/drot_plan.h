@@ -221,7 +221,7 @@ inline Static make_static(const Problem& P, const Options& O) {
       S.grid_tall = sweeps64;
     }
   }
-  if (units > 0 && P.from_points && O.skip_unchanged != 0 && !S.points_screen) {
+  if (units > 0 && P.from_points && O.fused_update != 0 && O.skip_unchanged != 0 && !S.points_screen) {
     const int per_wg = ceil_div(S.ntiles, units);
     const int owners = ceil_div(ceil_div(m, kGridBlock) + ceil_div(n, kGridBlock), kGridWaves32);
     const int wgs = ceil_div(S.ntiles, per_wg) > 1 + owners ? ceil_div(S.ntiles, per_wg) : 1 + owners;
@@ -230,8 +230,9 @@ inline Static make_static(const Problem& P, const Options& O) {
       S.grid_wgs = wgs;
     }
   }
-  // (group lasso: every workgroup holds slabs, none owns blocks only)
-  if (units > 0 && P.slab_k && (S.small ? S.fused : (size_t)S.nstrips * (size_t)P.nruns <= P.tilesum_half)) {
+  // (group lasso: every workgroup holds slabs, none owns blocks only.  Here and above the option that asks for the vector
+  // update in a launch of its own is the one that keeps a call off launches that hold every compute unit)
+  if (units > 0 && P.slab_k && O.fused_update != 0 && (S.small || (size_t)S.nstrips * (size_t)P.nruns <= P.tilesum_half)) {
     const int k = P.slab_k < kGridSlabLeastK ? kGridSlabLeastK : P.slab_k;
     const int slabs = S.nstrips * P.nruns, blocks = ceil_div(m, kGridBlock) + ceil_div(n, kGridBlock);
     auto take = [&](int lanes, int per_wg) {

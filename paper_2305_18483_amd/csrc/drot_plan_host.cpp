@@ -242,6 +242,7 @@ int drot_plan_run(const int* problem, const int* options, int compute_units, int
   Options O;
   O.check_every = options[0];
   O.resident = options[1];
+  O.fused_update = options[2];
   O.skip_unchanged = options[4];
   O.screening = options[5];
   O.gap_every = options[8];

@@ -578,3 +578,17 @@ def test_grid_resident_slabs_where_every_workgroup_holds_one(planlib):
     # not beside the separate vector update it is compared with, nor without cooperative launches; a smaller partition
     assert slabs(1500, 1000, 8, 2, fused_update=0)[0] == 0 and slabs(1500, 1000, 8, 2, units=0)[0] == 0
     assert slabs(1500, 1000, 8, 2, units=64) == (1, 8, 8, 64) and slabs(1500, 1000, 8, 2, units=32)[0] == 0
+
+
+def test_separate_vector_updates_keep_point_clouds_and_slabs_off_the_cooperative_launches(planlib):
+    # the option says so: a launch for every sweep
+    out = (ctypes.c_int * 4)()
+    for m, n, k, nruns, mapped in ((1500, 1000, 8, 2, 0), (1000, 3001, 8, 1, 0), (2000, 2500, 4, 5, 0), (2000, 1500, 4, 5, 1), (1024, 8192, 8, 1, 1)):
+        for fused, held in ((-1, True), (0, False)):
+            planlib.drot_plan_slabs(m, n, k, nruns, mapped, fused, 256, out)
+            assert (out[0] > 0) == held, (m, n, fused)
+    for m, n in ((100, 100), (1000, 1000), (3200, 3072)):
+        problem = (ctypes.c_int * 14)(m, n, 1, 1, 0, 0, 0, 1, 1, 0, 0, 1, 1, 1000)
+        for fused, sweeps in ((-1, 1000), (0, 0)):
+            options = (ctypes.c_int * 9)(100, -1, fused, -1, -1, -1, -1, 0, 0)
+            assert planlib.drot_plan_run(problem, options, 256, 0, 0) == sweeps, (m, n, fused)
