@@ -303,6 +303,11 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
 // the first iterations of a cold start also looks at the density only, after 16 and then every 32
 // iterations: a plan goes through phases -- empty, dense, then as sparse as it will be -- and a wrong
 // choice of sweep should not last a whole check interval).
+//
+// A launch that runs on through the checks, and one of point clouds or slabs whatever the call, has at most kRunSweeps sweeps
+// (or reaches one check): the largest tiles take 10 us, the largest slabs 14, so that other work on the GPU waits no longer
+// than 60 ms.
+constexpr int kRunSweeps = 4096, kRunChecks = 256;
 struct Stretch {
   int chunk = 0;
   bool prompt = false;     // the host waits for the status at its end before it plans on
@@ -331,6 +336,8 @@ inline Stretch next_stretch(const Static& S, const Problem& P, const Options& O,
       }
     }
   }
+  // (a call without checks, in launches of a bounded length where its sweeps were launches of their own)
+  if (!S.status_at_checks && (S.grid_points || S.grid_slab_lanes) && R.chunk > kRunSweeps) R.chunk = kRunSweeps;
   R.skip_cost = S.can_pair && (O.skip_cost == 1 || (S.adaptive_pairs && T.dense_plan));
   R.tall = !S.small && !R.skip_cost && !P.from_points && P.reg_kind != kGroupLasso && O.skip_unchanged != 0;
   const int end = k + R.chunk;
@@ -508,10 +515,8 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
 // Checks inside the launch: where the sweeps between two checks are one launch anyway and nothing but the residual test hangs
 // on a check, the launch runs on through the checks and tests by itself.  Per check that saves the launch, the last vector
 // update, the norms, the status and its copy, and the fetching of X and C: 40 us in grid-resident stretches, 17 in the
-// resident kernel, of stretches of 100 sweeps that take 300 and 95.  The host looks at the checks after kRunSweeps sweeps
-// (of some 10 us at most, so that other work on the GPU waits no longer than tens of milliseconds) or kRunChecks checks.
-constexpr int kRunSweeps = 4096, kRunChecks = 256;
-
+// resident kernel, of stretches of 100 sweeps that take 300 and 95.  The host looks at the checks after kRunSweeps sweeps or
+// kRunChecks checks.
 inline bool runs_through_checks(const Static& S, const Problem& P, const Options& O) {
   return (S.resident || S.grid_tiles > 0 || S.grid_points > 0) && P.feedback && P.checking && !P.single_launches && !S.adaptive && O.gap_every < 1;
 }

@@ -253,6 +253,28 @@ int drot_plan_run(const int* problem, const int* options, int compute_units, int
   return draw_out(P, O, T, next_stretch(S, P, O, T)).chunk;
 }
 
+// Sweeps of the next stretch of a call that has done k iterations: problem and options as in drot_plan_trace.
+int drot_plan_stretch(const int* problem, const int* options, int compute_units, int k) {
+  Problem P;
+  P.m = problem[0];
+  P.n = problem[1];
+  P.reg_kind = problem[2];
+  P.from_points = problem[3] != 0;
+  P.slab_k = problem[9];
+  P.nruns = problem[10];
+  P.tilesum_half = 4096;
+  P.checking = problem[12] != 0;
+  P.max_iters = problem[13];
+  P.compute_units = compute_units;
+  Options O;
+  O.check_every = options[0];
+  O.fused_update = options[2];
+  const Static S = make_static(P, O);
+  State T = start_state(S, P, Carry{});
+  T.k = k;
+  return next_stretch(S, P, O, T).chunk;
+}
+
 // Label analysis of the group-lasso path: returns slab_k (0: two-pass), -1 for a label out of range;
 // *nruns receives the number of runs.
 int drot_plan_labels(const int* labels, int m, int num_classes, int max_runs, int force_two_pass, int* nruns) {

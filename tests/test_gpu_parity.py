@@ -1409,6 +1409,30 @@ def test_grid_resident_point_clouds_give_the_bits_of_single_launches(drot, m, n,
     same(17, phi0=torch.from_numpy(phi40).cuda(), varphi0=torch.from_numpy(varphi40).cuda())
 
 
+@pytest.mark.parametrize("kind", ["points", "slabs"])
+def test_calls_longer_than_one_launch_give_the_bits_of_single_launches(drot, kind):
+    # 4096 sweeps to a launch without checks, and 4200 of them; the same with a tolerance
+    m, n = 400, 500
+    P = drot_inputs.random_problem(m, n, seed=2990, reg_kind=2 if kind == "slabs" else 1, lam=0.1, mu=0.02 if kind == "slabs" else 0.0,
+                                   num_classes=2 if kind == "slabs" else 0)
+    C, p, q, rc = pu.to_dev(P)
+    g = torch.Generator(device=C.device).manual_seed(5)
+    xs, xt = (torch.rand(k, 3, device=C.device, generator=g) for k in (m, n))
+    _say(f"longer than one launch, {kind}")
+    for tol in (0.0, 1e-12):
+        outs = []
+        for profile in (False, True):
+            solver = drot.Solver(m, n)
+            solver.set_profile(profile)
+            if kind == "points":
+                res = solver.solve_points(xs, xt, 1.0 / 3, p, q, reg_kind=1, lam=P.lam, max_iters=4200, tol=tol)
+            else:
+                res = solver.solve(C, p, q, reg_kind=2, lam=P.lam, mu=P.mu, row_class=rc, num_classes=2, max_iters=4200, tol=tol)
+            outs.append((res.X.cpu().numpy(), *(v.cpu().numpy() for v in solver.duals(m, n, C.device)), res.iters, [c.iters for c in solver.checks()]))
+        for u, v in zip(*outs):
+            assert np.array_equal(u, v)
+
+
 def test_two_threads_solve_on_two_streams(drot):
     # launches whose workgroups wait for one another, from two handles at once: one after the other on the chip
     import threading

@@ -592,3 +592,18 @@ def test_separate_vector_updates_keep_point_clouds_and_slabs_off_the_cooperative
         for fused, sweeps in ((-1, 1000), (0, 0)):
             options = (ctypes.c_int * 9)(100, -1, fused, -1, -1, -1, -1, 0, 0)
             assert planlib.drot_plan_run(problem, options, 256, 0, 0) == sweeps, (m, n, fused)
+
+
+def test_launches_of_calls_without_checks_are_bounded_where_sweeps_were_launches(planlib):
+    # point clouds and slabs; stored costs on tiles have always run such a call in one launch
+    def stretch(m, n, iters, k=0, reg_kind=1, from_points=0, slab_k=0, nruns=0, checking=0, units=256, fused_update=-1, check_every=100):
+        problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, 0, 0, 0, 1, 1, slab_k, nruns, 1, checking, iters)
+        return planlib.drot_plan_stretch(problem, (ctypes.c_int * 9)(check_every, -1, fused_update, -1, -1, -1, -1, 0, 0), units, k)
+
+    for kw in (dict(from_points=1), dict(reg_kind=2, slab_k=8, nruns=2)):
+        assert stretch(1500, 1000, 100000, **kw) == 4096 and stretch(1500, 1000, 100000, k=98304, **kw) == 1696
+        assert stretch(1500, 1000, 4096, **kw) == 4096 and stretch(1500, 1000, 500, **kw) == 500
+        assert stretch(1500, 1000, 100000, checking=1, **kw) == 100 and stretch(1500, 1000, 100000, checking=1, check_every=5000, **kw) == 5000
+        # (single launches need no bound)
+        assert stretch(1500, 1000, 100000, units=0, **kw) == 100000 and stretch(1500, 1000, 100000, fused_update=0, **kw) == 100000
+    assert stretch(1500, 1000, 100000) == 100000
