@@ -27,12 +27,13 @@
 // their entries, too, the first workgroup adds them up, tests, and sends the answer behind 2 eta - theta: one hop more,
 // 2 us.  Ending the launch at every check instead (the launch, fetching X and C, the last vector update, norms, status and
 // its copy to the host) cost 40 us: 1000 x 1000, 1000 sweeps checked every 100 3.48 -> 3.11 ms, every 10 7.18 -> 3.39.
-// The sweeps without a check are a loop of their own, which the check costs no register.
+// The sweeps without a check are a loop of their own, without its branches; its registers are the kernel's, though (kFull).
 //
 // Two halves of the exchange buffers, used in turn, are enough: a word of iteration k is overwritten in iteration
 // k + 2, whose sweep needs the 2 eta - theta of k + 1, which needs the total of every tile of k + 1, which every
 // workgroup publishes after it has read all it needs of k.  (A workgroup without tiles, which only owns blocks, forms
-// nothing of k + 2 before that either, and nobody gets past k + 1 without what it publishes there.)  The words of eight entries and one partial sum lie together
+// nothing of k + 2 before that either, and nobody gets past k + 1 without what it publishes there; the answer of a check that
+// it still has to read is overwritten at a later check only, for which the first workgroup needs its squared residuals.)  The words of eight entries and one partial sum lie together
 // (64 bytes), the partial sums of a block of eight one after the other: a wave reads 512 contiguous bytes per load.
 //
 // The arithmetic and its order are those of the launches this kernel stands for, so that the results are the same
@@ -47,6 +48,8 @@
 // This kernel has not been seen to give up of itself.  The same exchange, in a first form for the slabs of the group lasso
 // (three slabs, five workgroups that only owned blocks, a kernel with spilled registers), has, and neither reading it nor
 // running it on a CPU showed why (drot_grid_slab.h has the present form): a wait that runs out is taken for possible here.
+// No kernel with such waits uses scratch memory any more (a test of the built library holds them to it); workgroups that only
+// own blocks are left, in this kernel, for oblong problems.
 // ------------------------------------------------------------------------------------------
 typedef unsigned long long u64;
 constexpr int kGridPolls = 1 << 25;
@@ -125,6 +128,13 @@ __device__ __forceinline__ void grid_store(u64* half, unsigned word, unsigned v,
 }
 __device__ __forceinline__ float grid_value(u64 w) { return __builtin_bit_cast(float, (int)(unsigned)w); }
 __device__ __forceinline__ double grid_value(u64 hi, u64 lo) { return __builtin_bit_cast(double, (hi << 32) | (unsigned)lo); }
+
+// The number of the lane in a form that the compiler can't lift out of a loop, nor what is made of it.
+__device__ __forceinline__ int lane_again() {
+  int zero = 0;
+  asm volatile("" : "+v"(zero));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero));
+}
 
 // Fetches the words at[0 .. N-1] until every lane has all of its own with the number `tag`.  All of them are asked for
 // again together: a word waited for by itself would cost a trip to the memory-side cache each.  PAUSE: between two
@@ -240,6 +250,16 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   constexpr bool kDotsApart = kPoints && kTiles * NT * kSegCols < kTileRows * kDotPitch;
   __shared__ float dots_apart[kDotsApart ? kTileRows * kDotPitch : 1];
   __shared__ double red[kShareBlocks];
+  // kFull: X and C fill the registers.  What a check, the end of the launch and the keeper alone need (constants, addresses) is
+  // formed there then; the compiler keeps it in registers, or in scratch memory, through all the sweeps otherwise.  kTight: the
+  // lane numbers of the exchange, too, and theta lies in LDS.  Registers without the checks, with them, and so (in brackets
+  // the bytes of scratch memory): one tile 85, 116, 116; two 104, 128 (24), 120; three 124, 128 (24), 111; four 128 (28),
+  // 128 (88), 108; five 128 (96), 128 (140), 121; three of 64 rows 249, 256 (56), 246; point clouds of two to five tiles
+  // 128 (76 to 172) with the checks, 127, 114, 114, 128 so.  Times per iteration, with the scratch memory and without: 2048 x 3072
+  // 6.20 and 6.21 us, 2999 x 3307 7.97 and 7.95, 2047 x 5101 9.25 and 9.36; point clouds 1400 x 1400 5.18 and 5.08, 3000 x 3300
+  // 12.55 and 12.45.
+  constexpr bool kFull = U == 8 ? TW == 3 : TW > 1, kTight = U == 2 && (TW >= 4 || (kPoints && TW >= 3));
+  __shared__ double theta_sum[2];  // (kTight, the first workgroup: theta, 1^T p)
   __shared__ double sq64[kGridSquares<NW>];  // checks: squared residuals of 64 entries each
   __shared__ int failed[2];  // a word that never came: among the tile totals; among the others
   const SweepArgs& S = A.S;
@@ -312,7 +332,8 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     target = (double)(own_rows ? A.p[entry] : A.q[entry]);
   }
   double theta = vector_load_uniform(A.theta_in);
-  const double sum_p = vector_load_uniform(A.sum_p);
+  double sum_p = vector_load_uniform(A.sum_p);
+  if (kTight && t < 2) theta_sum[t] = t == 0 ? theta : sum_p;
   constexpr bool kRecip = U == 8 || TW <= 3;  // (beyond that the registers are worth more)
   const double recip_n = kRecip ? reciprocal_of((double)S.n) : 0.0, recip_m = kRecip ? reciprocal_of((double)S.m) : 0.0;
   auto over = [&](double v, double count, double recip) { return (float)(kRecip ? divide_by(v, count, recip) : v / count); };
@@ -326,9 +347,6 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
   const int nparts = own_rows ? A.nseg : A.ntr, round_parts = grouped ? 16 * G : 8 * NP;
   const unsigned part_word = (own_rows ? 0u : A.col_word) + (unsigned)(bi * nparts * kGridBlock);
   const unsigned part_lane = (unsigned)min(lane & 7, entries - 1 - bi * kGridBlock);
-  auto part_index = [&](int k0, int b) {  // which partial sum the b-th word of the round from k0 on is
-    return k0 + (grouped ? ((lane >> 3) + 8 * (b / G)) * G + b % G : (lane >> 3) + 8 * b);
-  };
   // tile totals: the groups e = 64 (wave + NW sb) + lane, + 1024, ..., G words each
   const int ngroups = (A.ntr + G - 1) / G * A.nseg, last_g = (A.ntr - 1) % G;
   auto total_there = [&](int e, int b) { return b <= (e >= ngroups - A.nseg ? last_g : G - 1); };
@@ -387,11 +405,15 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     __syncthreads();
   };
   // Publishes the sums of sweep `it` and brings phi and varphi back.  check_here: with the check that stands behind it
-  // (the sweeps without one, nearly all of them, pay nothing for it: neither registers nor branches).
+  // (the sweeps without one, nearly all of them, pay no branches for it).
   enum { kGoesOn, kPasses, kGaveUp };
   int nchecks = 0;
-  auto exchange = [&](auto check_here, int it) __attribute__((always_inline)) -> int {
+  auto exchange = [&, kept_lane = lane](auto check_here, int it) __attribute__((always_inline)) -> int {
     constexpr bool check = decltype(check_here)::value;
+    const int lane = kTight ? lane_again() : kept_lane;
+    auto part_index = [&](int k0, int b) {  // which partial sum the b-th word of the round from k0 on is
+      return k0 + (grouped ? ((lane >> 3) + 8 * (b / G)) * G + b % G : (lane >> 3) + 8 * b);
+    };
     // ---- publish the sums of the tiles ----
     const unsigned tag = A.tag0 + (unsigned)it;
     u64* __restrict__ half = A.xchg + (size_t)(tag & 1u) * A.half_words;
@@ -488,7 +510,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         const u64 w = __builtin_bit_cast(u64, sq);
         const GridArgs& L = late_args();
         if (lane < 2) grid_store(half, L.sq_word + (unsigned)(blk * 2 + lane), lane == 0 ? (unsigned)(w >> 32) : (unsigned)w, tag);
-        if (entry_exists && lane < kGridBlock) (own_rows ? L.r : L.s)[entry] = res;
+        if (entry_exists && lane < kGridBlock) (own_rows ? L.r : L.s)[kTight ? bi * kGridBlock + lane : entry] = res;
       }
     }
     if (keeper) {
@@ -537,15 +559,24 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
       if (lost) failed[0] = 1;
       __syncthreads();
       if (failed[0]) return kGaveUp;
-      double sum_x = 0.0;
+      if (!kTight || wave == 0) {
+        int first = 0;
+        if (kFull) asm volatile("" : "+v"(first));
+        double sum_x = 0.0;
 #pragma unroll
-      for (int k = 0; k < kShareBlocks; ++k) sum_x += red[k];
-      const double eta = (sum_x - sum_p) / ((double)S.m + (double)S.n);
-      const u64 cst = __builtin_bit_cast(u64, 2.0 * eta - theta);
-      theta = theta - eta;
-      static_assert(kGridCopies == 32, "two words per copy, one wave");
-      if (wave == 0)
-        grid_store(half, A.cst_word + 32u * (unsigned)(lane >> 1) + (unsigned)(lane & 1), (lane & 1) ? (unsigned)cst : (unsigned)(cst >> 32), tag);
+        for (int k = 0; k < kShareBlocks; ++k) sum_x += red[first + k];
+        if (kTight) {
+          theta = theta_sum[0];
+          sum_p = theta_sum[1];
+        }
+        const double eta = (sum_x - sum_p) / ((double)S.m + (double)S.n);
+        const u64 cst = __builtin_bit_cast(u64, 2.0 * eta - theta);
+        theta = theta - eta;
+        static_assert(kGridCopies == 32, "two words per copy, one wave");
+        if (wave == 0)
+          grid_store(half, A.cst_word + 32u * (unsigned)(lane >> 1) + (unsigned)(lane & 1), (lane & 1) ? (unsigned)cst : (unsigned)(cst >> 32), tag);
+        if (kTight && lane == 0) theta_sum[0] = theta;
+      }
       if (check) {
         const GridArgs& L = late_args();
         if (wave == 0) {  // (at most 1024 blocks of 64 entries: one to a share)
@@ -557,7 +588,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
             norm2[side_n] = sum;
           }
           bool pass = false;
-          if (lane == 0) pass = make_check<false>(L.check, nchecks, it, norm2[0], norm2[1]);
+          if (lane == 0) pass = make_check<kFull>(L.check, nchecks, it, norm2[0], norm2[1]);
           const unsigned word = __builtin_amdgcn_ballot_w64(pass) != 0 ? 1u : 0u;
           if (lane < kGridCopies) grid_store(half, L.cst_word + 32u * (unsigned)lane + 2u, word, tag);
         }
@@ -633,11 +664,12 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
 
   const GridArgs& E = late_args();
   // ---- leave the last sweep's plan and sums, and the state after the last update, in memory ----
+  const int lane_now = kFull ? lane_again() : lane;
 #pragma unroll
   for (int q = 0; q < TW; ++q) {
     const int tl = tile0 + q * kSide + side;
     const int seg = tl / A.ntr, tr = tl - seg * A.ntr;
-    const int j0 = seg * kSegCols + lane * 4;
+    const int j0 = seg * kSegCols + lane_now * 4;
     const int r0 = tr * kRows + stack * U;
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -649,7 +681,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     if (tl >= ntiles) break;
     const int seg = tl / A.ntr, tr = tl - seg * A.ntr;
     if (part < 4) {
-      const int cc = part * 64 + lane, j = seg * kSegCols + cc;
+      const int cc = part * 64 + lane_now, j = seg * kSegCols + cc;
       float sum = 0.f;
 #pragma unroll
       for (int k = 0; k < NT; ++k) sum += cs[lt][k][cc];
@@ -658,18 +690,18 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
         if (tr == 0) E.varphi_out[j] = lds_varphi[lt][cc];
       }
     } else {
-      const int i = tr * kRows + lane;
-      if (lane < kRows && i < S.m) {
-        E.S.rowpart[(size_t)seg * E.S.mp + i] = lds_row[lt][lane];
-        if (seg == 0) E.phi_out[i] = lds_phi[lt][lane];
+      const int i = tr * kRows + lane_now;
+      if (lane_now < kRows && i < S.m) {
+        E.S.rowpart[(size_t)seg * E.S.mp + i] = lds_row[lt][lane_now];
+        if (seg == 0) E.phi_out[i] = lds_phi[lt][lane_now];
       }
       float tot = 0.f;
 #pragma unroll
       for (int k = 0; k < NT; ++k) tot += wt[lt][k];
-      if (lane == 0) E.S.tilesum[(size_t)tr * A.nseg + seg] = tot;
+      if (lane_now == 0) E.S.tilesum[(size_t)tr * A.nseg + seg] = tot;
     }
   }
   const bool alt = (it & 1) == 0;  // (behind an odd number of updates)
-  if (entry_exists && lane < kGridBlock) (own_rows ? (alt ? E.a_alt : E.a_in) : (alt ? E.b_alt : E.b_in))[entry] = state;
-  if (keeper && t == 0) *(alt ? E.theta_alt : E.theta_in) = theta;
+  if (entry_exists && lane_now < kGridBlock) (own_rows ? (alt ? E.a_alt : E.a_in) : (alt ? E.b_alt : E.b_in))[kTight ? bi * kGridBlock + lane_now : entry] = state;
+  if (keeper && wave == 0 && lane_now == 0) *(alt ? E.theta_alt : E.theta_in) = kTight ? theta_sum[0] : theta;
 }

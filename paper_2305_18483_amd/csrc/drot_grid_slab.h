@@ -18,9 +18,10 @@
 // two classes, 10.8 and 5.3 us (64 workgroups on 256 compute units there), rows in no order 13.6 and 5.8; 2000 x 1500, five
 // classes in no order 13.7 and 7.3; 150 x 300 6.7 and 3.9; two slabs to a workgroup 1203 x 2047, five classes 13.2 and 7.1,
 // 2000 x 2500, five in no order 16.8 and 9.9; 1000 x 8000, one class 22.4 and 14.0.
-// No kernel here may need scratch memory, and every workgroup holds a slab: the planner gives none to the owner waves alone.
-// (A first version of this, whose workgroups could be owners only and whose registers spilled, gave up waiting once, at
-// 700 x 90 with one class; why was not found.)
+// No kernel here uses scratch memory (a test of the built library holds them to it), and every workgroup holds a slab: the
+// planner gives none to the owner waves alone.  (A first version of this, whose workgroups could be owners only and whose
+// registers spilled, gave up waiting once, at 700 x 90 with one class; why was not found, nor which of the two had a part in
+// it.  The tiles of drot_grid.h have always had workgroups that are owners only.)
 // ------------------------------------------------------------------------------------------
 struct GridSlabArgs {
   const int* run_start;  // [nruns] first row of every class, counted class by class

@@ -3,6 +3,8 @@ argument validation answers without a GPU (no compute calls here)."""
 import ctypes
 import os
 import re
+import struct
+import subprocess
 
 import pytest
 
@@ -141,3 +143,32 @@ def test_public_header_is_plain_c(tmp_path):
                            "-c", str(src), "-o", str(tmp_path / "use_header.o")],
                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert proc.returncode == 0, proc.stdout
+
+
+def _kernel_resources(tmp_path):
+    """{kernel name: (bytes of scratch memory per lane, registers)} of the gfx950 code in the built library."""
+    from paper_2305_18483_amd import binding
+
+    data = open(binding.LIB_PATH, "rb").read()
+    at = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    (count,), pos = struct.unpack_from("<Q", data, at + 24), at + 32
+    for _ in range(count):
+        offset, size, length = struct.unpack_from("<QQQ", data, pos)
+        name = data[pos + 24:pos + 24 + length].decode()
+        pos += 24 + length
+        if name.endswith("gfx950"):
+            elf = tmp_path / "device.elf"
+            elf.write_bytes(data[at + offset:at + offset + size])
+    notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(elf)], check=True, stdout=subprocess.PIPE, text=True).stdout
+    found = {}
+    for kernel in notes.split("- .agpr_count:")[1:]:
+        field = lambda key: re.search(r"^ +\." + key + r": +(\S+)", kernel, re.M).group(1)  # noqa: E731
+        found[field("symbol")] = int(field("private_segment_fixed_size")), int(field("vgpr_count"))
+    return found
+
+
+def test_kernels_whose_workgroups_wait_for_one_another_use_no_scratch_memory(lib, tmp_path):
+    # (spilled registers: a form of such a kernel that had them gave up waiting once, and what spills inside the loop costs time)
+    kernels = {k: v for k, v in _kernel_resources(tmp_path).items() if "grid_resident_kernel" in k or "grid_slab_kernel" in k}
+    assert len(kernels) == 8 + 5 + 10, sorted(kernels)
+    assert all(scratch == 0 for scratch, _ in kernels.values()), {k: v for k, v in kernels.items() if v[0]}
