@@ -114,6 +114,7 @@ struct drot_handle_s {
   // padded working copies: which caller arrays they were made from (a continued solve reuses them)
   const float* cpad_of = nullptr;
   bool xpad_live = false;
+  int xpad_n = -1;        // the columns of xpad from this one on are zero (-1: not known)
   // sweep timing (profile mode): event pairs recorded on the solve's stream
   hipEvent_t prof_ev[2 * kMaxProfiled] = {};
   int prof_count = 0;
@@ -920,6 +921,12 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
     Z.Xw = h->xpad;
     Z.ldx = S.ld_pad;
     const bool reuse = resume && had >= padded && h->xpad_live;
+    if (had < padded) h->xpad_n = n;
+    if (!reuse) {
+      if (h->xpad_n != n)  // (an earlier, wider plan lies there; the mask alone does not hold back an infinite entry)
+        hipLaunchKernelGGL(clear_padding_kernel, dim3(1024), dim3(256), 0, stream, h->xpad, h->xpad_len / (size_t)S.ld_pad, S.ld_pad, n);
+      h->xpad_n = n;
+    }
     if ((resume && !reuse) || A.warm)  // the plan to start from is in X_out
       copy_rows(h->xpad, (size_t)S.ld_pad, A.X_out, (size_t)n, m, n, stream);
   }
@@ -1138,6 +1145,7 @@ int solve_once(drot_handle h, const SolveCall& A) {
     (void)hipGetLastError();
     h->solved = false;
     h->carry = plan::Carry{};
+    h->xpad_n = -1;
     return code;
   };
   bool converged = false;
@@ -1183,6 +1191,7 @@ int solve_once(drot_handle h, const SolveCall& A) {
   h->info.dual_res = h->compute_gap ? st.dual_res : 0.0;
   h->carry = plan::finish(S, Z.P, Z.T, st.converged != 0, iters);
   h->xpad_live = S.pad_x && !untouched;
+  if (S.pad_x && !(st.r2 < INFINITY && st.s2 < INFINITY)) h->xpad_n = -1;
   h->solved = true;
   h->last_m = Z.m;
   h->last_n = Z.n;

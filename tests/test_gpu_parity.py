@@ -523,6 +523,35 @@ def test_slabs_do_not_see_what_lies_behind_a_padded_row(drot, m, n, classes, ord
         assert np.array_equal(u, v)
 
 
+@pytest.mark.parametrize("m,n,reg,classes", [(200, 140, 2, 2), (300, 415, 2, 3), (200, 140, 1, 0), (2100, 2013, 1, 0)])
+@pytest.mark.parametrize("start", ["warm", "cold"])
+def test_an_infinite_plan_behind_a_padded_row_has_no_part_in_the_next_solve(drot, m, n, reg, classes, start):
+    # a call that only takes an infinite plan in leaves it behind the rows of the next, narrower one; that one starts from the
+    # caller's plan, or from nothing and goes on in a second call
+    P = drot_inputs.random_problem(m, n, seed=83 + m + n, reg_kind=reg, lam=0.1, mu=0.02 if classes else 0.0, num_classes=classes)
+    C, p, q, rc = pu.to_dev(P)
+    wide = n + 110
+    _say(f"infinite plan on used padding {m}x{n}, regularizer {reg}, {start}")
+    kw = dict(reg_kind=reg, lam=P.lam, mu=P.mu, row_class=rc, num_classes=classes)
+    outs = []
+    for used in (True, False):
+        solver = drot.Solver(m, wide)
+        if used:
+            solver.solve(torch.zeros(m, wide, device=C.device), p, torch.ones(wide, device=C.device) / wide, max_iters=0,
+                         X_out=torch.full((m, wide), float("inf"), device=C.device),
+                         phi0=torch.zeros(m, device=C.device), varphi0=torch.zeros(wide, device=C.device))
+        X = torch.full_like(C, 1.0 / (m * n))
+        if start == "warm":
+            solver.solve(C, p, q, max_iters=5, X_out=X, phi0=torch.zeros(m, device=C.device), varphi0=torch.zeros(n, device=C.device), **kw)
+        else:
+            solver.solve(C, p, q, max_iters=12, X_out=X, **kw)
+            solver.set_continue(True)
+            solver.solve(C, p, q, max_iters=3, X_out=X, **kw)
+        outs.append((X.cpu().numpy(), *(v.cpu().numpy() for v in solver.duals(m, n, C.device))))
+    for u, v in zip(*outs):
+        assert np.array_equal(u, v) and np.isfinite(u).all()
+
+
 @pytest.mark.parametrize("m,n", [(16, 96), (16, 97), (5, 129), (17, 1), (20, 129), (61, 176), (64, 256), (65, 17), (100, 112),
                                  (113, 193), (127, 241), (128, 65), (128, 225)])
 def test_resident_kernel_at_the_edges_of_its_sets_of_rows_and_columns(drot, oracle, m, n):
