@@ -255,6 +255,13 @@ typedef struct {
 int drot_get_profile(drot_handle h, drot_sweep_timing* out, int capacity, int* count);
 
 /*
+ * Cooperative launches of this handle since it was created: accepted by the runtime (those that gave up among them), refused,
+ * and given up waiting (DROT_OPT_GRID_POLLS).  After one that was refused or gave up the handle makes no more of them; a
+ * solve that could have run that way comes out with the same bits, so these numbers are what tells.  Errors: INVALID_ARG.
+ */
+int drot_get_launches(drot_handle h, int* accepted, int* refused, int* given_up);
+
+/*
  * Solve problem (1) by the iteration of eq. (8) + eq. (6), starting from X_0 = 0 and the
  * phi_0, varphi_0 of the Initialization paragraph.
  *

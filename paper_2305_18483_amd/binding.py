@@ -24,6 +24,7 @@ DROT_STATIC_MAX_M = DROT_STATIC_MAX_N = 4096
 # every symbol include/drot.h declares
 EXPORTED_SYMBOLS = (
     "drot_create", "drot_destroy", "drot_set_option", "drot_set_gap_tolerance", "drot_get_checks", "drot_get_profile",
+    "drot_get_launches",
     "drot_solve", "drot_solve_points", "drot_solve_warm", "drot_solve_points_warm", "drot_solve_static", "drot_get_info", "drot_get_duals",
     "drot_strerror",
 )
@@ -82,6 +83,7 @@ def load_library() -> ctypes.CDLL:
     lib.drot_set_gap_tolerance.argtypes = [vp, cf]
     lib.drot_get_checks.argtypes = [vp, ctypes.POINTER(drot_check), ci, ctypes.POINTER(ci)]
     lib.drot_get_profile.argtypes = [vp, ctypes.POINTER(drot_sweep_timing), ci, ctypes.POINTER(ci)]
+    lib.drot_get_launches.argtypes = [vp, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(ci)]
     lib.drot_solve.argtypes = [vp, vp, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf, vp, vp]
     lib.drot_solve_warm.argtypes = [vp, vp, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf, vp, vp, vp, vp]
     lib.drot_solve_points.argtypes = [vp, vp, vp, ci, cf, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf,
@@ -260,6 +262,14 @@ class Solver:
         """Fraction of the row segments of C (the sweep by lines, kind 7: of its lines) that each timed sweep of the last
         solve read."""
         return [float(r.c_fraction) for r in self.profile_records()]
+
+    def cooperative_launches(self) -> tuple:
+        """drot_get_launches: (accepted, refused, given up) since the handle was created."""
+        n = [ctypes.c_int() for _ in range(3)]
+        rc = self._lib.drot_get_launches(self._h, *map(ctypes.byref, n))
+        if rc != DROT_OK:
+            raise DrotError(rc, "drot_get_launches")
+        return tuple(k.value for k in n)
 
     def solve(self, C: torch.Tensor, p: torch.Tensor, q: torch.Tensor, *, stepsize: float = 0.0,
               reg_kind: int = DROT_REG_NONE, lam: float = 0.0, mu: float = 0.0,

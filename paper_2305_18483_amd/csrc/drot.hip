@@ -161,6 +161,7 @@ struct drot_handle_s {
   // waits last, the exchange buffer (made on demand) and the last number used in it
   int compute_units = 0;
   int grid_polls = kGridPolls;
+  int launches_accepted = 0, launches_refused = 0, launches_given_up = 0;
   u64* xchg = nullptr;
   size_t xchg_len = 0;
   unsigned xchg_tag = 0;
@@ -1041,11 +1042,13 @@ int iterate(Solve& Z, bool* converged_out) {
         const int rc = enqueue_grid(Z, F, L);
         Z.check = CheckArgs{};
         if (rc == DROT_OK) {
+          ++h->launches_accepted;
           Z.T.norms_pending = false;
           if (S.grid_slab_lanes) Z.T.sums_gen = -1;  // (the slabs leave no sums)
           break;
         }
         if (rc != kGridRefused) return rc;
+        ++h->launches_refused;
         Z.T = before;  // (one by one, here and in the solves to come)
         Z.P.single_launches = true;
         h->compute_units = 0;
@@ -1207,6 +1210,7 @@ int solve_impl(drot_handle h, const SolveCall& A) {
   if (rc != kGridGaveUp) return rc;
   fprintf(stderr, "drot: a launch whose workgroups wait for one another gave up; single launches from now on\n");
   h->compute_units = 0;
+  ++h->launches_given_up;
   return cold ? solve_once(h, A) : DROT_ERR_HIP;
 }
 
@@ -1543,6 +1547,14 @@ int drot_get_profile(drot_handle h, drot_sweep_timing* out, int capacity, int* c
     out[e].c_fraction = (kind >= 5 && kind <= 8) ? h->prof_counts_host[2 * e] / counted : (kind == 2 ? 0.0 : 1.0);
     out[e].x_fraction = kind >= 4 ? h->prof_counts_host[2 * e + 1] / segments : -1.0;
   }
+  return DROT_OK;
+}
+
+int drot_get_launches(drot_handle h, int* accepted, int* refused, int* given_up) {
+  if (!h || !accepted || !refused || !given_up) return DROT_ERR_INVALID_ARG;
+  *accepted = h->launches_accepted;
+  *refused = h->launches_refused;
+  *given_up = h->launches_given_up;
   return DROT_OK;
 }
 

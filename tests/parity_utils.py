@@ -12,6 +12,7 @@ Tolerances (the bar the benchmark definition states, fp32 arithmetic on the GPU,
 from __future__ import annotations
 
 import numpy as np
+import pytest
 import torch
 
 PLAN_TOL = 1e-4
@@ -52,6 +53,15 @@ def gpu_solve(solver, P, max_iters, tol=0.0, stepsize=0.0, stream=None, X_out=No
     phi, varphi = solver.duals(P.m, P.n, C.device)
     torch.cuda.synchronize()
     return res, res.X.cpu().numpy(), phi.cpu().numpy(), varphi.cpu().numpy()
+
+
+def assert_held_on_the_chip(*solvers, given_up=0):
+    """The handles' solves ran in cooperative launches (single launches give the same bits: nothing else tells)."""
+    for solver in solvers:
+        accepted, refused, gave_up = solver.cooperative_launches()
+        if refused:
+            pytest.skip("no cooperative launches for this process on this system: the solves ran in single launches")
+        assert accepted > 0 and gave_up == given_up, (accepted, refused, gave_up)
 
 
 def oracle_solve(oracle, P, max_iters, tol=0.0, check_every=1, stepsize=None):

@@ -57,6 +57,7 @@ for m, n in ((600, 1024), (2300, 2528)):
     single.set_profile(True)
     ref = single.solve(C, p, q, **kw).X
     assert torch.equal(X, ref) and torch.equal(again, ref)
+    assert solver.cooperative_launches() == (0, 1, 0) and single.cooperative_launches() == (0, 0, 0)
     Xs = torch.empty_like(C)
     info = torch.zeros(64, dtype=torch.uint8, device=dev)
     drot.solve_static(C, p, q, Xs, info_out=info, **kw)
@@ -151,7 +152,9 @@ def test_a_second_process_on_the_gpu(drot, tmp_path):
     # this process has launched that way, and stays: the second one may be refused (it was, with an error as the result)
     P = drot_inputs.random_problem(900, 1000, seed=2670, reg_kind=1, lam=0.3)
     _say("a second process")
-    _, X, _, _ = pu.gpu_solve(drot.Solver(P.m, P.n), P, 130)
+    solver = drot.Solver(P.m, P.n)
+    _, X, _, _ = pu.gpu_solve(solver, P, 130)
+    pu.assert_held_on_the_chip(solver)
     out = tmp_path / "second.npy"
     proc = subprocess.run([sys.executable, "-c", _SECOND, str(out)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                           text=True, timeout=100, env=_child_env())
@@ -174,6 +177,7 @@ def test_a_launch_that_gives_up_is_replaced_by_single_launches(drot, m, n):
         res, X, phi, varphi = pu.gpu_solve(solver, P, 150, tol=1e-12)
         assert res.iters == 150 and [c.iters for c in solver.checks()] == [100, 150]
         assert np.array_equal(X, X_ref) and np.array_equal(phi, phi_ref) and np.array_equal(varphi, varphi_ref)
+    pu.assert_held_on_the_chip(solver, given_up=1)
     solver = drot.Solver(m, n)
     solver.set_grid_polls(1)
     phi0, varphi0 = torch.zeros(m, device=C.device), torch.zeros(n, device=C.device)
@@ -181,6 +185,7 @@ def test_a_launch_that_gives_up_is_replaced_by_single_launches(drot, m, n):
     with pytest.raises(drot.DrotError) as e:
         solver.solve(C, p, q, X_out=torch.zeros_like(C), **kw)
     assert e.value.code == drot.binding.DROT_ERR_HIP
+    assert solver.cooperative_launches() == (1, 0, 1)
     again = solver.solve(C, p, q, X_out=torch.zeros_like(C), **kw).X
     assert torch.equal(again, drot.Solver(m, n).solve(C, p, q, X_out=torch.zeros_like(C), **kw).X)
     for bad in (0, -1, (1 << 30) + 1):
@@ -198,3 +203,4 @@ def test_a_launch_of_slabs_that_gives_up_is_replaced_by_single_launches(drot):
         res, X, phi, varphi = pu.gpu_solve(solver, P, 150, tol=1e-12)
         assert res.iters == 150 and [c.iters for c in solver.checks()] == [100, 150]
         assert np.array_equal(X, X_ref) and np.array_equal(phi, phi_ref) and np.array_equal(varphi, varphi_ref)
+    pu.assert_held_on_the_chip(solver, given_up=1)

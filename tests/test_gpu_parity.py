@@ -1324,6 +1324,7 @@ def test_grid_resident_stretches_give_the_bits_of_single_launches(drot, m, n):
     solver.set_profile(False)
     assert np.array_equal(X, X1) and np.array_equal(phi, phi1) and np.array_equal(varphi, varphi1)
     assert (res.r_row, res.r_col, res.objective, res.gap) == (res1.r_row, res1.r_col, res1.objective, res1.gap)
+    pu.assert_held_on_the_chip(solver)
 
 
 @pytest.mark.parametrize("m,n", [(16, 200), (60, 60), (128, 256), (129, 2), (1000, 1000), (2047, 5101), (2300, 2500), (2999, 3307),
@@ -1363,6 +1364,9 @@ def test_checks_inside_a_launch_are_those_of_a_launch_each(drot, m, n):
     solver.set_check_every(1), ref.set_check_every(1)
     _, checks = same(300, tol=1e-12)
     assert [c.iters for c in checks] == list(range(1, 301))
+    assert ref.cooperative_launches()[0] == 0
+    if m > 128 or n > 256:  # (one workgroup otherwise)
+        pu.assert_held_on_the_chip(solver)
 
 
 @pytest.mark.parametrize("m,n,classes,order", [(1500, 1000, 2, "runs"), (1201, 1001, 2, "anywhere"), (333, 517, 3, "runs"), (258, 1057, 2, "anywhere"),
@@ -1402,10 +1406,12 @@ def test_grid_resident_slabs_give_the_bits_of_single_launches(drot, m, n, classe
         X.copy_(torch.from_numpy(X60))
         outs.append(s.solve(C, p, q, X_out=X, phi0=phi, varphi0=varphi, max_iters=17, **kw).X.cpu().numpy())
     assert np.array_equal(*outs)
+    assert ref.cooperative_launches()[0] == 0
+    pu.assert_held_on_the_chip(solver)
 
 
 @pytest.mark.parametrize("m,n,d", [(33, 257, 2), (400, 401, 7), (257, 9000, 3), (1000, 1003, 32), (1500, 2100, 17), (2600, 2500, 4), (3333, 3111, 16),
-                                   (12000, 640, 5)])
+                                   (12000, 640, 5), (3000, 3301, 16)])
 def test_grid_resident_point_clouds_give_the_bits_of_single_launches(drot, m, n, d):
     # 1 to 5 tiles per workgroup, groups of eight tile rows of which the last is short, last column segments of one to four
     # quarters; checks in the middle, a stop at one, a continued call, a warm start.  Profile mode launches every sweep by itself.
@@ -1436,6 +1442,11 @@ def test_grid_resident_point_clouds_give_the_bits_of_single_launches(drot, m, n,
     for X in Xs:
         X.copy_(torch.from_numpy(X40))
     same(17, phi0=torch.from_numpy(phi40).cuda(), varphi0=torch.from_numpy(varphi40).cuda())
+    assert ref.cooperative_launches()[0] == 0
+    if (m, n) == (3333, 3111):  # (1365 tiles, more than five to a workgroup)
+        assert solver.cooperative_launches()[0] == 0
+    else:
+        pu.assert_held_on_the_chip(solver)
 
 
 @pytest.mark.parametrize("kind", ["points", "slabs"])
@@ -1458,8 +1469,12 @@ def test_calls_longer_than_one_launch_give_the_bits_of_single_launches(drot, kin
             else:
                 res = solver.solve(C, p, q, reg_kind=2, lam=P.lam, mu=P.mu, row_class=rc, num_classes=2, max_iters=4200, tol=tol)
             outs.append((res.X.cpu().numpy(), *(v.cpu().numpy() for v in solver.duals(m, n, C.device)), res.iters, [c.iters for c in solver.checks()]))
+            if not profile:
+                held = solver
         for u, v in zip(*outs):
             assert np.array_equal(u, v)
+        pu.assert_held_on_the_chip(held)
+        assert held.cooperative_launches()[0] == 2
 
 
 def test_two_threads_solve_on_two_streams(drot):
@@ -1469,12 +1484,12 @@ def test_two_threads_solve_on_two_streams(drot):
     P = drot_inputs.random_problem(1500, 1500, seed=2700, reg_kind=1, lam=0.3)
     _say("two threads, two streams")
     _, X_ref, _, _ = pu.gpu_solve(drot.Solver(P.m, P.n), P, 300)
-    out = [None, None]
+    out, solvers = [None, None], [None, None]
 
     def work(k):
         s = torch.cuda.Stream()
         with torch.cuda.stream(s):
-            solver = drot.Solver(P.m, P.n)
+            solver = solvers[k] = drot.Solver(P.m, P.n)
             for _ in range(5):
                 out[k] = pu.gpu_solve(solver, P, 300, stream=s)[1]
 
@@ -1484,6 +1499,7 @@ def test_two_threads_solve_on_two_streams(drot):
     for t in threads:
         t.join()
     assert np.array_equal(out[0], X_ref) and np.array_equal(out[1], X_ref)
+    pu.assert_held_on_the_chip(*solvers)
 
 
 @pytest.mark.parametrize("m,n,scale,forbid", [(2049, 5633, 1.0, 0.0), (3400, 3393, 3.0e4, 0.3), (5639, 2079, 1.0e-3, 0.0)])
