@@ -168,7 +168,7 @@ struct drot_handle_s {
   bool xchg_clean = false;  // no word carries a number above xchg_tag
   int* done = nullptr;
   DeviceStatus* status = nullptr;
-  CheckRecord* run_checks = nullptr;  // ... behind the status block (none in a fixed workspace)
+  CheckRecord* run_checks = nullptr;  // ... behind the status block: what checks inside a launch write
   // pinned host mirror of the status block, two slots for the pipelined residual checks, and of the block with its records
   DeviceStatus* host_status = nullptr;
   StatusBlock* host_run = nullptr;

@@ -4,7 +4,7 @@
 // ------------------------------------------------------------------------------------------
 // Problems too large for one workgroup but whose X and C fit the register files of the whole chip (8 bytes per
 // entry; 256 compute units hold 10 to 12 million entries).  One workgroup per compute unit keeps TW tiles of X and C in
-// registers from one residual check to the next, so an iteration moves no matrix at all; what is left of it is the
+// registers for all the iterations of a call, so an iteration moves no matrix at all; what is left of it is the
 // arithmetic (a microsecond) and the trip of the partial sums to whoever forms eq. (6), and of phi and varphi back.
 //
 // That trip is what bounds the kernel.  The eight L2s are not coherent with one another, so the exchanged words go

@@ -6,7 +6,8 @@
 // class x 4 CX columns -- of X and C in registers; 32 columns (CX = 8) are the slab of the single launches, 16 (CX = 4) a half of
 // one.  Sums of a row over the 32 columns, and totals of a slab, are put together from those of its SUB
 // parts in the order in which the lanes of a whole slab add them up, every column is folded by its own threads as there, so
-// the results are the same bits.
+// the results are the same bits.  (But for the norms of the
+// residuals where classes lie anywhere, and the stopping test with them: their squares are added up class by class.)
 //
 // Rows are counted class by class here (`perm`: where the rows of a class are no run), so that a slab's rows lie together in
 // the exchange.

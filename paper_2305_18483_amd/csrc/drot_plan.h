@@ -77,7 +77,10 @@ constexpr int kGridSlabLeastK = 4, kGridSlabRows = 8;
 // Shorter stretches are not worth fetching the plan and the cost for.  Per iteration, in single launches and in one launch,
 // stretches of 4, 6, 8 and 10 sweeps: 200 x 300 10.4 and 13.6 us, 8.9 and 10.1, 8.3 and 8.5, 7.9 and 7.4; 1000 x 1000 11.3
 // and 13.7, 9.9 and 10.2, 9.9 and 8.5, 9.4 and 7.5 (one tile a workgroup); 2048 x 3072 24.0 and 18.5 at 4, 64-row tiles of
-// 2300 x 2500 17.8 and 17.8, 2999 x 3307 21.3 and 21.3.
+// 2300 x 2500 17.8 and 17.8, 2999 x 3307 21.3 and 21.3.  Slabs, and point clouds of one tile a workgroup, have the line of the one
+// tile; whole calls of 4, 6 and 8 sweeps, single launches and one: point clouds 400 x 400 115 and 103 us, 145 and 115, 166 and 120;
+// slabs 1500 x 1000 193 and 178, 212 and 184, 234 and 190; 2000 x 1500, five classes in no order 268 and 250, 297 and 257, 332
+// and 262.  So their line could lie at 4, too.
 constexpr int kGridMinSweeps = 4, kGridMinSweepsOneTile = 8;
 // (a full sweep takes 230 to 260 us at 12000 x 12000, d = 32, the screened one 7 for every percent of the row segments left)
 constexpr double kPointsSparse = 0.33;
