@@ -49,6 +49,7 @@ def test_argument_validation_without_a_gpu(lib):
     assert lib.drot_set_option(None, binding.DROT_OPT_CHECK_EVERY, 10) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_set_gap_tolerance(None, 0.1) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_get_info(None, None) == binding.DROT_ERR_INVALID_ARG
+    assert lib.drot_get_launches(None, None, None, None) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_solve(None, None, None, None, 1, 1, 0.0, 0, None, 1, 0.0, None, None) == binding.DROT_ERR_INVALID_ARG
     for code in (0, 1, -1, -2, -3, -4, 99):
         assert isinstance(binding.strerror(code), str) and binding.strerror(code)
