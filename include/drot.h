@@ -143,7 +143,11 @@ int drot_destroy(drot_handle h);
  *       bounds made it read in vain have added up to the price of new ones (at most 1024 sweeps apart).  -1 screens
  *       problems of 11.5 million entries
  *       and more (smaller ones are held in registers, or stream all of C from the caches just as fast), 1 every problem
- *       the skipping applies to, k >= 2 the same with the bounds renewed at least every k-th sweep, 0 never.
+ *       the skipping applies to, k >= 2 the same with the bounds renewed at least every k-th sweep, 0 never.  Under -1, once
+ *       such a plan is known to be thin, the entries that hold something or may come to are listed and held on the
+ *       chip, and one cooperative launch iterates on those alone, listing anew as phi and varphi move (up to 20480 x 20480
+ *       on a GPU of 256 compute units, with the other options of this section at their defaults; 32 bytes of device memory per row
+ *       segment more; not where profile or a gap every few iterations is asked for).  Same bits.
  *   DROT_OPT_SKIP_COST [-1], -1/0/1: the even/odd scheme of the paper's GPU appendix (Section
  *       "Quadratically Regularized DROT"): sweeps pair up, the first of a pair stores X - rho*C, the second
  *       reads that and needs no C (20 instead of 24 bytes per element and pair).  Row and column sums are
@@ -161,7 +165,8 @@ int drot_destroy(drot_handle h);
  *       the O(m+n) update of eq. (6) at the head of the next sweep, one launch per iteration instead of
  *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations and their
  *       residual checks in one cooperative launch (4096 iterations or 256 checks at a time, in which no other launch gets onto
- *       the GPU: up to 60 ms); point clouds and group lasso that fit do the same.  0 always runs the separate kernels, a launch for
+ *       the GPU: up to 60 ms); point clouds and group lasso that fit do the same, and large sparse problems
+ *       (DROT_OPT_SCREENING).  0 always runs the separate kernels, a launch for
  *       every sweep.  Same bits.  (Larger problems over a stored cost that fit, up to 12.6 million entries, take the one launch
  *       whatever this is set to, where they are neither screened nor paired.)
  *   DROT_OPT_RESIDENT [-1], -1/0: problems of at most 128 x 256 without group lasso, from a stored cost, run

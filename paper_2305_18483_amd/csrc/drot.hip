@@ -54,6 +54,7 @@ namespace {
 #include "drot_gap.h"
 #include "drot_grid.h"
 #include "drot_grid_slab.h"
+#include "drot_active.h"
 
 // ------------------------------------------------------------------------------------------
 // host side
@@ -68,6 +69,7 @@ static_assert(plan::kSlabCols == kSlabCols && plan::kSlabLanes == kSlabLanes && 
 static_assert(plan::kResidentMaxRows == kResidentMaxRows && plan::kResidentCols == kResidentCols, "resident kernel");
 static_assert(plan::kColGroup == kColGroup, "column-sum groups of the lean sweep");
 static_assert(plan::kGridBlock == kGridBlock, "owner blocks of the grid-resident kernel");
+static_assert(plan::kActiveSide == kActSide && plan::kActiveLocal == kActLocal && plan::kActiveEntries == kActEntries, "active entries");
 static_assert(plan::kStripRows == kStripRows && plan::kPointsColGroup == kPointsColGroup, "strips of the screened point-cloud sweep");
 
 // (e0, e1: events that take the start and the end of the kernel itself, as the hardware stamps them; null: none)
@@ -89,9 +91,10 @@ void launch_slab(bool first, bool pro, int k, dim3 grid, hipStream_t stream, hip
   else launch_slab_k<false, false, MAPPED>(k, grid, stream, e0, e1, a, f);
 }
 
-// The status block with, behind it, the records of the checks that the last launch made by itself.
+// The status block with, behind it, how far the last launch of active entries came and the records of the checks that the last launch made by itself.
 struct StatusBlock {
   DeviceStatus status;
+  ActiveRecord active;
   CheckRecord checks[plan::kRunChecks];
 };
 
@@ -165,9 +168,12 @@ struct drot_handle_s {
   u64* xchg = nullptr;
   size_t xchg_len = 0;
   unsigned xchg_tag = 0;
+  float *bound = nullptr, *bound_varphi = nullptr;  // active entries: bounds by line, made on demand, and the varphi they were left against
+  size_t bound_len = 0, bound_varphi_len = 0;
   bool xchg_clean = false;  // no word carries a number above xchg_tag
   int* done = nullptr;
   DeviceStatus* status = nullptr;
+  ActiveRecord* run_active = nullptr;
   CheckRecord* run_checks = nullptr;  // ... behind the status block: what checks inside a launch write
   // pinned host mirror of the status block, two slots for the pipelined residual checks, and of the block with its records
   DeviceStatus* host_status = nullptr;
@@ -213,7 +219,7 @@ int grow_buffer(T** buf, size_t* len, size_t need, hipStream_t stream) {
 
 void free_all(drot_handle h) {
   float* fbufs[] = {h->phi, h->varphi, h->rowpart, h->colpart, h->tilesum, h->gap_part, h->gbuf, h->mprime, h->mprime2,
-                    h->varphi0, h->cpad, h->xpad, h->ptbuf, h->gpart};
+                    h->varphi0, h->cpad, h->xpad, h->ptbuf, h->gpart, h->bound, h->bound_varphi};
   double* dbufs[] = {h->a, h->b, h->theta, h->sum_p, h->r, h->s, h->part, h->resid, h->prof_counts};
   int* ibufs[] = {h->done, h->runbuf, h->chunkbuf, h->wave_reads, h->screen_ctl, h->wg_reads, h->wg_waste};
   for (float* b : fbufs) (void)hipFree(b);
@@ -363,13 +369,15 @@ void enqueue_sweep(Solve& Z, const plan::Step& Q, bool timed, hipEvent_t e0, hip
       launch_resident(RS, stream, e0, e1);
       break;
     }
-    case plan::kPoints:
-      if (Q.first) launch_timed((sweep_points_kernel<true, false>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0);
-      else if (Q.refresh && nt) launch_timed((sweep_points_kernel<false, true, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0);
-      else if (Q.refresh) launch_timed((sweep_points_kernel<false, false, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0);
-      else if (nt) launch_timed((sweep_points_kernel<false, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0);
-      else launch_timed((sweep_points_kernel<false, false>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0);
+    case plan::kPoints: {
+      float* const bound = S.active ? h->bound : nullptr;
+      if (Q.first) launch_timed((sweep_points_kernel<true, false>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0, bound);
+      else if (Q.refresh && nt) launch_timed((sweep_points_kernel<false, true, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0, bound);
+      else if (Q.refresh) launch_timed((sweep_points_kernel<false, false, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0, bound);
+      else if (nt) launch_timed((sweep_points_kernel<false, true>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0, bound);
+      else launch_timed((sweep_points_kernel<false, false>), grid, sweep_block, stream, e0, e1, A, Z.PT, h->mprime, h->mprime2, h->jstar, h->varphi0, bound);
       break;
+    }
     case plan::kPointsLean: {
       const ScreenArgs SC{h->mprime, h->mprime, h->varphi0, nullptr, h->varphi0, h->wg_reads, nullptr,
                           h->mprime2, h->mprime2, h->jstar, h->jstar, nullptr};
@@ -501,6 +509,34 @@ int cooperative_units(int device) {
 // What a solve returns inside this file where a cooperative launch was not accepted, and where one gave up waiting.
 constexpr int kGridRefused = -1001, kGridGaveUp = -1002;
 
+// An exchange buffer of `need` words, with `iters` numbers left that no word carries.
+int ready_exchange(drot_handle h, size_t need, int iters, hipStream_t stream) {
+  const size_t had = h->xchg_len;
+  const int rc = grow_buffer(&h->xchg, &h->xchg_len, need, stream);
+  if (rc == DROT_ERR_ALLOC) {
+    (void)hipGetLastError();
+    return kGridRefused;
+  }
+  if (rc != DROT_OK) return rc;
+  // (words that carry no number yet, and, should the numbers ever run out, none that carries an old one)
+  if (h->xchg_len != had || h->xchg_tag > 0xffffffffu - (unsigned)iters - 1u) h->xchg_clean = false;
+  if (!h->xchg_clean) {
+    h->xchg_tag = 0;
+    h->xchg_clean = true;
+    hipLaunchKernelGGL(fill_kernel, dim3(1024), dim3(256), 0, stream, reinterpret_cast<float*>(h->xchg), 2 * h->xchg_len, 0.f,
+                       (const int*)nullptr);
+  }
+  return DROT_OK;
+}
+
+// After a cooperative launch that was not accepted.  (A device that reports more compute units than this process or stream
+// may use, for one; what is wrong with more than the launch shows at the single launches that follow.)
+int launch_refused(drot_handle h, hipError_t e) {
+  (void)hipGetLastError();
+  if (e == hipErrorIllegalState) g_no_cooperative[h->device].store(true, std::memory_order_relaxed);
+  return kGridRefused;
+}
+
 // The sweeps first .. last of a stretch, all their vector updates and the checks of Z.check in one launch.  kGridRefused:
 // nothing has been enqueued that counts.
 int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
@@ -512,21 +548,8 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   const int iters = (int)(last.sw - first.sw) + 1;
   // (totals: groups of kColGroup tile rows for the 64-row tiles, none missing)
   const GridWords W = grid_words(S, Z.P);
-  const size_t need = 2 * W.half, had = h->xchg_len;
-  const int rc = grow_buffer(&h->xchg, &h->xchg_len, need, Z.stream);
-  if (rc == DROT_ERR_ALLOC) {
-    (void)hipGetLastError();
-    return kGridRefused;
-  }
+  const int rc = ready_exchange(h, 2 * W.half, iters, Z.stream);
   if (rc != DROT_OK) return rc;
-  // (words that carry no number yet, and, should the numbers ever run out, none that carries an old one)
-  if (h->xchg_len != had || h->xchg_tag > 0xffffffffu - (unsigned)iters - 1u) h->xchg_clean = false;
-  if (!h->xchg_clean) {
-    h->xchg_tag = 0;
-    h->xchg_clean = true;
-    hipLaunchKernelGGL(fill_kernel, dim3(1024), dim3(256), 0, Z.stream, reinterpret_cast<float*>(h->xchg), 2 * h->xchg_len, 0.f,
-                       (const int*)nullptr);
-  }
   GridArgs A{};
   A.S = Z.SA;
   A.S.rowpart = Z.rowp(last.sw);
@@ -604,14 +627,83 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
       default: e = launch_grid<16, 16, 2, 5, 2, 1>(A, wgs, Z.stream); break;
     }
   }
-  // (a device that reports more compute units than this process or stream may use, for one; what is wrong with more than
-  // the launch shows at the single launches that follow)
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    if (e == hipErrorIllegalState) g_no_cooperative[h->device].store(true, std::memory_order_relaxed);
-    return kGridRefused;
+  return e == hipSuccess ? DROT_OK : launch_refused(h, e);
+}
+
+// Up to `iters` iterations on the active entries, with their vector updates and the checks of Z.check, from the state in
+// memory on.  kGridRefused: nothing has been enqueued that counts.
+int enqueue_active(Solve& Z, int iters) {
+  drot_handle h = Z.h;
+  const plan::Static& S = Z.S;
+  const long long now = Z.T.k_base + Z.T.k;
+  const int nblk_m = ceil_div(Z.m, kGridBlock), nblk_n = ceil_div(Z.n, kGridBlock);
+  const int ngroups = ceil_div(Z.m, 256);
+  const size_t nblk = (size_t)nblk_m + (size_t)nblk_n;
+  const size_t ent = nblk * kActSide * kGridBlock, tot = (ent + nblk * kGridBlock + 31) / 32 * 32;
+  const size_t sq = tot + (size_t)kActWgs * kActTotals;
+  const size_t cst = (sq + nblk * kActSquares + 31) / 32 * 32, half = cst + 32 * kGridCopies;
+  h->xchg_clean = false;  // (this launch starts from zeroed words, and leaves others than the next one of any kind may find)
+  const int rc = ready_exchange(h, 2 * half, iters, Z.stream);
+  h->xchg_clean = false;
+  if (rc != DROT_OK) return rc;
+  ActiveArgs A{};
+  A.S = Z.SA;
+  A.S.rowpart = Z.rowp(now);
+  A.points = Z.PT;
+  A.p = Z.p;
+  A.q = Z.q;
+  A.a_in = Z.a_buf(now);
+  A.b_in = Z.b_buf(now);
+  A.a_alt = Z.a_buf(now + 1);
+  A.b_alt = Z.b_buf(now + 1);
+  A.theta_in = h->theta + (now & 1);
+  A.theta_alt = h->theta + ((now + 1) & 1);
+  A.sum_p = h->sum_p;
+  A.status = h->status;
+  A.done = h->done;
+  A.record = h->run_active;
+  A.xchg = h->xchg;
+  A.half_words = (unsigned)half;
+  A.ent_word = (unsigned)ent;
+  A.tot_word = (unsigned)tot;
+  A.sq_word = (unsigned)sq;
+  A.cst_word = (unsigned)cst;
+  A.nseg = S.nseg;
+  A.ngroups = ngroups;
+  A.nblk_m = nblk_m;
+  A.nblk_n = nblk_n;
+  A.iters = iters;
+  A.tag0 = h->xchg_tag + 1;
+  h->xchg_tag += (unsigned)iters;
+  A.polls = h->grid_polls;
+  A.check = Z.check;
+  A.phi_out = h->phi;
+  A.varphi_out = h->varphi;
+  A.r = h->r;
+  A.s = h->s;
+  // the newer bounds: those the last launch of this kind left, or those of the last sweep that recorded some
+  const bool left = Z.T.bound_gen >= Z.T.epoch_gen;
+  A.bound = h->bound;
+  A.bound_varphi = h->bound_varphi;
+  A.since = left ? h->bound_varphi : h->varphi0;
+  if (!left && !Z.P.from_points) {
+    A.m1 = h->mprime;
+    A.codes = h->codes;
   }
-  return DROT_OK;
+  if (!Z.P.from_points) {
+    A.lines = h->xlines;
+    A.lines_known = Z.T.lines_gen == now ? 1 : 0;
+  }
+  const long long age = now - (left ? Z.T.bound_gen : Z.T.epoch_gen);
+  A.age = age > 0 ? (int)age : 1;
+  A.target = plan::kActiveTarget;
+  // (phi and varphi, of masses that add up to 1, rise by some 10 / (m + n)^2 together in an iteration, whatever the costs' size)
+  A.tau0 = 10.f * (float)plan::kActiveTarget / ((float)(Z.m + Z.n) * (float)(Z.m + Z.n));
+  void* args[] = {&A};
+  const void* kernel = Z.P.from_points ? reinterpret_cast<const void*>(grid_active_kernel<true>)
+                                       : reinterpret_cast<const void*>(grid_active_kernel<false>);
+  const hipError_t e = hipLaunchCooperativeKernel(kernel, dim3(kActWgs), dim3(kActThreads), args, 0, Z.stream);
+  return e == hipSuccess ? DROT_OK : launch_refused(h, e);
 }
 
 // The vector update (S5) that completes the state in memory after sweep Q.sw.
@@ -879,6 +971,11 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   Z.S = plan::make_static(P, Z.O);
   // (a fixed workspace does not grow)
   if (A.fixed_schedule && Z.S.grid_tiles && 2 * grid_words(Z.S, P).half > h->xchg_len) P.single_launches = true;
+  if (Z.S.active && (grow_buffer(&h->bound, &h->bound_len, 8 * (size_t)Z.S.nseg * (size_t)(ceil_div(m, 64) * 64), stream) != DROT_OK ||
+                     grow_buffer(&h->bound_varphi, &h->bound_varphi_len, (size_t)n, stream) != DROT_OK)) {
+    (void)hipGetLastError();
+    Z.S.active = false;
+  }
   Z.T = plan::start_state(Z.S, P, h->carry);
   const plan::Static& S = Z.S;
 
@@ -1004,6 +1101,38 @@ int iterate(Solve& Z, bool* converged_out) {
     return DROT_OK;
   };
   while (Z.T.k < Z.P.max_iters && !converged) {
+    if (plan::active_next(S, Z.P, Z.T)) {
+      if (checks > 0) {  // (what the launches check by check have left to read comes first)
+        const int rc = read_status(slot ^ 1);
+        if (rc != DROT_OK) return rc;
+        checks = 0;
+        if (converged) break;
+      }
+      const int chunk = plan::active_stretch(Z.P, Z.O, Z.T).chunk, every = Z.O.check_every;
+      const int to_check = every - Z.T.k % every, first = (to_check < chunk ? to_check : chunk) - 1;
+      const int most = 1 + ceil_div(chunk - 1 - first, every);
+      Z.check = CheckArgs{h->run_checks, h->status, h->resid, h->done, (double)Z.tol, first, every, Z.T.k};
+      const int rc = enqueue_active(Z, chunk);
+      Z.check = CheckArgs{};
+      if (rc == kGridRefused) {
+        ++h->launches_refused;
+        Z.P.single_launches = true;
+        h->compute_units = 0;
+        continue;
+      }
+      if (rc != DROT_OK) return rc;
+      ++h->launches_accepted;
+      DROT_HIP(hipMemcpyAsync(h->host_run, h->status, offsetof(StatusBlock, checks) + sizeof(CheckRecord) * (size_t)most,
+                              hipMemcpyDeviceToHost, stream));
+      DROT_HIP(hipStreamSynchronize(stream));
+      if (h->host_run->status.broken) return kGridGaveUp;
+      const int ran = h->host_run->active.iters;
+      const int made = ran >= chunk ? most : ran > first ? 1 + (ran - 1 - first) / every : 0;
+      converged = record_run(h, h->host_run->checks, made);
+      plan::active_done(Z.T, Z.P, ran, h->host_run->active.why != kActDone);
+      if (ran == chunk || converged) Z.tested_k = Z.T.k;
+      continue;
+    }
     plan::Stretch R = plan::next_stretch(S, Z.P, Z.O, Z.T);
     bool run = plan::runs_through_checks(S, Z.P, Z.O);  // (the launch makes the checks)
     if (run) {
@@ -1285,6 +1414,7 @@ size_t carve_static(drot_handle_s& H, unsigned char* base) {
   StatusBlock* block = nullptr;
   take(&block, 1);
   H.status = block ? &block->status : nullptr;
+  H.run_active = block ? &block->active : nullptr;
   H.run_checks = block ? block->checks : nullptr;
   // (the largest grid-resident problem here has 2048 rows: 1024 tiles of 32 rows)
   H.xchg_len = 2 * ((size_t)2048 * nseg + (size_t)ceil_div(2048, kTileRows) * N + 2 * (M + N) + 4096);
@@ -1435,9 +1565,10 @@ int drot_create(drot_handle* out, int max_m, int max_n) {
   take(dev_alloc(&block, 1));
   if (block) {
     h->status = &block->status;
+    h->run_active = &block->active;
     h->run_checks = block->checks;
   }
-  static_assert(offsetof(StatusBlock, status) == 0 && sizeof(DeviceStatus) % alignof(StatusBlock) == 0, "one allocation each");
+  static_assert(offsetof(StatusBlock, status) == 0 && 2 * sizeof(DeviceStatus) % alignof(StatusBlock) == 0, "one allocation each");
   if (rc == DROT_OK &&
       hipHostMalloc(reinterpret_cast<void**>(&h->host_status), 2 * sizeof(DeviceStatus) + sizeof(StatusBlock)) != hipSuccess) {
     h->host_status = nullptr;

@@ -54,6 +54,10 @@
 typedef unsigned long long u64;
 constexpr int kGridPolls = 1 << 25;
 constexpr int kGridPollsMax = 1 << 30;
+// Attempts without a rest.  A word on its way can be held up for as long as every wave on the GPU asks without one: with 4000 waves
+// waiting for the answer of a check, the words of one owner out of 2500 did not reach the memory-side cache in 300000
+// attempts (a third of a second), one check in ten, and in none of hundreds once the waves rest between attempts.
+constexpr int kGridPatience = 32, kGridRest = 64;  // (rest: 4096 cycles, 1.7 us)
 constexpr int kGridBlock = 8;    // rows or columns per owner wave
 constexpr int kGridCopies = 32;  // of 2 eta - theta: workgroup b reads copy b % kGridCopies
 
@@ -138,8 +142,8 @@ __device__ __forceinline__ int lane_again() {
 
 // Fetches the words at[0 .. N-1] until every lane has all of its own with the number `tag`.  All of them are asked for
 // again together: a word waited for by itself would cost a trip to the memory-side cache each.  PAUSE: between two
-// attempts, in units of 64 cycles.
-template <int N, int PAUSE = 0>
+// attempts, in units of 64 cycles.  REST: and a long one once kGridPatience attempts have been in vain.
+template <int N, int PAUSE = 0, bool REST = false>
 __device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const unsigned (&at)[N], unsigned tag, int limit, bool& lost) {
   for (int polls = 1;; ++polls) {
     bool there = true;
@@ -152,7 +156,8 @@ __device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const 
       lost = true;
       return;
     }
-    if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
+    if (REST && polls >= kGridPatience) __builtin_amdgcn_s_sleep(kGridRest);
+    else if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
   }
 }
 

@@ -20,6 +20,7 @@
 //   Points      cost recomputed from point clouds on the matrix cores (32-row tiles); with `refresh` it
 //               also records the screening bounds
 //   PointsLean  the same cost for the rows a certificate does not cover only (256-row strips)
+//   (Active     entries that hold something or may come to, listed and kept on the chip: many iterations in one launch)
 //   Slab        group lasso, a whole class x 32 columns resident in one workgroup
 //   TwoPass     group lasso, any labels: norms first, then the scaled update
 //
@@ -84,6 +85,12 @@ constexpr int kGridSlabLeastK = 4, kGridSlabRows = 8;
 constexpr int kGridMinSweeps = 4, kGridMinSweepsOneTile = 8;
 // (a full sweep takes 230 to 260 us at 12000 x 12000, d = 32, the screened one 7 for every percent of the row segments left)
 constexpr double kPointsSparse = 0.33;
+// Active entries (drot_active.h): 16 x 16 workgroups of at most kActiveLocal groups of 256 rows and segments of 256 columns
+constexpr int kActiveSide = 16, kActiveLocal = 5;
+constexpr int kActiveEntries = 4096;   // ... and so many entries each
+constexpr double kActiveFill = 0.6;    // of them, on average, from the lines (point clouds: row segments) that hold something
+constexpr int kActiveLeast = 16;       // shorter calls are not worth a list
+constexpr int kActiveTarget = 48;      // iterations a list is meant to last
 constexpr int kPromptLooksUntil = 128; // ... of which the host waits for those of a point-cloud solve until the plan is sparse
 constexpr int kEarlyLooksUntil = 512;  // cold starts: extra density readings over this many iterations
 
@@ -146,6 +153,8 @@ struct Carry {
   bool lines_valid = false;      // the same for the lean sweep's line flags
   bool by_lines = false;         // the plan has thinned out enough for the lean sweep
   bool drift_valid = false;      // the last vector update left the drift of varphi for it
+  double lines = -1.0;           // fraction of nonzero lines last reported
+  long long bound_gen = -1;      // iteration whose varphi the bounds by line that a launch of active entries left are against
   long long iters_done = 0;
 };
 
@@ -161,6 +170,7 @@ struct Static {
   bool small_slab = false, small = false, fused = false;
   bool can_pair = false, adaptive_pairs = false, may_screen = false, adaptive = false;
   bool points_screen = false;    // point-cloud variant: screened sweeps once the plan is known to be sparse
+  bool active = false;           // active entries once the plan is known to be sparse
   int refresh_max = kMaxRefreshPeriod;
   bool lean_fits = false;        // the rows of a tile of the lean sweep are within 32 bits of bytes from its first one
   bool early_lines = false;      // the lean sweep does not wait for a sparse plan
@@ -256,6 +266,11 @@ inline Static make_static(const Problem& P, const Options& O) {
   // (offsets of 32 bits within a tile: rows of up to 16.7 million columns; wider ones stay with the 8-wave tiles)
   S.lean_fits = (size_t)kTallTileRows * 4 * (size_t)S.ld_pad <= 0xffffffffu;
   S.early_lines = S.lean_fits && P.line_bounds && S.may_screen && (size_t)m * (size_t)n >= kScreenFrom;
+  // (one workgroup per compute unit; the option that asks for the vector update in a launch of its own keeps a call off
+  // launches that hold every compute unit, here as elsewhere)
+  S.active = units >= kActiveSide * kActiveSide && O.fused_update != 0 && O.screening == -1 && P.feedback && O.gap_every < 1 &&
+             (S.early_lines || S.points_screen) && S.nseg <= kActiveSide * kActiveLocal &&
+             ceil_div(m, 256) <= kActiveSide * kActiveLocal;
   if (S.early_lines) S.pairs_until = 0.995;  // (the sweep by lines waits: whatever does not start the pairs ends them)
   S.refresh_max = O.screening >= 2 ? O.screening : kMaxRefreshPeriod;
   S.sums_strip = P.slab_k ? kSlabCols : kSegCols;
@@ -276,6 +291,11 @@ struct State {
   bool by_lines = false;         // the lean sweep may run (with line bounds): two epochs of bounds, or a sparse plan reported
   long long drift_gen = -1;      // sweep whose vector update left the drift of varphi since the epoch of the bounds
   bool dense_lines = false;      // ... but the last status found most lines nonzero
+  double lines = -1.0;           // fraction of nonzero lines the last status that counted them reported
+  long long bound_gen = -1;      // iteration whose varphi the bounds by line that a launch of active entries left are against
+  int active_from = 0;           // no such launch before this iteration of the call
+  int active_left = 0;           // launches of them that ended early
+  bool active_ran = false;
   bool last_lean = false;        // the sweep before the next status is a lean one
   bool materialized = true;      // phi, varphi, a, b, theta in memory are complete for the sweeps done
   bool norms_pending = false;    // the last vector update left the residual norms as per-workgroup sums
@@ -295,6 +315,8 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
   // the warm start's sums are those of 256-column segments)
   T.sums_gen = P.warm ? (P.slab_k ? -1 : 0)
                       : (P.resume && carry.sums_valid && carry.sums_strip == S.sums_strip) ? T.k_base : -1;
+  T.lines = P.resume ? carry.lines : -1.0;
+  T.bound_gen = bounds_hold ? carry.bound_gen : -1;
   T.lines_gen = (P.resume && carry.lines_valid && T.sums_gen >= 0) ? T.k_base : -1;
   T.epoch_gen = bounds_hold ? carry.epoch_gen : -1;
   T.refresh_period = bounds_hold ? carry.refresh_period : S.early_lines ? kFirstPeriodLines : kFirstRefreshPeriod;
@@ -332,7 +354,8 @@ inline Stretch next_stretch(const Static& S, const Problem& P, const Options& O,
       // become sparse costs 10 ms of 44 at 12000 x 12000, waiting 10 us a look)
       const bool often = P.from_points && k < kPromptLooksUntil && !(T.plan_density >= 0.0 && T.plan_density < kPointsSparse);
       const int next = k < 16 ? 16 : often ? (k / 8 + 1) * 8 : (k / 32 + 1) * 32;
-      R.prompt = often;
+      // (and where the active entries could be listed: a sweep by lines takes three times an iteration of theirs)
+      R.prompt = often || (S.active && !P.single_launches && !P.from_points && !T.active_ran && next <= kPromptLooksUntil);
       if (next - k < R.chunk) {
         R.chunk = next - k;
         R.probe = true;
@@ -545,6 +568,46 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
   return R.chunk - head >= least ? head : -1;
 }
 
+// Whether the next iterations run on the active entries: the plan is known to be thin enough, X in memory is plain, its
+// flags and the screening bounds describe it, and the call is not about to end.
+inline bool active_next(const Static& S, const Problem& P, const State& T) {
+  if (!S.active || P.single_launches || T.k < T.active_from || P.max_iters - T.k < kActiveLeast) return false;
+  const long long now = T.k_base + T.k;
+  if (!T.materialized || T.dense_plan || T.sums_gen != now || T.epoch_gen < 0 || T.epoch_gen > now) return false;
+  const double room = kActiveFill * (double)kActiveEntries * (kActiveSide * kActiveSide);
+  if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kPointsSparse && T.plan_density * P.m * S.nseg <= room;
+  return T.by_lines && !T.dense_lines && T.lines >= 0.0 && T.lines * P.m * ceil_div(P.n, 32) <= room;
+}
+
+// ... the iterations it may take: up to a check or the end of the call, drawn out over the checks that follow.
+inline Stretch active_stretch(const Problem& P, const Options& O, const State& T) {
+  Stretch R;
+  R.chunk = P.max_iters - T.k;
+  const int to_check = O.check_every - T.k % O.check_every;
+  if (to_check < R.chunk) R.chunk = to_check;
+  return draw_out(P, O, T, R);
+}
+
+// ... and it has come back, `iters` iterations later.  left: the entries no longer fit (or never did): the sweeps take over for
+// a while, longer every time.
+inline void active_done(State& T, const Problem& P, int iters, bool left) {
+  T.k += iters;
+  T.active_ran = true;
+  const long long now = T.k_base + T.k;
+  T.sums_gen = now;
+  if (!P.from_points && iters > 0) T.lines_gen = now;
+  T.bound_gen = now;
+  if (iters > 0) {
+    T.drift_gen = -1;
+    T.norms_pending = false;
+    T.last_lean = false;
+  }
+  if (left) {
+    T.active_from = T.k + (512 << (T.active_left < 6 ? T.active_left : 6));
+    ++T.active_left;
+  }
+}
+
 // A status has come back: the density of the plan it reports steers the next stretches
 // (hysteresis; the early looks never start the pairs: every plan is dense in its first iterations; where the sweep by lines
 // waits they end them below 99.5 %, the checks, which see the same number, where they would not start them).  Above 90 % of the row
@@ -556,6 +619,7 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
 inline void on_status(const Static& S, State& T, double density, double lines, bool was_probe) {
   if (!S.adaptive) return;
   T.plan_density = density;
+  if (lines >= 0.0) T.lines = lines;
   if (lines >= 0.0) T.dense_lines = lines > 0.92 && (T.dense_lines || !was_probe);
   else if (density < 0.995) T.dense_lines = false;  // (independent lines: 0.995 of the row segments are half of the lines)
   const bool dense = lines >= 0.0 ? lines > 0.85 : density > 0.9;
@@ -572,6 +636,8 @@ inline Carry finish(const Static& S, const Problem& P, const State& T, bool conv
   C.dense_plan = T.dense_plan;
   C.plan_density = T.plan_density;
   C.by_lines = T.by_lines;
+  C.lines = T.lines;
+  C.bound_gen = (converged || T.bound_gen > T.k_base + (long long)iters) ? -1 : T.bound_gen;
   C.drift_valid = !converged && epoch_kept && P.max_iters > 0 && T.drift_gen == T.k_base + T.k;
   C.epoch_gen = (converged || !epoch_ran) ? -1 : T.epoch_gen;
   C.refresh_period = (converged || !epoch_ran) ? kFirstRefreshPeriod : T.refresh_period;

@@ -173,6 +173,46 @@ void drot_renewals(int count, const int* waste, int price, int max_since, unsign
   }
 }
 
+// Active entries: problem, options as in drot_plan_trace.  state[7]: iterations of the call so far, density and lines reported
+// * 1e6 (negative: none), by_lines, generation of the bounds (negative: none), launches that ended early, iterations since the
+// last of them.  out[3]: iterations of a launch now (0: none), and if it ends early after 10: before which iteration of the call no
+// other starts, launches that ended early.  Returns whether the call could ever take one.
+int drot_plan_active(const int* problem, const int* options, int compute_units, int single_launches, const int* state, int* out) {
+  Problem P;
+  P.m = problem[0];
+  P.n = problem[1];
+  P.reg_kind = problem[2];
+  P.from_points = problem[3] != 0;
+  P.feedback = problem[11] != 0;
+  P.checking = problem[12] != 0;
+  P.max_iters = problem[13];
+  P.line_bounds = true;
+  P.compute_units = compute_units;
+  P.single_launches = single_launches != 0;
+  Options O;
+  O.check_every = options[0];
+  O.fused_update = options[2];
+  O.skip_cost = options[3];
+  O.skip_unchanged = options[4];
+  O.screening = options[5];
+  O.gap_every = options[8];
+  const Static S = make_static(P, O);
+  State T = start_state(S, P, Carry{});
+  T.k = state[0];
+  T.sums_gen = state[0];
+  T.plan_density = state[1] * 1e-6;
+  T.lines = state[2] * 1e-6;
+  T.by_lines = state[3] != 0;
+  T.epoch_gen = state[4];
+  T.active_left = state[5];
+  T.active_from = state[5] ? state[0] - state[6] + (512 << (state[5] - 1)) : 0;
+  out[0] = active_next(S, P, T) ? active_stretch(P, O, T).chunk : 0;
+  active_done(T, P, 10, true);
+  out[1] = T.active_from;
+  out[2] = T.active_left;
+  return S.active;
+}
+
 // Grid-resident stretches: problem, options as in drot_plan_trace.  out[4]: tiles per workgroup (0: none), rows per tile,
 // sweeps launched one by one at the head of the first stretch (-1: all of them), automatic even/odd pairs.
 void drot_plan_grid(const int* problem, const int* options, int compute_units, int single_launches, int* out) {

@@ -103,12 +103,13 @@ __device__ __forceinline__ void points_tile(const PointArgs& Pt, float (*__restr
 // REFRESH: the sweep also records, per row segment, the largest of varphi_j - rho C_ij, a column that attains
 // it and the largest of the others, and stores its varphi as the epoch's varphi0: the bounds the screened sweep
 // below certifies zero row segments with (same definition and use as in the stored-cost screening).
-// mprime, mprime2, jstar: [nseg][m]; varphi0: padded like varphi.
+// mprime, mprime2, jstar: [nseg][m]; varphi0: padded like varphi.  bound (or null): [nseg][mp][8], the largest of each line of
+// 32 columns, for the active entries (drot_active.h).
 template <bool FIRST, bool NT, bool REFRESH = false>
 __global__ __launch_bounds__(64 * kSweepWaves) void sweep_points_kernel(SweepArgs A, PointArgs Pt, float* __restrict__ mprime,
                                                                         float* __restrict__ mprime2,
                                                                         unsigned char* __restrict__ jstar,
-                                                                        float* __restrict__ varphi0) {
+                                                                        float* __restrict__ varphi0, float* __restrict__ bound) {
   if (*A.done) return;
   __shared__ float dots[kTileRows][kDotPitch];
   constexpr int U = kSweepRows;
@@ -187,6 +188,10 @@ __global__ __launch_bounds__(64 * kSweepWaves) void sweep_points_kernel(SweepArg
           mkeep = (lane == u) ? mm : mkeep;
           m2keep = (lane == u) ? mm2 : m2keep;
           jkeep = (lane == u) ? jj : jkeep;
+          if (bound) {
+            const float top = line_max(t);
+            if ((lane & 7) == 0) bound[8 * ((size_t)seg * A.mp + r0 + u) + (lane >> 3)] = top;
+          }
         }
       }
     }

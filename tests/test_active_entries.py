@@ -1,0 +1,144 @@
+"""Large sparse problems on the entries that hold something or may come to: the bits of the sweeps over everything."""
+import numpy as np
+import pytest
+import torch
+
+import drot_inputs
+
+from . import parity_utils as pu
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(f"[gpu-active] {msg}", flush=True)
+
+
+@pytest.fixture(scope="module")
+def drot():
+    import paper_2305_18483_amd as drot_mod
+
+    drot_mod.load_library()
+    assert torch.cuda.is_available()
+    return drot_mod
+
+
+def _checks(solver):
+    return [(c.iters, c.r_row, c.r_col) for c in solver.checks()]
+
+
+def _both(drot, m, n, solve, launches=1, check_every=100):
+    """solve(solver) -> tuple of arrays and numbers, with the default options and with every sweep in a launch of its own."""
+    out = []
+    for fused in (-1, 0):
+        solver = drot.Solver(m, n, check_every=check_every)
+        solver.set_fused_update(fused)
+        out.append(solve(solver) + (_checks(solver),))
+        accepted, refused, given_up = solver.cooperative_launches()
+        assert refused == 0 and given_up == 0
+        assert (accepted >= launches) if fused else accepted == 0, accepted
+        solver.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b) if isinstance(a, np.ndarray) else a == b
+    return out[0]
+
+
+# 256-row groups and 256-column segments: one entry more than a whole number of them, and one less; fewer of either than there
+# are rows and columns of workgroups; as many as a workgroup holds; pairs forbidden, costs far above and below 1
+@pytest.mark.parametrize("m,n,kind,scale,forbid", [(3585, 3329, 1, 1.0, 0.0), (3839, 4095, 0, 1.0, 0.3), (2049, 5633, 1, 3.0e4, 0.0),
+                                                   (2049, 20480, 1, 1.0, 0.0), (20480, 577, 0, 1.0, 0.0), (12289, 1000, 1, 1.0e-3, 0.1)])
+def test_active_entries_change_no_bit(drot, m, n, kind, scale, forbid):
+    P = drot_inputs.with_entrywise_terms(drot_inputs.random_problem(m, n, seed=4100 + m, d=5, reg_kind=kind, lam=0.01), seed=4101, forbid_frac=forbid)
+    P.C = (P.C * np.float32(scale)).astype(np.float32)
+
+    def solve(solver):
+        solver.set_skip_cost(0)
+        res, X, phi, varphi = pu.gpu_solve(solver, P, 330, tol=1e-12, stepsize=float(P.rho) / scale)
+        assert res.iters == 330
+        return X, phi, varphi, res.objective, res.gap, res.r_row, res.r_col
+
+    _say(f"stored cost {m}x{n}, kind {kind}, costs up to {scale:g}, forbidden {forbid:g}")
+    _both(drot, m, n, solve)
+
+
+@pytest.mark.parametrize("m,n,d", [(3585, 3329, 2), (3400, 4097, 17), (1200, 9729, 3)])
+def test_active_entries_of_point_clouds_change_no_bit(drot, m, n, d):
+    P = drot_inputs.random_problem(m, n, seed=4200 + m, d=d, reg_kind=1, lam=0.001)
+    dev = torch.device("cuda:0")
+    xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
+    scale = 1.0 / float((torch.cdist(xs, xt) ** 2).max())
+
+    def solve(solver):
+        res = solver.solve_points(xs, xt, scale, p, q, reg_kind=1, lam=P.lam, max_iters=330, tol=1e-12)
+        phi, varphi = solver.duals(m, n, dev)
+        return res.X.cpu().numpy(), phi.cpu().numpy(), varphi.cpu().numpy(), res.objective, res.gap, res.r_row, res.r_col
+
+    _say(f"point clouds {m}x{n}, d = {d}")
+    _both(drot, m, n, solve)
+
+
+def test_active_entries_across_calls_starts_and_stops(drot):
+    m, n = 4000, 3900
+    P = drot_inputs.random_problem(m, n, seed=4300, d=4, reg_kind=1, lam=0.01)
+    dev = torch.device("cuda:0")
+    C, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.p, P.q))
+    kw = dict(reg_kind=1, lam=P.lam)
+
+    def continued(solver):  # calls that go on where the last one ended, one of them too short for a list of its own
+        X = torch.empty(m, n, device=dev)
+        out = []
+        for k in (200, 5, 130, 16, 300):
+            res = solver.solve(C, p, q, X_out=X, max_iters=k, tol=1e-12, **kw)
+            solver.set_continue(True)
+            out += [res.X.cpu().numpy(), res.objective, res.r_row]
+        solver.set_continue(False)
+        return tuple(out)
+
+    _say("continued calls")
+    cut = _both(drot, m, n, continued, launches=4, check_every=50)
+    whole = _both(drot, m, n, lambda s: (s.solve(C, p, q, max_iters=651, tol=1e-12, **kw).X.cpu().numpy(),), check_every=50)
+    assert np.array_equal(cut[-4], whole[0])
+
+    def warm(solver):  # from potentials and a plan of another problem, then without a tolerance
+        X = torch.from_numpy(whole[0]).to(dev) * 0.5
+        res = solver.solve(C, p, q, X_out=X, phi0=torch.full((m,), 1e-5, device=dev), varphi0=torch.zeros(n, device=dev), max_iters=260, tol=1e-12, **kw)
+        first = res.X.cpu().numpy()
+        return first, solver.solve(C, p, q, max_iters=270, **kw).X.cpu().numpy()
+
+    _say("warm start, no tolerance")
+    _both(drot, m, n, warm, launches=2)
+
+    probe = drot.Solver(m, n, check_every=10)
+    probe.solve(C, p, q, max_iters=400, tol=1e-12, **kw)
+    stop = max(probe.checks()[25].r_row, probe.checks()[25].r_col) * 1.0001
+
+    def stopped(solver):  # at a check inside the launch, and on from there
+        res = solver.solve(C, p, q, max_iters=4000, tol=stop, **kw)
+        assert res.converged and 100 <= res.iters <= 260
+        X, iters = res.X.cpu().numpy(), res.iters
+        solver.set_continue(True)
+        res = solver.solve(C, p, q, X_out=res.X, max_iters=150, tol=1e-12, **kw)
+        return X, iters, res.X.cpu().numpy(), res.r_row
+
+    _say(f"stops at a residual of {stop:.3e}")
+    _both(drot, m, n, stopped, launches=2, check_every=10)
+
+
+def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot):
+    # row i holds its mass near column i: the workgroups on the diagonal of 16 x 16 have sixteen times their part of the entries, and
+    # a quadratic term of middling strength keeps dozens of them in every row
+    m = n = 6000
+    x = np.linspace(0.0, 1.0, m, dtype=np.float32)
+    P = drot_inputs.random_problem(m, n, seed=4400, d=2, reg_kind=1, lam=6.0)
+    P.C = np.ascontiguousarray((x[:, None] - x[None, :]) ** 2)
+    dev = torch.device("cuda:0")
+    C, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.p, P.q))
+
+    def solve(solver):
+        solver.set_skip_cost(0)
+        res = solver.solve(C, p, q, reg_kind=1, lam=6.0, max_iters=420, tol=1e-12)
+        return res.X.cpu().numpy(), res.objective, res.r_row
+
+    _say("a band of entries")
+    X = _both(drot, m, n, solve, launches=0)[0]
+    assert (X > 0).sum() > m

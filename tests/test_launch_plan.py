@@ -607,3 +607,41 @@ def test_launches_of_calls_without_checks_are_bounded_where_sweeps_were_launches
         # (single launches need no bound)
         assert stretch(1500, 1000, 100000, units=0, **kw) == 100000 and stretch(1500, 1000, 100000, fused_update=0, **kw) == 100000
     assert stretch(1500, 1000, 100000) == 100000
+
+
+def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
+    def active(m, n, k=32, iters=1000, density=0.3, lines=0.03, by_lines=1, epoch=8, left=0, ago=0, units=256, single=0, reg_kind=1,
+               from_points=0, feedback=1, check_every=100, fused_update=-1, skip_cost=-1, skip_unchanged=-1, screening=-1, gap_every=0):
+        problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, 0, 0, 0, 1, 1, 0, 0, feedback, 1, iters)
+        options = (ctypes.c_int * 9)(check_every, -1, fused_update, skip_cost, skip_unchanged, screening, -1, 0, gap_every)
+        state = (ctypes.c_int * 7)(k, int(density * 1e6), int(lines * 1e6), by_lines, epoch, left, ago)
+        out = (ctypes.c_int * 3)()
+        ever = planlib.drot_plan_active(problem, options, units, single, state, out)
+        return ever, tuple(out)
+
+    # runs on through the checks, 4096 iterations or 256 checks at a time
+    assert active(10000, 10000) == (1, (968, 42 + 512, 1))
+    assert active(10000, 10000, iters=100000)[1][0] == 68 + 4000
+    assert active(10000, 10000, k=30, iters=1000, check_every=1)[1][0] == 256
+    # sizes: 80 segments of 256 columns and groups of 256 rows at most, 11.5 million entries at least
+    assert active(20480, 20480)[0] == 1 and active(20481, 1000)[0] == 0 and active(1000, 20481)[0] == 0
+    assert active(3396, 3397)[0] == 1 and active(3396, 3396)[0] == 0 and active(2049, 20480)[0] == 1 and active(600, 20480, from_points=1)[0] == 1
+    assert active(2048, 16384)[0] == 0 and active(2049, 16384)[0] == 1  # (few enough rows for the vector update to ride on the sweep)
+    # who asks for something else, or where the host does not look
+    for other in (dict(units=255), dict(fused_update=0), dict(skip_cost=1), dict(skip_unchanged=0), dict(screening=0), dict(screening=1),
+                  dict(gap_every=1), dict(feedback=0), dict(reg_kind=2)):
+        assert active(10000, 10000, **other) == (0, (0, 42 + 512, 1)), other
+    assert active(10000, 10000, single=1)[1][0] == 0
+    # not before the plan is known to be thin (0.6 of the room for entries, on average), nor without bounds, nor for the last few
+    room = 0.6 * 4096 * 256
+    for m, n in ((10000, 10000), (20000, 20000), (4000, 4000)):
+        lines = m * -(-n // 32)
+        assert active(m, n, lines=0.99 * min(1.0, room / lines))[1][0] > 0
+        assert room > lines or active(m, n, lines=1.01 * room / lines)[1][0] == 0
+        assert active(m, n, lines=-1.0)[1][0] == 0 and active(m, n, by_lines=0)[1][0] == 0 and active(m, n, epoch=-1)[1][0] == 0
+        assert active(m, n, iters=48)[1][0] == 16 and active(m, n, iters=47)[1][0] == 0
+        assert active(m, n, from_points=1, lines=-1.0, by_lines=0)[1][0] > 0
+        assert active(m, n, from_points=1, density=0.34)[1][0] == 0 and active(m, n, from_points=1, density=-1.0)[1][0] == 0
+    # one that ended early is not tried again at once, and later every time
+    assert active(10000, 10000, k=200, left=1, ago=511)[1][0] == 0 and active(10000, 10000, k=200, left=1, ago=512)[1] == (800, 210 + 1024, 2)
+    assert active(10000, 10000, k=900, left=3, ago=2047)[1][0] == 0 and active(10000, 10000, k=900, left=3, ago=2048)[1][0] == 100
