@@ -34,8 +34,8 @@
 // What bounds it: the two hops (a number published by one workgroup is with another 1.2 to 1.5 us later), the slowest workgroup's
 // sweep and sums (2 to 4 us: chains of lane exchanges, and entries are not spread evenly), and the keeper's sum of the totals
 // (1.5 us, 2.7 at 20000 x 20000).  An iteration and calls, in place of sweeps launched one by one: 10000 x 10000 (1000 iterations)
-// 10 for 20 us, 20.5 -> 14.6 ms; 20000 x 20000 (500) 11.5 for 18 and more, 24.6 -> 18.6; point clouds of 12000 (500, d = 32) 9.5 for 45,
-// 31.1 -> 15.0, of 4001 x 3999 (400) 33.2 -> 7.8.  A list takes 75 to 150 us.
+// 10 for 20 us, 20.5 -> 13.7 ms; 20000 x 20000 (500) 11.5 for 18 and more, 24.6 -> 18.8; point clouds of 12000 (500, d = 32) 9.5 for 45,
+// 31.1 -> 14.9, of 4001 x 3999 (400) 33.2 -> 5.0.  A list takes 75 to 150 us.
 // Waiting: a workgroup that polls without a rest can keep another's write from being seen for as long as it polls, so polls that
 // have failed 32 times rest in between (kGridRest).
 // ------------------------------------------------------------------------------------------
@@ -479,8 +479,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
   int since_list = 0, lists = 0;
   // Iterations that a list has to be good for to be worth making: it takes 75 to 150 us, a sweep over everything 12 to 20 us longer
   // than an iteration here, with costs formed from points 25 and up (4001 x 3999: 83 us).  At 8 for stored costs 7000 x 7100
-  // takes 11.9 ms where the sweeps take 10.2.
-  constexpr float kActShort = POINTS ? 3.f : 24.f;
+  // takes 11.9 ms where the sweeps take 10.2, and 10.3 at 16.
+  constexpr float kActShort = POINTS ? 3.f : 16.f;
   int ask = 0;               // 1: a new list soon; 2: leave behind the next iteration; 4: this workgroup has no list
   bool relist = true, have_list = false;
   __syncthreads();

@@ -90,7 +90,10 @@ constexpr int kActiveSide = 16, kActiveLocal = 5;
 constexpr int kActiveEntries = 4096;   // ... and so many entries each
 constexpr double kActiveFill = 0.6;    // of them, on average, from the lines (point clouds: row segments) that hold something
 constexpr int kActiveLeast = 16;       // shorter calls are not worth a list
-constexpr int kActiveTarget = 48;      // iterations a list is meant to last
+// Iterations a list is meant to last: longer lists are made less often, and hold more.  At 48, 28 and 20: 10000 x 10000 (1000
+// iterations) 14.6, 13.6, 13.7 ms; 20000 x 20000 (500) 18.45, 18.6, 18.8; point clouds 4001 x 3999 (400) 7.7, 6.1, 5.0; 12000 x 12100, quadratic
+// (400) 16.25, 15.9, 15.5 (does not fit at 48).
+constexpr int kActiveTarget = 20;
 constexpr int kPromptLooksUntil = 128; // ... of which the host waits for those of a point-cloud solve until the plan is sparse
 constexpr int kEarlyLooksUntil = 512;  // cold starts: extra density readings over this many iterations
 
