@@ -35,7 +35,7 @@
 // sweep and sums (2 to 4 us: chains of lane exchanges, and entries are not spread evenly), and the keeper's sum of the totals
 // (1.5 us, 2.7 at 20000 x 20000).  An iteration and calls, in place of sweeps launched one by one: 10000 x 10000 (1000 iterations)
 // 10 for 20 us, 20.5 -> 13.7 ms; 20000 x 20000 (500) 11.5 for 18 and more, 24.6 -> 18.8; point clouds of 12000 (500, d = 32) 9.5 for 45,
-// 31.1 -> 14.9, of 4001 x 3999 (400) 33.2 -> 5.0.  A list takes 75 to 150 us.
+// 31.1 -> 13.5, of 4001 x 3999 (400) 33.2 -> 4.9.  A list takes 75 to 150 us.
 // Waiting: a workgroup that polls without a rest can keep another's write from being seen for as long as it polls, so polls that
 // have failed 32 times rest in between (kGridRest).
 // ------------------------------------------------------------------------------------------
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
   __shared__ __align__(8) unsigned short starts[2 * kActRows];  // ... and the place of their first one
   __shared__ int pieces[kActTasks * kActWaves];  // ... and how many times 64 places the rows or columns of a task take
   __shared__ int rounds[2][kActSlots][kActWaves];  // of the sums along the rows, along the columns
-  __shared__ int nlines, nfound, nofit;
+  __shared__ int nlines, nfound, nofit, left;
   __shared__ float risen[2][kActWaves];          // largest rise of phi, of varphi since the list
   __shared__ double red[kActWaves];
   __shared__ int asked;                          // the keeper: what the others ask for
@@ -556,6 +556,35 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
         }
         flags[e] = w;
       }
+      if (!(A.lines && A.lines_known)) {  // (a line of X costs less to read than one of the cost, from points above all)
+        __syncthreads();
+#pragma unroll 1
+        for (int q = wave; q < nrc * nlb; q += kActWaves) {
+          const int ls = q / nrc, lr0 = (q - ls * nrc) * 64, j = (wb + kActSide * ls) * kSegCols + 4 * lane;
+          unsigned char* const f = reinterpret_cast<unsigned char*>(flags) + ls * kActRows + lr0;
+          unsigned long long held = __builtin_amdgcn_ballot_w64(f[lane] != 0);
+          while (held != 0) {
+            int at[4];
+            f4v x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              at[u] = held != 0 ? (int)__builtin_ctzll(held) : u > 0 ? at[u - 1] : 0;
+              held &= held - 1ull;
+              const int lr = lr0 + at[u], row = (wa + kActSide * (lr >> 8)) * 256 + (lr & 255);
+              x[u] = f4v{0.f, 0.f, 0.f, 0.f};
+              if (j < S.n) x[u] = *reinterpret_cast<const f4v*>(S.X + (size_t)row * S.ldx + j);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              unsigned long long b = __builtin_amdgcn_ballot_w64((fbits(x[u].x) | fbits(x[u].y) | fbits(x[u].z) | fbits(x[u].w)) != 0);
+              unsigned lines = 0;
+#pragma unroll
+              for (int l = 0; l < 8; ++l) lines |= (b >> (8 * l) & 0xffull) != 0 ? 1u << l : 0u;
+              if (lane == 0) f[at[u]] = (unsigned char)lines;
+            }
+          }
+        }
+      }
     }
     add_rise();
     have_list = false;
@@ -656,123 +685,142 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
         col_at[k] = 0;
       });
       for (int e = t; e < 2 * kActRows; e += kActThreads) counts[e] = 0;
-      if (t < 3) (t == 0 ? nlines : t == 1 ? nfound : nofit) = 0;
+      if (t < 4) (t == 0 ? nlines : t == 1 ? nfound : t == 2 ? nofit : left) = 0;
       __syncthreads();
-      // the lines that may hold an active entry: 64 rows x a segment to a wave at a time
+      // the lines that may hold an active entry: 64 rows x a segment to a wave at a time, until there is no room for more
+      if (lane == 0) rounds[0][0][wave] = wave;  // (where a wave goes on: its own word, not in use yet)
+      for (bool more = true; more;) {
+        int q = __builtin_amdgcn_readfirstlane(rounds[0][0][wave]);
 #pragma unroll 1
-      for (int q = wave; q < nrc * nlb; q += kActWaves) {
-        const int ls = q / nrc, lr = (q - ls * nrc) * 64 + lane, row = (wa + kActSide * (lr >> 8)) * 256 + (lr & 255);
-        const int seg = wb + kActSide * ls;
-        unsigned held = 0;
-        if (row < S.m) {
-          const size_t at = (size_t)seg * S.mp + row;
-          float* __restrict__ bp = A.bound + 8 * at;
-          f4v lo, hi;
-          if (fresh && A.codes && attempt == 0) {
-            const float m1 = A.m1[at];
-            const uint2 cd = A.codes[at];
-            const int base = line_code_base(S.rho);
+        for (; q < nrc * nlb; q += kActWaves) {
+          const int ls = q / nrc, lr = (q - ls * nrc) * 64 + lane, row = (wa + kActSide * (lr >> 8)) * 256 + (lr & 255);
+          const int seg = wb + kActSide * ls;
+          unsigned held = 0;
+          if (row < S.m) {
+            const size_t at = (size_t)seg * S.mp + row;
+            float* __restrict__ bp = A.bound + 8 * at;
+            f4v lo, hi;
+            if (fresh && A.codes && attempt == 0) {
+              const float m1 = A.m1[at];
+              const uint2 cd = A.codes[at];
+              const int base = line_code_base(S.rho);
 #pragma unroll
-            for (int l = 0; l < 4; ++l) {
-              lo[l] = m1 - line_decode((cd.x >> (8 * l)) & 0xffu, base);
-              hi[l] = m1 - line_decode((cd.y >> (8 * l)) & 0xffu, base);
+              for (int l = 0; l < 4; ++l) {
+                lo[l] = m1 - line_decode((cd.x >> (8 * l)) & 0xffu, base);
+                hi[l] = m1 - line_decode((cd.y >> (8 * l)) & 0xffu, base);
+              }
+              *reinterpret_cast<f4v*>(bp) = lo;
+              *reinterpret_cast<f4v*>(bp + 4) = hi;
+            } else {
+              lo = *reinterpret_cast<const f4v*>(bp);
+              hi = *reinterpret_cast<const f4v*>(bp + 4);
             }
-            *reinterpret_cast<f4v*>(bp) = lo;
-            *reinterpret_cast<f4v*>(bp + 4) = hi;
-          } else {
-            lo = *reinterpret_cast<const f4v*>(bp);
-            hi = *reinterpret_cast<const f4v*>(bp + 4);
+            const float ph = dual[lr];
+            held = flags[ls * (kActRows / 4) + (lr >> 2)] >> (8 * (lr & 3)) & 0xffu;
+#pragma unroll
+            for (int l = 0; l < 8; ++l) {
+              const float b = l < 4 ? lo[l & 3] : hi[l & 3], s = rise[8 * ls + l];
+              if (((b + s) + ph) + tau > -kActEps * (((fabsf(b) + fabsf(s)) + fabsf(ph)) + tau)) held |= 1u << l;
+            }
+            // (columns past n: no line, whatever the flags made of row-segment sums say)
+            held &= (1u << min((S.n - seg * kSegCols + 31) / 32, 8)) - 1u;
           }
-          const float ph = dual[lr];
-          held = flags[ls * (kActRows / 4) + (lr >> 2)] >> (8 * (lr & 3)) & 0xffu;
-#pragma unroll
-          for (int l = 0; l < 8; ++l) {
-            const float b = l < 4 ? lo[l & 3] : hi[l & 3], s = rise[8 * ls + l];
-            if (((b + s) + ph) + tau > -kActEps * (((fabsf(b) + fabsf(s)) + fabsf(ph)) + tau)) held |= 1u << l;
-          }
-          // (columns past n: no line, whatever the flags made of row-segment sums say)
-          held &= (1u << min((S.n - seg * kSegCols + 31) / 32, 8)) - 1u;
-        }
-        if (__builtin_amdgcn_ballot_w64(held != 0) == 0) continue;
-        int all = 0;
-#pragma unroll
-        for (int l = 0; l < 8; ++l) all += __builtin_popcountll(__builtin_amdgcn_ballot_w64((held >> l) & 1u));
-        int at = 0;
-        if (lane == 0) at = atomicAdd(&nlines, all);
-        at = __builtin_amdgcn_readfirstlane(at);
-#pragma unroll
-        for (int l = 0; l < 8; ++l) {
-          const unsigned long long b = __builtin_amdgcn_ballot_w64((held >> l) & 1u);
-          const int mine = at + __builtin_popcountll(b & ((1ull << lane) - 1ull));
-          if (((held >> l) & 1u) && mine < kActLines) U.l.lines[mine] = (unsigned)lr | (unsigned)(8 * ls + l) << 16;
-          at += __builtin_popcountll(b);
-        }
-      }
-      __syncthreads();
-      // ... are fetched, eight lanes a line: their entries, and exact bounds
-      const int nl = min(nlines, kActLines);
-      constexpr int kAtOnce = POINTS ? 1 : 4;
-      const int l4 = 4 * (lane & 7);
-#pragma unroll 1
-      for (int k0 = 8 * wave; k0 < nl; k0 += 8 * kActWaves * kAtOnce) {
-        unsigned code[kAtOnce];
-        f4v cc[kAtOnce], xx[kAtOnce];
-#pragma unroll
-        for (int s = 0; s < kAtOnce; ++s) {
-          code[s] = U.l.lines[min(k0 + 8 * kActWaves * s + (lane >> 3), nl - 1)];
-          const unsigned lr = code[s] & 0xffffu, line = code[s] >> 16;
-          const int row = (wa + kActSide * (int)(lr >> 8)) * 256 + (int)(lr & 255u);
-          const int j = (wb + kActSide * (int)(line >> 3)) * kSegCols + (int)(line & 7u) * 32 + l4;
-          if constexpr (POINTS) cc[s] = active_points_cost(A.points, row, j, S.n);
-          else cc[s] = *reinterpret_cast<const f4v*>(S.C + (size_t)row * S.ldc + j);
-          xx[s] = f4v{0.f, 0.f, 0.f, 0.f};
-          if (flags[(line >> 3) * (kActRows / 4) + (lr >> 2)] >> (8 * (lr & 3) + (line & 7u)) & 1u)
-            xx[s] = *reinterpret_cast<const f4v*>(S.X + (size_t)row * S.ldx + j);
-        }
-#pragma unroll
-        for (int s = 0; s < kAtOnce; ++s) {
-          const int k = k0 + 8 * kActWaves * s + (lane >> 3);
-          const unsigned lr = code[s] & 0xffffu, line = code[s] >> 16;
-          const f4v vp = *reinterpret_cast<const f4v*>(&dual[kActRows + line * 32 + l4]);
-          const float ph = dual[lr], rho = S.rho;
-          const f4v tv = {fmaf(-rho, cc[s].x, vp.x), fmaf(-rho, cc[s].y, vp.y), fmaf(-rho, cc[s].z, vp.z), fmaf(-rho, cc[s].w, vp.w)};
-          unsigned act = 0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool in = fbits(xx[s][e]) != 0 || (tv[e] + ph) + tau > -kActEps * ((fabsf(tv[e]) + fabsf(ph)) + tau);
-            act |= in && k < nl ? 1u << e : 0u;
-          }
-          const float top = line_max(tv);
-          if (k < nl && (lane & 7) == 0) {
-            const int row = (wa + kActSide * (int)(lr >> 8)) * 256 + (int)(lr & 255u);
-            A.bound[8 * ((size_t)(wb + kActSide * (int)(line >> 3)) * S.mp + row) + (line & 7u)] = top - rise[line];
-          }
-          if (__builtin_amdgcn_ballot_w64(act != 0) == 0) continue;
+          if (__builtin_amdgcn_ballot_w64(held != 0) == 0) continue;
           int all = 0;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) all += __builtin_popcountll(__builtin_amdgcn_ballot_w64((act >> e) & 1u));
+          for (int l = 0; l < 8; ++l) all += __builtin_popcountll(__builtin_amdgcn_ballot_w64((held >> l) & 1u));
           int at = 0;
-          if (lane == 0) at = atomicAdd(&nfound, all);
-          at = __builtin_amdgcn_readfirstlane(at);
-          if (act != 0) atomicAdd(&counts[lr], (unsigned)__builtin_popcount(act));
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const unsigned long long b = __builtin_amdgcn_ballot_w64((act >> e) & 1u);
-            const int mine = at + __builtin_popcountll(b & ((1ull << lane) - 1ull));
-            if ((act >> e) & 1u) {
-              const unsigned lc = line * 32 + (unsigned)(l4 + e);
-              if (mine < kActEntries) {
-                U.l.x[mine] = xx[s][e];
-                U.l.c[mine] = cc[s][e];
-                U.l.id[mine] = lr | lc << 16;
-              }
-              atomicAdd(&counts[kActRows + lc], 1u);
+          if (lane == 0) {
+            at = nlines;
+            for (int seen = -1; at != seen && at + all <= kActLines;) {
+              seen = at;
+              at = (int)atomicCAS((unsigned*)&nlines, (unsigned)seen, (unsigned)(seen + all));
             }
+          }
+          at = __builtin_amdgcn_readfirstlane(at);
+          if (at + all > kActLines) {  // (these are found once more)
+            if (lane == 0) left = 1;
+            break;
+          }
+#pragma unroll
+          for (int l = 0; l < 8; ++l) {
+            const unsigned long long b = __builtin_amdgcn_ballot_w64((held >> l) & 1u);
+            const int mine = at + __builtin_popcountll(b & ((1ull << lane) - 1ull));
+            if ((held >> l) & 1u) U.l.lines[mine] = (unsigned)lr | (unsigned)(8 * ls + l) << 16;
             at += __builtin_popcountll(b);
           }
         }
+        if (lane == 0) rounds[0][0][wave] = q;
+        __syncthreads();
+        // ... are fetched, eight lanes a line: their entries, and exact bounds
+        const int nl = nfound <= kActEntries ? nlines : 0;  // (too many: the bounds of the rest only)
+        constexpr int kAtOnce = POINTS ? 1 : 4;
+        const int l4 = 4 * (lane & 7);
+#pragma unroll 1
+        for (int k0 = 8 * wave; k0 < nl; k0 += 8 * kActWaves * kAtOnce) {
+          unsigned code[kAtOnce];
+          f4v cc[kAtOnce], xx[kAtOnce];
+#pragma unroll
+          for (int s = 0; s < kAtOnce; ++s) {
+            code[s] = U.l.lines[min(k0 + 8 * kActWaves * s + (lane >> 3), nl - 1)];
+            const unsigned lr = code[s] & 0xffffu, line = code[s] >> 16;
+            const int row = (wa + kActSide * (int)(lr >> 8)) * 256 + (int)(lr & 255u);
+            const int j = (wb + kActSide * (int)(line >> 3)) * kSegCols + (int)(line & 7u) * 32 + l4;
+            if constexpr (POINTS) cc[s] = active_points_cost(A.points, row, j, S.n);
+            else cc[s] = *reinterpret_cast<const f4v*>(S.C + (size_t)row * S.ldc + j);
+            xx[s] = f4v{0.f, 0.f, 0.f, 0.f};
+            if (flags[(line >> 3) * (kActRows / 4) + (lr >> 2)] >> (8 * (lr & 3) + (line & 7u)) & 1u)
+              xx[s] = *reinterpret_cast<const f4v*>(S.X + (size_t)row * S.ldx + j);
+          }
+#pragma unroll
+          for (int s = 0; s < kAtOnce; ++s) {
+            const int k = k0 + 8 * kActWaves * s + (lane >> 3);
+            const unsigned lr = code[s] & 0xffffu, line = code[s] >> 16;
+            const f4v vp = *reinterpret_cast<const f4v*>(&dual[kActRows + line * 32 + l4]);
+            const float ph = dual[lr], rho = S.rho;
+            const f4v tv = {fmaf(-rho, cc[s].x, vp.x), fmaf(-rho, cc[s].y, vp.y), fmaf(-rho, cc[s].z, vp.z), fmaf(-rho, cc[s].w, vp.w)};
+            unsigned act = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const bool in = fbits(xx[s][e]) != 0 || (tv[e] + ph) + tau > -kActEps * ((fabsf(tv[e]) + fabsf(ph)) + tau);
+              act |= in && k < nl ? 1u << e : 0u;
+            }
+            const float top = line_max(tv);
+            if (k < nl && (lane & 7) == 0) {
+              const int row = (wa + kActSide * (int)(lr >> 8)) * 256 + (int)(lr & 255u);
+              A.bound[8 * ((size_t)(wb + kActSide * (int)(line >> 3)) * S.mp + row) + (line & 7u)] = top - rise[line];
+            }
+            if (__builtin_amdgcn_ballot_w64(act != 0) == 0) continue;
+            int all = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) all += __builtin_popcountll(__builtin_amdgcn_ballot_w64((act >> e) & 1u));
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&nfound, all);
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (act != 0) atomicAdd(&counts[lr], (unsigned)__builtin_popcount(act));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const unsigned long long b = __builtin_amdgcn_ballot_w64((act >> e) & 1u);
+              const int mine = at + __builtin_popcountll(b & ((1ull << lane) - 1ull));
+              if ((act >> e) & 1u) {
+                const unsigned lc = line * 32 + (unsigned)(l4 + e);
+                if (mine < kActEntries) {
+                  U.l.x[mine] = xx[s][e];
+                  U.l.c[mine] = cc[s][e];
+                  U.l.id[mine] = lr | lc << 16;
+                }
+                atomicAdd(&counts[kActRows + lc], 1u);
+              }
+              at += __builtin_popcountll(b);
+            }
+          }
+        }
+        __syncthreads();
+        more = left != 0;
+        __syncthreads();
+        if (t < 2) (t == 0 ? nlines : left) = 0;
+        __syncthreads();
       }
-      __syncthreads();
       // places: a row's entries lie within 64 of them, a column's too; the pieces a task takes
 #pragma unroll 1
       for (int k = 0; k < kActTasks; ++k) {
@@ -803,7 +851,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       row_pieces = col_pieces = 0;
       for (int q = 0; q < ntask; ++q) (q < nrc ? row_pieces : col_pieces) += pieces[q];
       cnt = nfound;
-      fits = nlines <= kActLines && nfound <= kActEntries && row_pieces <= 64 && col_pieces <= 64 && nofit == 0;
+      fits = nfound <= kActEntries && row_pieces <= 64 && col_pieces <= 64 && nofit == 0;
       if (fits) order();
       if (fits) break;
       row_pieces = col_pieces = 0;
@@ -822,7 +870,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     }
     if (rate >= 0.f ? tau < kActShort * rate : tau == 0.f) ask = 2;  // (a list that does not last)
     for (int e = t; e < kActLocal * kActRows; e += kActThreads) (&U.f.rowseg[0][0])[e] = 0.f;
-    for (int e = t; e < 2 * kActRows; e += kActThreads) U.f.share[e] = 0.0;
+    for (int e = t; e < 4 * kActRows; e += kActThreads) reinterpret_cast<float*>(U.f.share)[e] = 0.f;
     have_list = true;
     ++lists;
     since_list = 0;

@@ -89,6 +89,9 @@ constexpr double kPointsSparse = 0.33;
 constexpr int kActiveSide = 16, kActiveLocal = 5;
 constexpr int kActiveEntries = 4096;   // ... and so many entries each
 constexpr double kActiveFill = 0.6;    // of them, on average, from the lines (point clouds: row segments) that hold something
+// ... of point clouds below this many nonzero row segments: 12000 x 12000, d = 32, 276 us a full sweep: listed at 0.31, iteration 32, 15.1 ms for
+// 500 iterations; at 0.53, iteration 24, 13.5; tried in vain at 0.88 and listed at 0.53 15.4.
+constexpr double kActivePoints = 0.6;
 constexpr int kActiveLeast = 16;       // shorter calls are not worth a list
 // Iterations a list is meant to last: longer lists are made less often, and hold more.  At 48, 28 and 20: 10000 x 10000 (1000
 // iterations) 14.6, 13.6, 13.7 ms; 20000 x 20000 (500) 18.45, 18.6, 18.8; point clouds 4001 x 3999 (400) 7.7, 6.1, 5.0; 12000 x 12100, quadratic
@@ -578,7 +581,7 @@ inline bool active_next(const Static& S, const Problem& P, const State& T) {
   const long long now = T.k_base + T.k;
   if (!T.materialized || T.dense_plan || T.sums_gen != now || T.epoch_gen < 0 || T.epoch_gen > now) return false;
   const double room = kActiveFill * (double)kActiveEntries * (kActiveSide * kActiveSide);
-  if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kPointsSparse && T.plan_density * P.m * S.nseg <= room;
+  if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kActivePoints && T.plan_density * P.m * S.nseg <= room;
   return T.by_lines && !T.dense_lines && T.lines >= 0.0 && T.lines * P.m * ceil_div(P.n, 32) <= room;
 }
 
@@ -606,7 +609,9 @@ inline void active_done(State& T, const Problem& P, int iters, bool left) {
     T.last_lean = false;
   }
   if (left) {
-    T.active_from = T.k + (512 << (T.active_left < 6 ? T.active_left : 6));
+    // (early in a point-cloud solve every look finds a thinner plan, and a sweep over everything costs as much as an attempt)
+    const int again = P.from_points && T.k < kPromptLooksUntil ? 8 : 512;
+    T.active_from = T.k + (again << (T.active_left < 6 ? T.active_left : 6));
     ++T.active_left;
   }
 }

@@ -641,7 +641,9 @@ def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
         assert active(m, n, lines=-1.0)[1][0] == 0 and active(m, n, by_lines=0)[1][0] == 0 and active(m, n, epoch=-1)[1][0] == 0
         assert active(m, n, iters=48)[1][0] == 16 and active(m, n, iters=47)[1][0] == 0
         assert active(m, n, from_points=1, lines=-1.0, by_lines=0)[1][0] > 0
-        assert active(m, n, from_points=1, density=0.34)[1][0] == 0 and active(m, n, from_points=1, density=-1.0)[1][0] == 0
+        assert active(m, n, from_points=1, density=0.61)[1][0] == 0 and active(m, n, from_points=1, density=-1.0)[1][0] == 0
+    assert active(12000, 12000, from_points=1, density=0.59)[1][0] > 0
     # one that ended early is not tried again at once, and later every time
+    assert active(12000, 12000, k=16, from_points=1)[1][1] == 26 + 8
     assert active(10000, 10000, k=200, left=1, ago=511)[1][0] == 0 and active(10000, 10000, k=200, left=1, ago=512)[1] == (800, 210 + 1024, 2)
     assert active(10000, 10000, k=900, left=3, ago=2047)[1][0] == 0 and active(10000, 10000, k=900, left=3, ago=2048)[1][0] == 100
