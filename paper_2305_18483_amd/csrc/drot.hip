@@ -681,8 +681,8 @@ int enqueue_active(Solve& Z, int iters) {
   A.varphi_out = h->varphi;
   A.r = h->r;
   A.s = h->s;
-  // the newer bounds: those the last launch of this kind left, or those of the last sweep that recorded some
-  const bool left = Z.T.bound_gen >= Z.T.epoch_gen;
+  // (active_bounds: those the last launch of this kind left, or those of the last sweep that recorded some)
+  const bool left = plan::active_bounds(Z.P, Z.T) == plan::kLeftBounds;
   A.bound = h->bound;
   A.bound_varphi = h->bound_varphi;
   A.since = left ? h->bound_varphi : h->varphi0;
@@ -971,10 +971,14 @@ int prepare(drot_handle h, const SolveCall& A, Solve& Z) {
   Z.S = plan::make_static(P, Z.O);
   // (a fixed workspace does not grow)
   if (A.fixed_schedule && Z.S.grid_tiles && 2 * grid_words(Z.S, P).half > h->xchg_len) P.single_launches = true;
-  if (Z.S.active && (grow_buffer(&h->bound, &h->bound_len, 8 * (size_t)Z.S.nseg * (size_t)(ceil_div(m, 64) * 64), stream) != DROT_OK ||
-                     grow_buffer(&h->bound_varphi, &h->bound_varphi_len, (size_t)n, stream) != DROT_OK)) {
-    (void)hipGetLastError();
-    Z.S.active = false;
+  if (Z.S.active) {
+    const size_t need = 8 * (size_t)Z.S.nseg * (size_t)(ceil_div(m, 64) * 64);
+    if (h->bound_len < need || h->bound_varphi_len < (size_t)n) h->carry.bound_gen = h->carry.recorded_gen = -1;  // (what they hold is lost)
+    if (grow_buffer(&h->bound, &h->bound_len, need, stream) != DROT_OK ||
+        grow_buffer(&h->bound_varphi, &h->bound_varphi_len, (size_t)n, stream) != DROT_OK) {
+      (void)hipGetLastError();
+      Z.S.active = false;
+    }
   }
   Z.T = plan::start_state(Z.S, P, h->carry);
   const plan::Static& S = Z.S;

@@ -161,6 +161,7 @@ struct Carry {
   bool drift_valid = false;      // the last vector update left the drift of varphi for it
   double lines = -1.0;           // fraction of nonzero lines last reported
   long long bound_gen = -1;      // iteration whose varphi the bounds by line that a launch of active entries left are against
+  long long recorded_gen = -1;   // sweep over point clouds that last recorded bounds by line
   long long iters_done = 0;
 };
 
@@ -299,6 +300,7 @@ struct State {
   bool dense_lines = false;      // ... but the last status found most lines nonzero
   double lines = -1.0;           // fraction of nonzero lines the last status that counted them reported
   long long bound_gen = -1;      // iteration whose varphi the bounds by line that a launch of active entries left are against
+  long long recorded_gen = -1;   // sweep over point clouds that last recorded bounds by line: not every epoch of theirs has some
   int active_from = 0;           // no such launch before this iteration of the call
   int active_left = 0;           // launches of them that ended early
   bool active_ran = false;
@@ -306,6 +308,16 @@ struct State {
   bool materialized = true;      // phi, varphi, a, b, theta in memory are complete for the sweeps done
   bool norms_pending = false;    // the last vector update left the residual norms as per-workgroup sums
 };
+
+// The bounds by line a launch of active entries would start from, the newer ones of two: what the last such launch left (against the
+// varphi it left, which stays with them), or what the last sweep to record any did, against the varphi of the last epoch.  Over a
+// stored cost every epoch has bounds by line; over point clouds those of calls that could take such a launch.
+enum ActiveBounds { kNoBounds = 0, kLeftBounds, kRecordedBounds };
+inline ActiveBounds active_bounds(const Problem& P, const State& T) {
+  const long long recorded = P.from_points ? T.recorded_gen : T.epoch_gen;
+  if (T.bound_gen >= 0 && T.bound_gen >= recorded) return kLeftBounds;
+  return recorded >= 0 && recorded == T.epoch_gen ? kRecordedBounds : kNoBounds;
+}
 
 inline State start_state(const Static& S, const Problem& P, const Carry& carry) {
   State T;
@@ -323,8 +335,11 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
                       : (P.resume && carry.sums_valid && carry.sums_strip == S.sums_strip) ? T.k_base : -1;
   T.lines = P.resume ? carry.lines : -1.0;
   T.bound_gen = bounds_hold ? carry.bound_gen : -1;
+  T.recorded_gen = bounds_hold ? carry.recorded_gen : -1;
   T.lines_gen = (P.resume && carry.lines_valid && T.sums_gen >= 0) ? T.k_base : -1;
   T.epoch_gen = bounds_hold ? carry.epoch_gen : -1;
+  // (an epoch without bounds by line is none where active entries may come: the next full sweep records both)
+  if (S.active && P.from_points && active_bounds(P, T) == kNoBounds) T.epoch_gen = -1;
   T.refresh_period = bounds_hold ? carry.refresh_period : S.early_lines ? kFirstPeriodLines : kFirstRefreshPeriod;
   if (T.refresh_period > S.refresh_max) T.refresh_period = S.refresh_max;
   return T;
@@ -445,6 +460,7 @@ inline Step next_sweep(const Static& S, const Problem& P, const Options& O, Stat
         if (T.epoch_gen >= 0 && due && sparse)
           T.refresh_period = T.refresh_period * 2 < S.refresh_max ? T.refresh_period * 2 : S.refresh_max;
         T.epoch_gen = sw;
+        if (S.active) T.recorded_gen = sw;
       }
     }
   } else if (P.slab_k) {
@@ -580,6 +596,7 @@ inline bool active_next(const Static& S, const Problem& P, const State& T) {
   if (!S.active || P.single_launches || T.k < T.active_from || P.max_iters - T.k < kActiveLeast) return false;
   const long long now = T.k_base + T.k;
   if (!T.materialized || T.dense_plan || T.sums_gen != now || T.epoch_gen < 0 || T.epoch_gen > now) return false;
+  if (active_bounds(P, T) == kNoBounds) return false;
   const double room = kActiveFill * (double)kActiveEntries * (kActiveSide * kActiveSide);
   if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kActivePoints && T.plan_density * P.m * S.nseg <= room;
   return T.by_lines && !T.dense_lines && T.lines >= 0.0 && T.lines * P.m * ceil_div(P.n, 32) <= room;
@@ -646,6 +663,7 @@ inline Carry finish(const Static& S, const Problem& P, const State& T, bool conv
   C.by_lines = T.by_lines;
   C.lines = T.lines;
   C.bound_gen = (converged || T.bound_gen > T.k_base + (long long)iters) ? -1 : T.bound_gen;
+  C.recorded_gen = (converged || T.recorded_gen > T.k_base + (long long)iters) ? -1 : T.recorded_gen;
   C.drift_valid = !converged && epoch_kept && P.max_iters > 0 && T.drift_gen == T.k_base + T.k;
   C.epoch_gen = (converged || !epoch_ran) ? -1 : T.epoch_gen;
   C.refresh_period = (converged || !epoch_ran) ? kFirstRefreshPeriod : T.refresh_period;

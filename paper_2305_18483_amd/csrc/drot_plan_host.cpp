@@ -203,7 +203,7 @@ int drot_plan_active(const int* problem, const int* options, int compute_units, 
   T.plan_density = state[1] * 1e-6;
   T.lines = state[2] * 1e-6;
   T.by_lines = state[3] != 0;
-  T.epoch_gen = state[4];
+  T.epoch_gen = T.recorded_gen = state[4];
   T.active_left = state[5];
   T.active_from = state[5] ? state[0] - state[6] + (512 << (state[5] - 1)) : 0;
   out[0] = active_next(S, P, T) ? active_stretch(P, O, T).chunk : 0;
@@ -211,6 +211,67 @@ int drot_plan_active(const int* problem, const int* options, int compute_units, 
   out[1] = T.active_from;
   out[2] = T.active_left;
   return S.active;
+}
+
+// Continued calls of one handle (problem as in drot_plan_trace; options[ncalls][9], iters[ncalls]), every status of which reports
+// density and lines (* 1e6), every launch of active entries lasting to its end.  events[capacity][4]: 0, sweep, whether bounds by line
+// were recorded, 0: a sweep that started an epoch; 1, iterations before it, iterations after it, where its bounds come from
+// (ActiveBounds): a launch of active entries.  Returns the number of events, or -1 if capacity was too small.
+int drot_plan_active_calls(const int* problem, int ncalls, const int* options, const int* iters, int compute_units, int density, int lines,
+                           long long* events, int capacity) {
+  Carry C;
+  int count = 0;
+  auto event = [&](long long a, long long b, long long c, long long d) {
+    if (count < capacity) {
+      events[4 * count] = a;
+      events[4 * count + 1] = b;
+      events[4 * count + 2] = c;
+      events[4 * count + 3] = d;
+    }
+    ++count;
+  };
+  for (int call = 0; call < ncalls; ++call) {
+    Problem P;
+    P.m = problem[0];
+    P.n = problem[1];
+    P.reg_kind = problem[2];
+    P.from_points = problem[3] != 0;
+    P.resume = call > 0;
+    P.feedback = true;
+    P.checking = problem[12] != 0;
+    P.line_bounds = true;
+    P.compute_units = compute_units;
+    P.max_iters = iters[call];
+    P.rho = 1e-3f;
+    P.tilesum_half = (size_t)ceil_div(P.n, kSegCols) * (size_t)ceil_div(P.m, kTileRows);
+    const int* o = options + 9 * call;
+    Options O;
+    O.check_every = o[0];
+    O.fused_update = o[2];
+    O.skip_cost = o[3];
+    O.skip_unchanged = o[4];
+    O.screening = o[5];
+    O.gap_every = o[8];
+    const Static S = make_static(P, O);
+    State T = start_state(S, P, C);
+    while (T.k < P.max_iters) {
+      if (active_next(S, P, T)) {
+        const long long before = T.k_base + T.k;
+        const ActiveBounds from = active_bounds(P, T);
+        active_done(T, P, active_stretch(P, O, T).chunk, false);
+        event(1, before, T.k_base + T.k, from);
+        continue;
+      }
+      const Stretch R = next_stretch(S, P, O, T);
+      for (int c = 0, end = T.k + R.chunk; T.k < end; ++c) {
+        const Step Q = next_sweep(S, P, O, T, R, c);
+        if (Q.refresh) event(0, Q.sw, P.from_points ? (S.active ? 1 : 0) : 1, 0);
+      }
+      if (S.status_at_checks) on_status(S, T, density * 1e-6, T.last_lean ? lines * 1e-6 : -1.0, R.probe);
+    }
+    C = finish(S, P, T, false, P.max_iters);
+  }
+  return count <= capacity ? count : -1;
 }
 
 // Grid-resident stretches: problem, options as in drot_plan_trace.  out[4]: tiles per workgroup (0: none), rows per tile,

@@ -124,6 +124,51 @@ def test_active_entries_across_calls_starts_and_stops(drot):
     _both(drot, m, n, stopped, launches=2, check_every=10)
 
 
+# calls that continue one another with the options that keep them off active entries in between, on a handle that holds the bounds of
+# another problem: which launches record bounds by line, and which may read them, hangs on the options of each call
+@pytest.mark.parametrize("off", ["gap_every", "fused_update", "screening", "gap_tolerance"])
+@pytest.mark.parametrize("order", [(0, 1), (1, 0, 1)])
+def test_active_entries_of_point_clouds_across_options(drot, off, order):
+    m, n = 3585, 3329
+    dev = torch.device("cuda:0")
+
+    def points(seed):
+        P = drot_inputs.random_problem(m, n, seed=seed, d=5)
+        xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
+        return xs, xt, 1.0 / float((torch.cdist(xs, xt) ** 2).max()), p, q
+
+    def switch(solver, on):
+        if off == "gap_every":
+            solver.set_gap_every(0 if on else 1)
+        elif off == "fused_update":
+            solver.set_fused_update(-1 if on else 0)
+        elif off == "screening":
+            solver.set_screening(-1 if on else 1)
+        else:
+            solver.set_gap_tolerance(0.0 if on else 1e-12)
+
+    kw = dict(tol=1e-12)
+    A, B = points(4500), points(4501)
+    _say(f"point clouds, {off}, {order}")
+    out = []
+    for use in (True, False):
+        solver = drot.Solver(m, n, check_every=20)
+        solver.set_profile(not use)  # (every sweep in a launch of its own)
+        solver.solve_points(*B, max_iters=200, **kw)
+        taken, X = [], torch.empty(m, n, device=dev)
+        for call, on in enumerate(order):
+            solver.set_continue(call > 0)
+            switch(solver, on)
+            before = solver.cooperative_launches()[0]
+            res = solver.solve_points(*A, X_out=X, max_iters=(200, 60, 120)[call], **kw)
+            taken.append(solver.cooperative_launches()[0] - before)
+        assert [t > 0 for t in taken] == [use and bool(on) for on in order], taken
+        out.append((res.X.cpu().numpy(), *(v.cpu().numpy() for v in solver.duals(m, n, dev)), np.float64([res.objective, res.r_row, res.r_col])))
+        solver.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
 def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot):
     # row i holds its mass near column i: the workgroups on the diagonal of 16 x 16 have sixteen times their part of the entries, and
     # a quadratic term of middling strength keeps dozens of them in every row

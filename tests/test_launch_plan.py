@@ -647,3 +647,37 @@ def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
     assert active(12000, 12000, k=16, from_points=1)[1][1] == 26 + 8
     assert active(10000, 10000, k=200, left=1, ago=511)[1][0] == 0 and active(10000, 10000, k=200, left=1, ago=512)[1] == (800, 210 + 1024, 2)
     assert active(10000, 10000, k=900, left=3, ago=2047)[1][0] == 0 and active(10000, 10000, k=900, left=3, ago=2048)[1][0] == 100
+
+
+# calls of one handle, each continuing the last: what the options of a call leave out (the defaults of a case are those of the first)
+@pytest.mark.parametrize("from_points", [1, 0])
+@pytest.mark.parametrize("off", [dict(gap_every=1), dict(fused_update=0), dict(screening=1)])
+@pytest.mark.parametrize("order", [(0, 1), (1, 0, 1), (1, 0, 0, 1), (0, 1, 0, 1)])
+def test_active_entries_start_from_bounds_that_are_there(planlib, from_points, off, order):
+    calls = []
+    for on in order:
+        o = dict(check_every=20, fused_update=-1, screening=-1, gap_every=0)
+        o.update({} if on else off)
+        calls += [o["check_every"], -1, o["fused_update"], 0, -1, o["screening"], -1, 0, o["gap_every"]]
+    problem = (ctypes.c_int * 14)(6000, 6000, 1, from_points, 0, 0, 0, 1, 1, 0, 0, 1, 1, 0)
+    events = (ctypes.c_longlong * 4000)()
+    count = planlib.drot_plan_active_calls(problem, len(order), (ctypes.c_int * len(calls))(*calls),
+                                           (ctypes.c_int * len(order))(*([300, 240, 180, 200][:len(order)])), 256, 200000, 20000, events, 1000)
+    assert 0 < count <= 1000
+    # what is in memory: the iteration whose varphi the bounds by line are against, that of the last epoch's varphi and that of the
+    # varphi a launch left with its bounds
+    bounds = epoch = left = None
+    launches = 0
+    for e in range(count):
+        launch, a, b, source = events[4 * e:4 * e + 4]
+        if not launch:
+            epoch = a
+            if b:
+                bounds = a
+        else:
+            launches += 1
+            against = {1: left, 2: epoch}[source]
+            assert bounds is not None and against == bounds, (e, a, source)
+            bounds = left = b
+    # ... and every call at the defaults takes such launches, the first one of a continued call as soon as there are bounds
+    assert launches >= sum(order)
