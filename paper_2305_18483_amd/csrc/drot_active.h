@@ -53,7 +53,6 @@ static_assert(kActEntries == 64 * 64 && kActLocal <= 5, "packed places; the unit
 constexpr int kActTotals = 32;                 // words of a workgroup for its totals
 constexpr int kActSquares = 16;                // ... of an owned block for its squared residuals
 static_assert(kActLocal * kActLocal < kActTotals, "the last word is the workgroup's request");
-constexpr float kActEps = 9.53674316e-7f;      // 2^-20: 16 half units in the last place of every term of a comparison (4 would do)
 static_assert(2 * 4 * kActLocal <= kActTasks * kActWaves, "tasks");
 
 enum { kActDone = 0, kActLeave = 1, kActAbort = 2 };
@@ -361,7 +360,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
   __shared__ float val[kActEntries];             // X of the entries, rows in order and columns within a row
   __shared__ unsigned idx[kActEntries];          // row of the workgroup | column of the workgroup << 16; all bits: no entry
   __shared__ unsigned flags[kActLocal * kActRows / 4];  // [segment][row], a byte each: lines of X that hold something
-  __shared__ float rise[kLines];                 // how far varphi has risen since `since`, the largest of a line added up
+  __shared__ __align__(16) float rise[kLines];   // how far varphi has risen since `since`, the largest of a line added up
+  __shared__ __align__(16) float mags[kLines];   // ... and the magnitude of that with the largest of varphi, at the last list
   union Shared {
     struct {
       float rowseg[kActLocal][kActRows];         // sums of the row segments
@@ -521,13 +521,17 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       if (!T.live || T.rows) return;
       const float v = dual[T.local + lane];
       const float from = ref[T.local + lane];
-      float d = lane < T.count ? (v - from) + kActEps * (fabsf(v) + fabsf(from)) : -INFINITY;
+      float d = lane < T.count ? active_rise(v, from) : -INFINITY, mag = lane < T.count ? fabsf(v) : 0.f;
 #pragma unroll
-      for (int off = 16; off > 0; off >>= 1) d = fmaxf(d, __shfl_xor(d, off, 64));
+      for (int off = 16; off > 0; off >>= 1) {
+        d = fmaxf(d, __shfl_xor(d, off, 64));
+        mag = fmaxf(mag, __shfl_xor(mag, off, 64));
+      }
       if ((lane & 31) == 0) {
         const int line = (T.local - kActRows + lane) >> 5;
-        const float s = d == -INFINITY ? 0.f : rise[line] + d;
-        rise[line] = s + kActEps * fabsf(s);
+        const float risen = d == -INFINITY ? 0.f : active_rises(rise[line], d);
+        rise[line] = risen;
+        mags[line] = fabsf(risen) + mag;
       }
       ref[T.local + lane] = v;
     });
@@ -720,7 +724,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
 #pragma unroll
             for (int l = 0; l < 8; ++l) {
               const float b = l < 4 ? lo[l & 3] : hi[l & 3], s = rise[8 * ls + l];
-              if (((b + s) + ph) + tau > -kActEps * (((fabsf(b) + fabsf(s)) + fabsf(ph)) + tau)) held |= 1u << l;
+              if (active_line(b, s, mags[8 * ls + l], ph, tau)) held |= 1u << l;
             }
             // (columns past n: no line, whatever the flags made of row-segment sums say)
             held &= (1u << min((S.n - seg * kSegCols + 31) / 32, 8)) - 1u;
@@ -782,7 +786,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
             unsigned act = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const bool in = fbits(xx[s][e]) != 0 || (tv[e] + ph) + tau > -kActEps * ((fabsf(tv[e]) + fabsf(ph)) + tau);
+              const bool in = fbits(xx[s][e]) != 0 || active_entry(tv[e], vp[e], ph, tau);
               act |= in && k < nl ? 1u << e : 0u;
             }
             const float top = line_max(tv);
@@ -1177,7 +1181,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
         if (T.count <= 0 || next == 4u) return;
         const float d = (float)divide_by(active_signed(v[k]) + cst, T.rows ? (double)S.n : (double)S.m, T.rows ? recip_n : recip_m);
         const float from = ref[T.local + lane];
-        const float r = (d - from) + kActEps * (fabsf(d) + fabsf(from));
+        const float r = active_rise(d, from);
         if (lane < T.count) {
           dual[T.local + lane] = d;
           if (T.rows) up_rows = fmaxf(up_rows, r);
@@ -1229,7 +1233,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     rc = wave_max(rc);
     ++since_list;
     if (some) {
-      const float now = (rr + rc) + kActEps * (fabsf(rr) + fabsf(rc));
+      const float now = active_rises(rr, rc);
       const float step = fmaxf(now - risen_last, 0.f);
       risen_last = active_uniform(now);
       relist = !(now < tau);
@@ -1288,7 +1292,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
       const float s = rise[8 * ls + l], w = b[l >> 2][l & 3];
-      b[l >> 2][l & 3] = (w + s) + (w == -INFINITY ? 0.f : kActEps * (fabsf(w) + fabsf(s)));
+      b[l >> 2][l & 3] = w == -INFINITY ? w : active_rises(w, s);
     }
     bp[0] = b[0];
     bp[1] = b[1];

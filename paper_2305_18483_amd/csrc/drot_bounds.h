@@ -35,6 +35,21 @@ DROT_FN bool certified_line(float m1, float below, float drift, float mag, float
   return bound + kLeanEps * (fabsf(m1) + fabsf(ph) + mag) <= 0.f;
 }
 
+// The active entries (drot_active.h): may a zero entry come to hold something while phi_i and varphi_j together rise by less than tau?
+// t: varphi_j - rho C_ij as the sweep's own fmaf gives it.  A line of entries: its bound, which was of some earlier varphi's t and is
+// off by u of itself, plus the rise of varphi since; mag: the rise's magnitude plus the largest of varphi in the line.  The margin, 16 u of every term,
+// covers u |t| of t, 2 u of the sums here, and u (|varphi_j| + |phi_i|) of the sum that the sweep forms of phi_i and varphi_j before it
+// takes off rho C_ij (t cancels, varphi_j does not); what that sum is off by in a later sweep is part of the rise (active_rise).
+DROT_FN bool active_entry(float t, float vp, float ph, float tau) {
+  return (t + ph) + tau > -kLeanEps * (((fabsf(t) + fabsf(vp)) + fabsf(ph)) + tau);
+}
+DROT_FN bool active_line(float bound, float rise, float mag, float ph, float tau) {
+  return ((bound + rise) + ph) + tau > -kLeanEps * (((fabsf(bound) + mag) + fabsf(ph)) + tau);
+}
+// How far a number of phi or varphi has risen, and two rises, or a rise and one that is known already, together.
+DROT_FN float active_rise(float now, float from) { return (now - from) + kLeanEps * (fabsf(now) + fabsf(from)); }
+DROT_FN float active_rises(float a, float b) { return (a + b) + kLeanEps * (fabsf(a) + fabsf(b)); }
+
 // When the lean sweep renews its bounds, the classic rent-or-buy rule: reading lines in vain (zero before and zero after:
 // the bounds failed to certify them) is the rent, renewing the bounds (all of C once) the purchase.  Renew when the rent
 // paid since the last renewal has reached the price.  That stays within a factor 2 of the best schedule in hindsight,

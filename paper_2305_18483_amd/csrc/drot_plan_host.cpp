@@ -164,6 +164,17 @@ void drot_certify_lines(int count, float rho, const float* m1, const float* belo
     out[k] = certified_line(m1[k], line_decode(line_code(below[k], base), base), drift[k], mag[k], phi[k]);
 }
 
+// Which of `count` zero entries, and lines of entries, a list of active entries would hold; the rises it is checked with.
+void drot_active_entries(int count, const float* t, const float* varphi, const float* phi, const float* tau, unsigned char* out) {
+  for (int k = 0; k < count; ++k) out[k] = active_entry(t[k], varphi[k], phi[k], tau[k]);
+}
+void drot_active_lines(int count, const float* bound, const float* rise, const float* mag, const float* phi, const float* tau, unsigned char* out) {
+  for (int k = 0; k < count; ++k) out[k] = active_line(bound[k], rise[k], mag[k], phi[k], tau[k]);
+}
+void drot_active_rises(int count, const float* now, const float* from, const float* other, float* rise, float* both) {
+  for (int k = 0; k < count; ++k) both[k] = active_rises(rise[k] = active_rise(now[k], from[k]), other[k]);
+}
+
 // The renewals of `count` lean sweeps, waste[k] the lines the k-th reads in vain unless it renews the bounds: renewed[k].
 void drot_renewals(int count, const int* waste, int price, int max_since, unsigned char* renewed) {
   Renewal R{0, 0, 0};

@@ -310,6 +310,65 @@ def test_what_the_certificates_of_the_sweep_by_lines_pass_stays_zero(planlib):
             assert certify(planlib.drot_certify_segments, m1, m2, drift1, drift, mag, low).mean() > 0.5
 
 
+def test_what_a_list_of_active_entries_leaves_out_stays_zero(planlib):
+    # zero entries within a few units in the last place of the edge, with costs that cancel potentials up to 2^20 times as large as what
+    # is left: an entry or a line that is not listed stays zero in the sweep behind the list, and in any later one that a rise below the
+    # slack leads to, phi and varphi moving as they like
+    f = np.float32
+    fp, up = ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_ubyte)
+
+    def call(entry, outs, *arrays):
+        held = [np.ascontiguousarray(a, dtype=f) for a in arrays]
+        entry(len(held[0]), *[a.ctypes.data_as(fp) for a in held], *[o.ctypes.data_as(up if o.dtype == np.uint8 else fp) for o in outs])
+
+    def listed(entry, *arrays):
+        out = np.zeros(len(arrays[0]), dtype=np.uint8)
+        call(entry, [out], *arrays)
+        return out.astype(bool)
+
+    def rises(now, was, other):
+        one, both = np.zeros(now.size, dtype=f), np.zeros(now.size, dtype=f)
+        call(planlib.drot_active_rises, [one, both], now.ravel(), was.ravel(), other.ravel())
+        return one.reshape(now.shape), both.reshape(now.shape)
+
+    # (the sweep clamps fmaf(-rho, c, varphi + phi): its sign is that of the rounded sum less the exact product)
+    positive = lambda c, vp, ph: (vp + ph).astype(f).astype(np.float64) > float(rho) * c.astype(np.float64)  # noqa: E731
+    rng = np.random.default_rng(29)
+    N, rho, small = 200000, f(2.0 / 4000), 1.0e-4
+    for ratio in (1.0, 2.0 ** 8, 2.0 ** 14, 2.0 ** 20):
+        for slack in (0.0, 1e-3, 1.0):
+            phi = (small * rng.uniform(-1, 1, N)).astype(f)
+            varphi = (ratio * small * rng.uniform(-1, 1, (N, 4))).astype(f)
+            tau = np.full(N, slack * small, dtype=f)
+            unit = 2.0 ** -24 * (np.abs(varphi) + np.abs(phi)[:, None] + tau[:, None]).astype(np.float64)
+            edge = varphi.astype(np.float64) + phi[:, None] + tau[:, None]
+            cost = ((edge + rng.uniform(-24, 48, (N, 4)) * unit) / float(rho)).astype(f)
+            t = (-float(rho) * cost.astype(np.float64) + varphi).astype(f)
+            # later: they rise and fall by much, together by less than the slack as it is checked
+            fall = small * rng.uniform(0, 2, N) * rng.choice([0.0, 1.0], N)
+            later_phi = (phi + fall + tau * rng.uniform(-0.5, 1.0, N)).astype(f)
+            later = (varphi - fall[:, None]).astype(f)
+            up_cols = rises(later, varphi, np.zeros_like(later))[0].max(axis=1)
+            lasts = rises(later_phi, phi, up_cols)[1] < tau
+            assert slack == 0.0 or ratio > 2.0 ** 8 or lasts.mean() > 0.1
+            for e in range(4):
+                out = ~listed(planlib.drot_active_entries, t[:, e], varphi[:, e], phi, tau)
+                assert not (out & positive(cost[:, e], varphi[:, e], phi)).any(), (ratio, slack)
+                assert not (out & lasts & positive(cost[:, e], later[:, e], later_phi)).any(), (ratio, slack)
+                assert 0.05 < out.mean() < 0.95  # (neither all nor nothing)
+            # the four as a line whose bound is of an earlier varphi, or was made exact after some rise
+            earlier = (varphi + ratio * small * rng.uniform(-1, 1, (N, 4)) * rng.choice([0.0, 0.01], (N, 1))).astype(f)
+            top = (-float(rho) * cost.astype(np.float64) + earlier).astype(f).max(axis=1)
+            rise = rises(varphi, earlier, np.zeros_like(varphi))[0].max(axis=1)
+            before = (ratio * small * rng.uniform(-1, 1, N)).astype(f)
+            mag = np.abs(varphi).max(axis=1)
+            for bound, risen in ((top, rise), ((t.max(axis=1) - before).astype(f), before)):
+                out = ~listed(planlib.drot_active_lines, bound, risen, np.abs(risen) + mag, phi, tau)
+                for e in range(4):
+                    assert not (out & positive(cost[:, e], varphi[:, e], phi)).any(), (ratio, slack)
+                    assert not (out & lasts & positive(cost[:, e], later[:, e], later_phi)).any(), (ratio, slack)
+
+
 def test_the_sweep_by_lines_renews_when_the_rent_has_reached_the_price(planlib):
     def renewals(waste, price, max_since):
         w = np.ascontiguousarray(waste, dtype=np.int32)
