@@ -318,31 +318,16 @@ __device__ __forceinline__ double active_signed(u64 w) {
   const int e = e10 == 0 ? 0 : e10 == 0x3ff ? 0x7ff : e10 + 511;
   return __builtin_bit_cast(double, (w >> 62 & 1ull) << 63 | (u64)e << 52 | (w & ((1ull << 52) - 1ull)));
 }
-// grid_gather for such words, and for words with a tag beside them: what has come is not asked for again.
-template <int NA, int NB, int PAUSE>
-__device__ __forceinline__ void active_gather(const u64* half, u64 (&a)[NA], const unsigned (&at_a)[NA], unsigned phase, u64 (&b)[NB],
-                                              const unsigned (&at_b)[NB], unsigned tag, int limit, bool& lost) {
-  bool has_a = false, has_b = NB == 1;  // (one word: none)
+// grid_gather for such words.
+template <int N, int PAUSE>
+__device__ __forceinline__ void active_gather(const u64* half, u64 (&v)[N], const unsigned (&at)[N], unsigned phase, int limit, bool& lost) {
   for (int polls = 1;; ++polls) {
-    if (!has_a) {
-#pragma unroll
-      for (int k = 0; k < NA; ++k) a[k] = grid_load(half, at_a[k]);
-    }
-    if (!has_b) {
-#pragma unroll
-      for (int k = 0; k < NB; ++k) b[k] = grid_load(half, at_b[k]);
-    }
     bool there = true;
 #pragma unroll
-    for (int k = 0; k < NA; ++k) there = there && (unsigned)(a[k] >> 63) == phase;
-    has_a = __builtin_amdgcn_ballot_w64(!there) == 0;
-    if (NB > 1) {
-      there = true;
+    for (int k = 0; k < N; ++k) v[k] = grid_load(half, at[k]);
 #pragma unroll
-      for (int k = 0; k < NB; ++k) there = there && (unsigned)(b[k] >> 32) == tag;
-      has_b = __builtin_amdgcn_ballot_w64(!there) == 0;
-    }
-    if (has_a && has_b) return;
+    for (int k = 0; k < N; ++k) there = there && (unsigned)(v[k] >> 63) == phase;
+    if (__builtin_amdgcn_ballot_w64(!there) == 0) return;
     if (polls >= limit) {
       lost = true;
       return;
@@ -998,9 +983,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     if (!keeper && block(0) < nblk) {
       const ActiveArgs& A = late_active_args();
       const SweepArgs& S = A.S;
-      u64 v[2 * kActOwned], none[1];
+      u64 v[2 * kActOwned];
       unsigned at[2 * kActOwned];
-      const unsigned at_none[1] = {0};
 #pragma unroll
       for (int o = 0; o < kActOwned; ++o) {
         const int blk = block(o) < nblk ? block(o) : block(0);
@@ -1010,7 +994,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
 #pragma unroll
         for (int w = 0; w < 2; ++w) at[2 * o + w] = (unsigned)((blk * kActSide + min((lane >> 3) + 8 * w, shares - 1)) * kGridBlock + e);
       }
-      active_gather<2 * kActOwned, 1, kActPause>(half, v, at, phase, none, at_none, tag, A.polls, lost);
+      active_gather<2 * kActOwned, kActPause>(half, v, at, phase, A.polls, lost);
 #pragma unroll
       for (int o = 0; o < kActOwned; ++o) {
         const int blk = block(o);
@@ -1151,16 +1135,15 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       const ActiveArgs& A = late_active_args();
       const SweepArgs& S = A.S;
       // (the words that are the same for everybody: one wave asks for them, the last, which has the least to do)
-      u64 v[kActTasks], none[1];
+      u64 v[kActTasks];
       unsigned at[kActTasks];
-      const unsigned at_none[1] = {0};
 #pragma unroll
       for (int k = 0; k < kActTasks; ++k) {  // (a task of nothing asks for the wave's first word, or for the first of all)
         const Task T = task(k);
         const unsigned ent = A.ent_word + (unsigned)((T.rows ? 0 : A.nblk_m * kGridBlock) + T.first + min(lane, T.count - 1));
         at[k] = T.count > 0 ? ent : k > 0 ? at[0] : A.ent_word;
       }
-      active_gather<kActTasks, 1, kActPause>(half, v, at, phase, none, at_none, tag, A.polls, lost);
+      active_gather<kActTasks, kActPause>(half, v, at, phase, A.polls, lost);
       if (wave == kActWaves - 1) {
         u64 w[3];
         const unsigned cst_at = A.cst_word + 32u * (blockIdx.x % kGridCopies);
