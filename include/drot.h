@@ -178,7 +178,8 @@ int drot_destroy(drot_handle h);
  *       otherwise the two-pass path (any labels, 20 bytes per element); 1 forces the two-pass path.  Up to 512 such pieces
  *       (256 of classes of more than 512 rows) stay in the registers of the GPU for all the iterations of a call, the same bits.
  *   DROT_OPT_GRID_POLLS [33554432], 1 .. 1073741824: how often a workgroup of a cooperative launch asks for a
- *       number that another one owes it before the launch gives up (the default is about half a minute).  Such a
+ *       number that another one owes it before the launch gives up (the default is about half a minute; an attempt behind
+ *       a rest, which some of these waits take, counts for three).  Such a
  *       launch needs all its workgroups on the GPU at once; where it gives up, or is not accepted, the handle
  *       launches every sweep by itself from then on (every handle of the process, where the runtime has no such
  *       launches for it: it lets one process at a time have them on a GPU).  A solve that starts from X_0 = 0 is run again that way, within

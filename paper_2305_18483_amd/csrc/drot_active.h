@@ -332,8 +332,12 @@ __device__ __forceinline__ void active_gather(const u64* half, u64 (&v)[N], cons
       lost = true;
       return;
     }
-    if (polls >= kGridPatience) __builtin_amdgcn_s_sleep(kGridRest);
-    else if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
+    if (polls >= kGridPatience) {
+      __builtin_amdgcn_s_sleep(kGridRest);
+      polls += kGridRestPolls - 1;
+    } else if (PAUSE > 0) {
+      __builtin_amdgcn_s_sleep(PAUSE);
+    }
   }
 }
 
@@ -1134,7 +1138,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     {
       const ActiveArgs& A = late_active_args();
       const SweepArgs& S = A.S;
-      // (the words that are the same for everybody: one wave asks for them, the last, which has the least to do)
+      // (the words that are the same for everybody: one wave asks for them, the last, which has the least to do.  A wave that has lost a
+      // word asks once for the others: what the waits of a launch add up to is one in hop 1 and one in hop 2, of another wave)
       u64 v[kActTasks];
       unsigned at[kActTasks];
 #pragma unroll
@@ -1143,12 +1148,13 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
         const unsigned ent = A.ent_word + (unsigned)((T.rows ? 0 : A.nblk_m * kGridBlock) + T.first + min(lane, T.count - 1));
         at[k] = T.count > 0 ? ent : k > 0 ? at[0] : A.ent_word;
       }
-      active_gather<kActTasks, kActPause>(half, v, at, phase, A.polls, lost);
+      const int polls = lost ? 1 : A.polls;
+      active_gather<kActTasks, kActPause>(half, v, at, phase, polls, lost);
       if (wave == kActWaves - 1) {
         u64 w[3];
         const unsigned cst_at = A.cst_word + 32u * (blockIdx.x % kGridCopies);
         const unsigned at_w[3] = {cst_at, cst_at + 1u, cst_at + 2u};
-        grid_gather<3, 1, true>(half, w, at_w, tag, A.polls, lost);
+        grid_gather<3, 1, true>(half, w, at_w, tag, lost ? 1 : polls, lost);
         if (lane == 0) {
           constant = grid_value(w[0], w[1]);
           to_do = (unsigned)w[2];

@@ -58,6 +58,8 @@ constexpr int kGridPollsMax = 1 << 30;
 // waiting for the answer of a check, the words of one owner out of 2500 did not reach the memory-side cache in 300000
 // attempts (a third of a second), one check in ten, and in none of hundreds once the waves rest between attempts.
 constexpr int kGridPatience = 32, kGridRest = 64;  // (rest: 4096 cycles, 1.7 us)
+constexpr int kGridRestPolls = 3;  // ... and an attempt behind one, 2.6 us where others take 0.9, counts for three of them:
+static_assert((long long)kGridPolls / kGridRestPolls * 2600 < 30000000000ll, "half a minute");
 constexpr int kGridBlock = 8;    // rows or columns per owner wave
 constexpr int kGridCopies = 32;  // of 2 eta - theta: workgroup b reads copy b % kGridCopies
 
@@ -156,8 +158,12 @@ __device__ __forceinline__ void grid_gather(const u64* half, u64 (&v)[N], const 
       lost = true;
       return;
     }
-    if (REST && polls >= kGridPatience) __builtin_amdgcn_s_sleep(kGridRest);
-    else if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
+    if (REST && polls >= kGridPatience) {
+      __builtin_amdgcn_s_sleep(kGridRest);
+      polls += kGridRestPolls - 1;
+    } else if (PAUSE > 0) {
+      __builtin_amdgcn_s_sleep(PAUSE);
+    }
   }
 }
 

@@ -169,6 +169,38 @@ def test_active_entries_of_point_clouds_across_options(drot, off, order):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("points", [False, True])
+def test_a_launch_of_active_entries_that_gives_up_is_replaced_by_single_launches(drot, points):
+    # one attempt per wait: every workgroup returns by itself.  A cold start comes out all the same, a warm one says that it has lost its point
+    m, n = 3585, 3329
+    dev = torch.device("cuda:0")
+    P = drot_inputs.random_problem(m, n, seed=4600, d=5)
+    C, xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
+    scale = 1.0 / float((torch.cdist(xs, xt) ** 2).max())
+    kw = dict(max_iters=200, tol=1e-12)
+
+    def solve(solver, **more):
+        return solver.solve_points(xs, xt, scale, p, q, **kw, **more) if points else solver.solve(C, p, q, **kw, **more)
+
+    def state(solver, res):
+        return res.X.clone(), *solver.duals(m, n, dev), res.objective, res.r_row, _checks(solver)
+
+    single, solver = drot.Solver(m, n), drot.Solver(m, n)
+    single.set_fused_update(0)
+    ref = state(single, solve(single))
+    _say(f"a launch that gives up, points {points}")
+    solver.set_grid_polls(1)
+    for _ in range(2):
+        got = state(solver, solve(solver))
+        assert all(torch.equal(a, b) if torch.is_tensor(a) else a == b for a, b in zip(got, ref))
+        assert solver.cooperative_launches() == (1, 0, 1)
+    solver = drot.Solver(m, n)
+    solver.set_grid_polls(1)
+    with pytest.raises(drot.DrotError) as e:
+        solve(solver, X_out=ref[0].clone(), phi0=ref[1], varphi0=ref[2])
+    assert e.value.code == drot.binding.DROT_ERR_HIP and solver.cooperative_launches() == (1, 0, 1)
+
+
 def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot):
     # row i holds its mass near column i: the workgroups on the diagonal of 16 x 16 have sixteen times their part of the entries, and
     # a quadratic term of middling strength keeps dozens of them in every row
