@@ -268,6 +268,22 @@ int drot_get_profile(drot_handle h, drot_sweep_timing* out, int capacity, int* c
 int drot_get_launches(drot_handle h, int* accepted, int* refused, int* given_up);
 
 /*
+ * Those of them that iterated on active entries (DROT_OPT_SCREENING) and did not give up: how many there were; how many ended before
+ * their first iteration, because the entries did not fit on the chip; ended later for that reason; ended because a list would not
+ * have lasted; and the iterations and lists of all of them.  (Where one ends early, the sweeps over everything go on, the same
+ * bits.)  Errors: INVALID_ARG.
+ */
+typedef struct {
+  int launches;
+  int misfits;
+  int outgrown;
+  int short_lists;
+  long long iterations;
+  long long lists;
+} drot_active_runs;
+int drot_get_active(drot_handle h, drot_active_runs* out);
+
+/*
  * Solve problem (1) by the iteration of eq. (8) + eq. (6), starting from X_0 = 0 and the
  * phi_0, varphi_0 of the Initialization paragraph.
  *

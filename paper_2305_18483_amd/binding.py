@@ -24,7 +24,7 @@ DROT_STATIC_MAX_M = DROT_STATIC_MAX_N = 4096
 # every symbol include/drot.h declares
 EXPORTED_SYMBOLS = (
     "drot_create", "drot_destroy", "drot_set_option", "drot_set_gap_tolerance", "drot_get_checks", "drot_get_profile",
-    "drot_get_launches",
+    "drot_get_launches", "drot_get_active",
     "drot_solve", "drot_solve_points", "drot_solve_warm", "drot_solve_points_warm", "drot_solve_static", "drot_get_info", "drot_get_duals",
     "drot_strerror",
 )
@@ -57,6 +57,11 @@ class drot_sweep_timing(ctypes.Structure):
                 ("x_fraction", ctypes.c_double)]
 
 
+class drot_active_runs(ctypes.Structure):
+    _fields_ = [("launches", ctypes.c_int), ("misfits", ctypes.c_int), ("outgrown", ctypes.c_int), ("short_lists", ctypes.c_int),
+                ("iterations", ctypes.c_longlong), ("lists", ctypes.c_longlong)]
+
+
 class DrotError(RuntimeError):
     def __init__(self, code: int, what: str):
         super().__init__(f"{what}: {strerror(code)} (code {code})")
@@ -84,6 +89,7 @@ def load_library() -> ctypes.CDLL:
     lib.drot_get_checks.argtypes = [vp, ctypes.POINTER(drot_check), ci, ctypes.POINTER(ci)]
     lib.drot_get_profile.argtypes = [vp, ctypes.POINTER(drot_sweep_timing), ci, ctypes.POINTER(ci)]
     lib.drot_get_launches.argtypes = [vp, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(ci)]
+    lib.drot_get_active.argtypes = [vp, ctypes.POINTER(drot_active_runs)]
     lib.drot_solve.argtypes = [vp, vp, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf, vp, vp]
     lib.drot_solve_warm.argtypes = [vp, vp, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf, vp, vp, vp, vp]
     lib.drot_solve_points.argtypes = [vp, vp, vp, ci, cf, vp, vp, ci, ci, cf, ci, ctypes.POINTER(drot_reg_params), ci, cf,
@@ -270,6 +276,14 @@ class Solver:
         if rc != DROT_OK:
             raise DrotError(rc, "drot_get_launches")
         return tuple(k.value for k in n)
+
+    def active_runs(self) -> drot_active_runs:
+        """drot_get_active: launches on the active entries since the handle was created, and how they ended."""
+        runs = drot_active_runs()
+        rc = self._lib.drot_get_active(self._h, ctypes.byref(runs))
+        if rc != DROT_OK:
+            raise DrotError(rc, "drot_get_active")
+        return runs
 
     def solve(self, C: torch.Tensor, p: torch.Tensor, q: torch.Tensor, *, stepsize: float = 0.0,
               reg_kind: int = DROT_REG_NONE, lam: float = 0.0, mu: float = 0.0,

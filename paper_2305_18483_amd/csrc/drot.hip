@@ -165,6 +165,7 @@ struct drot_handle_s {
   int compute_units = 0;
   int grid_polls = kGridPolls;
   int launches_accepted = 0, launches_refused = 0, launches_given_up = 0;
+  drot_active_runs active_runs = {};
   u64* xchg = nullptr;
   size_t xchg_len = 0;
   unsigned xchg_tag = 0;
@@ -1130,10 +1131,16 @@ int iterate(Solve& Z, bool* converged_out) {
                               hipMemcpyDeviceToHost, stream));
       DROT_HIP(hipStreamSynchronize(stream));
       if (h->host_run->status.broken) return kGridGaveUp;
-      const int ran = h->host_run->active.iters;
+      const ActiveRecord& record = h->host_run->active;
+      const int ran = record.iters;
       const int made = ran >= chunk ? most : ran > first ? 1 + (ran - 1 - first) / every : 0;
       converged = record_run(h, h->host_run->checks, made);
-      plan::active_done(Z.T, Z.P, ran, h->host_run->active.why != kActDone);
+      drot_active_runs& runs = h->active_runs;
+      ++runs.launches;
+      if (record.why != kActDone) ++(ran == 0 ? runs.misfits : record.why == kActAbort ? runs.outgrown : runs.short_lists);
+      runs.iterations += ran;
+      runs.lists += record.lists;
+      plan::active_done(Z.T, Z.P, ran, record.why != kActDone);
       if (ran == chunk || converged) Z.tested_k = Z.T.k;
       continue;
     }
@@ -1690,6 +1697,12 @@ int drot_get_launches(drot_handle h, int* accepted, int* refused, int* given_up)
   *accepted = h->launches_accepted;
   *refused = h->launches_refused;
   *given_up = h->launches_given_up;
+  return DROT_OK;
+}
+
+int drot_get_active(drot_handle h, drot_active_runs* out) {
+  if (!h || !out) return DROT_ERR_INVALID_ARG;
+  *out = h->active_runs;
   return DROT_OK;
 }
 

@@ -58,9 +58,8 @@ static_assert(2 * 4 * kActLocal <= kActTasks * kActWaves, "tasks");
 enum { kActDone = 0, kActLeave = 1, kActAbort = 2 };
 struct ActiveRecord {
   int iters;    // iterations done
-  int why;      // kActDone: all, or a check passed; else the entries no longer fit
+  int why;      // kActDone: all, or a check passed; kActLeave: a list would not have lasted; kActAbort: the entries do not fit
   int lists;    // times listed
-  int entries;  // of the keeper, at the end
 };
 
 struct ActiveArgs {
@@ -1300,6 +1299,5 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     A.record->iters = it;
     A.record->why = why;
     A.record->lists = lists;
-    A.record->entries = cnt;
   }
 }

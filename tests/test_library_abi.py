@@ -50,6 +50,7 @@ def test_argument_validation_without_a_gpu(lib):
     assert lib.drot_set_gap_tolerance(None, 0.1) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_get_info(None, None) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_get_launches(None, None, None, None) == binding.DROT_ERR_INVALID_ARG
+    assert lib.drot_get_active(None, None) == binding.DROT_ERR_INVALID_ARG
     assert lib.drot_solve(None, None, None, None, 1, 1, 0.0, 0, None, 1, 0.0, None, None) == binding.DROT_ERR_INVALID_ARG
     for code in (0, 1, -1, -2, -3, -4, 99):
         assert isinstance(binding.strerror(code), str) and binding.strerror(code)
@@ -62,6 +63,7 @@ def test_struct_layouts_match_the_header():
     assert ctypes.sizeof(binding.drot_info) == 40
     assert binding.drot_info.objective.offset == 16
     assert ctypes.sizeof(binding.drot_check) == 40 and binding.drot_check.objective.offset == 16
+    assert ctypes.sizeof(binding.drot_active_runs) == 32 and binding.drot_active_runs.iterations.offset == 16
     assert ctypes.sizeof(binding.drot_sweep_timing) == 24 and binding.drot_sweep_timing.c_fraction.offset == 8
     assert ctypes.sizeof(binding.drot_reg_params) == 32
     assert binding.drot_reg_params.row_class.offset == 16
