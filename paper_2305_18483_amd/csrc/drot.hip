@@ -698,6 +698,7 @@ int enqueue_active(Solve& Z, int iters) {
   const long long age = now - (left ? Z.T.bound_gen : Z.T.epoch_gen);
   A.age = age > 0 ? (int)age : 1;
   A.target = plan::kActiveTarget;
+  A.shortest = (float)plan::active_shortest(Z.P, S);
   // (phi and varphi, of masses that add up to 1, rise by some 10 / (m + n)^2 together in an iteration, whatever the costs' size)
   A.tau0 = 10.f * (float)plan::kActiveTarget / ((float)(Z.m + Z.n) * (float)(Z.m + Z.n));
   void* args[] = {&A};

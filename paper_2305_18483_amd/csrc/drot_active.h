@@ -103,6 +103,7 @@ struct ActiveArgs {
   int age;                // iterations since `since`
   float tau0;             // slack where nothing is known about how fast phi and varphi rise
   int target;             // iterations a list is meant to last
+  float shortest;         // ... and has to, to be worth making
 };
 
 // How the 64 entries of a wave's lanes, sorted, are added up.  Made when the entries are listed, good for as long as the list.
@@ -465,10 +466,6 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
   float rate = -1.f;         // rise per iteration (not known: negative)
   float risen_last = 0.f;    // ... of phi and varphi together since the list, at the last look
   int since_list = 0, lists = 0;
-  // Iterations that a list has to be good for to be worth making: it takes 75 to 150 us, a sweep over everything 12 to 20 us longer
-  // than an iteration here, with costs formed from points 25 and up (4001 x 3999: 83 us).  At 8 for stored costs 7000 x 7100
-  // takes 11.9 ms where the sweeps take 10.2, and 10.3 at 16.
-  constexpr float kActShort = POINTS ? 3.f : 16.f;
   int ask = 0;               // 1: a new list soon; 2: leave behind the next iteration; 4: this workgroup has no list
   bool relist = true, have_list = false;
   __syncthreads();
@@ -847,8 +844,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       if (fits) order();
       if (fits) break;
       row_pieces = col_pieces = 0;
-      if (tau == 0.f || (rate >= 0.f && ((fresh && !POINTS) || 0.5f * tau < kActShort * rate))) break;
-      tau = active_uniform(rate >= 0.f ? fmaxf(0.3f * tau, kActShort * rate) : attempt == 3 ? 0.f : 0.25f * tau);
+      if (tau == 0.f || (rate >= 0.f && ((fresh && !POINTS) || 0.5f * tau < A.shortest * rate))) break;
+      tau = active_uniform(rate >= 0.f ? fmaxf(0.3f * tau, A.shortest * rate) : attempt == 3 ? 0.f : 0.25f * tau);
       __syncthreads();
     }
     active_each<kActTasks>([&](auto k) __attribute__((always_inline)) {
@@ -860,7 +857,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       ask = 4;
       return;
     }
-    if (rate >= 0.f ? tau < kActShort * rate : tau == 0.f) ask = 2;  // (a list that does not last)
+    if (rate >= 0.f ? tau < A.shortest * rate : tau == 0.f) ask = 2;  // (a list that does not last)
     for (int e = t; e < kActLocal * kActRows; e += kActThreads) (&U.f.rowseg[0][0])[e] = 0.f;
     for (int e = t; e < 4 * kActRows; e += kActThreads) reinterpret_cast<float*>(U.f.share)[e] = 0.f;
     have_list = true;

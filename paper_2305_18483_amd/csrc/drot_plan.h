@@ -97,6 +97,15 @@ constexpr int kActiveLeast = 16;       // shorter calls are not worth a list
 // iterations) 14.6, 13.6, 13.7 ms; 20000 x 20000 (500) 18.45, 18.6, 18.8; point clouds 4001 x 3999 (400) 7.7, 6.1, 5.0; 12000 x 12100, quadratic
 // (400) 16.25, 15.9, 15.5 (does not fit at 48).
 constexpr int kActiveTarget = 20;
+// ... and has to last to be worth making.  A list takes 75 to 150 us (300 where the plan is dense), of point clouds of few dimensions 150 to 300.  A sweep over everything takes
+// 12 to 20 us longer than an iteration on the active entries over a stored cost (7000 x 7100 with lists of 8 iterations and up 11.9 ms, with
+// sweeps alone 10.2, with lists of 16 and up 10.3); over point clouds, d = 2 or 3, a third of a nanosecond per row segment.  Point clouds with lists
+// of 3, of 6 and of 10 iterations and up, ms (and with sweeps alone): 75000 row segments (7552 x 2460, 211 iterations) 14.6, 12.2, 9.0 (12.1);
+// 80000 (5000 x 4000, 400) 16.9, 16.9, 15.8 (16.6); 128000 (3875 x 8384, 200) 17.6, 11.3, 11.1 (13.4); 200000 (7480 x 6816, 200) 10.7, 10.7, 13.9
+// (18.7); 324000 (9000 x 9000, 400) 51.8, 47.8, 47.6 (44.8); 564000 (12000 x 12000, 200) 13.5, 13.6, 17.1 (30.3), with d = 2 39.5, 35.8, 35.5 (40.3).
+constexpr int kActiveShortest = 16, kActiveShortestPoints = 10, kActiveShortestPointsLarge = 6, kActivePointsLarge = 150000;
+// Point clouds whose entries did not fit are tried again early where this share, or less, of the row segments is left that held something then.
+constexpr double kActiveFallen = 0.8;
 constexpr int kPromptLooksUntil = 128; // ... of which the host waits for those of a point-cloud solve until the plan is sparse
 constexpr int kEarlyLooksUntil = 512;  // cold starts: extra density readings over this many iterations
 
@@ -302,6 +311,8 @@ struct State {
   long long bound_gen = -1;      // iteration whose varphi the bounds by line that a launch of active entries left are against
   long long recorded_gen = -1;   // sweep over point clouds that last recorded bounds by line: not every epoch of theirs has some
   int active_from = 0;           // no such launch before this iteration of the call
+  int active_again = 0;          // ... or, once the plan has thinned out since, before this one
+  double active_density = -1.0;  // plan_density when the last one that ended early started
   int active_left = 0;           // launches of them that ended early
   bool active_ran = false;
   bool last_lean = false;        // the sweep before the next status is a lean one
@@ -375,8 +386,9 @@ inline Stretch next_stretch(const Static& S, const Problem& P, const Options& O,
       // become sparse costs 10 ms of 44 at 12000 x 12000, waiting 10 us a look)
       const bool often = P.from_points && k < kPromptLooksUntil && !(T.plan_density >= 0.0 && T.plan_density < kPointsSparse);
       const int next = k < 16 ? 16 : often ? (k / 8 + 1) * 8 : (k / 32 + 1) * 32;
-      // (and where the active entries could be listed: a sweep by lines takes three times an iteration of theirs)
-      R.prompt = often || (S.active && !P.single_launches && !P.from_points && !T.active_ran && next <= kPromptLooksUntil);
+      // (and where the active entries could be listed: a sweep by lines takes three times an iteration of theirs; over point clouds, where
+      // they did not fit: the plan soon fills up then, 13.7 ms in place of 17.0 for 400 iterations of 3585 x 3329 in two dimensions)
+      R.prompt = often || (S.active && !P.single_launches && next <= kPromptLooksUntil && (P.from_points ? T.active_left > 0 : !T.active_ran));
       if (next - k < R.chunk) {
         R.chunk = next - k;
         R.probe = true;
@@ -593,13 +605,20 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
 // Whether the next iterations run on the active entries: the plan is known to be thin enough, X in memory is plain, its
 // flags and the screening bounds describe it, and the call is not about to end.
 inline bool active_next(const Static& S, const Problem& P, const State& T) {
-  if (!S.active || P.single_launches || T.k < T.active_from || P.max_iters - T.k < kActiveLeast) return false;
+  if (!S.active || P.single_launches || P.max_iters - T.k < kActiveLeast) return false;
+  if (T.k < T.active_from && (T.k < T.active_again || T.plan_density > kActiveFallen * T.active_density)) return false;
   const long long now = T.k_base + T.k;
   if (!T.materialized || T.dense_plan || T.sums_gen != now || T.epoch_gen < 0 || T.epoch_gen > now) return false;
   if (active_bounds(P, T) == kNoBounds) return false;
   const double room = kActiveFill * (double)kActiveEntries * (kActiveSide * kActiveSide);
   if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kActivePoints && T.plan_density * P.m * S.nseg <= room;
   return T.by_lines && !T.dense_lines && T.lines >= 0.0 && T.lines * P.m * ceil_div(P.n, 32) <= room;
+}
+
+// ... iterations a list of its entries has to last.
+inline int active_shortest(const Problem& P, const Static& S) {
+  if (!P.from_points) return kActiveShortest;
+  return (long long)P.m * S.nseg >= kActivePointsLarge ? kActiveShortestPointsLarge : kActiveShortestPoints;
 }
 
 // ... the iterations it may take: up to a check or the end of the call, drawn out over the checks that follow.
@@ -626,9 +645,15 @@ inline void active_done(State& T, const Problem& P, int iters, bool left) {
     T.last_lean = false;
   }
   if (left) {
-    // (early in a point-cloud solve every look finds a thinner plan, and a sweep over everything costs as much as an attempt)
-    const int again = P.from_points && T.k < kPromptLooksUntil ? 8 : 512;
-    T.active_from = T.k + (again << (T.active_left < 6 ? T.active_left : 6));
+    // (early in a point-cloud solve a look may find a thinner plan, and a sweep over everything costs half as much as an attempt;
+    // tried again whatever the look has found, 9000 x 9000 in two dimensions spent 2 ms of 48 on three more attempts in vain)
+    const int times = T.active_left < 6 ? T.active_left : 6;
+    T.active_from = T.k + (512 << times);
+    T.active_again = P.from_points && T.k < kPromptLooksUntil ? T.k + (8 << times) : T.active_from;
+    T.active_density = T.plan_density;
+    // (what the last look found is as old as the launch was long, and the plan has filled up where the entries no longer fit: over point clouds
+    // the sweeps that go by certificates, 120 us at 5000 x 4000 where the others take 27, wait for the next look)
+    if (P.from_points && iters > 0) T.plan_density = -1.0;
     ++T.active_left;
   }
 }

@@ -668,15 +668,36 @@ def test_launches_of_calls_without_checks_are_bounded_where_sweeps_were_launches
     assert stretch(1500, 1000, 100000) == 100000
 
 
+def _active(planlib, m, n, k=32, iters=1000, density=0.3, lines=0.03, by_lines=1, epoch=8, left=0, ago=0, before=0.3, units=256, single=0, reg_kind=1,
+            from_points=0, feedback=1, check_every=100, fused_update=-1, skip_cost=-1, skip_unchanged=-1, screening=-1, gap_every=0):
+    problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, 0, 0, 0, 1, 1, 0, 0, feedback, 1, iters)
+    options = (ctypes.c_int * 9)(check_every, -1, fused_update, skip_cost, skip_unchanged, screening, -1, 0, gap_every)
+    state = (ctypes.c_int * 8)(k, int(density * 1e6), int(lines * 1e6), by_lines, epoch, left, ago, int(before * 1e6))
+    out = (ctypes.c_int * 6)()
+    ever = planlib.drot_plan_active(problem, options, units, single, state, out)
+    return ever, tuple(out)
+
+
+def test_active_entries_of_point_clouds_that_did_not_fit(planlib):
+    def active(m=5000, n=4000, **kw):
+        return _active(planlib, m, n, from_points=1, lines=-1.0, **kw)[1]
+
+    # tried again early where the plan has thinned out since, and else like any other
+    assert active(k=40, left=1, ago=8, density=0.3, before=0.5)[0] > 0 and active(k=40, left=1, ago=7, density=0.3, before=0.5)[0] == 0
+    assert active(k=40, left=1, ago=8, density=0.41, before=0.5)[0] == 0 and active(k=40, left=2, ago=15, density=0.1, before=0.5)[0] == 0
+    assert active(k=700, left=1, ago=511, density=0.1, before=0.5)[0] == 0 and active(k=700, left=1, ago=512, density=0.5, before=0.3)[0] > 0
+    # what was known of the plan before such a launch is not known of it behind it, and the host waits for the next look
+    assert active(k=40)[3:5] == (-1, 1)
+    assert _active(planlib, 10000, 10000)[1][3:5] == (300000, 0)
+    # a list has to last the longer, the less a sweep over everything takes
+    assert active(2500, 15360, k=16)[5] == 6 and active(2499, 15360, k=16)[5] == 10 and active(20000, 20000, k=16)[5] == 6
+    assert _active(planlib, 10000, 10000)[1][5] == 16
+
+
 def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
-    def active(m, n, k=32, iters=1000, density=0.3, lines=0.03, by_lines=1, epoch=8, left=0, ago=0, units=256, single=0, reg_kind=1,
-               from_points=0, feedback=1, check_every=100, fused_update=-1, skip_cost=-1, skip_unchanged=-1, screening=-1, gap_every=0):
-        problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, 0, 0, 0, 1, 1, 0, 0, feedback, 1, iters)
-        options = (ctypes.c_int * 9)(check_every, -1, fused_update, skip_cost, skip_unchanged, screening, -1, 0, gap_every)
-        state = (ctypes.c_int * 7)(k, int(density * 1e6), int(lines * 1e6), by_lines, epoch, left, ago)
-        out = (ctypes.c_int * 3)()
-        ever = planlib.drot_plan_active(problem, options, units, single, state, out)
-        return ever, tuple(out)
+    def active(*args, **kw):
+        ever, out = _active(planlib, *args, **kw)
+        return ever, out[:3]
 
     # runs on through the checks, 4096 iterations or 256 checks at a time
     assert active(10000, 10000) == (1, (968, 42 + 512, 1))
