@@ -172,6 +172,7 @@ def _kernel_resources(tmp_path):
 
 def test_kernels_whose_workgroups_wait_for_one_another_use_no_scratch_memory(lib, tmp_path):
     # (spilled registers: a form of such a kernel that had them gave up waiting once, and what spills inside the loop costs time)
-    kernels = {k: v for k, v in _kernel_resources(tmp_path).items() if "grid_resident_kernel" in k or "grid_slab_kernel" in k}
-    assert len(kernels) == 8 + 5 + 10, sorted(kernels)
+    kernels = {k: v for k, v in _kernel_resources(tmp_path).items()
+               if any(name in k for name in ("grid_resident_kernel", "grid_slab_kernel", "grid_active_kernel"))}
+    assert len(kernels) == 8 + 5 + 10 + 2, sorted(kernels)
     assert all(scratch == 0 for scratch, _ in kernels.values()), {k: v for k, v in kernels.items() if v[0]}
