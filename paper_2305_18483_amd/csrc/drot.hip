@@ -69,7 +69,8 @@ static_assert(plan::kSlabCols == kSlabCols && plan::kSlabLanes == kSlabLanes && 
 static_assert(plan::kResidentMaxRows == kResidentMaxRows && plan::kResidentCols == kResidentCols, "resident kernel");
 static_assert(plan::kColGroup == kColGroup, "column-sum groups of the lean sweep");
 static_assert(plan::kGridBlock == kGridBlock, "owner blocks of the grid-resident kernel");
-static_assert(plan::kActiveSide == kActSide && plan::kActiveLocal == kActLocal && plan::kActiveEntries == kActEntries, "active entries");
+static_assert(plan::kActiveSide == kActSide && plan::kActiveLocal == kActLocal && plan::kActiveEntries == kActEntries &&
+              plan::kActiveShortest == kActShortest, "active entries");
 static_assert(plan::kStripRows == kStripRows && plan::kPointsColGroup == kPointsColGroup, "strips of the screened point-cloud sweep");
 
 // (e0, e1: events that take the start and the end of the kernel itself, as the hardware stamps them; null: none)
@@ -172,6 +173,7 @@ struct drot_handle_s {
   float *bound = nullptr, *bound_varphi = nullptr;  // active entries: bounds by line, made on demand, and the varphi they were left against
   size_t bound_len = 0, bound_varphi_len = 0;
   bool xchg_clean = false;  // no word carries a number above xchg_tag
+  bool xchg_zero = false;   // ... and every word is zero
   int* done = nullptr;
   DeviceStatus* status = nullptr;
   ActiveRecord* run_active = nullptr;
@@ -526,6 +528,7 @@ int ready_exchange(drot_handle h, size_t need, int iters, hipStream_t stream) {
     h->xchg_clean = true;
     hipLaunchKernelGGL(fill_kernel, dim3(1024), dim3(256), 0, stream, reinterpret_cast<float*>(h->xchg), 2 * h->xchg_len, 0.f,
                        (const int*)nullptr);
+    h->xchg_zero = true;
   }
   return DROT_OK;
 }
@@ -551,6 +554,7 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   const GridWords W = grid_words(S, Z.P);
   const int rc = ready_exchange(h, 2 * W.half, iters, Z.stream);
   if (rc != DROT_OK) return rc;
+  h->xchg_zero = false;
   GridArgs A{};
   A.S = Z.SA;
   A.S.rowpart = Z.rowp(last.sw);
@@ -631,6 +635,30 @@ int enqueue_grid(Solve& Z, const plan::Step& first, const plan::Step& last) {
   return e == hipSuccess ? DROT_OK : launch_refused(h, e);
 }
 
+// Where the words of one half of the exchange buffer start for a launch on the active entries, and how many there are (ActiveArgs).
+struct ActiveWords {
+  size_t ent, tot, sq, cst, half;
+};
+ActiveWords active_words(int m, int n) {
+  const size_t nblk = (size_t)ceil_div(m, kGridBlock) + (size_t)ceil_div(n, kGridBlock);
+  ActiveWords W;
+  W.ent = nblk * kActSide * kGridBlock;
+  W.tot = (W.ent + nblk * kGridBlock + 31) / 32 * 32;
+  W.sq = W.tot + (size_t)kActWgs * kActTotals;
+  W.cst = (W.sq + nblk * kActSquares + 31) / 32 * 32;
+  W.half = W.cst + 32 * kGridCopies;
+  return W;
+}
+
+// ... which starts from zeroed words, and leaves others than the next launch of any kind may find.
+int zero_exchange(drot_handle h, size_t need, int iters, hipStream_t stream) {
+  if (!h->xchg_zero) h->xchg_clean = false;
+  return ready_exchange(h, need, iters, stream);
+}
+
+// (phi and varphi, of masses that add up to 1, rise by some 10 / (m + n)^2 together in an iteration, whatever the costs' size)
+float active_tau0(const Solve& Z) { return 10.f * (float)plan::kActiveTarget / ((float)(Z.m + Z.n) * (float)(Z.m + Z.n)); }
+
 // Up to `iters` iterations on the active entries, with their vector updates and the checks of Z.check, from the state in
 // memory on.  kGridRefused: nothing has been enqueued that counts.
 int enqueue_active(Solve& Z, int iters) {
@@ -639,14 +667,10 @@ int enqueue_active(Solve& Z, int iters) {
   const long long now = Z.T.k_base + Z.T.k;
   const int nblk_m = ceil_div(Z.m, kGridBlock), nblk_n = ceil_div(Z.n, kGridBlock);
   const int ngroups = ceil_div(Z.m, 256);
-  const size_t nblk = (size_t)nblk_m + (size_t)nblk_n;
-  const size_t ent = nblk * kActSide * kGridBlock, tot = (ent + nblk * kGridBlock + 31) / 32 * 32;
-  const size_t sq = tot + (size_t)kActWgs * kActTotals;
-  const size_t cst = (sq + nblk * kActSquares + 31) / 32 * 32, half = cst + 32 * kGridCopies;
-  h->xchg_clean = false;  // (this launch starts from zeroed words, and leaves others than the next one of any kind may find)
-  const int rc = ready_exchange(h, 2 * half, iters, Z.stream);
-  h->xchg_clean = false;
+  const ActiveWords W = active_words(Z.m, Z.n);
+  const int rc = zero_exchange(h, 2 * W.half, iters, Z.stream);
   if (rc != DROT_OK) return rc;
+  h->xchg_clean = h->xchg_zero = false;
   ActiveArgs A{};
   A.S = Z.SA;
   A.S.rowpart = Z.rowp(now);
@@ -664,11 +688,11 @@ int enqueue_active(Solve& Z, int iters) {
   A.done = h->done;
   A.record = h->run_active;
   A.xchg = h->xchg;
-  A.half_words = (unsigned)half;
-  A.ent_word = (unsigned)ent;
-  A.tot_word = (unsigned)tot;
-  A.sq_word = (unsigned)sq;
-  A.cst_word = (unsigned)cst;
+  A.half_words = (unsigned)W.half;
+  A.ent_word = (unsigned)W.ent;
+  A.tot_word = (unsigned)W.tot;
+  A.sq_word = (unsigned)W.sq;
+  A.cst_word = (unsigned)W.cst;
   A.nseg = S.nseg;
   A.ngroups = ngroups;
   A.nblk_m = nblk_m;
@@ -695,12 +719,10 @@ int enqueue_active(Solve& Z, int iters) {
     A.lines = h->xlines;
     A.lines_known = Z.T.lines_gen == now ? 1 : 0;
   }
-  const long long age = now - (left ? Z.T.bound_gen : Z.T.epoch_gen);
-  A.age = age > 0 ? (int)age : 1;
+  A.age = plan::active_age(Z.P, Z.T);
   A.target = plan::kActiveTarget;
   A.shortest = (float)plan::active_shortest(Z.P, S);
-  // (phi and varphi, of masses that add up to 1, rise by some 10 / (m + n)^2 together in an iteration, whatever the costs' size)
-  A.tau0 = 10.f * (float)plan::kActiveTarget / ((float)(Z.m + Z.n) * (float)(Z.m + Z.n));
+  A.tau0 = active_tau0(Z);
   void* args[] = {&A};
   const void* kernel = Z.P.from_points ? reinterpret_cast<const void*>(grid_active_kernel<true>)
                                        : reinterpret_cast<const void*>(grid_active_kernel<false>);
@@ -795,6 +817,16 @@ void enqueue_status(Solve& Z, int k, bool test, bool gap_fresh) {
   Z.T.norms_pending = false;
   hipLaunchKernelGGL(status_kernel, dim3(1), dim3(1), 0, Z.stream, Z.V, k, test ? (double)Z.tol : 0.0,
                      test ? (double)Z.h->gap_tol : 0.0, gap_fresh ? 1 : 0);
+}
+
+// What a list of active entries would hold behind the sweeps so far, counted into the status block.
+void enqueue_forecast(Solve& Z) {
+  drot_handle h = Z.h;
+  const plan::Static& S = Z.S;
+  const long long now = Z.T.k_base + Z.T.k, age = now - Z.T.epoch_gen;
+  const ForecastArgs A{h->phi, h->varphi, h->varphi0, h->mprime, h->codes, Z.T.lines_gen == now ? h->xlines : nullptr, h->status, h->done, Z.m, Z.n,
+                       Z.SA.mp, S.nseg, ceil_div(Z.m, 256), Z.rho, active_tau0(Z), age > 0 ? (int)age : 1, plan::kActiveTarget, h->screen_ctl, Z.T.k};
+  hipLaunchKernelGGL(active_forecast_kernel, dim3(kActWgs), dim3(kActThreads), 0, Z.stream, A);
 }
 
 void record_check(drot_handle h, const DeviceStatus& st) {
@@ -1244,6 +1276,8 @@ int iterate(Solve& Z, bool* converged_out) {
     if (S.status_at_checks) {
       // the test runs on the device; the host reads it one stretch late so the queue never drains
       if (R.gap) enqueue_gap(Z, h->done, true);  // (behind the stop flag: it runs only if every sweep before it ran)
+      const bool forecast = R.prompt && plan::active_forecast(S, Z.P, Z.T);
+      if (forecast) enqueue_forecast(Z);
       enqueue_status(Z, Z.T.k, Z.P.checking && !R.probe, R.gap);
       if (!R.probe) Z.tested_k = Z.T.k;
       if (!Z.P.feedback) {  // (the stop flag alone ends the solve: the sweeps queued behind it return at once)
@@ -1253,8 +1287,14 @@ int iterate(Solve& Z, bool* converged_out) {
       DROT_HIP(hipMemcpyAsync(&h->host_status[slot], h->status, sizeof(DeviceStatus), hipMemcpyDeviceToHost, stream));
       DROT_HIP(hipEventRecord(h->ev[slot], stream));
       was_probe[slot] = R.probe;
+      // (while the host waits: 15 us less between the look and the launch)
+      if (forecast && !h->xchg_zero) (void)zero_exchange(h, 2 * active_words(Z.m, Z.n).half, 1, stream);
       int rc = checks > 0 ? read_status(slot ^ 1) : DROT_OK;
       if (rc == DROT_OK && R.prompt) rc = read_status(slot);  // (read again, to no effect, when the next stretch is queued)
+      if (rc == DROT_OK && forecast && !converged) {
+        const unsigned long long f = h->host_status[slot].forecast;
+        plan::on_forecast(Z.T, Z.P, (int)(f >> 32), (double)((unsigned)f >> kForecastBits), (int)(f & ((1u << kForecastBits) - 1u)));
+      }
       if (rc != DROT_OK) return rc;
       slot ^= 1;
       ++checks;

@@ -49,6 +49,7 @@ constexpr int kActTasks = 3;                   // a wave's shares of 64 rows or 
 constexpr int kActOwned = 2;                   // blocks of eight rows or columns per owner wave
 constexpr int kActLines = 8192;                // lines of C a workgroup looks at while listing
 constexpr int kActPause = 2;
+constexpr int kActShortest = 16;               // iterations a list over a stored cost has to last (point clouds: ActiveArgs)
 static_assert(kActEntries == 64 * 64 && kActLocal <= 5, "packed places; the units of a row");
 constexpr int kActTotals = 32;                 // words of a workgroup for its totals
 constexpr int kActSquares = 16;                // ... of an owned block for its squared residuals
@@ -100,10 +101,10 @@ struct ActiveArgs {
   const uint2* codes;
   unsigned char* lines;   // line flags of X, or null: none are kept
   int lines_known;        // they hold; else the row-segment sums do
-  int age;                // iterations since `since`
+  int age;                // iterations since `since`, at most
   float tau0;             // slack where nothing is known about how fast phi and varphi rise
   int target;             // iterations a list is meant to last
-  float shortest;         // ... and has to, to be worth making
+  float shortest;         // ... and has to, to be worth making (point clouds; over a stored cost the same everywhere)
 };
 
 // How the 64 entries of a wave's lanes, sorted, are added up.  Made when the entries are listed, good for as long as the list.
@@ -526,6 +527,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
   auto make_list = [&]() __attribute__((always_inline)) {
     if (have_list) put_back();
     const ActiveArgs& A = late_active_args();
+    auto shortest = [&]() __attribute__((always_inline)) { return POINTS ? A.shortest : (float)kActShortest; };
     const SweepArgs& S = A.S;
     const int lane = lane_again(), t = wave * 64 + lane;
     const bool fresh = lists == 0;
@@ -844,8 +846,8 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       if (fits) order();
       if (fits) break;
       row_pieces = col_pieces = 0;
-      if (tau == 0.f || (rate >= 0.f && ((fresh && !POINTS) || 0.5f * tau < A.shortest * rate))) break;
-      tau = active_uniform(rate >= 0.f ? fmaxf(0.3f * tau, A.shortest * rate) : attempt == 3 ? 0.f : 0.25f * tau);
+      if (tau == 0.f || (rate >= 0.f && ((fresh && !POINTS) || 0.5f * tau < shortest() * rate))) break;
+      tau = active_uniform(rate >= 0.f ? fmaxf(0.3f * tau, shortest() * rate) : attempt == 3 ? 0.f : 0.25f * tau);
       __syncthreads();
     }
     active_each<kActTasks>([&](auto k) __attribute__((always_inline)) {
@@ -857,7 +859,7 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
       ask = 4;
       return;
     }
-    if (rate >= 0.f ? tau < A.shortest * rate : tau == 0.f) ask = 2;  // (a list that does not last)
+    if (rate >= 0.f ? tau < shortest() * rate : tau == 0.f) ask = 2;  // (a list that does not last)
     for (int e = t; e < kActLocal * kActRows; e += kActThreads) (&U.f.rowseg[0][0])[e] = 0.f;
     for (int e = t; e < 4 * kActRows; e += kActThreads) reinterpret_cast<float*>(U.f.share)[e] = 0.f;
     have_list = true;
@@ -1296,5 +1298,90 @@ __global__ __launch_bounds__(kActThreads) void grid_active_kernel(ActiveArgs arg
     A.record->iters = it;
     A.record->why = why;
     A.record->lists = lists;
+  }
+}
+
+// Whether a first list over a stored cost would fit, before a launch is made for it: the lines that it would look at, counted as make_list does,
+// and from their share the entries of the busiest workgroup (each entry by its own chance; one a line at least).  A launch whose
+// entries do not fit costs 0.13 to 0.3 ms, 1 to 4 % of a call, this 5 us.
+constexpr int kForecastBits = 11;
+static_assert(kActRows * kActRows < 1 << (32 - kForecastBits), "entries and an age in a word");
+struct ForecastArgs {
+  const float* phi;
+  const float* varphi;
+  const float* since;          // varphi the bounds are against
+  const float* m1;             // bounds (ScreenArgs)
+  const uint2* codes;
+  const unsigned char* lines;  // line flags of X, or null
+  DeviceStatus* status;
+  const int* done;
+  int m, n, mp, nseg, ngroups;
+  float rho, tau0;
+  int age;                     // iterations since `since`, at most
+  int target;
+  const int* ctl;              // control words of the sweep by lines, which renews the bounds by itself
+  int k;                       // iteration of the call
+};
+__global__ __launch_bounds__(kActThreads) void active_forecast_kernel(ForecastArgs A) {
+  constexpr int kLines = 8 * kActLocal;
+  __shared__ float rise[kLines], mags[kLines];
+  __shared__ int lines_found;
+  if (*A.done) return;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wa = blockIdx.x / kActSide, wb = blockIdx.x % kActSide;
+  if (wa >= A.ngroups || wb >= A.nseg) return;
+  const int nla = (A.ngroups - wa + kActSide - 1) / kActSide, nlb = (A.nseg - wb + kActSide - 1) / kActSide;
+  if (t == 0) lines_found = 0;
+  for (int e = 2 * wave + (lane >> 5); e < 8 * nlb; e += 2 * kActWaves) {
+    const int j = (wb + kActSide * (e >> 3)) * kSegCols + (e & 7) * 32 + (lane & 31);
+    const float v = j < A.n ? A.varphi[j] : 0.f;
+    float d = j < A.n ? active_rise(v, A.since[j]) : -INFINITY, mag = fabsf(v);
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) {
+      d = fmaxf(d, __shfl_xor(d, off, 64));
+      mag = fmaxf(mag, __shfl_xor(mag, off, 64));
+    }
+    if ((lane & 31) == 0) {
+      rise[e] = d == -INFINITY ? 0.f : d;
+      mags[e] = fabsf(rise[e]) + mag;
+    }
+  }
+  __syncthreads();
+  float most_risen = 0.f;
+  for (int e = 0; e < 8 * nlb; ++e) most_risen = fmaxf(most_risen, rise[e]);
+  const int age = min(A.age, A.ctl[kCtlSince] + 1);
+  const float tau = most_risen > 0.f ? fmaxf(2.5f * most_risen / (float)age * (float)A.target, 0.0625f * A.tau0) : A.tau0;
+  const int nrc = 4 * nla, base = line_code_base(A.rho);
+  int found = 0;
+  for (int q = wave; q < nrc * nlb; q += kActWaves) {
+    const int ls = q / nrc, lr = (q - ls * nrc) * 64 + lane, row = (wa + kActSide * (lr >> 8)) * 256 + (lr & 255), seg = wb + kActSide * ls;
+    if (row >= A.m) continue;
+    const size_t at = (size_t)seg * A.mp + row;
+    const float m1 = A.m1[at], ph = A.phi[row];
+    const uint2 cd = A.codes[at];
+    unsigned held = A.lines ? A.lines[at] : 0u;
+#pragma unroll
+    for (int l = 0; l < 8; ++l) {
+      const float b = m1 - line_decode(((l < 4 ? cd.x : cd.y) >> (8 * (l & 3))) & 0xffu, base);
+      if (active_line(b, rise[8 * ls + l], mags[8 * ls + l], ph, tau)) held |= 1u << l;
+    }
+    found += __builtin_popcount(held & ((1u << min((A.n - seg * kSegCols + 31) / 32, 8)) - 1u));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) found += __shfl_xor(found, off, 64);
+  if (lane == 0) atomicAdd(&lines_found, found);
+  __syncthreads();
+  if (t == 0) {
+    int rows = 0, cols = 0, lines = 0;
+    for (int g = wa; g < A.ngroups; g += kActSide) rows += min(A.m - 256 * g, 256);
+    for (int g = wb; g < A.nseg; g += kActSide) {
+      cols += min(A.n - kSegCols * g, kSegCols);
+      lines += min((A.n - kSegCols * g + 31) / 32, 8);
+    }
+    const float share = (float)lines_found / ((float)rows * (float)lines);
+    const float one = share < 1.f ? 1.f - exp2f(log2f(1.f - share) / 32.f) : 1.f;
+    const unsigned entries = (unsigned)fmaxf(one * (float)rows * (float)cols, (float)lines_found);
+    atomicMax(&A.status->forecast, (u64)(unsigned)A.k << 32 | entries << kForecastBits | (unsigned)min(age, (1 << kForecastBits) - 1));
   }
 }

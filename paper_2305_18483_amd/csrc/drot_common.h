@@ -161,6 +161,7 @@ struct DeviceStatus {
   double cost, h, dual_lin, h_conj, gap, dual_res;
   double nz_lines;               // lines of X that hold a nonzero, where the last sweep was a lean one (else -1)
   double nz_segments;            // row partial sums of the last reduction that were not zero (density of the plan)
+  unsigned long long forecast;   // iteration of the call << 32 | entries << 11 | age of the bounds: active_forecast_kernel
   int iters;                     // iteration the residuals belong to
   int converged;
   int gap_iters;                 // iteration the objective / gap / dual residual above belong to (0: none yet)

@@ -33,6 +33,7 @@
 #ifndef DROT_PLAN_H_
 #define DROT_PLAN_H_
 
+#include <cmath>
 #include <cstddef>
 #include <vector>
 
@@ -88,7 +89,13 @@ constexpr double kPointsSparse = 0.33;
 // Active entries (drot_active.h): 16 x 16 workgroups of at most kActiveLocal groups of 256 rows and segments of 256 columns
 constexpr int kActiveSide = 16, kActiveLocal = 5;
 constexpr int kActiveEntries = 4096;   // ... and so many entries each
-constexpr double kActiveFill = 0.6;    // of them, on average, from the lines (point clouds: row segments) that hold something
+constexpr double kActiveFill = 0.6;    // point clouds: of them, on average, from the row segments that hold something
+// Stored costs: of them, expected in the busiest workgroup where the entries of a list have been counted in advance, those within the slack among
+// them (of the fast rise of the first iterations it is taken for more than it comes to), and else by what the plan holds.  Of 92 calls of
+// 3393 x 4150 to 20000 x 20000 those with less at a look made their lists but for five, and those with more in vain: at iteration 16 up to 1.15
+// in time, from 1.11 on in vain (where the plan alone held more than there is room for), from iteration 32 on 0.94 and 0.97.
+constexpr double kActiveForecastEarly = 1.15, kActiveForecast = 0.95, kActiveExpected = 0.75;
+constexpr int kActiveEarly = 32;
 // ... of point clouds below this many nonzero row segments: 12000 x 12000, d = 32, 276 us a full sweep: listed at 0.31, iteration 32, 15.1 ms for
 // 500 iterations; at 0.53, iteration 24, 13.5; tried in vain at 0.88 and listed at 0.53 15.4.
 constexpr double kActivePoints = 0.6;
@@ -313,6 +320,9 @@ struct State {
   int active_from = 0;           // no such launch before this iteration of the call
   int active_again = 0;          // ... or, once the plan has thinned out since, before this one
   double active_density = -1.0;  // plan_density when the last one that ended early started
+  int forecast_k = -1;           // iteration of the call at which the entries of a list were last counted in advance ...
+  int forecast_age = 0;          // ... how old the bounds are, which the sweep by lines renews by itself ...
+  double forecast = 0.0;         // ... and how many the busiest workgroup would have, of kActiveEntries
   int active_left = 0;           // launches of them that ended early
   bool active_ran = false;
   bool last_lean = false;        // the sweep before the next status is a lean one
@@ -602,6 +612,26 @@ inline int grid_head(const Static& S, const Problem& P, const State& T, const St
   return R.chunk - head >= least ? head : -1;
 }
 
+// Rows (or columns) of the workgroup that has the most: every kActiveSide-th group of 256, the last one of all may be shorter.
+inline int active_side_most(int m) {
+  const int groups = ceil_div(m, 256), most = ceil_div(groups, kActiveSide), others = (groups - 1) % kActiveSide;
+  return others != 0 || most == 1 ? (256 * most < m ? 256 * most : m) : 256 * (most - 1) + m - 256 * (groups - 1);
+}
+
+// Entries that the busiest workgroup is expected to hold where so many lines of 32 hold something, each entry by its own chance.
+inline double active_expected(const Problem& P, double lines) {
+  const double one = lines < 1.0 ? -std::expm1(std::log1p(-lines) / 32.0) : 1.0;
+  return one * active_side_most(P.m) * active_side_most(P.n);
+}
+
+// Whether a look counts in advance what a list over a stored cost would hold: where such a launch may come next.
+inline bool active_forecast(const Static& S, const Problem& P, const State& T) {
+  return S.active && !P.single_launches && !P.from_points && P.max_iters - T.k >= kActiveLeast && T.k >= T.active_from && T.materialized &&
+         T.by_lines && T.epoch_gen >= 0 && T.sums_gen == T.k_base + T.k && active_bounds(P, T) == kRecordedBounds;
+}
+
+inline double active_forecast_limit(int k) { return k < kActiveEarly ? kActiveForecastEarly : kActiveForecast; }
+
 // Whether the next iterations run on the active entries: the plan is known to be thin enough, X in memory is plain, its
 // flags and the screening bounds describe it, and the call is not about to end.
 inline bool active_next(const Static& S, const Problem& P, const State& T) {
@@ -612,13 +642,23 @@ inline bool active_next(const Static& S, const Problem& P, const State& T) {
   if (active_bounds(P, T) == kNoBounds) return false;
   const double room = kActiveFill * (double)kActiveEntries * (kActiveSide * kActiveSide);
   if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kActivePoints && T.plan_density * P.m * S.nseg <= room;
-  return T.by_lines && !T.dense_lines && T.lines >= 0.0 && T.lines * P.m * ceil_div(P.n, 32) <= room;
+  if (!T.by_lines || T.dense_lines || T.lines < 0.0) return false;
+  const double held = active_expected(P, T.lines) / kActiveEntries;
+  return T.forecast_k == T.k ? held <= 1.0 && T.forecast <= active_forecast_limit(T.k) : held <= kActiveExpected;
 }
 
 // ... iterations a list of its entries has to last.
 inline int active_shortest(const Problem& P, const Static& S) {
   if (!P.from_points) return kActiveShortest;
   return (long long)P.m * S.nseg >= kActivePointsLarge ? kActiveShortestPointsLarge : kActiveShortestPoints;
+}
+
+// ... the age of the bounds it starts from, at most.
+inline int active_age(const Problem& P, const State& T) {
+  const bool left = active_bounds(P, T) == kLeftBounds;
+  const long long age = T.k_base + T.k - (left ? T.bound_gen : T.epoch_gen);
+  const long long most = !left && T.forecast_k == T.k && T.forecast_age < age ? T.forecast_age : age;
+  return most > 0 ? (int)most : 1;
 }
 
 // ... the iterations it may take: up to a check or the end of the call, drawn out over the checks that follow.
@@ -654,6 +694,19 @@ inline void active_done(State& T, const Problem& P, int iters, bool left) {
     // (what the last look found is as old as the launch was long, and the plan has filled up where the entries no longer fit: over point clouds
     // the sweeps that go by certificates, 120 us at 5000 x 4000 where the others take 27, wait for the next look)
     if (P.from_points && iters > 0) T.plan_density = -1.0;
+    ++T.active_left;
+  }
+}
+
+// ... or it has been counted in advance.  Where the entries that hold something would fit by half and those within the slack do not let them, a
+// list waits as long as behind a launch that ended early: they lie that close for hundreds of iterations.
+inline void on_forecast(State& T, const Problem& P, int k, double entries, int age) {
+  T.forecast_k = k;
+  T.forecast_age = age;
+  T.forecast = entries / kActiveEntries;
+  if (k == T.k && T.lines >= 0.0 && !T.dense_lines && T.forecast > active_forecast_limit(k) && active_expected(P, T.lines) <= 0.5 * kActiveForecast * kActiveEntries) {
+    T.active_ran = true;
+    T.active_again = T.active_from = T.k + (512 << (T.active_left < 6 ? T.active_left : 6));
     ++T.active_left;
   }
 }

@@ -184,11 +184,12 @@ void drot_renewals(int count, const int* waste, int price, int max_since, unsign
   }
 }
 
-// Active entries: problem, options as in drot_plan_trace.  state[8]: iterations of the call so far, density and lines reported
+// Active entries: problem, options as in drot_plan_trace.  state[9]: iterations of the call so far, density and lines reported
 // * 1e6 (negative: none), by_lines, generation of the bounds (negative: none), launches that ended early, iterations since the
-// last of them, the density it started from * 1e6.  out[6]: iterations of a launch now (0: none), and if it ends early after 10: before which
+// last of them, the density it started from * 1e6, entries counted in advance at this look * 1e6 (of kActiveEntries; negative: not
+// counted).  out[8]: iterations of a launch now (0: none), and if it ends early after 10: before which
 // iteration of the call no other starts, launches that ended early, the density that is known then * 1e6 (negative: none), whether the host
-// waits for the next look; iterations that a list has to last.  Returns whether the call could ever take one.
+// waits for the next look; iterations that a list has to last; whether a look here counts in advance, and what the plan alone has * 1e6.  Returns whether the call could ever take one.
 int drot_plan_active(const int* problem, const int* options, int compute_units, int single_launches, const int* state, int* out) {
   Problem P;
   P.m = problem[0];
@@ -222,8 +223,11 @@ int drot_plan_active(const int* problem, const int* options, int compute_units, 
     T.active_from = state[0] - state[6] + (512 << (state[5] - 1));
     T.active_again = P.from_points && state[0] - state[6] < kPromptLooksUntil ? state[0] - state[6] + (8 << (state[5] - 1)) : T.active_from;
   }
+  out[6] = active_forecast(S, P, T);
+  out[7] = (int)(active_expected(P, T.lines) / kActiveEntries * 1e6 + 0.5);
+  if (state[8] >= 0) on_forecast(T, P, T.k, state[8] * 1e-6 * kActiveEntries, state[0] - state[4]);
   out[0] = active_next(S, P, T) ? active_stretch(P, O, T).chunk : 0;
-  active_done(T, P, 10, true);
+  if (T.active_left == state[5]) active_done(T, P, 10, true);  // (else it waits as if it had ended)
   out[1] = T.active_again;
   out[2] = T.active_left;
   out[3] = T.plan_density < 0.0 ? -1 : (int)(T.plan_density * 1e6 + 0.5);

@@ -27,7 +27,7 @@ def _checks(solver):
     return [(c.iters, c.r_row, c.r_col) for c in solver.checks()]
 
 
-def _both(drot, m, n, solve, launches=1, check_every=100):
+def _both(drot, m, n, solve, launches=1, iterations=1, check_every=100):
     """solve(solver) -> tuple of arrays and numbers, with the default options and with every sweep in a launch of its own."""
     out = []
     for fused in (-1, 0):
@@ -37,18 +37,20 @@ def _both(drot, m, n, solve, launches=1, check_every=100):
         accepted, refused, given_up = solver.cooperative_launches()
         assert refused == 0 and given_up == 0
         assert (accepted >= launches) if fused else accepted == 0, accepted
+        runs = solver.active_runs()  # (an attempt whose entries do not fit is a launch as well)
+        assert runs.launches == accepted and (runs.iterations >= iterations if fused else runs.iterations == 0), runs.iterations
         solver.close()
     for a, b in zip(*out):
-        assert np.array_equal(a, b) if isinstance(a, np.ndarray) else a == b
+        assert np.array_equal(a, b) if isinstance(a, np.ndarray) else torch.equal(a, b) if torch.is_tensor(a) else a == b
     return out[0]
 
 
 # 256-row groups and 256-column segments: one entry more than a whole number of them, and one less; fewer of either than there
-# are rows and columns of workgroups; as many as a workgroup holds; pairs forbidden, costs far above and below 1
-@pytest.mark.parametrize("m,n,kind,scale,forbid", [(3585, 3329, 1, 1.0, 0.0), (3839, 4095, 0, 1.0, 0.3), (2049, 5633, 1, 3.0e4, 0.0),
-                                                   (2049, 20480, 1, 1.0, 0.0), (20480, 577, 0, 1.0, 0.0), (12289, 1000, 1, 1.0e-3, 0.1)])
-def test_active_entries_change_no_bit(drot, m, n, kind, scale, forbid):
-    P = drot_inputs.with_entrywise_terms(drot_inputs.random_problem(m, n, seed=4100 + m, d=5, reg_kind=kind, lam=0.01), seed=4101, forbid_frac=forbid)
+# are rows and columns of workgroups; pairs forbidden, costs far above and below 1 (in few dimensions too many entries lie near the edge)
+@pytest.mark.parametrize("m,n,kind,scale,forbid,d", [(3585, 3329, 1, 1.0, 0.0, 12), (3839, 4095, 0, 1.0, 0.3, 20), (2049, 5633, 1, 3.0e4, 0.0, 12),
+                                                     (12289, 1000, 1, 1.0e-3, 0.1, 20)])
+def test_active_entries_change_no_bit(drot, m, n, kind, scale, forbid, d):
+    P = drot_inputs.with_entrywise_terms(drot_inputs.random_problem(m, n, seed=4100 + m, d=d, reg_kind=kind, lam=0.01), seed=4101, forbid_frac=forbid)
     P.C = (P.C * np.float32(scale)).astype(np.float32)
 
     def solve(solver):
@@ -58,28 +60,52 @@ def test_active_entries_change_no_bit(drot, m, n, kind, scale, forbid):
         return X, phi, varphi, res.objective, res.gap, res.r_row, res.r_col
 
     _say(f"stored cost {m}x{n}, kind {kind}, costs up to {scale:g}, forbidden {forbid:g}")
-    _both(drot, m, n, solve)
+    _both(drot, m, n, solve, iterations=300)
 
 
-@pytest.mark.parametrize("m,n,d", [(3585, 3329, 2), (3400, 4097, 17), (1200, 9729, 3)])
-def test_active_entries_of_point_clouds_change_no_bit(drot, m, n, d):
+# as many groups and segments as a workgroup holds, of both or of one, the last ones of one row and of one column; more blocks of
+# eight rows and columns than waves to own them (32640 rows and columns), so that a wave owns two
+@pytest.mark.parametrize("m,n", [(20225, 16641), (4097, 20480), (20480, 3073)])
+def test_active_entries_of_the_largest_shapes_change_no_bit(drot, m, n):
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(4150)
+    xs, xt = torch.randn(m, 32, device=dev, generator=g), 0.3 + 1.4 * torch.randn(n, 32, device=dev, generator=g)
+    C = torch.cdist(xs, xt) ** 2
+    C /= C.max()
+    p, q = (torch.rand(k, dtype=torch.float64, device=dev, generator=g) + 0.5 for k in (m, n))
+    p, q = (p / p.sum()).float(), (q / q.sum()).float()
+
+    def solve(solver):
+        res = solver.solve(C, p, q, max_iters=150, tol=1e-12)
+        return (res.X, *solver.duals(m, n, dev), res.objective, res.r_row, res.r_col)
+
+    _say(f"stored cost {m}x{n}")
+    _both(drot, m, n, solve, iterations=50)
+
+
+# costs formed entry by entry as the sweeps' matrix instructions form them: more dimensions than one pass of theirs holds, points so small
+# that products of their coordinates are denormal
+@pytest.mark.parametrize("m,n,d,size", [(3585, 3329, 2, 1.0), (3400, 4097, 17, 1.0), (1200, 9729, 3, 1.0), (3585, 3329, 80, 1.0e-18),
+                                        (1200, 9729, 201, 3.0e-19)])
+def test_active_entries_of_point_clouds_change_no_bit(drot, m, n, d, size):
     P = drot_inputs.random_problem(m, n, seed=4200 + m, d=d, reg_kind=1, lam=0.001)
     dev = torch.device("cuda:0")
-    xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
-    scale = 1.0 / float((torch.cdist(xs, xt) ** 2).max())
+    xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in ((P.xs * size).astype(np.float32), (P.xt * size).astype(np.float32), P.p, P.q))
+    scale = 1.0 / float((torch.cdist(xs.double(), xt.double()) ** 2).max())
 
     def solve(solver):
         res = solver.solve_points(xs, xt, scale, p, q, reg_kind=1, lam=P.lam, max_iters=330, tol=1e-12)
         phi, varphi = solver.duals(m, n, dev)
         return res.X.cpu().numpy(), phi.cpu().numpy(), varphi.cpu().numpy(), res.objective, res.gap, res.r_row, res.r_col
 
-    _say(f"point clouds {m}x{n}, d = {d}")
-    _both(drot, m, n, solve)
+    _say(f"point clouds {m}x{n}, d = {d}, of size {size:g}")
+    _both(drot, m, n, solve, iterations=280 if d > 8 else 1)
 
 
 def test_active_entries_across_calls_starts_and_stops(drot):
     m, n = 4000, 3900
-    P = drot_inputs.random_problem(m, n, seed=4300, d=4, reg_kind=1, lam=0.01)
+    P = drot_inputs.random_problem(m, n, seed=4300, d=8, reg_kind=1, lam=0.01)
     dev = torch.device("cuda:0")
     C, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.p, P.q))
     kw = dict(reg_kind=1, lam=P.lam)
@@ -95,8 +121,8 @@ def test_active_entries_across_calls_starts_and_stops(drot):
         return tuple(out)
 
     _say("continued calls")
-    cut = _both(drot, m, n, continued, launches=4, check_every=50)
-    whole = _both(drot, m, n, lambda s: (s.solve(C, p, q, max_iters=651, tol=1e-12, **kw).X.cpu().numpy(),), check_every=50)
+    cut = _both(drot, m, n, continued, launches=4, iterations=600, check_every=50)
+    whole = _both(drot, m, n, lambda s: (s.solve(C, p, q, max_iters=651, tol=1e-12, **kw).X.cpu().numpy(),), iterations=600, check_every=50)
     assert np.array_equal(cut[-4], whole[0])
 
     def warm(solver):  # from potentials and a plan of another problem, then without a tolerance
@@ -201,7 +227,31 @@ def test_a_launch_of_active_entries_that_gives_up_is_replaced_by_single_launches
     assert e.value.code == drot.binding.DROT_ERR_HIP and solver.cooperative_launches() == (1, 0, 1)
 
 
-def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot):
+# launches that end early: entries that do not fit at the first list (misfits), and later on (outgrown: X goes back to what it was before an
+# iteration that nobody counts, in the workgroups that have lists)
+@pytest.mark.parametrize("points,d,lam,ended", [(False, 2, 0.0, "misfits"), (False, 5, 0.0, "outgrown"), (False, 5, 100.0, "outgrown"), (True, 1, 0.0, "misfits"),
+                                                (True, 2, 100.0, "outgrown")])
+def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot, points, d, lam, ended):
+    m, n = 3585, 3329
+    P = drot_inputs.random_problem(m, n, seed=4400, d=d, reg_kind=1 if lam else 0, lam=lam)
+    dev = torch.device("cuda:0")
+    C, xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
+    scale = 1.0 / float((torch.cdist(xs, xt) ** 2).max())
+    kw = dict(reg_kind=1 if lam else 0, lam=lam, max_iters=420, tol=1e-12)
+
+    def solve(solver):
+        solver.set_skip_cost(0)
+        res = solver.solve_points(xs, xt, scale, p, q, **kw) if points else solver.solve(C, p, q, **kw)
+        if solver.cooperative_launches()[0]:
+            runs = solver.active_runs()
+            assert (runs.misfits, runs.outgrown) == ((1, 0) if ended == "misfits" else (0, 1)), (runs.misfits, runs.outgrown)
+        return (res.X.cpu().numpy(), *(v.cpu().numpy() for v in solver.duals(m, n, dev)), res.objective, res.r_row)
+
+    _say(f"entries that do not fit, points {points}, d = {d}, lam = {lam:g}")
+    _both(drot, m, n, solve, iterations=1 if ended == "outgrown" else 0)
+
+
+def test_a_band_of_entries_leaves_the_solve_to_the_sweeps(drot):
     # row i holds its mass near column i: the workgroups on the diagonal of 16 x 16 have sixteen times their part of the entries, and
     # a quadratic term of middling strength keeps dozens of them in every row
     m = n = 6000
@@ -217,5 +267,5 @@ def test_active_entries_that_do_not_fit_leave_the_solve_to_the_sweeps(drot):
         return res.X.cpu().numpy(), res.objective, res.r_row
 
     _say("a band of entries")
-    X = _both(drot, m, n, solve, launches=0)[0]
+    X = _both(drot, m, n, solve)[0]
     assert (X > 0).sum() > m

@@ -668,12 +668,12 @@ def test_launches_of_calls_without_checks_are_bounded_where_sweeps_were_launches
     assert stretch(1500, 1000, 100000) == 100000
 
 
-def _active(planlib, m, n, k=32, iters=1000, density=0.3, lines=0.03, by_lines=1, epoch=8, left=0, ago=0, before=0.3, units=256, single=0, reg_kind=1,
+def _active(planlib, m, n, k=32, iters=1000, density=0.3, lines=0.03, by_lines=1, epoch=8, left=0, ago=0, before=0.3, forecast=-1.0, units=256, single=0, reg_kind=1,
             from_points=0, feedback=1, check_every=100, fused_update=-1, skip_cost=-1, skip_unchanged=-1, screening=-1, gap_every=0):
     problem = (ctypes.c_int * 14)(m, n, reg_kind, from_points, 0, 0, 0, 1, 1, 0, 0, feedback, 1, iters)
     options = (ctypes.c_int * 9)(check_every, -1, fused_update, skip_cost, skip_unchanged, screening, -1, 0, gap_every)
-    state = (ctypes.c_int * 8)(k, int(density * 1e6), int(lines * 1e6), by_lines, epoch, left, ago, int(before * 1e6))
-    out = (ctypes.c_int * 6)()
+    state = (ctypes.c_int * 9)(k, int(density * 1e6), int(lines * 1e6), by_lines, epoch, left, ago, int(before * 1e6), int(forecast * 1e6))
+    out = (ctypes.c_int * 8)()
     ever = planlib.drot_plan_active(problem, options, units, single, state, out)
     return ever, tuple(out)
 
@@ -694,6 +694,23 @@ def test_active_entries_of_point_clouds_that_did_not_fit(planlib):
     assert _active(planlib, 10000, 10000)[1][5] == 16
 
 
+def test_active_entries_counted_in_advance(planlib):
+    def active(forecast, lines=0.1, **kw):  # (10000 x 10000: lines of 0.1, 0.15 and 0.19 are 0.47, 0.73 and 0.95 of the room)
+        return _active(planlib, 10000, 10000, lines=lines, forecast=forecast, **kw)[1]
+
+    # where such a launch may come, over a stored cost, and bounds are there to count by
+    assert active(-1.0)[6] == 1 and active(-1.0, lines=0.5)[6] == 1
+    for other in (dict(by_lines=0), dict(epoch=-1), dict(iters=47), dict(left=1, ago=511, k=600), dict(units=255), dict(from_points=1), dict(single=1)):
+        assert active(-1.0, **other)[6] == 0, other
+    # the count decides: more of it in the first iterations, whose rise does not last, and never past what the plan alone would take
+    assert active(0.94)[0] > 0 and active(0.96)[0] == 0 and active(0.94, lines=0.19)[0] > 0 and active(0.94, lines=0.21)[0] == 0
+    assert active(1.14, k=16)[0] > 0 and active(1.16, k=16)[0] == 0 and active(1.14, k=16, lines=0.21)[0] == 0
+    # what lies within the slack does not go away: the host neither waits for the looks that follow nor tries before 512 iterations are over; a plan
+    # that is still thinning is looked at again
+    assert active(0.96, lines=0.095)[:2] == (0, 32 + 512) and active(0.96, lines=0.095)[4] == 0
+    assert active(0.96, lines=0.15)[:2] == (0, 42 + 512)
+
+
 def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
     def active(*args, **kw):
         ever, out = _active(planlib, *args, **kw)
@@ -712,12 +729,14 @@ def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
                   dict(gap_every=1), dict(feedback=0), dict(reg_kind=2)):
         assert active(10000, 10000, **other) == (0, (0, 42 + 512, 1)), other
     assert active(10000, 10000, single=1)[1][0] == 0
-    # not before the plan is known to be thin (0.6 of the room for entries, on average), nor without bounds, nor for the last few
-    room = 0.6 * 4096 * 256
-    for m, n in ((10000, 10000), (20000, 20000), (4000, 4000)):
-        lines = m * -(-n // 32)
-        assert active(m, n, lines=0.99 * min(1.0, room / lines))[1][0] > 0
-        assert room > lines or active(m, n, lines=1.01 * room / lines)[1][0] == 0
+    # not before the plan is known to be thin (0.75 of the room for entries of the workgroup that has most rows and columns, each entry by its
+    # own chance), nor without bounds, nor for the last few
+    for m, n in ((10000, 10000), (20000, 20000), (4000, 4000), (4200, 12290), (5000, 5000)):
+        most = [max(sum(min(256, k - at) for at in range(256 * w, k, 4096)) for w in range(16) if 256 * w < k) for k in (m, n)]
+        share = 0.75 * 4096 / (most[0] * most[1])
+        lines = 1.0 - (1.0 - share) ** 32
+        assert active(m, n, lines=0.99 * lines)[1][0] > 0 and active(m, n, lines=1.01 * lines)[1][0] == 0
+        assert abs(_active(planlib, m, n, lines=lines)[1][7] - 750000) < 200
         assert active(m, n, lines=-1.0)[1][0] == 0 and active(m, n, by_lines=0)[1][0] == 0 and active(m, n, epoch=-1)[1][0] == 0
         assert active(m, n, iters=48)[1][0] == 16 and active(m, n, iters=47)[1][0] == 0
         assert active(m, n, from_points=1, lines=-1.0, by_lines=0)[1][0] > 0
