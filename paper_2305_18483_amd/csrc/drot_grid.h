@@ -57,6 +57,9 @@ constexpr int kGridPollsMax = 1 << 30;
 // Attempts without a rest.  A word on its way can be held up for as long as every wave on the GPU asks without one: with 4000 waves
 // waiting for the answer of a check, the words of one owner out of 2500 did not reach the memory-side cache in 300000
 // attempts (a third of a second), one check in ten, and in none of hundreds once the waves rest between attempts.
+// So the waits for a check's answer, in which every wave waits for one workgroup, rest in every kernel (quad 1000 x 1000, ten checks, 3.06 ms
+// either way).  With the others resting as well, which are over in 1 to 2 us, this kernel and the slabs' took 1 to 2.5 % longer (one
+// more way out of the loops that poll), and a form of the slabs' spilled.
 constexpr int kGridPatience = 32, kGridRest = 64;  // (rest: 4096 cycles, 1.7 us)
 constexpr int kGridRestPolls = 3;  // ... and an attempt behind one, 2.6 us where others take 0.9, counts for three of them:
 static_assert((long long)kGridPolls / kGridRestPolls * 2600 < 30000000000ll, "half a minute");
@@ -641,7 +644,7 @@ __global__ __launch_bounds__(64 * NW) void grid_resident_kernel(GridArgs A) {
     if (check) {  // (whether it passes, for everybody; the word comes behind all of the iteration's others)
       u64 v[1];
       const unsigned at[1] = {cst_at + 2u};
-      grid_gather<1>(half, v, at, tag, A.polls, lost);
+      grid_gather<1, 0, true>(half, v, at, tag, A.polls, lost);
       if (!lost && (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v[0]) != 0) result = kPasses;
     }
     if (lost) failed[1] = 1;
