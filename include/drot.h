@@ -166,7 +166,7 @@ int drot_destroy(drot_handle h);
  *       three, or, where X and C fit the registers of the GPU (10.5 million entries), run all the iterations and their
  *       residual checks in one cooperative launch (4096 iterations or 256 checks at a time, in which no other launch gets onto
  *       the GPU: up to 60 ms); point clouds and group lasso that fit do the same, and large sparse problems
- *       (DROT_OPT_SCREENING).  0 always runs the separate kernels, a launch for
+ *       (DROT_OPT_SCREENING; 2048 iterations at a time, over point clouds 1024).  0 always runs the separate kernels, a launch for
  *       every sweep.  Same bits.  (Larger problems over a stored cost that fit, up to 12.6 million entries, take the one launch
  *       whatever this is set to, where they are neither screened nor paired.)
  *   DROT_OPT_RESIDENT [-1], -1/0: problems of at most 128 x 256 without group lasso, from a stored cost, run

@@ -375,6 +375,8 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
 // (or reaches one check): the largest tiles take 10 us, the largest slabs 14, so that other work on the GPU waits no longer
 // than 60 ms.
 constexpr int kRunSweeps = 4096, kRunChecks = 256;
+// (... on active entries: an iteration of 12 us and its share of the lists, 300 us at most for 16 iterations, over point clouds for 6)
+constexpr int kRunActive = 2048, kRunActivePoints = 1024;
 struct Stretch {
   int chunk = 0;
   bool prompt = false;     // the host waits for the status at its end before it plans on
@@ -592,10 +594,10 @@ inline bool runs_through_checks(const Static& S, const Problem& P, const Options
 }
 
 // Stretch R, which ends at a check or with the call, drawn out over the checks that follow.
-inline Stretch draw_out(const Problem& P, const Options& O, const State& T, Stretch R) {
+inline Stretch draw_out(const Problem& P, const Options& O, const State& T, Stretch R, int sweeps = kRunSweeps) {
   for (int checks = 1; checks < kRunChecks && T.k + R.chunk < P.max_iters; ++checks) {
     const int left = P.max_iters - (T.k + R.chunk), more = O.check_every < left ? O.check_every : left;
-    if (R.chunk > kRunSweeps - more) break;
+    if (R.chunk > sweeps - more) break;
     R.chunk += more;
   }
   return R;
@@ -667,7 +669,7 @@ inline Stretch active_stretch(const Problem& P, const Options& O, const State& T
   R.chunk = P.max_iters - T.k;
   const int to_check = O.check_every - T.k % O.check_every;
   if (to_check < R.chunk) R.chunk = to_check;
-  return draw_out(P, O, T, R);
+  return draw_out(P, O, T, R, P.from_points ? kRunActivePoints : kRunActive);
 }
 
 // ... and it has come back, `iters` iterations later.  left: the entries no longer fit (or never did): the sweeps take over for

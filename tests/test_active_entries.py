@@ -125,6 +125,12 @@ def test_active_entries_across_calls_starts_and_stops(drot):
     whole = _both(drot, m, n, lambda s: (s.solve(C, p, q, max_iters=651, tol=1e-12, **kw).X.cpu().numpy(),), iterations=600, check_every=50)
     assert np.array_equal(cut[-4], whole[0])
 
+    def often(solver):  # 256 checks to a launch, and the next one goes on from there
+        solver.set_skip_cost(0)
+        return (solver.solve(C, p, q, max_iters=600, tol=1e-12, **kw).X.cpu().numpy(),)
+
+    _both(drot, m, n, often, launches=2, iterations=580, check_every=2)
+
     def warm(solver):  # from potentials and a plan of another problem, then without a tolerance
         X = torch.from_numpy(whole[0]).to(dev) * 0.5
         res = solver.solve(C, p, q, X_out=X, phi0=torch.full((m,), 1e-5, device=dev), varphi0=torch.zeros(n, device=dev), max_iters=260, tol=1e-12, **kw)

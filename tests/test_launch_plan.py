@@ -716,9 +716,11 @@ def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
         ever, out = _active(planlib, *args, **kw)
         return ever, out[:3]
 
-    # runs on through the checks, 4096 iterations or 256 checks at a time
+    # runs on through the checks, 2048 iterations (point clouds: 1024) or 256 checks at a time
     assert active(10000, 10000) == (1, (968, 42 + 512, 1))
-    assert active(10000, 10000, iters=100000)[1][0] == 68 + 4000
+    assert active(10000, 10000, iters=100000)[1][0] == 68 + 1900 and active(10000, 10000, iters=2032 + 48)[1][0] == 2048
+    assert active(12000, 12000, iters=100000, from_points=1)[1][0] == 68 + 900
+    assert active(10000, 10000, iters=100000, check_every=5000)[1][0] == 4968  # (or to one check)
     assert active(10000, 10000, k=30, iters=1000, check_every=1)[1][0] == 256
     # sizes: 80 segments of 256 columns and groups of 256 rows at most, 11.5 million entries at least
     assert active(20480, 20480)[0] == 1 and active(20481, 1000)[0] == 0 and active(1000, 20481)[0] == 0
