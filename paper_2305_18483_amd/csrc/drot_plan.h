@@ -91,10 +91,10 @@ constexpr int kActiveSide = 16, kActiveLocal = 5;
 constexpr int kActiveEntries = 4096;   // ... and so many entries each
 constexpr double kActiveFill = 0.6;    // point clouds: of them, on average, from the row segments that hold something
 // Stored costs: of them, expected in the busiest workgroup where the entries of a list have been counted in advance, those within the slack among
-// them (of the fast rise of the first iterations it is taken for more than it comes to), and else by what the plan holds.  Of 92 calls of
-// 3393 x 4150 to 20000 x 20000 those with less at a look made their lists but for five, and those with more in vain: at iteration 16 up to 1.15
-// in time, from 1.11 on in vain (where the plan alone held more than there is room for), from iteration 32 on 0.94 and 0.97.
-constexpr double kActiveForecastEarly = 1.15, kActiveForecast = 0.95, kActiveExpected = 0.75;
+// them, and else by what the plan holds.  Of 240 calls of 3000 x 5595 to 20000 x 20000, each listed at the first count below a higher line: at
+// iteration 16, whose fast rise does not last, the lists held up to 1.18 (of 73 calls, 10 in vain, in few dimensions) and of 25 above once (1.27);
+// later, where the plan alone held no more than 0.56, up to 1.12 (all of 33), and where it held more up to 0.85, in vain from 0.95 on (8).
+constexpr double kActiveForecastEarly = 1.2, kActiveForecastThin = 1.12, kActiveForecast = 0.94, kActiveThin = 0.58, kActiveExpected = 0.75;
 constexpr int kActiveEarly = 32;
 // ... of point clouds below this many nonzero row segments: 12000 x 12000, d = 32, 276 us a full sweep: listed at 0.31, iteration 32, 15.1 ms for
 // 500 iterations; at 0.53, iteration 24, 13.5; tried in vain at 0.88 and listed at 0.53 15.4.
@@ -632,7 +632,9 @@ inline bool active_forecast(const Static& S, const Problem& P, const State& T) {
          T.by_lines && T.epoch_gen >= 0 && T.sums_gen == T.k_base + T.k && active_bounds(P, T) == kRecordedBounds;
 }
 
-inline double active_forecast_limit(int k) { return k < kActiveEarly ? kActiveForecastEarly : kActiveForecast; }
+inline double active_forecast_limit(int k, double held) {
+  return k < kActiveEarly ? kActiveForecastEarly : held <= kActiveThin ? kActiveForecastThin : kActiveForecast;
+}
 
 // Whether the next iterations run on the active entries: the plan is known to be thin enough, X in memory is plain, its
 // flags and the screening bounds describe it, and the call is not about to end.
@@ -646,7 +648,7 @@ inline bool active_next(const Static& S, const Problem& P, const State& T) {
   if (P.from_points) return T.plan_density >= 0.0 && T.plan_density < kActivePoints && T.plan_density * P.m * S.nseg <= room;
   if (!T.by_lines || T.dense_lines || T.lines < 0.0) return false;
   const double held = active_expected(P, T.lines) / kActiveEntries;
-  return T.forecast_k == T.k ? held <= 1.0 && T.forecast <= active_forecast_limit(T.k) : held <= kActiveExpected;
+  return T.forecast_k == T.k ? held <= 1.0 && T.forecast <= active_forecast_limit(T.k, held) : held <= kActiveExpected;
 }
 
 // ... iterations a list of its entries has to last.
@@ -706,7 +708,8 @@ inline void on_forecast(State& T, const Problem& P, int k, double entries, int a
   T.forecast_k = k;
   T.forecast_age = age;
   T.forecast = entries / kActiveEntries;
-  if (k == T.k && T.lines >= 0.0 && !T.dense_lines && T.forecast > active_forecast_limit(k) && active_expected(P, T.lines) <= 0.5 * kActiveForecast * kActiveEntries) {
+  const double held = T.lines >= 0.0 ? active_expected(P, T.lines) / kActiveEntries : 1.0;
+  if (k == T.k && !T.dense_lines && T.forecast > active_forecast_limit(k, held) && held <= 0.5 * kActiveForecast) {
     T.active_ran = true;
     T.active_again = T.active_from = T.k + (512 << (T.active_left < 6 ? T.active_left : 6));
     ++T.active_left;

@@ -702,13 +702,15 @@ def test_active_entries_counted_in_advance(planlib):
     assert active(-1.0)[6] == 1 and active(-1.0, lines=0.5)[6] == 1
     for other in (dict(by_lines=0), dict(epoch=-1), dict(iters=47), dict(left=1, ago=511, k=600), dict(units=255), dict(from_points=1), dict(single=1)):
         assert active(-1.0, **other)[6] == 0, other
-    # the count decides: more of it in the first iterations, whose rise does not last, and never past what the plan alone would take
-    assert active(0.94)[0] > 0 and active(0.96)[0] == 0 and active(0.94, lines=0.19)[0] > 0 and active(0.94, lines=0.21)[0] == 0
-    assert active(1.14, k=16)[0] > 0 and active(1.16, k=16)[0] == 0 and active(1.14, k=16, lines=0.21)[0] == 0
+    # the count decides: more of it in the first iterations, whose rise does not last, and where the plan alone has little; never past what the
+    # plan alone would take
+    assert active(0.93, lines=0.15)[0] > 0 and active(0.95, lines=0.15)[0] == 0 and active(0.93, lines=0.19)[0] > 0 and active(0.93, lines=0.21)[0] == 0
+    assert active(1.11)[0] > 0 and active(1.13)[0] == 0
+    assert active(1.19, k=16)[0] > 0 and active(1.21, k=16)[0] == 0 and active(1.19, k=16, lines=0.21)[0] == 0
     # what lies within the slack does not go away: the host neither waits for the looks that follow nor tries before 512 iterations are over; a plan
     # that is still thinning is looked at again
-    assert active(0.96, lines=0.095)[:2] == (0, 32 + 512) and active(0.96, lines=0.095)[4] == 0
-    assert active(0.96, lines=0.15)[:2] == (0, 42 + 512)
+    assert active(1.13, lines=0.095)[:2] == (0, 32 + 512) and active(1.13, lines=0.095)[4] == 0
+    assert active(0.95, lines=0.15)[:2] == (0, 42 + 512)
 
 
 def test_active_entries_once_a_large_plan_is_known_to_be_thin(planlib):
