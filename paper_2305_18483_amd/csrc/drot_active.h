@@ -31,11 +31,11 @@
 // column's entries within 256 rows by groups of 8 rows, tiles of 64 and their four tiles (point clouds: pairs, tiles of 32, eight
 // tiles), each in order.  Zeros drop out of all of these, and where two entries at most are not zero any order is the same.
 //
-// What bounds it: the two hops (a number published by one workgroup is with another 1.2 to 1.5 us later), the slowest workgroup's
-// sweep and sums (2 to 4 us: chains of lane exchanges, and entries are not spread evenly), and the keeper's sum of the totals
-// (1.5 us, 2.7 at 20000 x 20000).  An iteration and calls, in place of sweeps launched one by one: 10000 x 10000 (1000 iterations)
-// 10 for 20 us, 20.5 -> 13.7 ms; 20000 x 20000 (500) 11.5 for 18 and more, 24.6 -> 18.8; point clouds of 12000 (500, d = 32) 9.5 for 45,
-// 31.1 -> 13.5, of 4001 x 3999 (400) 33.2 -> 4.9.  A list takes 75 to 150 us.
+// What bounds it, per iteration of 10000 x 10000, by the clock of one workgroup (profiles): the sweep and its sums 1.9 to 2.7 us (chains of lane
+// exchanges; 6 where 3000 entries are held), hop 1 2.4 to 2.8 (of the keeper, with its sum of the totals, 5.1), hop 2 1.3 to 3.0, the rest
+// 1.3, and the lists, 25 to 38 us each in one workgroup, one in 22 iterations: 10.8 us in all (20000 x 20000 13, point clouds of 12000 12).
+// In place of sweeps launched one by one: 10000 x 10000 (1000 iterations) 20.1 -> 13.6 ms; 20000 x 20000 (500) 24.4 -> 18.7; point clouds of 12000
+// (500, d = 32) 30.3 -> 12.9, of 4001 x 3999 (400, d = 8) 28.2 -> 4.6.
 // Waiting: a workgroup that polls without a rest can keep another's write from being seen for as long as it polls, so polls that
 // have failed 32 times rest in between (kGridRest).
 // ------------------------------------------------------------------------------------------

@@ -104,7 +104,7 @@ constexpr int kActiveLeast = 16;       // shorter calls are not worth a list
 // iterations) 14.6, 13.6, 13.7 ms; 20000 x 20000 (500) 18.45, 18.6, 18.8; point clouds 4001 x 3999 (400) 7.7, 6.1, 5.0; 12000 x 12100, quadratic
 // (400) 16.25, 15.9, 15.5 (does not fit at 48).
 constexpr int kActiveTarget = 20;
-// ... and has to last to be worth making.  A list takes 75 to 150 us (300 where the plan is dense), of point clouds of few dimensions 150 to 300.  A sweep over everything takes
+// ... and has to last to be worth making.  A list takes 25 to 80 us in a workgroup, the slowest one's counts; of point clouds of few dimensions 150 to 300.  A sweep over everything takes
 // 12 to 20 us longer than an iteration on the active entries over a stored cost (7000 x 7100 with lists of 8 iterations and up 11.9 ms, with
 // sweeps alone 10.2, with lists of 16 and up 10.3); over point clouds, d = 2 or 3, a third of a nanosecond per row segment.  Point clouds with lists
 // of 3, of 6 and of 10 iterations and up, ms (and with sweeps alone): 75000 row segments (7552 x 2460, 211 iterations) 14.6, 12.2, 9.0 (12.1);
@@ -375,7 +375,7 @@ inline State start_state(const Static& S, const Problem& P, const Carry& carry) 
 // (or reaches one check): the largest tiles take 10 us, the largest slabs 14, so that other work on the GPU waits no longer
 // than 60 ms.
 constexpr int kRunSweeps = 4096, kRunChecks = 256;
-// (... on active entries: an iteration of 12 us and its share of the lists, 300 us at most for 16 iterations, over point clouds for 6)
+// (... on active entries: an iteration of 11 to 15 us and its share of the lists, 300 us at most for 16 iterations, over point clouds for 6)
 constexpr int kRunActive = 2048, kRunActivePoints = 1024;
 struct Stretch {
   int chunk = 0;
