@@ -1,4 +1,8 @@
 """Large sparse problems on the entries that hold something or may come to: the bits of the sweeps over everything."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +12,7 @@ import drot_inputs
 from . import parity_utils as pu
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _say(msg):
@@ -231,6 +236,56 @@ def test_a_launch_of_active_entries_that_gives_up_is_replaced_by_single_launches
     with pytest.raises(drot.DrotError) as e:
         solve(solver, X_out=ref[0].clone(), phi0=ref[1], varphi0=ref[2])
     assert e.value.code == drot.binding.DROT_ERR_HIP and solver.cooperative_launches() == (1, 0, 1)
+
+
+_REFUSED = '''
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # first, so that its symbol is found before the runtime's own
+import numpy as np, torch
+import drot_inputs
+import paper_2305_18483_amd as drot
+m, n = 3585, 3329
+dev = torch.device("cuda:0")
+P = drot_inputs.random_problem(m, n, seed=4700, d=12)
+C, xs, xt, p, q = (torch.from_numpy(a).to(dev) for a in (P.C, P.xs.astype(np.float32), P.xt.astype(np.float32), P.p, P.q))
+scale = 1.0 / float((torch.cdist(xs, xt) ** 2).max())
+for points in (False, True):
+    out = []
+    for single in (False, True):
+        solver = drot.Solver(m, n)
+        if single:
+            solver.set_fused_update(0)
+        before = shim.refusals()
+        for _ in range(2):  # (the handle asks once)
+            kw = dict(max_iters=200, tol=1e-12)
+            res = solver.solve_points(xs, xt, scale, p, q, **kw) if points else solver.solve(C, p, q, **kw)
+            out.append((res.X.clone(), *solver.duals(m, n, dev), res.objective, res.r_row))
+        assert shim.refusals() - before == solver.cooperative_launches()[1] == (0 if single else 1)
+        assert solver.cooperative_launches()[0] == solver.active_runs().launches == 0
+    for got in out[:-1]:
+        assert all(torch.equal(a, b) if torch.is_tensor(a) else a == b for a, b in zip(got, out[-1]))
+print("refused and done", shim.refusals(), flush=True)
+'''
+
+
+def test_a_launch_of_active_entries_that_is_refused_is_replaced_by_single_launches(tmp_path):
+    # a function of the same name, loaded ahead of the runtime in a child process, accepts no cooperative launch
+    src, lib = tmp_path / "refuse.cpp", tmp_path / "librefuse.so"
+    src.write_text('''
+struct dim3 { unsigned x, y, z; };
+static int refused;
+extern "C" int refusals() { return refused; }
+extern "C" int hipLaunchCooperativeKernel(const void*, dim3, dim3, void**, unsigned, void*) {
+  ++refused;
+  return 720;  // hipErrorCooperativeLaunchTooLarge
+}
+''')
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", str(lib), str(src)], check=True)
+    _say("refused launches, in a child process")
+    env = dict(os.environ, PYTHONPATH=os.pathsep.join(x for x in (ROOT, os.environ.get("PYTHONPATH")) if x))
+    proc = subprocess.run([sys.executable, "-c", _REFUSED, str(lib)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                          timeout=100, env=env)
+    assert proc.returncode == 0 and "refused and done 2" in proc.stdout, proc.stdout
 
 
 # launches that end early: entries that do not fit at the first list (misfits), and later on (outgrown: X goes back to what it was before an
