@@ -306,7 +306,8 @@ __device__ __forceinline__ u64 active_word(double share, unsigned phase) {
   return (__builtin_bit_cast(u64, share) & ~(1ull << 63)) | (u64)phase << 63;
 }
 __device__ __forceinline__ double active_share(u64 w) { return __builtin_bit_cast(double, w & ~(1ull << 63)); }
-// a - 2r is of the size of sums of fp32 numbers (or zero, or not finite): ten bits of exponent do.  [phase][sign][exponent][fraction]
+// a - 2r is of the size of sums of fp32 numbers (or zero, or not finite): ten bits of exponent do, and what is below 2^-511 becomes zero.
+// [phase][sign][exponent][fraction]
 __device__ __forceinline__ u64 active_signed_word(double v, unsigned phase) {
   const u64 b = __builtin_bit_cast(u64, v);
   const int e = (int)(b >> 52 & 0x7ffu);
