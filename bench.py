@@ -173,13 +173,13 @@ def main() -> int:
         defaults()
         solver.solve(C, p, q, max_iters=W, **kw)
         solver.set_continue(True)
-        launches = solver.cooperative_launches()[0]
+        iterated = solver.active_runs().iterations
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         res = solver.solve(C, p, q, max_iters=K, **kw)
         torch.cuda.synchronize()
         elapsed = time.perf_counter() - t0
-        on_active_entries = solver.cooperative_launches()[0] > launches and m * n > HELD_ENTRIES
+        on_active_entries = solver.active_runs().iterations > iterated  # (a launch whose entries did not fit has none)
         assert res.iters == K
         checksum = (float(X.sum(dtype=torch.float64)), float(X.max()), int((X != 0).sum()))
         # the same iterations again, profiled (the first 256 of the K)
