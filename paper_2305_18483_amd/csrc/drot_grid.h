@@ -57,7 +57,7 @@ constexpr int kGridPollsMax = 1 << 30;
 // Attempts without a rest.  A word on its way can be held up for as long as every wave on the GPU asks without one: with 4000 waves
 // waiting for the answer of a check, the words of one owner out of 2500 did not reach the memory-side cache in 300000
 // attempts (a third of a second), one check in ten, and in none of hundreds once the waves rest between attempts.
-// So the waits for a check's answer, in which every wave waits for one workgroup, rest in every kernel (quad 1000 x 1000, ten checks, 3.06 ms
+// So the waits for a check's answer, in which everybody waits for one workgroup, rest in every kernel (quad 1000 x 1000, ten checks, 3.06 ms
 // either way).  With the others resting as well, which are over in 1 to 2 us, this kernel and the slabs' took 1 to 2.5 % longer (one
 // more way out of the loops that poll), and a form of the slabs' spilled.
 constexpr int kGridPatience = 32, kGridRest = 64;  // (rest: 4096 cycles, 1.7 us)

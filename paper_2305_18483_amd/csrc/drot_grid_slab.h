@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kSlabRowLanes * CX) void grid_slab_kernel(GridArgs 
   __shared__ float lds_phi[TW][RL * K];
   __shared__ double shares[16];
   __shared__ double sq64[kGridSquares<NW>];
-  __shared__ int failed[2];
+  __shared__ int failed[3];
   const SweepArgs& S = A.S;
   if (*A.done) return;
   const int t = threadIdx.x, lane = t & 63;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kSlabRowLanes * CX) void grid_slab_kernel(GridArgs 
     }
     if (t < COLS) lds_varphi[q][t] = t < M.cols ? S.varphi[M.col0 + t] : kMaskedOut;
   }
-  if (t < 2) failed[t] = 0;
+  if (t < 3) failed[t] = 0;
   // (WIDE: more than 32 strips in one round, where that needs no scratch)
   GridOwner<NW, SUB, kPause, CX == 4 || (K == 4 && TW == 1)> own;
   own.init(A, MAPPED ? B.perm : nullptr, wave, lane);
@@ -447,17 +447,17 @@ __global__ __launch_bounds__(kSlabRowLanes * CX) void grid_slab_kernel(GridArgs 
         if (t_now < M.cols) lds_varphi[q][t_now] = (float)((grid_value(v[2 * kPos], v[2 * kPos + 1]) + cst) / (double)S.m);
       }
     }
-    int result = kGoesOn;
-    if (check) {
+    // (one wave asks for all of its workgroup, which waits at the barrier: 1500 x 1000, 500 iterations, 2.62 ms; with every wave asking
+    // 2.66, with a rest behind every attempt of theirs 2.71)
+    if (check && wave == 0) {
       u64 v[1];
       const unsigned at[1] = {cst_at + 2u};
-      // (a rest behind every attempt: behind the first 32 only, 1500 x 1000 takes 2 % longer; so a third of the attempts)
-      grid_gather<1, kGridRest>(half, v, at, tag, A.polls / kGridRestPolls, lost);
-      if (!lost && (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v[0]) != 0) result = kPasses;
+      grid_gather<1, 0, true>(half, v, at, tag, A.polls, lost);
+      if (!lost && (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v[0]) != 0) failed[2] = 1;
     }
     if (lost) failed[1] = 1;
     __syncthreads();
-    return failed[1] ? kGaveUp : result;
+    return failed[1] ? kGaveUp : check && failed[2] ? kPasses : kGoesOn;
   };
 
   int result = kGoesOn, it = 0, next_check = A.check.first;
